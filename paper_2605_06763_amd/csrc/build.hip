@@ -94,36 +94,16 @@ __device__ __forceinline__ uint32_t f32_to_e4m3_directed(float x, bool up) {
     return c;
 }
 
-// fp32 -> e2m3 code (1 sign, 2 exponent bits of bias 1, 3 mantissa bits: magnitudes 0, 1/8, ..., 15/8, 2, 2.25, ...,
-// 3.75, 4, 4.5, ..., 7.5) of x * inv_scale, round to nearest (ties to the even code), saturating at 7.5.
-__device__ __forceinline__ uint32_t f32_to_e2m3(float x, float inv_scale) {
-    const uint32_t sign = (__float_as_uint(x) >> 26) & 0x20u;
-    const float a = fabsf(x) * inv_scale;
-    uint32_t code;
-    if (a < 2.f) code = (uint32_t)(int)rintf(a * 8.f);                       // 0..16 (16 = the first code of the next binade)
-    else if (a < 4.f) code = 16u + (uint32_t)(int)rintf((a - 2.f) * 4.f);    // 16..24
-    else code = 24u + (uint32_t)(int)rintf((fminf(a, 7.5f) - 4.f) * 2.f);    // 24..31
-    return sign | code;
-}
-
 typedef __attribute__((__vector_size__(6 * sizeof(uint32_t)))) uint32_t lvr_u32x6;
 typedef __attribute__((__vector_size__(32 * sizeof(float)))) float lvr_f32x32;
 
 // CF = 1: the centre is stored as 128 e4m3 codes in the order the matrix-core operand wants them
 // (byte kq*32 + kk*8 + j holds coordinate kk*32 + kq*8 + j); only for bf16 caches.
-// CF = 2: as 128 e2m3 codes of 6 bits in the same order (bits 6 (kk*8 + j) .. of the 24 bytes at kq*24), times
-// one power-of-two scale per kq: the 32 coordinates of a scale block are the ones a lane of the query
-// kernel holds.  The scale is the smallest power of two that brings the block's largest magnitude to
-// at most 7.5; its biased exponent byte goes into the group's record in `radii` (byte kq of the third word).
-// chan_exp (CF = 2 only, may be NULL): 128 signed bytes at the start of every LVR_CHAN_STRIDE bytes, one set per
-// (sequence, KV head); the index then describes the keys
-// with coordinate c divided by 2^e_c: centre, codes and radii are all formed in that space (an exact rescaling: powers
-// of two), and the query multiplies q_c by 2^e_c, which leaves every dot product as it was.
+// (6-bit codes have a kernel of their own below.)
 template <typename KT, int CF = 0>
 __global__ void __launch_bounds__(256)
 build_groups_kernel(void *__restrict__ K, void *__restrict__ centres, float *__restrict__ radii,
-                    int64_t cap_rows, int64_t max_groups, int64_t g0, int64_t g1, int r, int S, const BuildSrc src,
-                    const int8_t *__restrict__ chan_exp = nullptr) {
+                    int64_t cap_rows, int64_t max_groups, int64_t g0, int64_t g1, int r, int S, const BuildSrc src) {
     const int bh = blockIdx.y;
     const int li = threadIdx.x & 15;
     int64_t g = g0 + (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
@@ -168,57 +148,9 @@ build_groups_kernel(void *__restrict__ K, void *__restrict__ centres, float *__r
     const float inv = 1.0f / (float)r;
 #pragma unroll
     for (int e = 0; e < 8; ++e) c[e] *= inv;
-    float chs[8];   // 2^-e_c of this lane's eight coordinates
-#pragma unroll
-    for (int e = 0; e < 8; ++e) chs[e] = 1.0f;
-    if constexpr (CF == 2) {
-        if (chan_exp) {
-            const int8_t *ce = chan_exp + (int64_t)bh * LVR_CHAN_STRIDE + li * 8;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                chs[e] = __uint_as_float((uint32_t)(127 - (int)ce[e]) << 23);
-                c[e] *= chs[e];
-            }
-        }
-    }
-
     constexpr bool CF8 = CF == 1;
-    char *Cb = static_cast<char *>(centres) + ((int64_t)bh * max_groups + g) * (CF == 2 ? LVR_D * 3 / 4 : LVR_D * (CF8 ? 1 : sizeof(KT)));
-    uint32_t scale_bytes = 0;   // CF = 2: the four blocks' exponent bytes (the same in all 16 lanes of the group)
-    (void)scale_bytes;
-    if constexpr (CF == 2) {
-        float amax = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(c[e]));
-        amax = fmaxf(amax, __shfl_xor(amax, 4, 64));    // the lanes of a block: same li & 3
-        amax = fmaxf(amax, __shfl_xor(amax, 8, 64));
-        // smallest E with amax <= 7.5 * 2^E; held to [-100, 120] so that scale, its inverse and every decoded
-        // value are normal numbers (a block beyond that saturates or rounds to zero; the radius measures it)
-        int p;
-        const float f = frexpf(amax, &p);   // amax = f * 2^p, f in [0.5, 1)
-        int E = (amax > 0.f) ? (f <= 0.9375f ? p - 3 : p - 2) : -100;
-        E = E < -100 ? -100 : (E > 120 ? 120 : E);
-        const float scale = __uint_as_float((uint32_t)(E + 127) << 23), inv_scale = __uint_as_float((uint32_t)(127 - E) << 23);
-        uint32_t code[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) code[e] = f32_to_e2m3(c[e], inv_scale);
-        const uint32_t lo = code[0] | (code[1] << 6) | (code[2] << 12) | (code[3] << 18) | (code[4] << 24) | (code[5] << 30);
-        const uint32_t hi = (code[5] >> 2) | (code[6] << 4) | (code[7] << 10);   // 16 bits
-        // from here on: the centre as stored (decoded by the conversion the query kernel uses, in its fp32 form)
-        const lvr_u32x6 src = {lo, hi, 0u, 0u, 0u, 0u};
-        const lvr_f32x32 dec = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(src, scale);
-        c[0] = dec[0]; c[1] = dec[1]; c[2] = dec[2]; c[3] = dec[3];
-        c[4] = dec[4]; c[5] = dec[5]; c[6] = dec[6]; c[7] = dec[7];
-        if (valid) {
-            uint16_t *dst = reinterpret_cast<uint16_t *>(Cb + (li & 3) * 24 + (li >> 2) * 6);
-            dst[0] = (uint16_t)lo;
-            dst[1] = (uint16_t)(lo >> 16);
-            dst[2] = (uint16_t)hi;
-        }
-        const int lane = threadIdx.x & 63, base = lane & ~15;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) scale_bytes |= (uint32_t)(__shfl(E, base + b, 64) + 127) << (8 * b);
-    } else if constexpr (CF8) {
+    char *Cb = static_cast<char *>(centres) + ((int64_t)bh * max_groups + g) * (LVR_D * (CF8 ? 1 : sizeof(KT)));
+    if constexpr (CF8) {
         uint32_t code[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) code[e] = f32_to_e4m3(c[e]);
@@ -258,7 +190,7 @@ build_groups_kernel(void *__restrict__ K, void *__restrict__ centres, float *__r
         float d2 = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            float t = x[e] * chs[e] - c[e];
+            float t = x[e] - c[e];
             d2 += t * t;
         }
         d2 = seg_sum(d2, lanes_per_sub);
@@ -298,18 +230,181 @@ build_groups_kernel(void *__restrict__ K, void *__restrict__ centres, float *__r
             for (int k = 0; k < 4; ++k)
                 if (k == sidx) slot[k] = up >> 16;
         }
-        if constexpr (CF == 2) {   // 12-byte record: the radii, then the scale bytes
-            if (valid && li == 0) {
-                uint32_t *rec = reinterpret_cast<uint32_t *>(radii) + ((int64_t)bh * max_groups + g) * 3;
-                rec[0] = slot[0] | (slot[1] << 16);
-                rec[1] = slot[2] | (slot[3] << 16);
-                rec[2] = scale_bytes;
-            }
-        } else if (valid && li == 0)
+        if (valid && li == 0)
             reinterpret_cast<uint2 *>(radii)[(int64_t)bh * max_groups + g] =
                 make_uint2(slot[0] | (slot[1] << 16), slot[2] | (slot[3] << 16));
     } else {
         if (valid && (li % lanes_per_sub) == 0) radii[((int64_t)bh * max_groups + g) * S + li / lanes_per_sub] = rho;
+    }
+}
+
+// Balls with 6-bit centres, the default index.  A centre is stored as 128 e2m3 codes of 6 bits in the order the matrix-core
+// operand wants them (bits 6 (kk*8 + j) .. of the 24 bytes at kq*24 hold coordinate kk*32 + kq*8 + j), times one power-of-two
+// scale per kq: the 32 coordinates of a scale block are the ones a lane of the query kernel holds.  The scale is the smallest
+// power of two that brings the block's largest magnitude to at most 7.5; its biased exponent byte goes into the group's
+// record in `radii` (byte kq of the third word).  `chan`: LVR_CHAN_STRIDE bytes per (sequence, KV head), at LVR_D the factors
+// 2^e_c; the index describes the keys with coordinate c divided by 2^e_c: centre, codes and radii are all formed in that space
+// (an exact rescaling: powers of two), and the query multiplies q_c by 2^e_c, which leaves every dot product as it was.
+//
+// Four lanes per group, lane b of the quad holding the 32
+// coordinates 32 kk + 8 b + e of scale block b in registers: the block's largest magnitude, its codes (one conversion
+// instruction there, one back) and its share of every distance need no other lane, and what the coordinate blocks of Eq. (1)
+// add up over the quad is two lane exchanges per radius.  A wave stores 16 groups' codes as 1536 consecutive bytes.
+// R = group size up to four (the members stay in registers between the two passes); R = 0: any r, members read twice.
+// Bound by memory: K in, K out and 108 bytes per group (650 MB for 8 heads of 131072 keys).  With 16 lanes per group, a software encoder
+// and a four-step exchange per reduction the vector ALU took longer than the traffic, 223 us; BUILD6.
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float lvr_f32x16;
+
+__device__ __forceinline__ float quad_sum(float v) {
+    v += lvr_dpp<0xB1>(v);   // lane ^ 1
+    v += lvr_dpp<0x4E>(v);   // lane ^ 2
+    return v;
+}
+
+template <int R, int S>
+__global__ void __launch_bounds__(256)
+build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__restrict__ radii, int64_t cap_rows,
+                     int64_t max_groups, int64_t g0, int64_t g1, int r, const BuildSrc src, const int8_t *__restrict__ chan) {
+    constexpr int KEEP = R ? R : 1;
+    const int bh = blockIdx.y;
+    const int b = threadIdx.x & 3;
+    int64_t g = g0 + (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2);
+    const bool valid = g < g1;
+    if (!valid) g = g0;   // keep every lane busy so the exchanges below see defined data
+    char *Kb = static_cast<char *>(K) + (int64_t)bh * cap_rows * LVR_D * 2;
+    const bool from_src = src.base != nullptr;   // uniform
+    const char *Sb = from_src ? src.base + ((int64_t)(bh / src.n_kv_heads) * src.sb + (int64_t)(bh % src.n_kv_heads) * src.sh) * 2 : Kb;
+    const int64_t row_stride = from_src ? src.st * 2 : (int64_t)LVR_D * 2;
+    const int members = R ? R : r;
+    uint4 raw[KEEP][4];
+    auto fetch = [&](int m, uint4 (&w)[4]) {   // this lane's four pieces of member m
+        const uint4 *p = reinterpret_cast<const uint4 *>(Sb + (g * members + m) * row_stride) + b;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) w[kk] = p[kk * 4];
+    };
+    auto keep_row = [&](int m, const uint4 (&w)[4]) {   // the arena's copy of the row
+        uint4 *p = reinterpret_cast<uint4 *>(Kb + (g * members + m) * (LVR_D * 2)) + b;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) p[kk * 4] = w[kk];
+    };
+    auto value = [](const uint4 &w, int e) {
+        const uint32_t u = e < 2 ? w.x : (e < 4 ? w.y : (e < 6 ? w.z : w.w));
+        return (e & 1) ? lvr_bf16_hi(u) : lvr_bf16_lo(u);
+    };
+    if constexpr (R != 0) {
+#pragma unroll
+        for (int m = 0; m < R; ++m) fetch(m, raw[m]);
+    }
+    // 2^-e_c of this lane's coordinates, from the factors 2^e_c: the exponent field of the reciprocal of a power of two
+    float chs[32];
+    {
+        const float4 *cf = reinterpret_cast<const float4 *>(chan + (int64_t)bh * LVR_CHAN_STRIDE + LVR_D) + b * 2;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const float4 x = cf[kk * 8], y = cf[kk * 8 + 1];
+            const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) chs[kk * 8 + e] = __uint_as_float((254u << 23) - __float_as_uint(f[e]));
+        }
+    }
+    float c[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) c[i] = 0.f;
+    auto add_member = [&](const uint4 (&w)[4]) {   // members in ascending row order
+#pragma unroll
+        for (int i = 0; i < 32; ++i) c[i] += value(w[i / 8], i % 8);
+    };
+    if constexpr (R != 0) {
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            if (from_src && valid) keep_row(m, raw[m]);
+            add_member(raw[m]);
+        }
+    } else {
+        for (int m = 0; m < members; ++m) {
+            fetch(m, raw[0]);
+            if (from_src && valid) keep_row(m, raw[0]);
+            add_member(raw[0]);
+        }
+    }
+    const float inv = 1.0f / (float)members;   // a power of two: exact
+    float amax = 0.f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        c[i] = c[i] * inv * chs[i];
+        amax = fmaxf(amax, fabsf(c[i]));
+    }
+    // smallest E with amax <= 7.5 * 2^E; held to [-100, 120] so that scale and every decoded value are normal numbers (a
+    // block beyond that saturates or rounds to zero; the radius measures it)
+    int p;
+    const float f = frexpf(amax, &p);   // amax = f * 2^p, f in [0.5, 1)
+    int E = (amax > 0.f) ? (f <= 0.9375f ? p - 3 : p - 2) : -100;
+    E = E < -100 ? -100 : (E > 120 ? 120 : E);
+    const float scale = __uint_as_float((uint32_t)(E + 127) << 23);
+    lvr_f32x16 even, odd;   // the conversion interleaves its two operands: code 2i from the first, 2i + 1 from the second
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        even[i] = c[2 * i];
+        odd[i] = c[2 * i + 1];
+    }
+    const lvr_u32x6 code = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, scale);
+    // from here on: the centre as stored (decoded by the conversion the query kernel uses, in its fp32 form)
+    const lvr_f32x32 dec = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(code, scale);
+    if (valid) {
+        uint2 *dst = reinterpret_cast<uint2 *>(static_cast<char *>(centres) + ((int64_t)bh * max_groups + g) * (LVR_D * 3 / 4) + b * 24);
+        dst[0] = make_uint2(code[0], code[1]);
+        dst[1] = make_uint2(code[2], code[3]);
+        dst[2] = make_uint2(code[4], code[5]);
+    }
+    constexpr int SPAN = 32 / S;   // this lane's coordinates of one coordinate block are consecutive: 4/S steps of 8
+    float cn2[S], max_d2[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < SPAN; ++i) t += dec[s * SPAN + i] * dec[s * SPAN + i];
+        cn2[s] = quad_sum(t);
+        max_d2[s] = 0.f;
+    }
+    auto distance = [&](const uint4 (&w)[4]) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            float d2 = 0.f;
+#pragma unroll
+            for (int i = s * SPAN; i < (s + 1) * SPAN; ++i) {
+                const float t = value(w[i / 8], i % 8) * chs[i] - dec[i];
+                d2 += t * t;
+            }
+            max_d2[s] = fmaxf(max_d2[s], quad_sum(d2));
+        }
+    };
+    if constexpr (R != 0) {
+#pragma unroll
+        for (int m = 0; m < R; ++m) distance(raw[m]);
+    } else {
+        for (int m = 0; m < members; ++m) {
+            fetch(m, raw[0]);
+            distance(raw[0]);
+        }
+    }
+    // lane b forms radius b of the record (slots S..3 are zero): widened as above, then rounded UP to bf16
+    float d2 = max_d2[0], n2 = cn2[0];
+#pragma unroll
+    for (int s = 1; s < S; ++s) {
+        d2 = b == s ? max_d2[s] : d2;
+        n2 = b == s ? cn2[s] : n2;
+    }
+    float rho = sqrtf(d2) * (1.0f + 0x1p-12f) + sqrtf(n2) * 0x1p-12f;
+    uint32_t up = __float_as_uint(rho) + 1u;   // one ulp up (rho >= 0)
+    if (up & 0xffffu) up = (up & 0xffff0000u) + 0x10000u;
+    const uint32_t mine = b < S ? up >> 16 : 0u;
+    const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xf, 0xf, false);   // lane ^ 1
+    uint32_t scales = (uint32_t)(E + 127) << (8 * b);
+    scales |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)scales, 0xB1, 0xf, 0xf, false);
+    scales |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)scales, 0x4E, 0xf, 0xf, false);
+    if (valid && b != 3) {   // 12-byte record: two words of radii (lanes 0 and 2 hold them), then the scale bytes
+        uint32_t *rec = reinterpret_cast<uint32_t *>(radii) + ((int64_t)bh * max_groups + g) * 3;
+        rec[b == 0 ? 0 : (b == 2 ? 1 : 2)] = b == 1 ? scales : mine | (next << 16);
     }
 }
 
@@ -448,11 +543,25 @@ hipError_t lvr_launch_build_groups(lvr_index *ix, int64_t g0, int64_t g1, hipStr
                                ix->max_groups, g0, g1, ix->cfg.group_size, src);
         return hipGetLastError();
     }
-    if (ix->cf6)
-        hipLaunchKernelGGL((build_groups_kernel<lvr_bf16_t, 2>), grid, dim3(256), 0, st, ix->K, ix->centres, ix->radii,
-                           ix->cap_rows, ix->max_groups, g0, g1, ix->cfg.group_size, ix->cfg.n_subspaces, src,
-                           ix->chan_scaled ? lvr_chan_exp(ix) : nullptr);
-    else if (ix->cf8)
+    if (ix->cf6) {
+        grid.x = (unsigned)((g1 - g0 + 63) / 64);   // four lanes per group
+        const int r = ix->cfg.group_size;
+#define LVR_B6_LAUNCH(R, S)                                                                                               \
+    hipLaunchKernelGGL((build_groups6_kernel<R, S>), grid, dim3(256), 0, st, ix->K, ix->centres, ix->radii, ix->cap_rows, \
+                       ix->max_groups, g0, g1, r, src, lvr_chan_exp(ix))
+#define LVR_B6_ANY(S)                 \
+    do {                              \
+        if (r == 1) LVR_B6_LAUNCH(1, S);      \
+        else if (r == 2) LVR_B6_LAUNCH(2, S); \
+        else if (r == 4) LVR_B6_LAUNCH(4, S); \
+        else LVR_B6_LAUNCH(0, S);             \
+    } while (0)
+        if (ix->cfg.n_subspaces == 1) LVR_B6_ANY(1);
+        else if (ix->cfg.n_subspaces == 2) LVR_B6_ANY(2);
+        else LVR_B6_ANY(4);
+#undef LVR_B6_ANY
+#undef LVR_B6_LAUNCH
+    } else if (ix->cf8)
         hipLaunchKernelGGL((build_groups_kernel<lvr_bf16_t, 1>), grid, dim3(256), 0, st, ix->K, ix->centres, ix->radii,
                            ix->cap_rows, ix->max_groups, g0, g1, ix->cfg.group_size, ix->cfg.n_subspaces, src);
     else if (ix->cfg.kv_dtype == LVR_BF16)
