@@ -39,18 +39,29 @@ __global__ void reservoir_update_kernel(int32_t *res, int R, uint64_t seed, int6
     if (j < R) atomicMax(&res[(int64_t)bh * R + j], (int32_t)i);
 }
 
-// One 256-thread workgroup per query head: scores of the reservoir keys (16 lanes per row),
-// bitonic sort in LDS (descending), then the rule.
+// One 256-thread workgroup per query head: scores of the reservoir keys (16 lanes per row), put in descending order,
+// then the rule.  Bound by latency: positions, then rows, then the ordering.  A wave's 64 positions come with one load and
+// all its rows are requested before the first is used (fp32 rows in two halves), and the order is found by counting:
+// thread t finds the rank of score t among the 256 (64 broadcast reads of LDS, no barrier between them) and stores it there.
+// With a dependent load of position and row per four keys, a bitonic sort (36 barriers) and a serial count of the valid
+// scores the launch took 28 us for 32 heads; with it gone, threshold and step together went from 50.0 to 33.6 us.
 template <typename KT>
 __global__ void __launch_bounds__(256)
 threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slot, const int32_t *__restrict__ res,
                  const float *__restrict__ q, float *__restrict__ tau_out, int R, int64_t cap_rows, int64_t n_total,
                  int n_q_heads, int n_kv_heads, int G, int mode, float param) {
+    __shared__ __align__(16) uint32_t s_key[256];
     __shared__ float s[256];
     const int64_t hq = blockIdx.x;
     const int b = (int)(hq / n_q_heads), h = (int)(hq % n_q_heads);
     const int bh = b * n_kv_heads + h / G;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, sub = lane >> 4, li = lane & 15;
+    const int t = threadIdx.x, lane = t & 63, li = lane & 15;
+    const int32_t *rb = res + (int64_t)bh * R;
+    const int32_t *pslot = pos_slot ? pos_slot + (int64_t)bh * cap_rows : nullptr;
+    // a lane quarter takes the 16 reservoir slots its lanes' threads are numbered by; lane li holds the arena row of slot li
+    const int pos = t < R ? rb[t] : -1;
+    const bool have = pos >= 0 && pos < n_total;
+    const int slot = have ? (pslot ? pslot[pos] : pos) : -1;
     float qv[8];
     {
         const float *qh = q + hq * LVR_D + li * 8;
@@ -58,41 +69,44 @@ threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slo
         for (int e = 0; e < 8; ++e) qv[e] = qh[e];
     }
     const char *Kb = static_cast<const char *>(K) + (int64_t)bh * cap_rows * LVR_D * sizeof(KT);
-    const int32_t *pslot = pos_slot ? pos_slot + (int64_t)bh * cap_rows : nullptr;
-    const int32_t *rb = res + (int64_t)bh * R;
-    for (int j0 = 0; j0 < 256; j0 += 16) {
-        const int j = j0 + wave * 4 + sub;
-        int pos = (j < R) ? rb[j] : -1;
-        const bool valid = pos >= 0 && pos < n_total;
-        if (!valid) pos = 0;
-        const int64_t slot = pslot ? (int64_t)pslot[pos] : pos;
-        float x[8];
-        lvr_load8<KT>(Kb, n_total > 0 ? slot : 0, li, x);
-        float d = 0.f;
+    constexpr int BATCH = sizeof(KT) == sizeof(lvr_bf16_t) ? 16 : 8;
+    float score = -INFINITY;   // of slot t
 #pragma unroll
-        for (int e = 0; e < 8; ++e) d += qv[e] * x[e];
-        d = lvr_row16_sum(d);
-        if (li == 0) s[j] = valid ? d : -INFINITY;
-    }
-    __syncthreads();
-    // bitonic sort, descending
-    for (int k = 2; k <= 256; k <<= 1) {
-        for (int jj = k >> 1; jj > 0; jj >>= 1) {
-            const int partner = t ^ jj;
-            if (partner > t) {
-                const float a = s[t], c = s[partner];
-                const bool desc = (t & k) == 0;
-                if (desc ? (a < c) : (a > c)) {
-                    s[t] = c;
-                    s[partner] = a;
-                }
-            }
-            __syncthreads();
+    for (int u0 = 0; u0 < 16; u0 += BATCH) {
+        lvr_raw8<KT> raw[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int row = __shfl(slot, (lane & 48) + u0 + u, 64);
+            lvr_load_raw(Kb, row < 0 ? 0 : row, li, raw[u]);   // row 0 is part of the arena whatever it holds
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            float x[8];
+            lvr_unpack(raw[u], x);
+            float d = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d += qv[e] * x[e];
+            d = lvr_row16_sum(d);
+            score = (li == u0 + u && have) ? d : score;
         }
     }
+    // descending order: unsigned keys in the order of the floats, equal scores in the order of their slots
+    const uint32_t bits = __float_as_uint(score);
+    const uint32_t key = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
+    s_key[t] = key;
+    const int m = __syncthreads_count(score != -INFINITY);   // valid scores come first
+    int rank = 0;
+#pragma unroll 8
+    for (int i = 0; i < 256; i += 4) {
+        const uint4 o = *reinterpret_cast<const uint4 *>(&s_key[i]);
+        rank += (o.x > key || (o.x == key && i < t)) ? 1 : 0;
+        rank += (o.y > key || (o.y == key && i + 1 < t)) ? 1 : 0;
+        rank += (o.z > key || (o.z == key && i + 2 < t)) ? 1 : 0;
+        rank += (o.w > key || (o.w == key && i + 3 < t)) ? 1 : 0;
+    }
+    s[rank] = score;
+    __syncthreads();
     if (t == 0) {
-        int m = 0;
-        while (m < 256 && s[m] != -INFINITY) ++m;   // valid scores sort first
         float tau = -INFINITY;
         if (m > 0) {
             tau = s[0];

@@ -51,3 +51,68 @@ def test_channel_exponents_over_sample_sizes(G, n, splits):
         shift = np.rint(np.median(e[kv] - want))
         sure = np.abs((lg - o) - np.floor(lg - o) - 0.5) > 1e-3
         assert np.array_equal(e[kv][sure], np.clip(want + shift, -8, 8)[sure]), (n, kv)
+
+
+@pytest.mark.parametrize("r,S,groups", [(1, 4, 1), (1, 1, 65), (2, 2, 63), (4, 4, 64), (4, 1, 129), (8, 2, 65), (16, 4, 17)])
+def test_6_bit_balls_enclose_their_members_tightly(G, r, S, groups):
+    """Every group size and block count of the 6-bit build at the edges of its 64-group tiles, from a strided source with a
+    tail of ungrouped keys, and once more for a chunk grouped out of the arena: the key rows come back unchanged, a member
+    lies within the stored radius of the stored centre in the rescaled space, and the radius is at most the largest
+    distance plus what rounding up adds (2^-12 of distance and centre norm, then up to bf16: 2^-7)."""
+    L = G.L
+    g = np.random.default_rng(groups * 100 + r)
+    hkv, chunk = 2, 64
+    n = groups * r + (r - 1)
+    mag = 2.0 ** g.uniform(-3.0, 3.0, size=(hkv, 128))
+    K = W.round_to_bf16((g.standard_normal((1, hkv, n + chunk, 128)) * mag[None, :, None, :]).astype(np.float32))
+    cfg = L.make_config(batch=1, n_q_heads=hkv, n_kv_heads=hkv, capacity=n + chunk, group_size=r, n_subspaces=S, buffer_size=chunk)
+    h = L.lvr_create(cfg)
+    try:
+        Kd = G.to_device(K, "bf16")
+        first = Kd[:, :, :n].transpose(1, 2).contiguous().transpose(1, 2)
+        L.lvr_build(h, first, first)
+        L.lvr_append(h, Kd[:, :, n:].contiguous(), Kd[:, :, n:].contiguous())
+        centres, radii, _, keys = L.lvr_export_index(h, cfg)
+        fac = 2.0 ** L.lvr_export_channel_scales(h, cfg)[0].astype(np.float64)
+        n_indexed = L.lvr_length(h)[1]
+    finally:
+        L.lvr_destroy(h)
+    assert n_indexed == (n // r) * r + (chunk // r) * r
+    assert np.array_equal(keys, W.f32_to_bf16_bits(K).reshape(keys.shape))
+    ng = n_indexed // r
+    for kv in range(hkv):
+        x = K[0, kv, :n_indexed].astype(np.float64).reshape(ng, r, 128) / fac[kv]
+        c = (centres[0, kv].astype(np.uint32) << 16).view(np.float32).astype(np.float64) / fac[kv]
+        d = np.sqrt(((x - c[:, None, :]) ** 2).reshape(ng, r, S, 128 // S).sum(-1)).max(1)
+        cn = np.sqrt((c ** 2).reshape(ng, S, 128 // S).sum(-1))
+        rho = radii[0, kv].astype(np.float64)
+        assert (d <= rho).all()
+        assert (rho <= (d * (1 + 2.0 ** -11) + cn * 2.0 ** -11) * (1 + 2.0 ** -7)).all()
+
+
+@pytest.mark.parametrize("dtype,R,n,tree", [("bf16", 256, 3000, False), ("bf16", 17, 3000, False), ("bf16", 256, 100, False),
+                                            ("f32", 255, 700, False), ("f32", 1, 64, False), ("bf16", 100, 1024, True)])
+def test_threshold_ranks(G, dtype, R, n, tree):
+    """Order statistics of the reservoir's scores against fp64: reservoirs of every fill, slots that are not a multiple of a
+    lane quarter, equal scores (half the keys are repeated), and rows moved by the tree."""
+    L = G.L
+    g = np.random.default_rng(R + n)
+    hkv, hq = 2, 8
+    K = g.standard_normal((1, hkv, n, 128)).astype(np.float32)
+    K[:, :, n // 2:] = K[:, :, :n - n // 2]
+    K = W.round_to_bf16(K) if dtype == "bf16" else K
+    q = g.standard_normal((1, hq, 128)).astype(np.float32)
+    kw = dict(grouping=L.LVR_GROUP_TREE) if tree else {}
+    with G.Index(K, K, dtype, hq, capacity=n, reservoir_size=R, seed=5, **kw) as ix:
+        res = ix.reservoir()
+        for mode, param in (("sample-max", 0.0), ("sample-topk", 1.0), ("sample-topk", 7.0), ("budget", 0.02), ("budget", 1.0)):
+            tau = ix.threshold(q, mode, param)
+            for h in range(hq):
+                pos = res[0, h // 4]
+                pos = pos[pos >= 0]
+                m = pos.size
+                s = np.sort(K[0, h // 4, pos].astype(np.float64) @ q[0, h].astype(np.float64))[::-1]
+                k = 1 if mode == "sample-max" else (int(param) if mode == "sample-topk" else math.ceil(float(np.float32(param)) * m))
+                want = s[min(max(k, 1), m) - 1]
+                # an fp32 dot product of 128 terms: 128 * 2^-24 of the sum of magnitudes, which is below 200 here
+                assert abs(tau[0, h] - want) <= 200 * 128 * 2.0 ** -24, (mode, param, h)
