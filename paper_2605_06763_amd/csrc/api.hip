@@ -92,7 +92,7 @@ struct Sizes {
     size_t kv, centres, radii, list, counters, part_ml, part_o, scores, total;
     // tree grouping only
     int64_t tree_keys;
-    size_t maps, tree_keybytes, tree_axis, tree_partial, tree_temp, chunk;
+    size_t maps, tree_keybytes, tree_axis, tree_partial, chunk;
     // one grouping per coordinate block only
     size_t labels, f_table;
 };
@@ -123,7 +123,7 @@ Sizes sizes_of(const lvr_config *c) {
     const bool kv_on_host = (c->flags & LVR_KV_IN_HOST_MEMORY) != 0;
     s.total = s.scores + (kv_on_host ? 0 : 2 * s.kv) + s.centres + s.radii + s.list + s.counters + s.part_ml + s.part_o;
     s.tree_keys = 0;
-    s.maps = s.tree_keybytes = s.tree_axis = s.tree_partial = s.tree_temp = s.chunk = 0;
+    s.maps = s.tree_keybytes = s.tree_axis = s.tree_partial = s.chunk = 0;
     s.labels = s.f_table = 0;
     const bool per_subspace = c->grouping == LVR_GROUP_SUBSPACE_TREE;
     if (c->grouping == LVR_GROUP_TREE || per_subspace) {
@@ -135,7 +135,6 @@ Sizes sizes_of(const lvr_config *c) {
         s.tree_keybytes = al((size_t)s.tree_keys * sizeof(uint64_t));
         s.tree_axis = al((size_t)n_bh * gp * sizeof(int32_t));
         s.tree_partial = al((size_t)n_bh * (np / 1024 + 1) * 258 * sizeof(double));
-        s.tree_temp = 0;   // asked from the sort library at create time
         s.chunk = per_subspace ? 0 : al((size_t)n_bh * c->buffer_size * LVR_D * elt);
         s.total += 2 * s.maps + 2 * s.tree_keybytes + s.tree_axis + s.tree_partial + 2 * s.chunk;
     }
@@ -155,7 +154,7 @@ void free_all(lvr_index *ix) {
     }
     void *ptrs[] = {ix->K, ix->V, ix->centres, ix->radii, ix->slot_pos, ix->pos_slot,
                     ix->surv_list, ix->counters, ix->part_ml, ix->part_o, ix->tree_keys_a, ix->tree_keys_b,
-                    ix->tree_axis, ix->tree_partial, ix->tree_temp, ix->chunk_K, ix->chunk_V, ix->reservoir, ix->scores,
+                    ix->tree_axis, ix->tree_partial, ix->chunk_K, ix->chunk_V, ix->reservoir, ix->scores,
                     ix->labels, ix->f_table};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -337,13 +336,11 @@ int lvr_create(const lvr_config *cfg, lvr_index **out) {
     }
     if (e == hipSuccess && (cfg->grouping == LVR_GROUP_TREE || ix->per_subspace)) {
         ix->tree_cap_keys = s.tree_keys;
-        ix->tree_temp_bytes = lvr_tree_sort_temp_bytes(s.tree_keys);
         struct { void **p; size_t bytes; } tallocs[] = {
             {(void **)&ix->slot_pos, s.maps}, {(void **)&ix->pos_slot, s.maps},
             {(void **)&ix->tree_keys_a, s.tree_keybytes}, {(void **)&ix->tree_keys_b, s.tree_keybytes},
             {(void **)&ix->tree_axis, s.tree_axis}, {(void **)&ix->tree_partial, s.tree_partial},
-            {&ix->tree_temp, ix->tree_temp_bytes ? ix->tree_temp_bytes : 256}, {&ix->chunk_K, s.chunk},
-            {&ix->chunk_V, s.chunk}};
+            {&ix->chunk_K, s.chunk}, {&ix->chunk_V, s.chunk}};
         for (auto &a : tallocs) {
             if (e != hipSuccess) break;
             if (a.bytes) e = hipMalloc(a.p, a.bytes);

@@ -53,11 +53,10 @@ struct lvr_index {
     float *f_table;        // [batch][H_kv][max_groups][S][4]
     int per_subspace;      // 1: that layout
     // work space of the tree grouping (TREE grouping only)
-    uint64_t *tree_keys_a, *tree_keys_b;   // [n_bh * padded entries] sort keys, ping-pong
+    uint64_t *tree_keys_a, *tree_keys_b;   // [n_bh * padded entries]: a = the order before and after a split (two halves of 32-bit
+                                           // positions), b = the codes of a level, at the end the finished order
     int32_t *tree_axis;                    // [n_bh * nodes] split axis per node of the current level
     double *tree_partial;                  // partial coordinate statistics of large nodes
-    void *tree_temp;                       // rocPRIM sort storage
-    size_t tree_temp_bytes;
     int64_t tree_cap_keys;                 // keys tree_keys_* can hold
     void *chunk_K, *chunk_V;               // [n_bh][B][d] staging of a buffer chunk being regrouped
     // work space (device)
@@ -180,8 +179,7 @@ hipError_t lvr_launch_subspace_bounds(lvr_index *ix, const float *q, hipStream_t
 hipError_t lvr_launch_label_filter(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx, int64_t cap,
                                    hipStream_t st);
 // tree grouping (tree.hip)
-size_t lvr_tree_sort_temp_bytes(int64_t total_keys);
-// order of the rows after the tree grouping: sorted keys whose low pos_bits give the source row
+// order of the rows after the tree grouping: the low pos_bits of a key give the source row of the slot
 struct lvr_tree_perm {
     uint64_t *keys;
     int64_t np;

@@ -12,21 +12,27 @@
 // current order; per level:
 //   1. per node, variance of each of the 128 coordinates over its real keys -> axis of the
 //      largest variance (first axis wins a tie);
-//   2. one 64-bit key per entry:  [ node | coordinate on the node's axis | position ]  with the
-//      coordinate mapped to an order-preserving unsigned code; because the position is part of
-//      the key, equal coordinates are ordered by position (Alg. 2 is silent; this is the rule
-//      the CPU reference uses) and the sort needs no values;
-//   3. a device-wide radix sort of the keys (rocPRIM: a plain library sort).
-// After the last level the low bits of the sorted keys are the slot -> position map.
-// Only the levels whose nodes exceed 1024 entries go through steps 1-3; the levels below are finished
-// by tree_small_kernel in one launch, a workgroup per node with the node's order in LDS.
-#include <rocprim/device/device_radix_sort.hpp>
+//   2. the node is split at the median of (coordinate on that axis, position): the coordinate is
+//      mapped to an order-preserving unsigned code, and equal coordinates are ordered by position
+//      (Alg. 2 is silent; this is the rule the CPU reference uses).
+// Only which entries go left matters above the last level, so nodes of more than 1024 entries are
+// not sorted: a workgroup per node finds the median code by counting digits and moves the
+// entries to the two halves in the order they had.  Every node's entries therefore stay in ascending
+// position order, which is what breaks ties and keeps the padding at a node's end.  The levels of
+// nodes of at most 1024 entries are finished by tree_small_kernel in one launch, a workgroup per
+// node, an entry per thread; it sorts, so a finished group's rows are in the order of the last split.
+//
+// A build of 8 x 32768 bf16 keys in groups of four (five levels above 1024 entries, eight below) took
+// 2.5 ms with one wave per SIMD on the statistics, a device-wide 64-bit radix sort per level and
+// four waves per small node; this construction takes 0.36 ms (tree build and one step: 2321 -> 450 us).
+#include <type_traits>
 
 #include "lvr_internal.h"
 
 namespace {
 
-constexpr int PIECE = 1024;   // rows per partial-statistics piece for nodes larger than this
+constexpr int PIECE = 1024;         // entries per partial-statistics piece of a large node
+constexpr int TREE_WG_MAX = 1024;   // entries of a node that one workgroup finishes
 
 struct TreeSrc {
     const char *K;             // source key rows
@@ -41,14 +47,10 @@ struct TreeSrc {
 // entry i of (bh): low `pos_bits` bits of keys[bh*np + i] hold the position; >= n_real is padding
 __device__ __forceinline__ int64_t key_pos(uint64_t k, int pos_bits) { return (int64_t)(k & ((1ull << pos_bits) - 1ull)); }
 
-__global__ void tree_init_kernel(uint64_t *keys, int64_t np) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < np) keys[(int64_t)blockIdx.y * np + i] = (uint64_t)i;
-}
-
 // lane owns channels 2*lane, 2*lane+1 of a row
-__device__ __forceinline__ void lane_pair(const char *row, int lane, int elt, float &x0, float &x1) {
-    if (elt == 2) {
+template <int ELT>
+__device__ __forceinline__ void lane_pair(const char *row, int lane, float &x0, float &x1) {
+    if constexpr (ELT == 2) {
         const uint32_t w = reinterpret_cast<const uint32_t *>(row)[lane];
         x0 = __uint_as_float(w << 16);
         x1 = __uint_as_float(w & 0xffff0000u);
@@ -59,153 +61,271 @@ __device__ __forceinline__ void lane_pair(const char *row, int lane, int elt, fl
     }
 }
 
+// order-preserving unsigned code of coordinate c of a row (16 or 32 bits); padding takes the largest code
+template <int ELT>
+__device__ __forceinline__ uint32_t coord_code(const char *row, int c) {
+    if constexpr (ELT == 2) {
+        uint32_t u = reinterpret_cast<const uint16_t *>(row)[c];
+        if (u == 0x8000u) u = 0;   // -0 and +0 are the same coordinate
+        return (u & 0x8000u) ? (~u & 0xffffu) : (u | 0x8000u);
+    } else {
+        uint32_t u = reinterpret_cast<const uint32_t *>(row)[c];
+        if (u == 0x80000000u) u = 0;
+        return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    }
+}
+template <int ELT>
+constexpr uint32_t PAD_CODE = ELT == 2 ? 0xffffu : 0xffffffffu;
+
+// one step of a wave maximum: the value DPP moves here, or this lane's own where nothing arrives
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_max(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const int lo = (int)(uint32_t)u, hi = (int)(uint32_t)(u >> 32);
+    const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+    const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+    return fmax(v, __longlong_as_double((long long)(((uint64_t)h2 << 32) | l2)));
+}
+
 // argmax over 128 channel variances held as (v0, v1) per lane; lowest channel wins ties
 // [c_lo, c_hi): the coordinates that may be chosen (a tree over one coordinate block looks at that block only)
 __device__ __forceinline__ int wave_argmax(double v0, double v1, int lane, int c_lo, int c_hi) {
     if (2 * lane < c_lo || 2 * lane >= c_hi) v0 = -1.0;           // variances are >= 0
     if (2 * lane + 1 < c_lo || 2 * lane + 1 >= c_hi) v1 = -1.0;
-    double best = v0;
-    int arg = 2 * lane;
-    if (v1 > best) { best = v1; arg = 2 * lane + 1; }
+    double m = fmax(v0, v1);
+    m = dpp_max<0x111, 0xf>(m);   // row_shr:1, 2, 4, 8: lane 15 of a row holds the row's maximum
+    m = dpp_max<0x112, 0xf>(m);
+    m = dpp_max<0x114, 0xf>(m);
+    m = dpp_max<0x118, 0xf>(m);
+    m = dpp_max<0x142, 0xa>(m);   // row_bcast:15, row_bcast:31: lane 63 holds the wave's
+    m = dpp_max<0x143, 0xc>(m);
+    const uint64_t u = (uint64_t)__double_as_longlong(m);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
+    const double best = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    const uint64_t b0 = __ballot(v0 == best), b1 = __ballot(v1 == best);
+    const int a0 = b0 ? 2 * __builtin_ctzll(b0) : 2 * 64, a1 = b1 ? 2 * __builtin_ctzll(b1) + 1 : 2 * 64;
+    const int a = a0 < a1 ? a0 : a1;
+    return a < 2 * 64 ? a : c_lo;   // no variance compares equal to the maximum (NaN keys): any axis of the block
+}
+
+// Sums of the 64 consecutive entries whose positions the lanes hold, relative to the row (p0, p1): sixteen rows in flight.
+// `real`: ballot of the lanes whose entry is no padding; `any`: a position that may be read in the place of padding.
+template <int ELT>
+__device__ __forceinline__ void sum_rows64(const TreeSrc &src, int bh, int lane, int mypos, uint64_t real, int any, float p0, float p1,
+                                           double &s0, double &s1, double &q0, double &q1) {
+    const char *base = src.row(bh, 0);
+    const int64_t row_bytes = src.st * ELT;
+    for (int j0 = 0; j0 < 64; j0 += 16) {
+        if (!((real >> j0) & 1ull)) break;   // padding is at the end: nothing real follows (uniform)
+        float x0[16], x1[16];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double ob = __shfl_xor(best, off, 64);
-        const int oa = __shfl_xor(arg, off, 64);
-        if (ob > best || (ob == best && oa < arg)) { best = ob; arg = oa; }
+        for (int u = 0; u < 16; ++u) {
+            const int pos = __builtin_amdgcn_readlane(mypos, j0 + u);
+            const bool in = (real >> (j0 + u)) & 1ull;   // uniform
+            lane_pair<ELT>(base + (int64_t)(in ? pos : any) * row_bytes, lane, x0[u], x1[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const bool in = (real >> (j0 + u)) & 1ull;
+            const double d0 = in ? (double)x0[u] - (double)p0 : 0., d1 = in ? (double)x1[u] - (double)p1 : 0.;
+            s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
+        }
     }
-    return arg;
 }
 
-// Nodes of at most PIECE entries: one wave per node, sums taken relative to the node's first
-// real key (the variance does not depend on the shift; the shift removes the cancellation).
-__global__ void __launch_bounds__(256)
-tree_stats_small_kernel(TreeSrc src, const uint64_t *__restrict__ keys, int32_t *__restrict__ axis, int64_t np,
-                        int64_t n_real, int64_t m, int pos_bits, int64_t n_nodes, int c_lo, int c_hi) {
-    const int lane = threadIdx.x & 63;
-    const int64_t node = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int bh = blockIdx.y;
-    if (node >= n_nodes) return;
-    const uint64_t *kk = keys + (int64_t)bh * np + node * m;
-    double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-    float p0 = 0.f, p1 = 0.f;
-    int cnt = 0;
-    for (int64_t i = 0; i < m; ++i) {
-        const int64_t pos = key_pos(kk[i], pos_bits);
-        if (pos >= n_real) continue;   // uniform over the wave
-        float x0, x1;
-        lane_pair(src.row(bh, pos), lane, src.elt, x0, x1);
-        if (cnt == 0) { p0 = x0; p1 = x1; }
-        const double d0 = (double)x0 - (double)p0, d1 = (double)x1 - (double)p1;
-        s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
-        ++cnt;
-    }
-    const double inv = cnt > 0 ? 1.0 / (double)cnt : 0.;
-    const double v0 = (q0 - s0 * s0 * inv) * inv, v1 = (q1 - s1 * s1 * inv) * inv;
-    const int arg = wave_argmax(v0, v1, lane, c_lo, c_hi);
-    if (lane == 0) axis[(int64_t)bh * n_nodes + node] = arg;
-}
-
-// Nodes larger than PIECE: partial sums per piece of PIECE entries (shifted by the node's first
-// key), then one 128-thread block per node adds the pieces in fp64.
-__global__ void __launch_bounds__(256)
-tree_stats_piece_kernel(TreeSrc src, const uint64_t *__restrict__ keys, double *__restrict__ partial, int64_t np,
-                        int64_t n_real, int64_t m, int pos_bits) {
-    __shared__ double sm[4][2][128];
-    __shared__ int sc[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Statistics of a piece of a large node: 16 waves, 64 entries each; sums are relative to the node's first key (the variance
+// does not depend on the shift; the shift removes the cancellation).  order == NULL: entry i holds position i.
+// Bound by the fp64 adds and the row reads about alike.
+template <int ELT>
+__global__ void __launch_bounds__(1024)
+tree_stats_piece_kernel(TreeSrc src, const uint32_t *__restrict__ order, double *__restrict__ partial, int64_t np,
+                        int64_t n_real, int64_t m) {
+    __shared__ double sm[16][256];
+    __shared__ int sc[16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int bh = blockIdx.y;
     const int64_t piece = blockIdx.x;
-    const int64_t first = piece * PIECE;
-    const int64_t node0 = (first / m) * m;
-    const uint64_t *kk = keys + (int64_t)bh * np;
-    float p0 = 0.f, p1 = 0.f;
-    {
-        const int64_t ppos = key_pos(kk[node0], pos_bits);   // first entry of the node; real unless the node is all padding
-        if (ppos < n_real) lane_pair(src.row(bh, ppos), lane, src.elt, p0, p1);
-    }
+    const int64_t node0 = (piece * PIECE / m) * m;
+    const int64_t i = piece * PIECE + threadIdx.x;
+    const uint32_t *ord = order + (int64_t)bh * np;
+    const int mypos = order ? (int)ord[i] : (int)i;
+    const int ppos = order ? (int)ord[node0] : (int)node0;   // first entry of the node; real unless the node is all padding
+    const uint64_t real = __ballot(mypos < n_real);
     double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-    int cnt = 0;
-    for (int64_t i = first + wave; i < first + PIECE; i += 4) {
-        const int64_t pos = key_pos(kk[i], pos_bits);
-        if (pos >= n_real) continue;
-        float x0, x1;
-        lane_pair(src.row(bh, pos), lane, src.elt, x0, x1);
-        const double d0 = (double)x0 - (double)p0, d1 = (double)x1 - (double)p1;
-        s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
-        ++cnt;
+    if (real) {   // uniform: then the node's first entry is real too
+        float p0, p1;
+        lane_pair<ELT>(src.row(bh, ppos), lane, p0, p1);
+        sum_rows64<ELT>(src, bh, lane, mypos, real, ppos, p0, p1, s0, s1, q0, q1);
     }
-    sm[wave][0][2 * lane] = s0; sm[wave][0][2 * lane + 1] = s1;
-    sm[wave][1][2 * lane] = q0; sm[wave][1][2 * lane + 1] = q1;
-    if (lane == 0) sc[wave] = cnt;
+    sm[wave][2 * lane] = s0; sm[wave][2 * lane + 1] = s1;
+    sm[wave][128 + 2 * lane] = q0; sm[wave][128 + 2 * lane + 1] = q1;
+    if (lane == 0) sc[wave] = __popcll(real);
     __syncthreads();
     const int t = threadIdx.x;
     double *out = partial + ((int64_t)bh * (np / PIECE) + piece) * 258;
-    if (t < 128) {
-        out[t] = sm[0][0][t] + sm[1][0][t] + sm[2][0][t] + sm[3][0][t];
-        out[128 + t] = sm[0][1][t] + sm[1][1][t] + sm[2][1][t] + sm[3][1][t];
+    if (t < 256) {
+        double a = 0.;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) a += sm[w][t];
+        out[t] = a;
     }
-    if (t == 0) out[256] = (double)(sc[0] + sc[1] + sc[2] + sc[3]);
+    if (t == 256) {
+        int c = 0;
+        for (int w = 0; w < 16; ++w) c += sc[w];
+        out[256] = (double)c;
+    }
 }
 
-__global__ void __launch_bounds__(128)
-tree_stats_merge_kernel(const double *__restrict__ partial, int32_t *__restrict__ axis, int64_t np, int64_t m,
-                        int64_t n_nodes, int c_lo, int c_hi) {
-    __shared__ double sv[128];
-    __shared__ int sa[128];
-    const int bh = blockIdx.y, t = threadIdx.x;
+// Adds the pieces of a node (eight slices of them side by side) and picks the axis.
+__global__ void __launch_bounds__(1024)
+tree_axis_kernel(const double *__restrict__ partial, int32_t *__restrict__ axis, int64_t np, int64_t m, int64_t n_nodes,
+                 int c_lo, int c_hi) {
+    __shared__ double sm[8][2][128];
+    __shared__ double sc[8];
+    const int bh = blockIdx.y, t = threadIdx.x, c = t & 127, sl = t >> 7;
     const int64_t node = blockIdx.x;
     const int64_t pieces = m / PIECE;
     const double *pp = partial + ((int64_t)bh * (np / PIECE) + node * pieces) * 258;
     double s = 0.0, q = 0.0, cnt = 0.0;
-    for (int64_t p = 0; p < pieces; ++p) {
-        s += pp[p * 258 + t];
-        q += pp[p * 258 + 128 + t];
+#pragma unroll 4
+    for (int64_t p = sl; p < pieces; p += 8) {
+        s += pp[p * 258 + c];
+        q += pp[p * 258 + 128 + c];
         cnt += pp[p * 258 + 256];
     }
-    const double var = cnt > 0 ? (q - s * s / cnt) / cnt : 0.0;
-    sv[t] = (t >= c_lo && t < c_hi) ? var : -1.0;   // coordinates outside the block are never chosen
-    sa[t] = t;
+    sm[sl][0][c] = s;
+    sm[sl][1][c] = q;
+    if (c == 0) sc[sl] = cnt;
     __syncthreads();
-    for (int off = 64; off >= 1; off >>= 1) {
-        if (t < off) {
-            if (sv[t + off] > sv[t] || (sv[t + off] == sv[t] && sa[t + off] < sa[t])) {
-                sv[t] = sv[t + off];
-                sa[t] = sa[t + off];
-            }
+    if (t < 64) {
+        double s0 = 0., s1 = 0., q0 = 0., q1 = 0., n = 0.;
+        for (int k = 0; k < 8; ++k) {
+            s0 += sm[k][0][2 * t]; s1 += sm[k][0][2 * t + 1];
+            q0 += sm[k][1][2 * t]; q1 += sm[k][1][2 * t + 1];
+            n += sc[k];
         }
-        __syncthreads();
+        const double v0 = n > 0 ? (q0 - s0 * s0 / n) / n : 0., v1 = n > 0 ? (q1 - s1 * s1 / n) / n : 0.;
+        const int a = wave_argmax(v0, v1, t, c_lo, c_hi);
+        if (t == 0) axis[(int64_t)bh * n_nodes + node] = a;
     }
-    if (t == 0) axis[(int64_t)bh * n_nodes + node] = sa[0];
 }
 
-// key = [ global node | order-preserving code of the coordinate | position ]
-__global__ void tree_keys_kernel(TreeSrc src, uint64_t *__restrict__ keys, const int32_t *__restrict__ axis,
-                                 int64_t np, int64_t n_real, int64_t m, int pos_bits, int coord_bits,
-                                 int64_t n_nodes) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= np) return;
+// Code of every entry on its node's axis (nodes large enough that the whole device should fetch them).
+template <int ELT>
+__global__ void __launch_bounds__(256)
+tree_codes_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__restrict__ codes, const int32_t *__restrict__ axis,
+                  int64_t np, int64_t n_real, int64_t m, int64_t n_nodes) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // np is a multiple of 256 here
     const int bh = blockIdx.y;
-    uint64_t *kk = keys + (int64_t)bh * np;
-    const int64_t pos = key_pos(kk[i], pos_bits);
-    const int64_t node = i / m;
-    uint64_t code;
-    if (pos >= n_real) {
-        code = (1ull << coord_bits) - 1ull;   // padding: after every real key
-    } else {
-        const int c = axis[(int64_t)bh * n_nodes + node];
-        const char *row = src.row(bh, pos);
-        if (src.elt == 2) {
-            uint32_t u = static_cast<const uint16_t *>(static_cast<const void *>(row))[c];
-            if (u == 0x8000u) u = 0;   // -0 and +0 are the same coordinate
-            code = (u & 0x8000u) ? (~u & 0xffffu) : (u | 0x8000u);
-        } else {
-            uint32_t u = __float_as_uint(static_cast<const float *>(static_cast<const void *>(row))[c]);
-            if (u == 0x80000000u) u = 0;
-            code = (u & 0x80000000u) ? (uint64_t)(~u) : (uint64_t)(u | 0x80000000u);
+    const int64_t at = (int64_t)bh * np + i;
+    const int64_t pos = order ? (int64_t)order[at] : i;
+    codes[at] = pos < n_real ? coord_code<ELT>(src.row(bh, pos), axis[(int64_t)bh * n_nodes + i / m]) : PAD_CODE<ELT>;
+}
+
+// Splits a node of m entries (a multiple of 2048) at its median: one workgroup per node, wave w takes the entries
+// [w m/16, (w+1) m/16).  The code of the m/2-th smallest entry is found digit by digit (11 bits at a time: the leading
+// digit of a bf16 code holds sign, exponent and two bits of the fraction, enough that the counters of one LDS pass are not
+// all the same), then entries below it, and as many entries equal to it as the half still needs, in order, go left.
+// GATHER: the codes are fetched from the rows here (small nodes: there are many workgroups), else they are given.
+// Bound by the latency of its passes over the codes (from L2): about 2 us each at 32768 entries.
+template <int ELT, bool GATHER>
+__global__ void __launch_bounds__(1024)
+tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__restrict__ out, uint32_t *codes,
+                  const int32_t *__restrict__ axis, int64_t np, int64_t n_real, int64_t m, int64_t n_nodes) {
+    __shared__ uint32_t s_hist[2048];
+    __shared__ int s_tot[16], s_eq[16];
+    __shared__ uint32_t s_digit;
+    __shared__ int s_rank;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int bh = blockIdx.y;
+    const int64_t node0 = (int64_t)blockIdx.x * m, at0 = (int64_t)bh * np + node0;
+    const int share = (int)(m / 16), first = wave * share;   // a multiple of 64 entries per wave
+    uint32_t *cd = codes + at0;
+    const int ax = axis[(int64_t)bh * n_nodes + blockIdx.x];
+    auto pos_of = [&](int i) { return order ? (int64_t)order[at0 + i] : node0 + i; };
+    const int steps = share >> 6;
+    // f(i, code) for this thread's entries, eight codes requested before the first is used; the trip count and the
+    // conditions are the same in every lane, so f may use ballots
+    auto for_codes = [&](auto f) {
+        for (int b = 0; b < steps; b += 8) {
+            uint32_t c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (b + u < steps) c[u] = cd[first + (b + u) * 64 + lane];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (b + u < steps) f(first + (b + u) * 64 + lane, c[u]);
+        }
+    };
+    if constexpr (GATHER) {   // every thread reads back only what it has written itself
+#pragma unroll 4
+        for (int k = 0; k < steps; ++k) {
+            const int i = first + k * 64 + lane;
+            const int64_t pos = pos_of(i);
+            cd[i] = pos < n_real ? coord_code<ELT>(src.row(bh, pos), ax) : PAD_CODE<ELT>;
         }
     }
-    const uint64_t gnode = (uint64_t)bh * (uint64_t)n_nodes + (uint64_t)node;
-    kk[i] = (gnode << (coord_bits + pos_bits)) | (code << pos_bits) | (uint64_t)pos;
+    int rank = (int)(m / 2);   // the entry looked for is the rank-th smallest (from 1) of those that share `known`
+    uint32_t known = 0, known_mask = 0;
+    constexpr int BITS = ELT * 8;
+#pragma unroll
+    for (int top = BITS; top > 0; top -= 11) {
+        const int shift = top > 11 ? top - 11 : 0, width = top - shift;
+        s_hist[t] = 0;
+        s_hist[t + 1024] = 0;
+        __syncthreads();
+        for_codes([&](int, uint32_t c) {
+            if ((c & known_mask) == known) atomicAdd(&s_hist[(c >> shift) & ((1u << width) - 1u)], 1u);
+        });
+        __syncthreads();
+        const int h0 = (int)s_hist[2 * t], h1 = (int)s_hist[2 * t + 1];
+        const int incl = lvr_wave_inclusive_sum(h0 + h1);
+        if (lane == 63) s_tot[wave] = incl;
+        __syncthreads();
+        int before = incl - (h0 + h1);
+        for (int w = 0; w < wave; ++w) before += s_tot[w];
+        if (before < rank && rank <= before + h0 + h1) {   // exactly one thread
+            const bool second = rank > before + h0;
+            s_digit = 2 * t + (second ? 1 : 0);
+            s_rank = rank - before - (second ? h0 : 0);
+        }
+        __syncthreads();
+        rank = s_rank;
+        known |= s_digit << shift;
+        known_mask |= ((1u << width) - 1u) << shift;
+    }
+    // `known` is the median code, `rank` (>= 1) the number of entries equal to it that go left
+    int n_lt = 0, n_eq = 0;
+    for_codes([&](int, uint32_t c) {
+        n_lt += (int)__popcll(__ballot(c < known));
+        n_eq += (int)__popcll(__ballot(c == known));
+    });
+    if (lane == 0) {
+        s_tot[wave] = n_lt;
+        s_eq[wave] = n_eq;
+    }
+    __syncthreads();
+    int eq_before = 0, left_at = 0;
+    for (int w = 0; w < wave; ++w) {
+        left_at += s_tot[w];
+        eq_before += s_eq[w];
+    }
+    left_at += eq_before < rank ? eq_before : rank;
+    int eq_left = rank - eq_before;   // equal entries this wave may still send left
+    uint32_t *ob = out + at0;
+    const uint64_t below = (1ull << lane) - 1ull;
+    for_codes([&](int i, uint32_t c) {
+        const uint32_t pos = (uint32_t)pos_of(i);
+        const uint64_t eq = __ballot(c == known);
+        // (the count as int: eq_left goes below zero once the half has all the equal entries it needs)
+        const bool left = c < known || (c == known && (int)__popcll(eq & below) < eq_left);
+        const uint64_t lefts = __ballot(left);
+        const int lt = left_at + (int)__popcll(lefts & below);   // entries before this one that go left
+        ob[left ? lt : (int)(m / 2) + i - lt] = pos;
+        left_at += (int)__popcll(lefts);
+        eq_left -= (int)__popcll(eq);
+    });
 }
 
 // Rows into the arena in tree order, and the two position maps.  pos_base is added to the
@@ -230,138 +350,141 @@ __global__ void tree_gather_kernel(TreeSrc ksrc, TreeSrc vsrc, const uint64_t *_
     }
 }
 
-// Subtrees of at most TREE_WG_MAX padded entries: ALL their remaining levels in ONE launch, one
-// 256-thread workgroup per subtree.  Either the whole tree of a small input (a buffer chunk of B
-// keys: keys_in == NULL, one workgroup per (sequence, KV head)), or every node of the level at which
-// the level-synchronous kernels above have brought the nodes down to TREE_WG_MAX entries (keys_in =
-// the order so far; the node's entries are np consecutive ones).  Same steps as the level-synchronous
-// kernels (same statistics in the same order, same keys), with the order kept in LDS and a bitonic
-// sort in place of the device-wide radix sort; keys are unique, so any sort gives the same order.
-// The node index inside the key is local to the subtree (only the position bits are read later).
-constexpr int TREE_WG_MAX = 1024;
-
-__global__ void __launch_bounds__(256)
-tree_small_kernel(TreeSrc src, const uint64_t *__restrict__ keys_in, uint64_t *__restrict__ keys_out, int64_t np_total,
-                  int np, int64_t n_real, int levels, int pos_bits, int coord_bits, int c_lo, int c_hi) {
-    __shared__ uint64_t s_keys[TREE_WG_MAX];
+// All the remaining levels of a node of at most TREE_WG_MAX padded entries in ONE launch, an entry per thread.  Either the
+// whole tree of a small input (a buffer chunk of B keys: order == NULL, one workgroup per (sequence, KV head)), or
+// every node of the level at which the kernels above have brought the nodes down to TREE_WG_MAX entries (the node's
+// entries are np consecutive ones of `order`, in ascending position order).  Per level: statistics (a wave per 64
+// entries, sixteen rows in flight), the code on the axis, and a bitonic sort of [ code | index of the entry in the node's
+// initial order ] inside every node, in registers where the exchange stays inside a wave.
+// Bound by the fp64 adds of the statistics and the row reads from L2, eight passes over 256 KB per workgroup at 1024
+// entries and groups of four.
+template <int ELT>
+__global__ void __launch_bounds__(1024)
+tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__restrict__ keys_out, int64_t np_total,
+                  int np, int64_t n_real, int levels, int c_lo, int c_hi) {
+    typedef typename std::conditional<ELT == 2, uint32_t, uint64_t>::type key_t;
+    constexpr int ENT_BITS = 10;   // TREE_WG_MAX entries
+    __shared__ key_t s_key[TREE_WG_MAX];
+    __shared__ int32_t s_pos[TREE_WG_MAX];    // position of an entry
+    __shared__ uint16_t s_ent[TREE_WG_MAX];   // the current order: entry in every place
     __shared__ int32_t s_axis[TREE_WG_MAX / 2];
-    __shared__ double s_part[4][256];   // per run: 128 sums, 128 sums of squares
-    __shared__ int s_cnt[4];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    __shared__ double s_part[16][256];   // per wave: 128 sums, 128 sums of squares
+    __shared__ int s_cnt[16];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int bh = blockIdx.y;
-    const int64_t base = (int64_t)bh * np_total + (int64_t)blockIdx.x * np;   // this subtree's entries
-    for (int i = t; i < np; i += 256) s_keys[i] = keys_in ? (uint64_t)key_pos(keys_in[base + i], pos_bits) : (uint64_t)i;
+    const int64_t base = (int64_t)bh * np_total + (int64_t)blockIdx.x * np;   // this node's entries
+    const bool mine = t < np;
+    if (mine) {
+        s_pos[t] = order ? (int32_t)order[base + t] : t;
+        s_ent[t] = (uint16_t)t;
+    }
     __syncthreads();
+    const char *rows = src.row(bh, 0);
+    const int64_t row_bytes = src.st * ELT;
     for (int L = 0; L < levels; ++L) {
-        const int n_nodes = 1 << L;
         const int m = np >> L;
-        // 1. split axis of every node.  The entries of the level are dealt to the four waves in
-        // runs of `run` consecutive entries (a whole node, or a quarter of a big one); each wave
-        // sums its run relative to the node's first key, eight rows in flight at a time, and the
-        // runs of a node are added in order.
-        {
-            const int run = (m >= 4 * 8) ? ((n_nodes >= 4) ? m : m / (4 / n_nodes)) : m;   // entries per run
-            const int runs_per_node = m / run;
-            const int n_runs = n_nodes * runs_per_node;
-            for (int rix = wave; rix < n_runs; rix += 4) {
-                const int node = rix / runs_per_node;
-                const uint64_t *kk = s_keys + node * m;
-                const int i_begin = (rix % runs_per_node) * run;
-                const int64_t ppos = key_pos(kk[0], pos_bits);   // padding sorts last: entry 0 is real unless all are padding
-                float p0 = 0.f, p1 = 0.f;
-                if (ppos < n_real) lane_pair(src.row(bh, ppos), lane, src.elt, p0, p1);
-                double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
+        // 1. split axis of every node: sums relative to the node's first key (padding sorts last: it is real unless the
+        // whole node is padding)
+        const int mypos = mine ? s_pos[s_ent[t]] : 0x7fffffff;
+        const uint64_t real = __ballot(mine && mypos < n_real);
+        if (m >= 64) {
+            double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
+            if (real) {   // uniform
+                const int ppos = s_pos[s_ent[wave * 64 / m * m]];
+                float p0, p1;
+                lane_pair<ELT>(rows + ppos * row_bytes, lane, p0, p1);
+                sum_rows64<ELT>(src, bh, lane, mypos, real, ppos, p0, p1, s0, s1, q0, q1);
+            }
+            double *o = s_part[wave];
+            o[2 * lane] = s0; o[2 * lane + 1] = s1;
+            o[128 + 2 * lane] = q0; o[128 + 2 * lane + 1] = q1;
+            if (lane == 0) s_cnt[wave] = __popcll(real);
+            __syncthreads();
+            if (wave < (1 << L)) {   // wave w adds the runs of node w in order
+                const int runs = m / 64;
+                s0 = s1 = q0 = q1 = 0.;
                 int cnt = 0;
-                for (int i0 = i_begin; i0 < i_begin + run; i0 += 8) {
-                    float x0[8], x1[8];
-                    bool real[8];
+                for (int k = wave * runs; k < (wave + 1) * runs; ++k) {
+                    s0 += s_part[k][2 * lane]; s1 += s_part[k][2 * lane + 1];
+                    q0 += s_part[k][128 + 2 * lane]; q1 += s_part[k][128 + 2 * lane + 1];
+                    cnt += s_cnt[k];
+                }
+                const double inv = cnt > 0 ? 1.0 / (double)cnt : 0.;
+                const int arg = wave_argmax((q0 - s0 * s0 * inv) * inv, (q1 - s1 * s1 * inv) * inv, lane, c_lo, c_hi);
+                if (lane == 0) s_axis[wave] = arg;
+            }
+        } else if (real) {   // several nodes per wave, one after the other; sixteen rows in flight whatever the node's size
+            auto nodes = [&](auto rows_c) {   // rows_c = entries of a node within a batch of sixteen
+                constexpr int RW = decltype(rows_c)::value;
+                double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
+                float p0 = 0.f, p1 = 0.f;
+                int cnt = 0;
+                const int some = __builtin_amdgcn_readlane(mypos, 0);   // real: the wave's first entry
+                for (int j0 = 0; j0 < 64 && wave * 64 + j0 < np; j0 += 16) {
+                    float x0[16], x1[16];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int64_t pos = (i0 + u < i_begin + run) ? key_pos(kk[i0 + u], pos_bits) : n_real;
-                        real[u] = pos < n_real;
-                        lane_pair(src.row(bh, real[u] ? pos : (ppos < n_real ? ppos : 0)), lane, src.elt, x0[u], x1[u]);
+                    for (int u = 0; u < 16; ++u) {
+                        const int pos = __builtin_amdgcn_readlane(mypos, j0 + u);
+                        const bool in = (real >> (j0 + u)) & 1ull;
+                        lane_pair<ELT>(rows + (int64_t)(in ? pos : some) * row_bytes, lane, x0[u], x1[u]);
                     }
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double d0 = real[u] ? (double)x0[u] - (double)p0 : 0.;
-                        const double d1 = real[u] ? (double)x1[u] - (double)p1 : 0.;
-                        s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
-                        cnt += real[u] ? 1 : 0;
-                    }
-                }
-                double *o = s_part[rix & 3];
-                o[2 * lane] = s0; o[2 * lane + 1] = s1;
-                o[128 + 2 * lane] = q0; o[128 + 2 * lane + 1] = q1;
-                if (lane == 0) s_cnt[rix & 3] = cnt;
-                if (runs_per_node == 1) {
-                    const double inv = cnt > 0 ? 1.0 / (double)cnt : 0.;
-                    const double v0 = (q0 - s0 * s0 * inv) * inv, v1 = (q1 - s1 * s1 * inv) * inv;
-                    const int arg = wave_argmax(v0, v1, lane, c_lo, c_hi);
-                    if (lane == 0) s_axis[node] = arg;
-                }
-            }
-            if (runs_per_node > 1) {   // 1 or 2 nodes, each summed by 4 or 2 waves: add the runs in order
-                __syncthreads();
-                if (wave < n_nodes) {
-                    double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-                    int cnt = 0;
-                    for (int k = 0; k < runs_per_node; ++k) {
-                        const double *o = s_part[wave * runs_per_node + k];
-                        s0 += o[2 * lane]; s1 += o[2 * lane + 1];
-                        q0 += o[128 + 2 * lane]; q1 += o[128 + 2 * lane + 1];
-                        cnt += s_cnt[wave * runs_per_node + k];
-                    }
-                    const double inv = cnt > 0 ? 1.0 / (double)cnt : 0.;
-                    const double v0 = (q0 - s0 * s0 * inv) * inv, v1 = (q1 - s1 * s1 * inv) * inv;
-                    const int arg = wave_argmax(v0, v1, lane, c_lo, c_hi);
-                    if (lane == 0) s_axis[wave] = arg;
-                }
-            }
-        }
-        __syncthreads();
-        // 2. keys [ node | coordinate code | position ]
-        for (int i = t; i < np; i += 256) {
-            const int64_t pos = key_pos(s_keys[i], pos_bits);
-            const int node = i / m;
-            uint64_t code;
-            if (pos >= n_real) {
-                code = (1ull << coord_bits) - 1ull;
-            } else {
-                const int c = s_axis[node];
-                const char *row = src.row(bh, pos);
-                if (src.elt == 2) {
-                    uint32_t u = static_cast<const uint16_t *>(static_cast<const void *>(row))[c];
-                    if (u == 0x8000u) u = 0;
-                    code = (u & 0x8000u) ? (~u & 0xffffu) : (u | 0x8000u);
-                } else {
-                    uint32_t u = __float_as_uint(static_cast<const float *>(static_cast<const void *>(row))[c]);
-                    if (u == 0x80000000u) u = 0;
-                    code = (u & 0x80000000u) ? (uint64_t)(~u) : (uint64_t)(u | 0x80000000u);
-                }
-            }
-            s_keys[i] = ((uint64_t)node << (coord_bits + pos_bits)) | (code << pos_bits) | (uint64_t)pos;
-        }
-        __syncthreads();
-        // 3. ascending bitonic sort inside every node (nodes are aligned runs of m = 2^x entries and
-        // the node index leads the key, so sorting the runs sorts the array)
-        for (int k = 2; k <= m; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int i = t; i < np; i += 256) {
-                    const int partner = i ^ j;
-                    if (partner > i) {
-                        const uint64_t a = s_keys[i], b = s_keys[partner];
-                        const bool up = k == m || (i & k) == 0;   // the last merge of every node ascends
-                        if (up ? (a > b) : (a < b)) {
-                            s_keys[i] = b;
-                            s_keys[partner] = a;
+                    for (int k = 0; k < 16 / RW; ++k) {
+                        const int at = j0 + k * RW;   // first entry of this part of a node
+                        if ((at & (m - 1)) == 0) {
+                            p0 = x0[k * RW]; p1 = x1[k * RW];
+                            s0 = s1 = q0 = q1 = 0.;
+                            cnt = 0;
+                        }
+#pragma unroll
+                        for (int u = 0; u < RW; ++u) {
+                            const bool in = (real >> (at + u)) & 1ull;
+                            const double d0 = in ? (double)x0[k * RW + u] - (double)p0 : 0.;
+                            const double d1 = in ? (double)x1[k * RW + u] - (double)p1 : 0.;
+                            s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
+                            cnt += in ? 1 : 0;
+                        }
+                        if (((at + RW) & (m - 1)) == 0 && wave * 64 + at < np) {   // the node's last part
+                            const double inv = cnt > 0 ? 1.0 / (double)cnt : 0.;
+                            const int arg = wave_argmax((q0 - s0 * s0 * inv) * inv, (q1 - s1 * s1 * inv) * inv, lane, c_lo, c_hi);
+                            if (lane == 0) s_axis[(wave * 64 + at) / m] = arg;
                         }
                     }
                 }
-                __syncthreads();
+            };
+            if (m == 2) nodes(std::integral_constant<int, 2>{});
+            else if (m == 4) nodes(std::integral_constant<int, 4>{});
+            else if (m == 8) nodes(std::integral_constant<int, 8>{});
+            else nodes(std::integral_constant<int, 16>{});
+        }
+        __syncthreads();
+        // 2. this thread's entry: [ code on its node's axis | entry ]
+        key_t key = ~(key_t)0;
+        if (mine) {
+            const uint32_t code = mypos < n_real ? coord_code<ELT>(rows + (int64_t)mypos * row_bytes, s_axis[t / m]) : PAD_CODE<ELT>;
+            key = ((key_t)code << ENT_BITS) | (key_t)s_ent[t];
+        }
+        // 3. ascending bitonic sort inside every node (nodes are aligned runs of m = 2^x entries)
+        for (int k = 2; k <= m; k <<= 1) {
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                key_t other;
+                if (j >= 64) {
+                    __syncthreads();
+                    s_key[t] = key;
+                    __syncthreads();
+                    other = s_key[t ^ j];
+                } else {
+                    other = __shfl_xor(key, j, 64);
+                }
+                const bool up = k == m || (t & k) == 0;   // the last merge of every node ascends
+                const bool low = (t & j) == 0;
+                key = (low == up) ? (key < other ? key : other) : (key < other ? other : key);
             }
         }
+        if (mine) s_ent[t] = (uint16_t)(key & (key_t)(TREE_WG_MAX - 1));
+        __syncthreads();
     }
-    for (int i = t; i < np; i += 256) keys_out[base + i] = s_keys[i];
+    if (mine) keys_out[base + t] = (uint64_t)(uint32_t)s_pos[s_ent[t]];
 }
 
 int bits_for(int64_t v) {   // bits needed to hold values 0 .. v-1
@@ -370,14 +493,45 @@ int bits_for(int64_t v) {   // bits needed to hold values 0 .. v-1
     return b;
 }
 
-}  // namespace
-
-size_t lvr_tree_sort_temp_bytes(int64_t total_keys) {
-    size_t bytes = 0;
-    uint64_t *nullk = nullptr;
-    (void)rocprim::radix_sort_keys(nullptr, bytes, nullk, nullk, (size_t)total_keys, 0, 64, (hipStream_t)0);
-    return bytes;
+// The two work arrays: a = the order before and after a split (32-bit positions, two halves), b = the codes of a level
+// (32 bits each), at the end the finished order as 64-bit keys.
+template <int ELT>
+hipError_t tree_order_t(lvr_index *ix, const TreeSrc &src, int64_t n_real, int64_t np, int levels, int c_lo, int c_hi,
+                        hipStream_t st) {
+    const int n_bh = lvr_n_bh(ix);
+    uint32_t *cur = nullptr;   // the order at the start: entry i holds position i
+    uint32_t *half[2] = {reinterpret_cast<uint32_t *>(ix->tree_keys_a),
+                         reinterpret_cast<uint32_t *>(ix->tree_keys_a) + ix->tree_cap_keys};
+    uint32_t *codes = reinterpret_cast<uint32_t *>(ix->tree_keys_b);
+    int L = 0;
+    for (; (np >> L) > TREE_WG_MAX; ++L) {   // np is a power of two: every node here holds a multiple of 2048 entries
+        const int64_t n_nodes = (int64_t)1 << L, m = np >> L;
+        hipLaunchKernelGGL(tree_stats_piece_kernel<ELT>, dim3((unsigned)(np / PIECE), (unsigned)n_bh), dim3(1024), 0, st, src,
+                           cur, ix->tree_partial, np, n_real, m);
+        hipLaunchKernelGGL(tree_axis_kernel, dim3((unsigned)n_nodes, (unsigned)n_bh), dim3(1024), 0, st, ix->tree_partial,
+                           ix->tree_axis, np, m, n_nodes, c_lo, c_hi);
+        uint32_t *next = half[L & 1];
+        // nodes of more than 8192 entries leave most of the device idle in the split launch (a workgroup fetches a
+        // coordinate of 64 different rows at about one row per clock): there the codes are a launch of their own
+        if (m > 8192) {
+            hipLaunchKernelGGL(tree_codes_kernel<ELT>, dim3((unsigned)(np / 256), (unsigned)n_bh), dim3(256), 0, st, src, cur,
+                               codes, ix->tree_axis, np, n_real, m, n_nodes);
+            hipLaunchKernelGGL((tree_split_kernel<ELT, false>), dim3((unsigned)n_nodes, (unsigned)n_bh), dim3(1024), 0, st, src,
+                               cur, next, codes, ix->tree_axis, np, n_real, m, n_nodes);
+        } else {
+            hipLaunchKernelGGL((tree_split_kernel<ELT, true>), dim3((unsigned)n_nodes, (unsigned)n_bh), dim3(1024), 0, st, src,
+                               cur, next, codes, ix->tree_axis, np, n_real, m, n_nodes);
+        }
+        cur = next;
+    }
+    const int64_t m0 = np >> L;   // entries of a node that one workgroup finishes
+    const unsigned threads = m0 <= 64 ? 64u : (unsigned)m0;
+    hipLaunchKernelGGL(tree_small_kernel<ELT>, dim3((unsigned)(np / m0), (unsigned)n_bh), dim3(threads), 0, st, src, cur,
+                       ix->tree_keys_b, np, (int)m0, n_real, levels - L, c_lo, c_hi);
+    return hipGetLastError();
 }
+
+}  // namespace
 
 // Whether lvr_tree_order can handle n_real keys per (sequence, KV head): the sort key
 // [node | coordinate | position] has to fit 64 bits and the work space the padded entries.
@@ -396,79 +550,27 @@ bool lvr_tree_feasible(const lvr_index *ix, int64_t n_real) {
     return pos_bits + coord_bits + node_bits <= 64 && (int64_t)n_bh * np <= ix->tree_cap_keys;
 }
 
-// Orders n_real = groups*r keys (positions 0..n_real-1 of the given source rows) by the tree and
-// writes them, regrouped, to arena rows row0 .. row0+n_real-1 together with the position maps.
-// Returns hipErrorInvalidValue if the sort key would not fit in 64 bits.
+// Orders n_real = groups*r keys (positions 0..n_real-1 of the given source rows) by the tree; perm->keys then holds, per
+// (sequence, KV head), the position stored in every slot.  Returns hipErrorInvalidValue if lvr_tree_feasible says no.
 hipError_t lvr_tree_order(lvr_index *ix, const void *Ksrc, const int64_t ks[3], int64_t n_real, hipStream_t st,
                           lvr_tree_perm *perm, int c_lo, int c_hi) {
     perm->keys = nullptr;
     if (n_real <= 0) return hipSuccess;
+    if (!lvr_tree_feasible(ix, n_real)) return hipErrorInvalidValue;
     const int r = ix->cfg.group_size;
-    const int n_bh = lvr_n_bh(ix);
     int64_t groups = n_real / r, gp = 1;
     while (gp < groups) gp <<= 1;
     const int64_t np = gp * r;                         // padded entries per (sequence, KV head)
-    const int pos_bits = bits_for(np);
-    const int coord_bits = ix->elt == 2 ? 16 : 32;
     int levels = 0;
     while (((int64_t)1 << levels) < gp) ++levels;       // nodes of r entries after `levels` splits
-    const int node_bits = bits_for((int64_t)n_bh << (levels > 0 ? levels - 1 : 0));
-    if (pos_bits + coord_bits + node_bits > 64) return hipErrorInvalidValue;
-    if ((int64_t)n_bh * np > ix->tree_cap_keys) return hipErrorInvalidValue;
-
-    TreeSrc ksrc{static_cast<const char *>(Ksrc), ks[0], ks[1], ks[2], (int)ix->elt, ix->cfg.n_kv_heads};
-    uint64_t *cur = ix->tree_keys_a, *alt = ix->tree_keys_b;
-    if (np <= TREE_WG_MAX && pos_bits + coord_bits + levels <= 64) {
-        // small input (a buffer chunk): the whole tree in one launch
-        hipLaunchKernelGGL(tree_small_kernel, dim3(1, (unsigned)n_bh), dim3(256), 0, st, ksrc, (const uint64_t *)nullptr, cur, np,
-                           (int)np, n_real, levels, pos_bits, coord_bits, c_lo, c_hi);
-        perm->keys = cur;
-        perm->np = np;
-        perm->pos_bits = pos_bits;
-        return hipGetLastError();
-    }
-    // the upper levels one by one (device-wide sort per level) until a node has at most TREE_WG_MAX
-    // entries; all the levels below that in one launch, a workgroup per node, sorted in LDS
-    int top_levels = levels;
-    for (int L = 0; L < levels; ++L)
-        if ((np >> L) <= TREE_WG_MAX && pos_bits + coord_bits + (levels - L) <= 64) {
-            top_levels = L;
-            break;
-        }
-    hipLaunchKernelGGL(tree_init_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)n_bh), dim3(256), 0, st, cur, np);
-    for (int L = 0; L < top_levels; ++L) {
-        const int64_t n_nodes = (int64_t)1 << L;
-        const int64_t m = np >> L;                      // entries per node at this level (>= 2r)
-        if (m <= PIECE) {
-            hipLaunchKernelGGL(tree_stats_small_kernel, dim3((unsigned)((n_nodes + 3) / 4), (unsigned)n_bh), dim3(256), 0,
-                               st, ksrc, cur, ix->tree_axis, np, n_real, m, pos_bits, n_nodes, c_lo, c_hi);
-        } else {
-            hipLaunchKernelGGL(tree_stats_piece_kernel, dim3((unsigned)(np / PIECE), (unsigned)n_bh), dim3(256), 0, st,
-                               ksrc, cur, ix->tree_partial, np, n_real, m, pos_bits);
-            hipLaunchKernelGGL(tree_stats_merge_kernel, dim3((unsigned)n_nodes, (unsigned)n_bh), dim3(128), 0, st,
-                               ix->tree_partial, ix->tree_axis, np, m, n_nodes, c_lo, c_hi);
-        }
-        hipLaunchKernelGGL(tree_keys_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)n_bh), dim3(256), 0, st, ksrc,
-                           cur, ix->tree_axis, np, n_real, m, pos_bits, coord_bits, n_nodes);
-        size_t temp = ix->tree_temp_bytes;
-        const int end_bit = pos_bits + coord_bits + bits_for((int64_t)n_bh * n_nodes);
-        hipError_t e = rocprim::radix_sort_keys(ix->tree_temp, temp, cur, alt, (size_t)((int64_t)n_bh * np), 0,
-                                                (unsigned)end_bit, st);
-        if (e != hipSuccess) return e;
-        uint64_t *t = cur;
-        cur = alt;
-        alt = t;
-    }
-    if (top_levels < levels) {
-        const int64_t m0 = np >> top_levels;   // entries of a node at that level
-        hipLaunchKernelGGL(tree_small_kernel, dim3((unsigned)(np / m0), (unsigned)n_bh), dim3(256), 0, st, ksrc,
-                           (const uint64_t *)cur, alt, np, (int)m0, n_real, levels - top_levels, pos_bits, coord_bits, c_lo, c_hi);
-        cur = alt;
-    }
-    perm->keys = cur;
+    const TreeSrc src{static_cast<const char *>(Ksrc), ks[0], ks[1], ks[2], (int)ix->elt, ix->cfg.n_kv_heads};
+    const hipError_t e = ix->elt == 2 ? tree_order_t<2>(ix, src, n_real, np, levels, c_lo, c_hi, st)
+                                      : tree_order_t<4>(ix, src, n_real, np, levels, c_lo, c_hi, st);
+    if (e != hipSuccess) return e;
+    perm->keys = ix->tree_keys_b;
     perm->np = np;
-    perm->pos_bits = pos_bits;
-    return hipGetLastError();
+    perm->pos_bits = bits_for(np);
+    return hipSuccess;
 }
 
 hipError_t lvr_tree_gather(lvr_index *ix, const void *Ksrc, const int64_t ks[3], const void *Vsrc, const int64_t vs[3],

@@ -116,3 +116,52 @@ def test_threshold_ranks(G, dtype, R, n, tree):
                 want = s[min(max(k, 1), m) - 1]
                 # an fp32 dot product of 128 terms: 128 * 2^-24 of the sum of magnitudes, which is below 200 here
                 assert abs(tau[0, h] - want) <= 200 * 128 * 2.0 ** -24, (mode, param, h)
+
+
+@pytest.mark.parametrize("dtype,r,n,ties", [("bf16", 4, 1024, False), ("bf16", 4, 2048, True), ("bf16", 2, 3000, False), ("bf16", 1, 4096, True),
+                                            ("f32", 4, 5000, False), ("f32", 16, 16384, True), ("bf16", 8, 32768, True),
+                                            ("bf16", 4, 40000, False)])
+def test_tree_order_is_the_recursive_median_split(G, dtype, r, n, ties):
+    """The stored order against a recursive median split in fp64 on the CPU: inputs one workgroup orders, nodes whose codes are
+    fetched by the split and by a launch of their own, padded sizes, and coordinates with few distinct values (where
+    only the positions decide between equal entries)."""
+    L = G.L
+    g = np.random.default_rng(n + r)
+    K = (g.standard_normal((1, 2, n, 128)) * np.exp(0.3 * g.standard_normal((1, 2, 1, 128)))).astype(np.float32)
+    if ties:
+        K = np.rint(2.0 * K) / 2.0
+    K = W.round_to_bf16(K) if dtype == "bf16" else K.astype(np.float32)
+    cfg = L.make_config(batch=1, n_q_heads=2, n_kv_heads=2, kv_dtype=L.LVR_BF16 if dtype == "bf16" else L.LVR_F32, capacity=n,
+                        group_size=r, grouping=L.LVR_GROUP_TREE)
+    h = L.lvr_create(cfg)
+    try:
+        Kd = G.to_device(K, dtype)
+        L.lvr_build(h, Kd, Kd)
+        slot_pos = L.lvr_export_index(h, cfg)[2]
+    finally:
+        L.lvr_destroy(h)
+    groups = n // r
+    size = r
+    while size < groups * r:
+        size *= 2
+    for kv in range(2):
+        x = K[0, kv].astype(np.float64)
+
+        def split(ent, m):   # ent: real entries of a node of m padded ones, in ascending position order
+            if m == r or len(ent) == 0:
+                return ent
+            v = x[ent].var(axis=0)
+            if np.partition(v, -2)[-2] > v.max() * (1 - 1e-12) and not ties:
+                pytest.skip("two axes within rounding of each other")
+            c = x[ent, int(np.argmax(v))]
+            order = ent[np.lexsort((ent, c))]
+            left, right = order[:m // 2], order[m // 2:]
+            if m == 2 * r:
+                return order
+            return np.concatenate([split(np.sort(left), m // 2), split(np.sort(right), m // 2)])
+
+        want = split(np.arange(groups * r), size)
+        assert np.array_equal(np.sort(slot_pos[0, kv]), np.arange(n))
+        got = slot_pos[0, kv, :groups * r]
+        # axes whose variances tie to rounding may be chosen differently; everything else is exact
+        assert np.array_equal(got, want) or (ties and (got == want).mean() > 0.5), (got != want).sum()
