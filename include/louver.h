@@ -91,7 +91,7 @@ enum lvr_flags {
     LVR_ATTEND_BUFFER_DENSE = 1u,
     /* Run the bound test and the exact check as two kernel launches (survivor list through
      * HBM) instead of the fused single launch.  Same results; lets the two stages be timed
-     * apart.  fp32 caches always run this way. */
+     * apart. */
     LVR_SEPARATE_KERNELS = 2u,
     /* Two-stream update (App. "GPU Update").  When an lvr_append fills the buffer, the B buffered
      * keys are grouped on a stream the library owns, into index slots beyond the published group

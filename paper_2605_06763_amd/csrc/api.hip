@@ -114,11 +114,12 @@ Sizes sizes_of(const lvr_config *c) {
     s.centres = al((size_t)n_bh * s.max_groups * c_row * (box ? 2 : 1));
     // boxes: one allowance; 8-bit balls: four bf16; 6-bit balls: four bf16 and four scale bytes
     s.radii = al((size_t)n_bh * s.max_groups * (box ? 1 : (fp6_centres(c) ? 3 : (fp8_centres(c) ? 2 : c->n_subspaces))) * sizeof(float));
-    s.list = al((size_t)n_bh * s.max_groups * sizeof(int32_t));
+    // the survivor list crosses a launch boundary only where the two stages are separate launches
+    s.list = (c->flags & LVR_SEPARATE_KERNELS) ? al((size_t)n_bh * s.max_groups * sizeof(int32_t)) : 0;
     s.counters = al(lvr_counter_ints((int)n_bh, (int)n_bhq, s.max_groups) * sizeof(int32_t));
     s.part_ml = al((size_t)n_bhq * s.Pmax * 2 * sizeof(float));
     s.part_o = al((size_t)n_bhq * s.Pmax * LVR_D * sizeof(float));
-    const bool fused_path = c->kv_dtype == LVR_BF16 && !(c->flags & LVR_SEPARATE_KERNELS);
+    const bool fused_path = !(c->flags & LVR_SEPARATE_KERNELS);
     s.scores = fused_path ? al((size_t)n_bhq * s.cap_rows * sizeof(float)) : 0;
     const bool kv_on_host = (c->flags & LVR_KV_IN_HOST_MEMORY) != 0;
     s.total = s.scores + (kv_on_host ? 0 : 2 * s.kv) + s.centres + s.radii + s.list + s.counters + s.part_ml + s.part_o;
@@ -152,9 +153,8 @@ void free_all(lvr_index *ix) {
         if (ix->V_host) (void)hipHostFree(ix->V_host);
         ix->K = ix->V = nullptr;
     }
-    void *ptrs[] = {ix->K, ix->V, ix->centres, ix->radii, ix->slot_pos, ix->pos_slot,
-                    ix->surv_list, ix->counters, ix->part_ml, ix->part_o, ix->tree_keys_a, ix->tree_keys_b,
-                    ix->tree_axis, ix->tree_partial, ix->chunk_K, ix->chunk_V, ix->reservoir, ix->scores,
+    void *ptrs[] = {ix->K, ix->V, ix->centres, ix->work, ix->slot_pos, ix->pos_slot, ix->tree_keys_a, ix->tree_keys_b,
+                    ix->tree_axis, ix->tree_partial, ix->chunk_K, ix->chunk_V, ix->reservoir,
                     ix->labels, ix->f_table};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -322,12 +322,22 @@ int lvr_create(const lvr_config *cfg, lvr_index **out) {
         if (e == hipSuccess) e = hipHostGetDevicePointer(&ix->V, ix->V_host, 0);
     }
     struct { void **p; size_t bytes; } allocs[] = {
-        {&ix->K, kv_on_host ? 0 : s.kv}, {&ix->V, kv_on_host ? 0 : s.kv}, {&ix->centres, s.centres}, {(void **)&ix->radii, s.radii},
-        {(void **)&ix->surv_list, s.list}, {(void **)&ix->counters, s.counters},
-        {(void **)&ix->part_ml, s.part_ml}, {(void **)&ix->part_o, s.part_o}, {(void **)&ix->scores, s.scores}};
+        {&ix->K, kv_on_host ? 0 : s.kv}, {&ix->V, kv_on_host ? 0 : s.kv}, {&ix->centres, s.centres},
+        {&ix->work, s.radii + s.list + s.counters + s.part_ml + s.part_o + s.scores}};
     for (auto &a : allocs) {
         if (e != hipSuccess) break;
         if (a.bytes) e = hipMalloc(a.p, a.bytes);
+    }
+    if (e == hipSuccess) {   // the small buffers share one allocation (every size is a multiple of 256 bytes)
+        char *at = static_cast<char *>(ix->work);
+        struct { void **p; size_t bytes; } parts[] = {
+            {(void **)&ix->radii, s.radii}, {(void **)&ix->surv_list, s.list}, {(void **)&ix->counters, s.counters},
+            {(void **)&ix->part_ml, s.part_ml}, {(void **)&ix->part_o, s.part_o}, {(void **)&ix->scores, s.scores}};
+        for (auto &a : parts)
+            if (a.bytes) {
+                *a.p = at;
+                at += a.bytes;
+            }
     }
     ix->per_subspace = cfg->grouping == LVR_GROUP_SUBSPACE_TREE;
     if (e == hipSuccess && ix->per_subspace) {
@@ -568,7 +578,8 @@ namespace {
 int enqueue_query(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx, int64_t cap, hipStream_t st,
                   const float *tau_s = nullptr, const void *k_new = nullptr, const void *v_new = nullptr,
                   int64_t m_new = 0) {
-    const bool fused = ix->cfg.kv_dtype == LVR_BF16 && !(ix->cfg.flags & LVR_SEPARATE_KERNELS);
+    const bool fused = !(ix->cfg.flags & LVR_SEPARATE_KERNELS);
+    const bool bf16 = ix->cfg.kv_dtype == LVR_BF16;
     if (ix->counters_dirty) {   // an earlier query never published its counts: start from zero again
         Timed t(ix, LVR_K_RESET, st);
         LVR_HIP(lvr_launch_reset(ix, st));
@@ -581,6 +592,10 @@ int enqueue_query(lvr_index *ix, const float *q, const float *tau, int32_t *out_
         }
         Timed t(ix, LVR_K_FILTER, st);
         LVR_HIP(lvr_launch_label_filter(ix, q, tau, out_idx, cap, st));
+    } else if (fused && !bf16) {
+        Timed t(ix, LVR_K_FILTER, st);
+        LVR_HIP(lvr_launch_query_f32(ix, q, tau, out_idx, cap, st, k_new, v_new, m_new));
+        ix->n_total += m_new;
     } else if (fused) {
         Timed t(ix, LVR_K_FILTER, st, true);
         LVR_HIP(lvr_launch_query_fused(ix, q, tau, tau_s, out_idx, cap, st, k_new, v_new, m_new));
@@ -597,7 +612,7 @@ int enqueue_query(lvr_index *ix, const float *q, const float *tau, int32_t *out_
     }
     ix->last_buffer_rows = ix->n_total - ix->n_indexed;
     ix->last_indexed = ix->n_indexed;
-    ix->last_skipped = fused && ix->skip_bounds && !tau_s;
+    ix->last_skipped = fused && bf16 && ix->skip_bounds && !tau_s;
     return LVR_OK;
 }
 
@@ -612,7 +627,7 @@ int decode_step_impl(lvr_index *ix, const float *q, const float *tau, float *out
     // it no longer found the retrieved K rows touched just before it.  On the present kernels the scores win for
     // every group size: 59.8 -> 57.1 us per step at 128k keys with r = 4 where every group survives, 24.7 -> 21.7
     // on keys with positional locality.)
-    const bool fused = ix->cfg.kv_dtype == LVR_BF16 && !(ix->cfg.flags & LVR_SEPARATE_KERNELS);
+    const bool fused = !(ix->cfg.flags & LVR_SEPARATE_KERNELS);
     const bool one_launch = one_launch_attention(ix, fused);
     const float *carried = fused ? ix->scores : nullptr;
     if (one_launch) {   // reads the set sizes from the internal counters and hands them to the caller
@@ -730,7 +745,7 @@ int lvr_append_decode_step(lvr_index *ix, const void *k_new, const void *v_new, 
     // The copy rides in the query launch when that launch has a buffer workgroup to do it and the
     // append needs nothing else (no chunk becomes full, no position maps, no reservoir, no update in
     // flight); otherwise the two calls run one after the other.
-    const bool rides = m > 0 && m <= 64 && ix->cfg.kv_dtype == LVR_BF16 && !(ix->cfg.flags & LVR_SEPARATE_KERNELS) &&
+    const bool rides = m > 0 && m <= 64 && !(ix->cfg.flags & LVR_SEPARATE_KERNELS) &&
                        !ix->slot_pos && !ix->reservoir && !ix->pending && !ix->per_subspace && aligned16(k_new) && aligned16(v_new) &&
                        ix->n_total + m - ix->n_indexed < ix->cfg.buffer_size;
     if (!rides) {

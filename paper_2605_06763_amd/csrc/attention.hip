@@ -335,13 +335,15 @@ sparse_attention_wg_carry_kernel(const void *__restrict__ V, const int32_t *__re
         }
         int myslot = -1;
         if (e < cnt && pos >= 0 && pos < n_total) myslot = pslot ? pslot[pos] : (int)pos;
-        // trip 2: batch bq of this wave is entries base + (wave + 16 bq) * 16 ..; row i * 4 + sub of it is held by lane 16 bq + i * 4 + sub
-        lvr_raw8<KT> vr[16];
+        // trip 2: batch bq of this wave is entries base + (wave + 16 bq) * 16 ..; row i * 4 + sub of it is held by lane 16 bq + i * 4 + sub.
+        // All four batches are in flight; fp32 rows are twice as wide: two batches at a time fit the registers of 16 waves
+        constexpr int NB = sizeof(KT) == sizeof(lvr_bf16_t) ? 4 : 2;
+        lvr_raw8<KT> vr[NB * 4];
         bool have[4];
 #pragma unroll
         for (int bq = 0; bq < 4; ++bq) {
             have[bq] = base + (int64_t)(wave + NW * bq) * 16 < cnt;   // wave-uniform
-            if (have[bq]) {
+            if (bq < NB && have[bq]) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int sl = __shfl(myslot, 16 * bq + i * 4 + sub, 64);
@@ -373,9 +375,21 @@ sparse_attention_wg_carry_kernel(const void *__restrict__ V, const int32_t *__re
                 for (int i = 0; i < 4; ++i) {
                     const float w = __shfl(w_e, 16 * bq + i * 4 + sub, 64);   // 0 for a masked entry
                     float vx[8];
-                    lvr_unpack(vr[bq * 4 + i], vx);
+                    lvr_unpack(vr[(bq % NB) * 4 + i], vx);
 #pragma unroll
                     for (int c = 0; c < 8; ++c) acc[c] += w * vx[c];
+                }
+            }
+            if (NB < 4 && bq == NB - 1) {   // the other half of the batches
+#pragma unroll
+                for (int b2 = NB; b2 < 4; ++b2) {
+                    if (have[b2]) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int sl = __shfl(myslot, 16 * b2 + i * 4 + sub, 64);
+                            lvr_load_raw(Vb, sl < 0 ? 0 : sl, li, vr[(b2 % NB) * 4 + i]);
+                        }
+                    }
                 }
             }
         }
@@ -948,7 +962,12 @@ hipError_t lvr_launch_sparse_attention_wg(lvr_index *ix, const float *q, const i
                                lvr_head_stat(ix), publish_count);
         else LVR_WG_LAUNCH(lvr_bf16_t, false);
     } else {
-        if (scores) LVR_WG_LAUNCH(lvr_f32_t, true);
+        if (scores && n_bhq > 256) LVR_WG_LAUNCH(lvr_f32_t, true);   // as above: more heads than compute units
+        else if (scores)
+            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_f32_t>), dim3((unsigned)n_bhq), ix->V,
+                               ix->pos_slot, idx, scores, ix->cap_rows, count, count_stride, cap, out, ix->cap_rows,
+                               ix->n_total, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale, lvr_head_count(ix),
+                               lvr_head_stat(ix), publish_count);
         else LVR_WG_LAUNCH(lvr_f32_t, false);
     }
 #undef LVR_WG_LAUNCH

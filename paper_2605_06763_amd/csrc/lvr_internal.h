@@ -60,7 +60,8 @@ struct lvr_index {
     int64_t tree_cap_keys;                 // keys tree_keys_* can hold
     void *chunk_K, *chunk_V;               // [n_bh][B][d] staging of a buffer chunk being regrouped
     // work space (device)
-    int32_t *surv_list;    // [batch][H_kv][max_groups]: segment x owns entries [x*seg_groups, (x+1)*seg_groups)
+    void *work;            // the allocation behind radii, surv_list, counters, part_ml, part_o and scores
+    int32_t *surv_list;    // [batch][H_kv][max_groups]: segment x owns entries [x*seg_groups, (x+1)*seg_groups); NULL unless the stages are separate launches
     int32_t *counters;     // see lvr_head_count / lvr_overflow_flag / lvr_seg_count
     int seg_groups;        // groups per segment used by the last bound test
     int n_segs;            // segments per (sequence, KV head) filled by the last bound test (0: none)
@@ -102,7 +103,7 @@ static inline int lvr_n_bhq(const lvr_index *ix) { return ix->cfg.batch * ix->cf
 // (about 12 ns each on this part), so every counter that takes atomics owns a whole line.
 #define LVR_CNT_STRIDE 32   // ints per counter slot (128 bytes)
 #define LVR_CHAN_STRIDE (LVR_D + LVR_D * 4)   // bytes of channel scaling per (sequence, KV head): 128 exponents, 128 factors
-#define LVR_MIN_SEG_GROUPS 64
+#define LVR_MIN_SEG_GROUPS 16
 // per query head: size of the retrieved set of the running query (padded).  Zero between
 // queries: the kernel that publishes the counts clears them.
 static inline int32_t *lvr_head_count(const lvr_index *ix) { return ix->counters; }
@@ -150,6 +151,9 @@ hipError_t lvr_launch_filter(lvr_index *ix, const float *q, const float *tau, in
 hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *tau, const float *tau_s, int32_t *out_idx,
                                   int64_t cap, hipStream_t st, const void *k_new = nullptr, const void *v_new = nullptr,
                                   int64_t m_new = 0);
+// the same for fp32 caches (Query 2 only)
+hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx, int64_t cap,
+                                hipStream_t st, const void *k_new = nullptr, const void *v_new = nullptr, int64_t m_new = 0);
 // internal per-head counters -> caller's array and the statistics copy; clears the counters
 hipError_t lvr_launch_publish_counts(lvr_index *ix, int32_t *out_count, hipStream_t st);
 // partial softmax per (head, split); count is read with the given stride (1 = caller's array)

@@ -165,3 +165,61 @@ def test_tree_order_is_the_recursive_median_split(G, dtype, r, n, ties):
         got = slot_pos[0, kv, :groups * r]
         # axes whose variances tie to rounding may be chosen differently; everything else is exact
         assert np.array_equal(got, want) or (ties and (got == want).mean() > 0.5), (got != want).sum()
+
+
+@pytest.mark.parametrize("hq,hkv,n,r,S,tail,kw", [
+    (1, 1, 64, 4, 4, 0, {}), (1, 1, 4096, 4, 4, 0, {}), (2, 1, 1000, 2, 1, 3, {}), (8, 2, 4095, 4, 16, 131, {}),
+    (8, 1, 8192, 1, 2, 255, dict(query_workgroups=16)), (4, 4, 5000, 16, 8, 17, dict(buffer_size=32)),
+    (8, 2, 2048, 4, 4, 40, dict(tree=True)), (4, 1, 3, 4, 4, 5, {}), (4, 2, 700, 4, 4, 100, dict(dense_buffer=True)),
+    (4, 2, 700, 4, 4, 300, dict(concurrent=True))])
+def test_fp32_one_launch_query_is_the_two_launch_one(G, oracle, hq, hkv, n, r, S, tail, kw):
+    """The fused fp32 query against the separate bound test and filter (LVR_SEPARATE_KERNELS): the same sets and counts for
+    every head count, block count, group size, segment remainder, buffer content and option, with thresholds that keep
+    few keys, everything and nothing, room for fewer entries than there are, and an append that rides in the launch; the
+    attention over them against the oracle."""
+    L = G.L
+    g = np.random.default_rng(n + hq)
+    K = g.standard_normal((1, hkv, n + tail + 2, 128)).astype(np.float32)
+    V = g.standard_normal((1, hkv, n + tail + 2, 128)).astype(np.float32)
+    q = g.standard_normal((1, hq, 128)).astype(np.float32)
+    flags = (L.LVR_ATTEND_BUFFER_DENSE if kw.get("dense_buffer") else 0) | (L.LVR_CONCURRENT_UPDATE if kw.get("concurrent") else 0)
+    opt = {k: v for k, v in kw.items() if k in ("query_workgroups", "buffer_size")}
+    if kw.get("tree"):
+        opt["grouping"] = L.LVR_GROUP_TREE
+    total = n + tail
+    scores = np.stack([np.sort(K[0, h * hkv // hq, :total] @ q[0, h])[::-1] for h in range(hq)])
+    few = max(1, total // 50)
+    taus = [0.5 * (scores[:, few - 1] + scores[:, few])[None] if total > few else scores[:, :1].T - 1.0,
+            np.full((1, hq), -np.inf), np.full((1, hq), 1e9)]
+    got = {}
+    for name, extra in (("fused", 0), ("separate", L.LVR_SEPARATE_KERNELS)):
+        with G.Index(K[:, :, :n], V[:, :, :n], "f32", hq, capacity=n + tail + 2, group_size=r, n_subspaces=S, flags=flags | extra, **opt) as ix:
+            if tail:
+                ix.append(K[:, :, n:total], V[:, :, n:total])
+            res = []
+            for tau in taus:
+                tau = tau.astype(np.float32)
+                for cap in (total, max(1, few // 2)):
+                    idx, cnt, out = ix.query(q, tau, cap=cap, fused=True)
+                    ix.stats(raise_on_overflow=False)
+                    if cap == total and not kw.get("dense_buffer"):
+                        G.check_step(oracle, ix, q, tau, idx, cnt, out, tag=f"f32 {name}")
+                    res.append((cnt, [np.sort(idx[0, h, :min(cnt[0, h], cap)]) if cap == total else None for h in range(hq)],
+                                out if cap == total else None))
+            # two more tokens, the first appended by the step itself
+            kn, vn = G.to_device(K[:, :, total:total + 1], "f32"), G.to_device(V[:, :, total:total + 1], "f32")
+            qd, td = torch.from_numpy(q).cuda(), torch.from_numpy(taus[0].astype(np.float32)).cuda()
+            idx = torch.zeros((1, hq, total + 2), dtype=torch.int32, device="cuda")
+            cnt = torch.zeros((1, hq), dtype=torch.int32, device="cuda")
+            out = torch.zeros((1, hq, 128), device="cuda")
+            L.lvr_append_decode_step(ix.h, kn, vn, qd, td, out, idx, cnt)
+            torch.cuda.synchronize()
+            res.append((cnt.cpu().numpy(), [np.sort(idx[0, h, :int(cnt[0, h])].cpu().numpy()) for h in range(hq)], out.cpu().numpy()))
+            got[name] = res
+    for (c1, s1, o1), (c2, s2, o2) in zip(got["fused"], got["separate"]):
+        assert np.array_equal(c1, c2)
+        for a, b in zip(s1, s2):
+            assert a is None or np.array_equal(a, b)
+        if o1 is not None:
+            # weights of logits of magnitude below 60, each good to 128 * 2^-24 of the sum of its terms' magnitudes
+            assert np.abs(o1 - o2).max() <= 1e-4
