@@ -24,7 +24,7 @@
 //
 // A build of 8 x 32768 bf16 keys in groups of four (five levels above 1024 entries, eight below) took
 // 2.5 ms with one wave per SIMD on the statistics, a device-wide 64-bit radix sort per level and
-// four waves per small node; this construction takes 0.36 ms (tree build and one step: 2321 -> 450 us).
+// four waves per small node; this construction takes 0.33 ms (tree build and one step: 2321 -> 424 us).
 #include <type_traits>
 
 #include "lvr_internal.h"
@@ -125,11 +125,19 @@ __device__ __forceinline__ void sum_rows64(const TreeSrc &src, int bh, int lane,
             const bool in = (real >> (j0 + u)) & 1ull;   // uniform
             lane_pair<ELT>(base + (int64_t)(in ? pos : any) * row_bytes, lane, x0[u], x1[u]);
         }
+        if (((real >> j0) & 0xffffull) == 0xffffull) {   // uniform: no padding among them
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const bool in = (real >> (j0 + u)) & 1ull;
-            const double d0 = in ? (double)x0[u] - (double)p0 : 0., d1 = in ? (double)x1[u] - (double)p1 : 0.;
-            s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
+            for (int u = 0; u < 16; ++u) {
+                const double d0 = (double)x0[u] - (double)p0, d1 = (double)x1[u] - (double)p1;
+                s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const bool in = (real >> (j0 + u)) & 1ull;
+                const double d0 = in ? (double)x0[u] - (double)p0 : 0., d1 = in ? (double)x1[u] - (double)p1 : 0.;
+                s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
+            }
         }
     }
 }
@@ -177,14 +185,12 @@ tree_stats_piece_kernel(TreeSrc src, const uint32_t *__restrict__ order, double 
     }
 }
 
-// Adds the pieces of a node (eight slices of them side by side) and picks the axis.
-__global__ void __launch_bounds__(1024)
-tree_axis_kernel(const double *__restrict__ partial, int32_t *__restrict__ axis, int64_t np, int64_t m, int64_t n_nodes,
-                 int c_lo, int c_hi) {
+// Adds the pieces of a node (eight slices of them side by side, 1024 threads) and picks the axis; every thread gets it.
+__device__ __forceinline__ int node_axis(const double *__restrict__ partial, int bh, int64_t np, int64_t m, int64_t node, int c_lo, int c_hi) {
     __shared__ double sm[8][2][128];
     __shared__ double sc[8];
-    const int bh = blockIdx.y, t = threadIdx.x, c = t & 127, sl = t >> 7;
-    const int64_t node = blockIdx.x;
+    __shared__ int s_axis;
+    const int t = threadIdx.x, c = t & 127, sl = t >> 7;
     const int64_t pieces = m / PIECE;
     const double *pp = partial + ((int64_t)bh * (np / PIECE) + node * pieces) * 258;
     double s = 0.0, q = 0.0, cnt = 0.0;
@@ -207,8 +213,18 @@ tree_axis_kernel(const double *__restrict__ partial, int32_t *__restrict__ axis,
         }
         const double v0 = n > 0 ? (q0 - s0 * s0 / n) / n : 0., v1 = n > 0 ? (q1 - s1 * s1 / n) / n : 0.;
         const int a = wave_argmax(v0, v1, t, c_lo, c_hi);
-        if (t == 0) axis[(int64_t)bh * n_nodes + node] = a;
+        if (t == 0) s_axis = a;
     }
+    __syncthreads();
+    return s_axis;
+}
+
+// The axis of every node whose codes are fetched by a launch of their own.
+__global__ void __launch_bounds__(1024)
+tree_axis_kernel(const double *__restrict__ partial, int32_t *__restrict__ axis, int64_t np, int64_t m, int64_t n_nodes,
+                 int c_lo, int c_hi) {
+    const int a = node_axis(partial, blockIdx.y, np, m, blockIdx.x, c_lo, c_hi);
+    if (threadIdx.x == 0) axis[(int64_t)blockIdx.y * n_nodes + blockIdx.x] = a;
 }
 
 // Code of every entry on its node's axis (nodes large enough that the whole device should fetch them).
@@ -227,12 +243,17 @@ tree_codes_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
 // [w m/16, (w+1) m/16).  The code of the m/2-th smallest entry is found digit by digit (11 bits at a time: the leading
 // digit of a bf16 code holds sign, exponent and two bits of the fraction, enough that the counters of one LDS pass are not
 // all the same), then entries below it, and as many entries equal to it as the half still needs, in order, go left.
-// GATHER: the codes are fetched from the rows here (small nodes: there are many workgroups), else they are given.
-// Bound by the latency of its passes over the codes (from L2): about 2 us each at 32768 entries.
-template <int ELT, bool GATHER>
+// STEPS: entries per thread that are held in registers with their codes (m <= 1024 STEPS); 0: any m, both re-read per pass.
+// GATHER: the workgroup picks the axis from the partial statistics and fetches the codes from the rows itself (small nodes:
+// there are many workgroups); else the codes are given.
+// Bound by latency: the fetch of the entries, a pass over LDS counters per digit, the stores: 18 us for 8 nodes of 32768
+// entries (22 with the codes read again in every pass), 20, 13 and 11 us for 32 to 128 nodes down to 2048 entries (with the
+// axis in a launch of its own 27, 19 and 16).
+template <int ELT, int STEPS, bool GATHER>
 __global__ void __launch_bounds__(1024)
-tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__restrict__ out, uint32_t *codes,
-                  const int32_t *__restrict__ axis, int64_t np, int64_t n_real, int64_t m, int64_t n_nodes) {
+tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__restrict__ out, const uint32_t *__restrict__ codes,
+                  const double *__restrict__ partial, int64_t np, int64_t n_real, int64_t m, int c_lo, int c_hi) {
+    static_assert(!GATHER || STEPS > 0, "fetched codes are held in registers");
     __shared__ uint32_t s_hist[2048];
     __shared__ int s_tot[16], s_eq[16];
     __shared__ uint32_t s_digit;
@@ -240,32 +261,45 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int bh = blockIdx.y;
     const int64_t node0 = (int64_t)blockIdx.x * m, at0 = (int64_t)bh * np + node0;
-    const int share = (int)(m / 16), first = wave * share;   // a multiple of 64 entries per wave
-    uint32_t *cd = codes + at0;
-    const int ax = axis[(int64_t)bh * n_nodes + blockIdx.x];
-    auto pos_of = [&](int i) { return order ? (int64_t)order[at0 + i] : node0 + i; };
-    const int steps = share >> 6;
-    // f(i, code) for this thread's entries, eight codes requested before the first is used; the trip count and the
-    // conditions are the same in every lane, so f may use ballots
-    auto for_codes = [&](auto f) {
-        for (int b = 0; b < steps; b += 8) {
-            uint32_t c[8];
+    const int steps = (int)(m / 1024), first = wave * steps * 64 + lane;   // this thread's entries: first + 64 k, k < steps
+    auto pos_of = [&](int i) { return order ? order[at0 + i] : (uint32_t)(node0 + i); };
+    uint32_t code[STEPS ? STEPS : 1], entry[STEPS ? STEPS : 1];
+    if constexpr (STEPS > 0) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (b + u < steps) c[u] = cd[first + (b + u) * 64 + lane];
+        for (int k = 0; k < STEPS; ++k)
+            if (k < steps) entry[k] = pos_of(first + 64 * k);   // uniform conditions throughout
+        if constexpr (GATHER) {
+            const int ax = node_axis(partial, bh, np, m, blockIdx.x, c_lo, c_hi);
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (b + u < steps) f(first + (b + u) * 64 + lane, c[u]);
-        }
-    };
-    if constexpr (GATHER) {   // every thread reads back only what it has written itself
-#pragma unroll 4
-        for (int k = 0; k < steps; ++k) {
-            const int i = first + k * 64 + lane;
-            const int64_t pos = pos_of(i);
-            cd[i] = pos < n_real ? coord_code<ELT>(src.row(bh, pos), ax) : PAD_CODE<ELT>;
+            for (int k = 0; k < STEPS; ++k)
+                if (k < steps) code[k] = entry[k] < n_real ? coord_code<ELT>(src.row(bh, entry[k]), ax) : PAD_CODE<ELT>;
+        } else {
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k)
+                if (k < steps) code[k] = codes[at0 + first + 64 * k];
         }
     }
+    // f(i, code, entry) for this thread's entries; the conditions are the same in every lane, so f may use ballots
+    auto for_codes = [&](bool entries, auto f) {
+        if constexpr (STEPS > 0) {
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k)
+                if (k < steps) f(first + 64 * k, code[k], entry[k]);
+        } else {
+            for (int b = 0; b < steps; b += 8) {   // eight at a time
+                uint32_t c[8], p[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (b + u < steps) {
+                        c[u] = codes[at0 + first + 64 * (b + u)];
+                        p[u] = entries ? pos_of(first + 64 * (b + u)) : 0u;
+                    }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (b + u < steps) f(first + 64 * (b + u), c[u], p[u]);
+            }
+        }
+    };
     int rank = (int)(m / 2);   // the entry looked for is the rank-th smallest (from 1) of those that share `known`
     uint32_t known = 0, known_mask = 0;
     constexpr int BITS = ELT * 8;
@@ -275,7 +309,7 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
         s_hist[t] = 0;
         s_hist[t + 1024] = 0;
         __syncthreads();
-        for_codes([&](int, uint32_t c) {
+        for_codes(false, [&](int, uint32_t c, uint32_t) {
             if ((c & known_mask) == known) atomicAdd(&s_hist[(c >> shift) & ((1u << width) - 1u)], 1u);
         });
         __syncthreads();
@@ -297,7 +331,7 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
     }
     // `known` is the median code, `rank` (>= 1) the number of entries equal to it that go left
     int n_lt = 0, n_eq = 0;
-    for_codes([&](int, uint32_t c) {
+    for_codes(false, [&](int, uint32_t c, uint32_t) {
         n_lt += (int)__popcll(__ballot(c < known));
         n_eq += (int)__popcll(__ballot(c == known));
     });
@@ -315,8 +349,7 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
     int eq_left = rank - eq_before;   // equal entries this wave may still send left
     uint32_t *ob = out + at0;
     const uint64_t below = (1ull << lane) - 1ull;
-    for_codes([&](int i, uint32_t c) {
-        const uint32_t pos = (uint32_t)pos_of(i);
+    for_codes(true, [&](int i, uint32_t c, uint32_t pos) {
         const uint64_t eq = __ballot(c == known);
         // (the count as int: eq_left goes below zero once the half has all the equal entries it needs)
         const bool left = c < known || (c == known && (int)__popcll(eq & below) < eq_left);
@@ -508,19 +541,23 @@ hipError_t tree_order_t(lvr_index *ix, const TreeSrc &src, int64_t n_real, int64
         const int64_t n_nodes = (int64_t)1 << L, m = np >> L;
         hipLaunchKernelGGL(tree_stats_piece_kernel<ELT>, dim3((unsigned)(np / PIECE), (unsigned)n_bh), dim3(1024), 0, st, src,
                            cur, ix->tree_partial, np, n_real, m);
-        hipLaunchKernelGGL(tree_axis_kernel, dim3((unsigned)n_nodes, (unsigned)n_bh), dim3(1024), 0, st, ix->tree_partial,
-                           ix->tree_axis, np, m, n_nodes, c_lo, c_hi);
         uint32_t *next = half[L & 1];
+        const dim3 nodes((unsigned)n_nodes, (unsigned)n_bh);
         // nodes of more than 8192 entries leave most of the device idle in the split launch (a workgroup fetches a
         // coordinate of 64 different rows at about one row per clock): there the codes are a launch of their own
         if (m > 8192) {
+            hipLaunchKernelGGL(tree_axis_kernel, nodes, dim3(1024), 0, st, ix->tree_partial, ix->tree_axis, np, m, n_nodes, c_lo, c_hi);
             hipLaunchKernelGGL(tree_codes_kernel<ELT>, dim3((unsigned)(np / 256), (unsigned)n_bh), dim3(256), 0, st, src, cur,
                                codes, ix->tree_axis, np, n_real, m, n_nodes);
-            hipLaunchKernelGGL((tree_split_kernel<ELT, false>), dim3((unsigned)n_nodes, (unsigned)n_bh), dim3(1024), 0, st, src,
-                               cur, next, codes, ix->tree_axis, np, n_real, m, n_nodes);
+            if (m <= 32768)
+                hipLaunchKernelGGL((tree_split_kernel<ELT, 32, false>), nodes, dim3(1024), 0, st, src, cur, next, codes,
+                                   ix->tree_partial, np, n_real, m, c_lo, c_hi);
+            else
+                hipLaunchKernelGGL((tree_split_kernel<ELT, 0, false>), nodes, dim3(1024), 0, st, src, cur, next, codes,
+                                   ix->tree_partial, np, n_real, m, c_lo, c_hi);
         } else {
-            hipLaunchKernelGGL((tree_split_kernel<ELT, true>), dim3((unsigned)n_nodes, (unsigned)n_bh), dim3(1024), 0, st, src,
-                               cur, next, codes, ix->tree_axis, np, n_real, m, n_nodes);
+            hipLaunchKernelGGL((tree_split_kernel<ELT, 8, true>), nodes, dim3(1024), 0, st, src, cur, next, codes,
+                               ix->tree_partial, np, n_real, m, c_lo, c_hi);
         }
         cur = next;
     }
