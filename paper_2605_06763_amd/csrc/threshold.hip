@@ -39,27 +39,30 @@ __global__ void reservoir_update_kernel(int32_t *res, int R, uint64_t seed, int6
     if (j < R) atomicMax(&res[(int64_t)bh * R + j], (int32_t)i);
 }
 
-// One 256-thread workgroup per query head: scores of the reservoir keys (16 lanes per row), put in descending order,
-// then the rule.  Bound by latency: positions, then rows, then the ordering.  A wave's 64 positions come with one load and
-// all its rows are requested before the first is used (fp32 rows in two halves), and the order is found by counting:
-// thread t finds the rank of score t among the 256 (64 broadcast reads of LDS, no barrier between them) and stores it there.
-// With a dependent load of position and row per four keys, a bitonic sort (36 barriers) and a serial count of the valid
-// scores the launch took 28 us for 32 heads; with it gone, threshold and step together went from 50.0 to 33.6 us.
+// One 1024-thread workgroup per query head: scores of the reservoir keys (16 lanes per row), put in descending order,
+// then the rule.  Bound by latency: positions, then rows, then the ordering.  A wave takes 16 slots: their positions come
+// with one load and their rows are in flight together.  The order is found by counting: four threads per score compare it
+// with a quarter of the 256 each (16 broadcast reads of LDS), and the score goes to the place its rank says.
+// With four waves, a dependent load of position and row per four keys, a bitonic sort (36 barriers) and a serial count of
+// the valid scores the launch took 28 us for 32 heads, with rows in flight and ranks but four waves 12.9; now 7.0 (threshold and step:
+// 50.0, 33.6, 27.7 us).
 template <typename KT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slot, const int32_t *__restrict__ res,
                  const float *__restrict__ q, float *__restrict__ tau_out, int R, int64_t cap_rows, int64_t n_total,
                  int n_q_heads, int n_kv_heads, int G, int mode, float param) {
     __shared__ __align__(16) uint32_t s_key[256];
+    __shared__ int s_rank[4][256];
     __shared__ float s[256];
     const int64_t hq = blockIdx.x;
     const int b = (int)(hq / n_q_heads), h = (int)(hq % n_q_heads);
     const int bh = b * n_kv_heads + h / G;
-    const int t = threadIdx.x, lane = t & 63, li = lane & 15;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, sub = lane >> 4, li = lane & 15;
     const int32_t *rb = res + (int64_t)bh * R;
     const int32_t *pslot = pos_slot ? pos_slot + (int64_t)bh * cap_rows : nullptr;
-    // a lane quarter takes the 16 reservoir slots its lanes' threads are numbered by; lane li holds the arena row of slot li
-    const int pos = t < R ? rb[t] : -1;
+    // lane li of every quarter holds the arena row of the wave's slot li
+    const int mine = wave * 16 + li;
+    const int pos = mine < R ? rb[mine] : -1;
     const bool have = pos >= 0 && pos < n_total;
     const int slot = have ? (pslot ? pslot[pos] : pos) : -1;
     float qv[8];
@@ -69,42 +72,44 @@ threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slo
         for (int e = 0; e < 8; ++e) qv[e] = qh[e];
     }
     const char *Kb = static_cast<const char *>(K) + (int64_t)bh * cap_rows * LVR_D * sizeof(KT);
-    constexpr int BATCH = sizeof(KT) == sizeof(lvr_bf16_t) ? 16 : 8;
-    float score = -INFINITY;   // of slot t
+    lvr_raw8<KT> raw[4];
+    int row[4];
 #pragma unroll
-    for (int u0 = 0; u0 < 16; u0 += BATCH) {
-        lvr_raw8<KT> raw[BATCH];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int row = __shfl(slot, (lane & 48) + u0 + u, 64);
-            lvr_load_raw(Kb, row < 0 ? 0 : row, li, raw[u]);   // row 0 is part of the arena whatever it holds
-        }
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            float x[8];
-            lvr_unpack(raw[u], x);
-            float d = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) d += qv[e] * x[e];
-            d = lvr_row16_sum(d);
-            score = (li == u0 + u && have) ? d : score;
-        }
+    for (int i = 0; i < 4; ++i) {
+        row[i] = __shfl(slot, 4 * i + sub, 64);
+        lvr_load_raw(Kb, row[i] < 0 ? 0 : row[i], li, raw[i]);   // row 0 is part of the arena whatever it holds
     }
-    // descending order: unsigned keys in the order of the floats, equal scores in the order of their slots
-    const uint32_t bits = __float_as_uint(score);
-    const uint32_t key = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
-    s_key[t] = key;
-    const int m = __syncthreads_count(score != -INFINITY);   // valid scores come first
-    int rank = 0;
-#pragma unroll 8
-    for (int i = 0; i < 256; i += 4) {
-        const uint4 o = *reinterpret_cast<const uint4 *>(&s_key[i]);
-        rank += (o.x > key || (o.x == key && i < t)) ? 1 : 0;
-        rank += (o.y > key || (o.y == key && i + 1 < t)) ? 1 : 0;
-        rank += (o.z > key || (o.z == key && i + 2 < t)) ? 1 : 0;
-        rank += (o.w > key || (o.w == key && i + 3 < t)) ? 1 : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x[8];
+        lvr_unpack(raw[i], x);
+        float d = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) d += qv[e] * x[e];
+        d = lvr_row16_sum(d);
+        // unsigned keys in the order of the floats
+        const uint32_t bits = __float_as_uint(row[i] >= 0 ? d : -INFINITY);
+        if (li == 0) s_key[wave * 16 + 4 * i + sub] = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
     }
-    s[rank] = score;
+    __syncthreads();
+    // descending order, equal scores in the order of their slots
+    const int j = t & 255, quarter = t >> 8;
+    const uint32_t key = s_key[j];
+    {
+        int rank = 0;
+#pragma unroll
+        for (int i = quarter * 64; i < quarter * 64 + 64; i += 4) {
+            const uint4 o = *reinterpret_cast<const uint4 *>(&s_key[i]);
+            rank += (o.x > key || (o.x == key && i < j)) ? 1 : 0;
+            rank += (o.y > key || (o.y == key && i + 1 < j)) ? 1 : 0;
+            rank += (o.z > key || (o.z == key && i + 2 < j)) ? 1 : 0;
+            rank += (o.w > key || (o.w == key && i + 3 < j)) ? 1 : 0;
+        }
+        s_rank[quarter][j] = rank;
+    }
+    const float score = __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xffffffffu));
+    const int m = __syncthreads_count(t < 256 && score != -INFINITY);   // valid scores come first
+    if (t < 256) s[s_rank[0][t] + s_rank[1][t] + s_rank[2][t] + s_rank[3][t]] = score;
     __syncthreads();
     if (t == 0) {
         float tau = -INFINITY;
@@ -156,11 +161,11 @@ hipError_t lvr_launch_reservoir_update(lvr_index *ix, int64_t pos0, int64_t coun
 hipError_t lvr_launch_threshold(lvr_index *ix, const float *q, int mode, float param, float *tau_out, hipStream_t st) {
     const int n_bhq = lvr_n_bhq(ix);
     if (ix->cfg.kv_dtype == LVR_BF16)
-        hipLaunchKernelGGL(threshold_kernel<lvr_bf16_t>, dim3((unsigned)n_bhq), dim3(256), 0, st, ix->K, ix->pos_slot,
+        hipLaunchKernelGGL(threshold_kernel<lvr_bf16_t>, dim3((unsigned)n_bhq), dim3(1024), 0, st, ix->K, ix->pos_slot,
                            ix->reservoir, q, tau_out, ix->cfg.reservoir_size, ix->cap_rows, ix->n_total,
                            ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, mode, param);
     else
-        hipLaunchKernelGGL(threshold_kernel<lvr_f32_t>, dim3((unsigned)n_bhq), dim3(256), 0, st, ix->K, ix->pos_slot,
+        hipLaunchKernelGGL(threshold_kernel<lvr_f32_t>, dim3((unsigned)n_bhq), dim3(1024), 0, st, ix->K, ix->pos_slot,
                            ix->reservoir, q, tau_out, ix->cfg.reservoir_size, ix->cap_rows, ix->n_total,
                            ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, mode, param);
     return hipGetLastError();
