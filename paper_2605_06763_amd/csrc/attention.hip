@@ -297,11 +297,10 @@ sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ 
 // Lists longer than 1024 entries take further rounds of two trips each.
 template <typename KT>
 __global__ void __launch_bounds__(1024)
-sparse_attention_wg_carry_kernel(const void *__restrict__ V, const int32_t *__restrict__ pos_slot,
-                                 const int32_t *__restrict__ idx, const float *__restrict__ scores, int64_t score_stride,
-                                 const int32_t *count, int count_stride,   // may alias head_count: not restrict
-                                 int64_t cap, float *__restrict__ out, int64_t cap_rows, int64_t n_total, int n_q_heads,
-                                 int n_kv_heads, int G, float qscale, int32_t *head_count,
+sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count: not restrict
+                                 const int32_t *__restrict__ idx, const float *__restrict__ scores, const void *__restrict__ V,
+                                 int64_t cap, int count_stride, int cap_rows, int n_total, int G,
+                                 const int32_t *__restrict__ pos_slot, float *__restrict__ out, float qscale, int32_t *head_count,
                                  int32_t *__restrict__ head_stat, int32_t *__restrict__ publish_count) {
     constexpr int NW = 16;
     __shared__ float s_m[NW], s_l[NW];
@@ -310,7 +309,7 @@ sparse_attention_wg_carry_kernel(const void *__restrict__ V, const int32_t *__re
     const int bh = (int)((uint32_t)hq / (uint32_t)G);   // (hq / H_q) * H_kv + (hq % H_q) / G with H_q = H_kv * G: one 32-bit division
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane >> 4, li = lane & 15;
     const int32_t *my_idx = idx + hq * cap;
-    const float *my_sc = scores + hq * score_stride;
+    const float *my_sc = scores + hq * (int64_t)cap_rows;
     const char *Vb = static_cast<const char *>(V) + (int64_t)bh * cap_rows * LVR_D * sizeof(KT);
     const int32_t *pslot = pos_slot ? pos_slot + (int64_t)bh * cap_rows : nullptr;
 
@@ -319,7 +318,7 @@ sparse_attention_wg_carry_kernel(const void *__restrict__ V, const int32_t *__re
     int64_t cnt = count[hq * count_stride];
     const int64_t e_rel = (int64_t)(wave + NW * sub) * 16 + li;   // this lane's entry within a round of 1024
     int32_t pos = (e_rel < cap) ? my_idx[e_rel] : -1;
-    float sc = (e_rel < cap && e_rel < score_stride) ? my_sc[e_rel] : 0.f;
+    float sc = (e_rel < cap && e_rel < cap_rows) ? my_sc[e_rel] : 0.f;
     const int32_t true_cnt = (int32_t)cnt;
     if (cnt > cap) cnt = cap;
     if (cnt < 0) cnt = 0;
@@ -331,7 +330,7 @@ sparse_attention_wg_carry_kernel(const void *__restrict__ V, const int32_t *__re
         const int64_t e = base + e_rel;
         if (base > 0) {
             pos = (e < cnt) ? my_idx[e] : -1;
-            sc = (e < cnt && e < score_stride) ? my_sc[e] : 0.f;
+            sc = (e < cnt && e < cap_rows) ? my_sc[e] : 0.f;
         }
         int myslot = -1;
         if (e < cnt && pos >= 0 && pos < n_total) myslot = pslot ? pslot[pos] : (int)pos;
@@ -435,11 +434,10 @@ sparse_attention_wg_carry_kernel(const void *__restrict__ V, const int32_t *__re
 // one that draws the second ticket publishes the count and clears the head's counter when it ends.
 template <typename KT, int SPLIT>
 __global__ void __launch_bounds__(1024)
-sparse_attention_wg_carry_split_kernel(const void *__restrict__ V, const int32_t *__restrict__ pos_slot,
-                                 const int32_t *__restrict__ idx, const float *__restrict__ scores, int64_t score_stride,
-                                 const int32_t *count, int count_stride,   // may alias head_count: not restrict
-                                 int64_t cap, float *__restrict__ out, int64_t cap_rows, int64_t n_total, int n_q_heads,
-                                 int n_kv_heads, int G, float qscale, int32_t *head_count,
+sparse_attention_wg_carry_split_kernel(const int32_t *count,   // may alias head_count: not restrict
+                                 const int32_t *__restrict__ idx, const float *__restrict__ scores, const void *__restrict__ V,
+                                 int64_t cap, int count_stride, int cap_rows, int n_total, int G,
+                                 const int32_t *__restrict__ pos_slot, float *__restrict__ out, float qscale, int32_t *head_count,
                                  int32_t *__restrict__ head_stat, int32_t *__restrict__ publish_count,
                                  int32_t *__restrict__ ticket) {
     constexpr int NW = 16;
@@ -455,7 +453,7 @@ sparse_attention_wg_carry_split_kernel(const void *__restrict__ V, const int32_t
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane >> 4, li = lane & 15;
     const int grp = lane / LPR, lp = lane % LPR;   // this lane's row within a load, its 16-byte piece of the row part
     const int32_t *my_idx = idx + hq * cap;
-    const float *my_sc = scores + hq * score_stride;
+    const float *my_sc = scores + hq * (int64_t)cap_rows;
     const char *Vb = static_cast<const char *>(V) + (int64_t)bh * cap_rows * LVR_D * sizeof(KT);
     const int32_t *pslot = pos_slot ? pos_slot + (int64_t)bh * cap_rows : nullptr;
 
@@ -464,7 +462,7 @@ sparse_attention_wg_carry_split_kernel(const void *__restrict__ V, const int32_t
     int64_t cnt = count[hq * count_stride];
     const int64_t e_rel = (int64_t)(wave + NW * sub) * 16 + li;   // this lane's entry within a round of 1024
     int32_t pos = (e_rel < cap) ? my_idx[e_rel] : -1;
-    float sc = (e_rel < cap && e_rel < score_stride) ? my_sc[e_rel] : 0.f;
+    float sc = (e_rel < cap && e_rel < cap_rows) ? my_sc[e_rel] : 0.f;
     const int32_t true_cnt = (int32_t)cnt;
     if (cnt > cap) cnt = cap;
     if (cnt < 0) cnt = 0;
@@ -484,7 +482,7 @@ sparse_attention_wg_carry_split_kernel(const void *__restrict__ V, const int32_t
         const int64_t e = base + e_rel;
         if (base > 0) {
             pos = (e < cnt) ? my_idx[e] : -1;
-            sc = (e < cnt && e < score_stride) ? my_sc[e] : 0.f;
+            sc = (e < cnt && e < cap_rows) ? my_sc[e] : 0.f;
         }
         int myslot = -1;
         if (e < cnt && pos >= 0 && pos < n_total) myslot = pslot ? pslot[pos] : (int)pos;
@@ -952,21 +950,18 @@ hipError_t lvr_launch_sparse_attention_wg(lvr_index *ix, const float *q, const i
         if (scores && n_bhq > 256) LVR_WG_LAUNCH(lvr_bf16_t, true);
         else if (scores && n_bhq <= 128 && publish_count && ix->n_total > 65536)
             LVR_AT_LAUNCH((sparse_attention_wg_carry_split_kernel<lvr_bf16_t, 2>), dim3((unsigned)n_bhq * 2),
-                               ix->V, ix->pos_slot, idx, scores, ix->cap_rows, count, count_stride, cap, out, ix->cap_rows,
-                               ix->n_total, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale, lvr_head_count(ix),
-                               lvr_head_stat(ix), publish_count, lvr_head_ticket(ix));
+                               count, idx, scores, ix->V, cap, count_stride, (int)ix->cap_rows, (int)ix->n_total, ix->G,
+                               ix->pos_slot, out, qscale, lvr_head_count(ix), lvr_head_stat(ix), publish_count, lvr_head_ticket(ix));
         else if (scores)
-            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_bf16_t>), dim3((unsigned)n_bhq), ix->V,
-                               ix->pos_slot, idx, scores, ix->cap_rows, count, count_stride, cap, out, ix->cap_rows,
-                               ix->n_total, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale, lvr_head_count(ix),
+            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_bf16_t>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
+                               (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
                                lvr_head_stat(ix), publish_count);
         else LVR_WG_LAUNCH(lvr_bf16_t, false);
     } else {
         if (scores && n_bhq > 256) LVR_WG_LAUNCH(lvr_f32_t, true);   // as above: more heads than compute units
         else if (scores)
-            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_f32_t>), dim3((unsigned)n_bhq), ix->V,
-                               ix->pos_slot, idx, scores, ix->cap_rows, count, count_stride, cap, out, ix->cap_rows,
-                               ix->n_total, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale, lvr_head_count(ix),
+            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_f32_t>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
+                               (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
                                lvr_head_stat(ix), publish_count);
         else LVR_WG_LAUNCH(lvr_f32_t, false);
     }

@@ -61,9 +61,14 @@ struct FusedArgs {
 // 16 sequences of 32k keys).  The launcher sees to that with unused dynamic LDS (a fifth of a compute unit's LDS and a
 // little more per workgroup) whenever a launch has more workgroups than fit at once; a launch that fits takes whatever
 // residency the registers allow, which is where the few workgroups beyond 1024 (the buffer's) find room.
+// What the first loads need comes as scalar arguments ahead of the struct: 14 words of them are in registers when a wave
+// starts, so the loads of q and the first centres do not wait for a read of the argument block (32.9 against 33.4 us per
+// step at 128k keys, 11.7 against 12.1 at 16k; the attention kernels order their arguments the same way).
 template <int HB, int S, int UA, int ENC, int Q1 = 0, int CF = 0, int W = 4>
 __global__ void __launch_bounds__(256, ((HB == 1 && !ENC && S <= 4) || W == 8) ? 4 : 1)
-query_fused_kernel(const FusedArgs a) {
+query_fused_kernel(const float *__restrict__ q_in, const int8_t *__restrict__ chan_exp, const void *__restrict__ centres,
+                   const float *__restrict__ radii, const float *__restrict__ tau_in, const int G, const int tiles_per_wave,
+                   const int max_groups, const int n_groups, const FusedArgs a) {
     static_assert(!(Q1 && ENC) || S <= 4, "Query 1 on boxes: blocks of whole MFMA steps");
     static_assert(!CF || S <= 4, "coded centres: at most four coordinate blocks");
     static_assert(CF != 2 || !ENC, "6-bit codes: balls only");
@@ -109,20 +114,20 @@ query_fused_kernel(const FusedArgs a) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
     // first query head of this (sequence, KV head): (bh / H_kv) * H_q + (bh % H_kv) * G with H_q = H_kv * G
-    const int64_t hq0 = (int64_t)bh * a.G;
+    const int64_t hq0 = (int64_t)bh * G;
     const bool buffer_wg = (int)blockIdx.x >= a.n_segs;
 
     // ---- phase A, first trip: the centre and radius loads do not depend on q, so they are put
     // in flight before the prologue builds the query operand ----
     constexpr int SP = (S <= 4) ? S : 1;      // radii are fetched ahead only when they are few
     // balls: one row per group (the centre); boxes: two rows per group (upper corner, lower corner)
-    const char *Cb = static_cast<const char *>(a.centres) + (int64_t)bh * a.max_groups * (C6 ? LVR_D * 3 / 4 : LVR_D * (CF ? 1 : 2)) * (ENC ? 2 : 1);
+    const char *Cb = static_cast<const char *>(centres) + (int64_t)bh * max_groups * (C6 ? LVR_D * 3 / 4 : LVR_D * (CF ? 1 : 2)) * (ENC ? 2 : 1);
     // boxes: one allowance per group, whatever S; 8-bit centres: 8 bytes of radii per group (four bf16); 6-bit centres:
     // 12 bytes (the radii, then the four scale bytes)
     constexpr int RW = C6 ? 3 : (RP ? 2 : (ENC ? 1 : S));   // 32-bit words per group in the radii array
-    const float *Rb = a.radii + (int64_t)bh * a.max_groups * RW;
-    const int64_t n_tiles = (a.n_groups + 15) >> 4;
-    const int64_t tile0 = ((int64_t)blockIdx.x * 4 + wave) * a.tiles_per_wave;
+    const float *Rb = radii + (int64_t)bh * max_groups * RW;
+    const int64_t n_tiles = (n_groups + 15) >> 4;
+    const int64_t tile0 = ((int64_t)blockIdx.x * 4 + wave) * tiles_per_wave;
     // RM: the radius term rides on the matrix cores as a fifth step (S <= 4, one threshold per head);
     // a lane then needs only its own row's radii.  Otherwise the lanes that hold the scores fetch
     // the radii of their four rows and add the terms on the vector ALU.
@@ -148,7 +153,7 @@ query_fused_kernel(const FusedArgs a) {
         for (int u = 0; u < UA; ++u) {
             const int64_t g0 = (tile0 + it + u) * 16;
             int64_t g = g0 + n;
-            if (g >= a.n_groups) g = a.n_groups - 1;
+            if (g >= n_groups) g = n_groups - 1;
             if (g < 0) g = 0;   // an empty index: the first trip is requested all the same (see below), from row 0
             if constexpr (C6) {
                 lvr_load_a_codes6(Cb, g, c6[u]);
@@ -182,7 +187,7 @@ query_fused_kernel(const FusedArgs a) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     int64_t gj = g0 + 4 * kq + j;
-                    if (gj >= a.n_groups) gj = a.n_groups - 1;
+                    if (gj >= n_groups) gj = n_groups - 1;
                     if (gj < 0) gj = 0;
                     const float *rp = Rb + gj * (ENC ? 1 : S);
                     if constexpr (ENC) {   // the box's allowance; S only counts the blocks of Query 1
@@ -220,9 +225,9 @@ query_fused_kernel(const FusedArgs a) {
     (void)cfac;
     if constexpr (W == 4) {
 #pragma unroll
-        for (int hb = 0; hb < HB; ++hb) lvr_q_frag_load(a.q + hq0 * LVR_D, a.G, hb, wave, qraw[hb]);
+        for (int hb = 0; hb < HB; ++hb) lvr_q_frag_load(q_in + hq0 * LVR_D, G, hb, wave, qraw[hb]);
         if constexpr (CSP) {
-            const float4 *cf = reinterpret_cast<const float4 *>(a.chan_exp + (int64_t)bh * LVR_CHAN_STRIDE + LVR_D) + wave * 8 + kq * 2;
+            const float4 *cf = reinterpret_cast<const float4 *>(chan_exp + (int64_t)bh * LVR_CHAN_STRIDE + LVR_D) + wave * 8 + kq * 2;
             cfac[0] = cf[0];
             cfac[1] = cf[1];
         }
@@ -232,14 +237,14 @@ query_fused_kernel(const FusedArgs a) {
     // workgroup instead of twice (a thousand workgroups ask for the same few lines at the same moment; measured
     // with per-workgroup timestamps, the operand was ready 1.7 to 4.9 us after entry)
     constexpr bool NQ = W == 4 && S <= 4;
-    const bool norm_thread = !NQ && !buffer_wg && (int)threadIdx.x < HB * W * 16 && (int)(threadIdx.x >> 4) < a.G;
+    const bool norm_thread = !NQ && !buffer_wg && (int)threadIdx.x < HB * W * 16 && (int)(threadIdx.x >> 4) < G;
     if constexpr (!NQ) {
-        const float *qh = a.q + (hq0 + (norm_thread ? (threadIdx.x >> 4) : 0)) * LVR_D + (threadIdx.x & 15) * 8;
+        const float *qh = q_in + (hq0 + (norm_thread ? (threadIdx.x >> 4) : 0)) * LVR_D + (threadIdx.x & 15) * 8;
         const float4 x = *reinterpret_cast<const float4 *>(qh), y = *reinterpret_cast<const float4 *>(qh + 4);
         qnv[0] = x.x; qnv[1] = x.y; qnv[2] = x.z; qnv[3] = x.w;
         qnv[4] = y.x; qnv[5] = y.y; qnv[6] = y.z; qnv[7] = y.w;
         if constexpr (CS8) {   // the norms that meet the radii are those of the rescaled query
-            const float4 *cf = reinterpret_cast<const float4 *>(a.chan_exp + (int64_t)bh * LVR_CHAN_STRIDE + LVR_D) + (threadIdx.x & 15) * 2;
+            const float4 *cf = reinterpret_cast<const float4 *>(chan_exp + (int64_t)bh * LVR_CHAN_STRIDE + LVR_D) + (threadIdx.x & 15) * 2;
             const float4 f0 = cf[0], f1 = cf[1];
             qnv[0] *= f0.x; qnv[1] *= f0.y; qnv[2] *= f0.z; qnv[3] *= f0.w;
             qnv[4] *= f1.x; qnv[5] *= f1.y; qnv[6] *= f1.z; qnv[7] *= f1.w;
@@ -249,8 +254,8 @@ query_fused_kernel(const FusedArgs a) {
 #pragma unroll
     for (int hb = 0; hb < HB; ++hb) {
         const int h = hb * W + n - 8;
-        const bool mine = n >= 8 && n < 8 + W && h < a.G;
-        const float tv = a.tau[hq0 + (mine ? h : 0)];
+        const bool mine = n >= 8 && n < 8 + W && h < G;
+        const float tv = tau_in[hq0 + (mine ? h : 0)];
         tau_raw[hb] = mine ? tv : INFINITY;
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -262,7 +267,7 @@ query_fused_kernel(const FusedArgs a) {
 
     // ---- prologue: subspace norms of q (phase A only) and the B operand of q ----
     if constexpr (CSP) {
-        lvr_stash_q_frags<HB>(qraw, a.G, 1.0f, s_qu.stash);   // q itself, for the key-row phase
+        lvr_stash_q_frags<HB>(qraw, G, 1.0f, s_qu.stash);   // q itself, for the key-row phase
         const float f[8] = {cfac[0].x, cfac[0].y, cfac[0].z, cfac[0].w, cfac[1].x, cfac[1].y, cfac[1].z, cfac[1].w};
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -279,12 +284,12 @@ query_fused_kernel(const FusedArgs a) {
             for (int e = 0; e < 8; ++e) ss += qraw[hb][e] * qraw[hb][e];
             ss += __shfl_xor(ss, 16, 64);
             ss += __shfl_xor(ss, 32, 64);
-            if (lane < 4 && hb * 4 + lane < a.G) s_qpart[hb * 4 + lane][wave] = ss;
+            if (lane < 4 && hb * 4 + lane < G) s_qpart[hb * 4 + lane][wave] = ss;
         }
     } else if (!buffer_wg && (int)threadIdx.x < HB * W * 16) {
         const int h = threadIdx.x >> 4, li = threadIdx.x & 15;
         float ss = 0.f;
-        if (h < a.G) {
+        if (h < G) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += qnv[e] * qnv[e];
         }
@@ -298,16 +303,16 @@ query_fused_kernel(const FusedArgs a) {
     lvr_bf16x8 bq[HB][4], bq2[ENC ? HB : 1][4];
     bool third = false;   // W = 8: some head's query has more than 16 significant bits (the same in every thread)
     if constexpr (CS8) {   // both sync; a third term is there for q exactly when it is there for q times powers of two
-        lvr_build_q_frags8_wg(a.q + hq0 * LVR_D, a.G, 1.0f, s_bq8);
-        third = lvr_build_q_frags8_wg(a.q + hq0 * LVR_D, a.G, 1.0f, s_qu.bq8s, 0,
-                                      reinterpret_cast<const float *>(a.chan_exp + (int64_t)bh * LVR_CHAN_STRIDE + LVR_D));
-    } else if constexpr (W == 8) third = lvr_build_q_frags8_wg(a.q + hq0 * LVR_D, a.G, 1.0f, s_bq8);   // syncs
-    else lvr_exchange_q_frags_wg<HB>(qraw, a.G, 1.0f, s_u.bq, bq, ENC ? 1 : 0);   // syncs
-    if constexpr (ENC) lvr_exchange_q_frags_wg<HB>(qraw, a.G, 1.0f, s_bq2, bq2, -1);
+        lvr_build_q_frags8_wg(q_in + hq0 * LVR_D, G, 1.0f, s_bq8);
+        third = lvr_build_q_frags8_wg(q_in + hq0 * LVR_D, G, 1.0f, s_qu.bq8s, 0,
+                                      reinterpret_cast<const float *>(chan_exp + (int64_t)bh * LVR_CHAN_STRIDE + LVR_D));
+    } else if constexpr (W == 8) third = lvr_build_q_frags8_wg(q_in + hq0 * LVR_D, G, 1.0f, s_bq8);   // syncs
+    else lvr_exchange_q_frags_wg<HB>(qraw, G, 1.0f, s_u.bq, bq, ENC ? 1 : 0);   // syncs
+    if constexpr (ENC) lvr_exchange_q_frags_wg<HB>(qraw, G, 1.0f, s_bq2, bq2, -1);
     if constexpr (NQ) {
         // after the barrier of the exchange: every wave forms the block norms it is about to read and stores them
         // (four waves store the same values; a wave's own stores precede its own loads)
-        if (lane < HB * 4 * S && lane / S < a.G) {
+        if (lane < HB * 4 * S && lane / S < G) {
             const int h = lane / S, sb = lane % S;
             constexpr int SPB = 4 / S;   // steps per block
             float ss = 0.f;
@@ -357,8 +362,8 @@ query_fused_kernel(const FusedArgs a) {
         if (!buffer_wg) {
 #pragma unroll
             for (int hb = 0; hb < HB; ++hb) {
-                if constexpr (W == 8) rbq[hb] = lvr_radius_b_frag8<S, RP ? 1 : 3>(s_qn, a.G);
-                else rbq[hb] = lvr_radius_b_frag<S, RP ? 1 : 3>(s_qn, a.G, hb);
+                if constexpr (W == 8) rbq[hb] = lvr_radius_b_frag8<S, RP ? 1 : 3>(s_qn, G);
+                else rbq[hb] = lvr_radius_b_frag<S, RP ? 1 : 3>(s_qn, G, hb);
             }
         }
     }
@@ -367,7 +372,7 @@ query_fused_kernel(const FusedArgs a) {
 #pragma unroll
     for (int hb = 0; hb < HB; ++hb) {
         const int h = hb * W + n - 8;
-        rep[hb] = n >= 8 && n < 8 + W && h < a.G;
+        rep[hb] = n >= 8 && n < 8 + W && h < G;
         taue[hb] = rep[hb] ? lvr_effective_tau(tau_raw[hb]) : INFINITY;
     }
     float taus[HB][Q1 ? S : 1];
@@ -400,9 +405,9 @@ query_fused_kernel(const FusedArgs a) {
     const bool direct = buffer_wg || a.skip_bounds;   // phase B walks a run of consecutive rows, not a survivor list
     if (!buffer_wg && a.skip_bounds) {
         // the exact filter alone: the segment's groups all count as survivors
-        const int64_t seg_groups = (int64_t)a.tiles_per_wave * 64;
+        const int64_t seg_groups = (int64_t)tiles_per_wave * 64;
         const int64_t g0 = (int64_t)blockIdx.x * seg_groups;
-        int64_t total = a.n_groups - g0;
+        int64_t total = n_groups - g0;
         if (total > seg_groups) total = seg_groups;
         if (total < 0) total = 0;
         if (threadIdx.x == 0) a.seg_count[(int64_t)bh * a.max_segs + blockIdx.x] = (int32_t)total;
@@ -480,7 +485,7 @@ query_fused_kernel(const FusedArgs a) {
 #pragma unroll
                             for (int j = 0; j < 4; ++j) {
                                 int64_t gj = g_row + 4 * kq + j;
-                                if (gj >= a.n_groups) gj = a.n_groups - 1;
+                                if (gj >= n_groups) gj = n_groups - 1;
                                 rp[j] = Rb + gj * S;
                             }
                             auto step = [&](auto kk_c) {
@@ -572,7 +577,7 @@ query_fused_kernel(const FusedArgs a) {
                             for (int s = 0; s < S; ++s) ub += rad[u][j][s] * qn[hb][s];
                         } else {
                             int64_t gj = g_row + 4 * kq + j;
-                            if (gj >= a.n_groups) gj = a.n_groups - 1;
+                            if (gj >= n_groups) gj = n_groups - 1;
                             const float4 *rp = reinterpret_cast<const float4 *>(Rb + gj * S);
 #pragma unroll
                             for (int s4 = 0; s4 < S / 4; ++s4) {
@@ -597,13 +602,13 @@ query_fused_kernel(const FusedArgs a) {
                                         ((uint32_t)__builtin_amdgcn_readlane((int)v, L0 + 32) << 8) |
                                         ((uint32_t)__builtin_amdgcn_readlane((int)v, L0 + 48) << 12);
                 // groups past the end of the index, tiles past the wave's share: a wave-uniform mask
-                const int64_t left = a.n_groups - g_row;
-                const uint32_t valid16 = (it + u) >= a.tiles_per_wave || left <= 0 ? 0u
+                const int64_t left = n_groups - g_row;
+                const uint32_t valid16 = (it + u) >= tiles_per_wave || left <= 0 ? 0u
                                          : (left >= 16 ? 0xffffu : ((1u << (int)left) - 1u));
                 if (lane == it + u) mybits = mask16 & valid16;
             }
         };
-        auto more = [&](int it) { return it < a.tiles_per_wave && tile0 + it < n_tiles; };   // wave-uniform
+        auto more = [&](int it) { return it < tiles_per_wave && tile0 + it < n_tiles; };   // wave-uniform
         if constexpr (DB) {
             for (int it = 0; more(it); it += 2 * UA) {
                 take_turn(it / (2 * UA));
@@ -647,7 +652,7 @@ query_fused_kernel(const FusedArgs a) {
             while (__ballot(left != 0)) {   // wave-uniform
                 if (left != 0) {
                     const int k = __builtin_ctz(left);
-                    s_list[o++] = (uint16_t)((wave * a.tiles_per_wave + lane) * 16 + k);
+                    s_list[o++] = (uint16_t)((wave * tiles_per_wave + lane) * 16 + k);
                     left &= left - 1;
                 }
             }
@@ -693,7 +698,7 @@ query_fused_kernel(const FusedArgs a) {
     const char *Kb = static_cast<const char *>(a.K) + (int64_t)bh * a.cap_rows * LVR_D * 2;
     const int32_t *spos = a.slot_pos ? a.slot_pos + (int64_t)bh * a.cap_rows : nullptr;
     const int rmask = (1 << a.log2r) - 1;
-    const int64_t seg_g0 = (int64_t)blockIdx.x * a.tiles_per_wave * 64;   // first group of this workgroup's segment
+    const int64_t seg_g0 = (int64_t)blockIdx.x * tiles_per_wave * 64;   // first group of this workgroup's segment
     const int64_t tiles = (rows + 15) >> 4;
     // This wave checks tiles wave, wave + 4, wave + 8, ...: m of them, two at a time in two register sets.
     // Rotated form: as soon as a set has been scored the wave's next tile but one is requested into it, so
@@ -806,8 +811,8 @@ struct LaunchEvents {
 };
 #define LVR_QF_LAUNCH(KERNEL)                                                                                        \
     do {                                                                                                             \
-        if (ev.start) hipExtLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, ev.start, ev.stop, 0, a);           \
-        else hipLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, a);                                            \
+        if (ev.start) hipExtLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, ev.start, ev.stop, 0, a.q, a.chan_exp, a.centres, a.radii, a.tau, a.G, a.tiles_per_wave, (int)a.max_groups, (int)a.n_groups, a);           \
+        else hipLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, a.q, a.chan_exp, a.centres, a.radii, a.tau, a.G, a.tiles_per_wave, (int)a.max_groups, (int)a.n_groups, a);                                            \
     } while (0)
 
 template <int UA, int W>
