@@ -11,9 +11,9 @@
 // the launch.  The per-head counters must be zero when the kernel starts.
 //
 // Bound by the key rows: 512 bytes each, and at fp32's group sizes on keys without locality most balls survive.  What
-// matters is therefore that the rows are spread over the device: segments are as small as 1024 workgroups ask for, down to
+// matters is therefore that the rows are spread over the device: segments are as small as one round of workgroups asks for, down to
 // a trip of 16 groups.  With segments of 256 groups and a launch per stage the steps took 62.7 us at 8 x 16384 keys and
-// 28.3 us at one head of 4096 keys; now 25.8 and 9.9 us.
+// 28.3 us at one head of 4096 keys; now 23.4 and 10.0 us.
 #include "emitter.h"
 
 namespace {
@@ -243,8 +243,13 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     a.S = ix->cfg.n_subspaces;
     a.buffer_dense = (ix->cfg.flags & LVR_ATTEND_BUFFER_DENSE) ? 1 : 0;
     const int n_bh = lvr_n_bh(ix);
-    // segments of a multiple of 16 groups (a trip of the four waves); aim at a fixed number of workgroups per launch
-    const int64_t target_wgs = ix->cfg.query_workgroups > 0 ? ix->cfg.query_workgroups : 1024;
+    // segments of a multiple of 16 groups (a trip of the four waves); aim at the workgroups that are resident at once (three
+    // per compute unit, two with eight heads: the registers of two tiles of rows and the query) less the buffers', so that
+    // the launch is one round (8 x 16384 keys: 23.6 us per step against 25.2 with 1024, which ran as 768 + 264)
+    const int64_t buffers = a.n_total > ix->n_indexed ? n_bh : 0;
+    int64_t target_wgs = (ix->G == 8 ? 512 : 768) - buffers;
+    if (target_wgs < 256) target_wgs = 256;
+    if (ix->cfg.query_workgroups > 0) target_wgs = ix->cfg.query_workgroups;
     int64_t seg = (a.n_groups * n_bh + target_wgs - 1) / target_wgs;
     seg = (seg + 15) & ~(int64_t)15;
     if (seg < LVR_MIN_SEG_GROUPS) seg = LVR_MIN_SEG_GROUPS;
