@@ -14,8 +14,12 @@
 
 namespace {
 
+typedef uint32_t lvr_u32x4 __attribute__((ext_vector_type(4)));
+
 // 16 bytes per thread, arbitrary source strides (in elements) for (batch, head, token).
-// blockIdx.z = 0 copies keys, 1 copies values, so an append is one launch.
+// blockIdx.z = 0 copies keys, 1 copies values, so an append is one launch.  The rows are streamed past the caches, here
+// and where the 6-bit build copies the key rows: they are larger than the caches and the next launch reads the index
+// (build and step at 8 x 131072 keys: 262 us, 277 with ordinary stores).
 struct CopySide {
     const char *src;
     char *dst;
@@ -45,7 +49,7 @@ __global__ void copy_rows_kernel(CopySide k, CopySide v, int n_kv_heads, int64_t
     int ch = (int)(i % chunks);
     const uint4 *s = reinterpret_cast<const uint4 *>(c.src + (b * c.sb + h * c.sh + row * c.st) * elt) + ch;
     uint4 *d = reinterpret_cast<uint4 *>(c.dst + ((int64_t)bh * cap_rows + dst_row0 + row) * row_bytes) + ch;
-    *d = *s;
+    __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const lvr_u32x4 *>(s)), reinterpret_cast<lvr_u32x4 *>(d));
 }
 
 __device__ __forceinline__ float seg_sum(float v, int lanes_per_sub) {
@@ -252,7 +256,7 @@ build_groups_kernel(void *__restrict__ K, void *__restrict__ centres, float *__r
 // add up over the quad is two lane exchanges per radius.  A wave stores 16 groups' codes as 1536 consecutive bytes.
 // R = group size up to four (the members stay in registers between the two passes); R = 0: any r, members read twice.
 // Bound by memory: K in, K out and 108 bytes per group (650 MB for 8 heads of 131072 keys).  With 16 lanes per group, a software encoder
-// and a four-step exchange per reduction the vector ALU took longer than the traffic, 223 us; now 126 us (5.2 TB/s).
+// and a four-step exchange per reduction the vector ALU took longer than the traffic, 223 us; now some 120 us.
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float lvr_f32x16;
 
 __device__ __forceinline__ float quad_sum(float v) {
@@ -285,7 +289,9 @@ build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__
     auto keep_row = [&](int m, const uint4 (&w)[4]) {   // the arena's copy of the row
         uint4 *p = reinterpret_cast<uint4 *>(Kb + (g * members + m) * (LVR_D * 2)) + b;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) p[kk * 4] = w[kk];
+        for (int kk = 0; kk < 4; ++kk) {
+            __builtin_nontemporal_store(__builtin_bit_cast(lvr_u32x4, w[kk]), reinterpret_cast<lvr_u32x4 *>(p + kk * 4));
+        }
     };
     auto value = [](const uint4 &w, int e) {
         const uint32_t u = e < 2 ? w.x : (e < 4 ? w.y : (e < 6 ? w.z : w.w));
