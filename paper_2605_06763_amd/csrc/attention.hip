@@ -41,12 +41,10 @@ __device__ __forceinline__ int64_t split_length(int64_t cnt, int P_max, int *use
 // list), so only V rows are gathered.
 template <typename KT, bool CARRY>
 __global__ void __launch_bounds__(64)
-sparse_attention_kernel(const void *__restrict__ K, const void *__restrict__ V, const int32_t *__restrict__ pos_slot,
-                        const float *__restrict__ q, const int32_t *__restrict__ idx,
-                        const float *__restrict__ scores, int64_t score_stride,
-                        const int32_t *__restrict__ count, int count_stride, int64_t cap,
-                        float *__restrict__ part_ml, float *__restrict__ part_o, int64_t cap_rows, int64_t n_total,
-                        int P, int n_q_heads, int n_kv_heads, int G, float qscale) {
+sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__restrict__ idx, const float *__restrict__ scores,
+                        const float *__restrict__ q, const void *__restrict__ V, int64_t cap, int count_stride, int P,
+                        int cap_rows, int n_total, int G, float qscale, const void *__restrict__ K,
+                        const int32_t *__restrict__ pos_slot, float *__restrict__ part_ml, float *__restrict__ part_o) {
     const int64_t hq = blockIdx.y;
     const int p = blockIdx.x;
     const int bh = (int)((uint32_t)hq / (uint32_t)G);   // (hq / H_q) * H_kv + (hq % H_q) / G with H_q = H_kv * G: one 32-bit division
@@ -58,9 +56,9 @@ sparse_attention_kernel(const void *__restrict__ K, const void *__restrict__ V, 
     // speculative load of the positions that goes out together with the count.
     const int64_t e_spec = (int64_t)p * 16 + lane;
     const int32_t pos_spec = (lane < 16 && e_spec < cap) ? my_idx[e_spec] : -1;
-    const float *my_sc = CARRY ? scores + hq * score_stride : nullptr;
+    const float *my_sc = CARRY ? scores + hq * (int64_t)cap_rows : nullptr;
     float sc_spec = 0.f;
-    if constexpr (CARRY) sc_spec = (lane < 16 && e_spec < cap && e_spec < score_stride) ? my_sc[e_spec] : 0.f;
+    if constexpr (CARRY) sc_spec = (lane < 16 && e_spec < cap && e_spec < cap_rows) ? my_sc[e_spec] : 0.f;
     int64_t cnt = count[hq * count_stride];
     if (cnt > cap) cnt = cap;
     if (cnt < 0) cnt = 0;
@@ -575,8 +573,8 @@ constexpr int COMBINE_MAX_P = 256;
 // both), so neither is declared restrict, every thread reads the count BEFORE the kernel's first
 // barrier and the counter is cleared only AFTER it.
 __global__ void __launch_bounds__(512)
-combine_kernel(const float *__restrict__ part_ml, const float *__restrict__ part_o, float *__restrict__ out, int P,
-               const int32_t *count, int count_stride, int64_t cap, int32_t *head_count,
+combine_kernel(const float *__restrict__ part_o, const float *__restrict__ part_ml, const int32_t *count, int64_t cap,
+               float *__restrict__ out, int P, int count_stride, int32_t *head_count,
                int32_t *__restrict__ head_stat, int32_t *__restrict__ publish_count) {
     __shared__ float s_w[COMBINE_MAX_P];
     __shared__ float s_red[8];
@@ -977,9 +975,9 @@ hipError_t lvr_launch_sparse_partial(lvr_index *ix, const float *q, const int32_
     dim3 grid((unsigned)P, (unsigned)n_bhq);
     const float qscale = ix->sigma * LOG2E;
 #define LVR_PART_LAUNCH(KT, CARRY)                                                                                       \
-    hipLaunchKernelGGL((sparse_attention_kernel<KT, CARRY>), grid, dim3(64), 0, st, ix->K, ix->V, ix->pos_slot, q, idx,  \
-                       scores, ix->cap_rows, count, count_stride, cap, ix->part_ml, ix->part_o, ix->cap_rows,            \
-                       ix->n_total, P, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale)
+    hipLaunchKernelGGL((sparse_attention_kernel<KT, CARRY>), grid, dim3(64), 0, st, count, idx, scores, q, ix->V, cap,     \
+                       count_stride, P, (int)ix->cap_rows, (int)ix->n_total, ix->G, qscale, ix->K, ix->pos_slot,         \
+                       ix->part_ml, ix->part_o)
     if (ix->cfg.kv_dtype == LVR_BF16) {
         if (scores) LVR_PART_LAUNCH(lvr_bf16_t, true);
         else LVR_PART_LAUNCH(lvr_bf16_t, false);
@@ -1018,7 +1016,7 @@ hipError_t lvr_launch_dense_partial(lvr_index *ix, const float *q, hipStream_t s
 hipError_t lvr_launch_combine(lvr_index *ix, float *out, int P, const int32_t *count, int count_stride, int64_t cap,
                               int32_t *publish_count, hipStream_t st) {
     const int n_bhq = lvr_n_bhq(ix);
-    hipLaunchKernelGGL(combine_kernel, dim3((unsigned)n_bhq), dim3(512), 0, st, ix->part_ml, ix->part_o, out, P, count,
-                       count_stride, cap, lvr_head_count(ix), lvr_head_stat(ix), publish_count);
+    hipLaunchKernelGGL(combine_kernel, dim3((unsigned)n_bhq), dim3(512), 0, st, ix->part_o, ix->part_ml, count, cap, out, P,
+                       count_stride, lvr_head_count(ix), lvr_head_stat(ix), publish_count);
     return hipGetLastError();
 }

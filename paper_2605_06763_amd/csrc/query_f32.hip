@@ -19,26 +19,24 @@
 namespace {
 
 struct FusedF32Args {
-    const void *centres;
-    const float *radii;
     const void *K;
     void *V;
     const int32_t *slot_pos;
-    const float *q;
-    const float *tau;
     const void *k_new, *v_new;   // rows appended by this launch ([batch][H_kv][m_new][d]), or NULL
     int m_new;                   // n_total already counts them
     int32_t *seg_count;          // survivors per segment, for statistics only
     lvr_emit_target emit;
     int64_t n_groups, max_groups, max_segs, cap_rows, n_indexed, n_total;
-    int log2r, S, buffer_dense, n_segs, seg_groups;
+    int log2r, buffer_dense;
 };
 
 constexpr int F32_SEG_MAX = 1024;   // groups of a segment: 64 trips of 16 groups, lane `it` of a wave keeps the bits of trip `it`
 
 template <int G>
 __global__ void __launch_bounds__(256)
-query_f32_kernel(const FusedF32Args a) {
+query_f32_kernel(const float *__restrict__ q_in, const void *__restrict__ centres, const float *__restrict__ tau_in,
+                 const float *__restrict__ radii, const int n_groups, const int max_groups, const int seg_groups, const int n_segs,
+                 const int S, const FusedF32Args a) {
     __shared__ int32_t s_queue[4][G][LVR_QCAP];
     __shared__ float s_qscore[4][G][LVR_QCAP];
     __shared__ uint16_t s_list[F32_SEG_MAX];   // surviving groups, as offsets from the segment's first group
@@ -48,25 +46,25 @@ query_f32_kernel(const FusedF32Args a) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = lane >> 4, li = lane & 15;
     const int64_t hq0 = (int64_t)bh * G;
-    const bool buffer_wg = (int)blockIdx.x >= a.n_segs;
+    const bool buffer_wg = (int)blockIdx.x >= n_segs;
 
     float qv[G][8], taue[G];
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-        const float *qh = a.q + (hq0 + h) * LVR_D + li * 8;
+        const float *qh = q_in + (hq0 + h) * LVR_D + li * 8;
 #pragma unroll
         for (int e = 0; e < 8; ++e) qv[h][e] = qh[e];
-        taue[h] = lvr_effective_tau(a.tau[hq0 + h]);
+        taue[h] = lvr_effective_tau(tau_in[hq0 + h]);
     }
 
     int64_t rows;        // key rows phase B has to check
     int64_t seg_g0 = 0;  // first group of this workgroup's segment
     if (!buffer_wg) {
         // ---------------- phase A: bound test over this segment's centres ----------------
-        seg_g0 = (int64_t)blockIdx.x * a.seg_groups;
-        const char *Cb = static_cast<const char *>(a.centres) + (int64_t)bh * a.max_groups * LVR_D * 4;
-        const float *Rb = a.radii + (int64_t)bh * a.max_groups * a.S;
-        const int lanes_per_sub = 16 / a.S;
+        seg_g0 = (int64_t)blockIdx.x * seg_groups;
+        const char *Cb = static_cast<const char *>(centres) + (int64_t)bh * max_groups * LVR_D * 4;
+        const float *Rb = radii + (int64_t)bh * max_groups * S;
+        const int lanes_per_sub = 16 / S;
         float qn[G];   // lanes li < S: |pi_li q_h|, rounded up; the others zero
 #pragma unroll
         for (int h = 0; h < G; ++h) {
@@ -74,22 +72,22 @@ query_f32_kernel(const FusedF32Args a) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += qv[h][e] * qv[h][e];
             for (int off = 1; off < lanes_per_sub; off <<= 1) ss += __shfl_xor(ss, off, 64);
-            const float mine = __shfl(ss, (lane & 48) + ((li < a.S) ? li * lanes_per_sub : li), 64);
-            qn[h] = (li < a.S) ? sqrtf(mine) * (1.0f + 0x1p-20f) : 0.f;
+            const float mine = __shfl(ss, (lane & 48) + ((li < S) ? li * lanes_per_sub : li), 64);
+            qn[h] = (li < S) ? sqrtf(mine) * (1.0f + 0x1p-20f) : 0.f;
         }
-        const int trips = a.seg_groups >> 4;   // trip `it` of wave w: groups 16 it + 4 w .. + 3
+        const int trips = seg_groups >> 4;   // trip `it` of wave w: groups 16 it + 4 w .. + 3
         uint32_t mybits = 0;
         for (int it0 = 0; it0 < trips; it0 += 2) {
-            if (seg_g0 + it0 * 16 >= a.n_groups) break;   // uniform
+            if (seg_g0 + it0 * 16 >= n_groups) break;   // uniform
             lvr_raw8<lvr_f32_t> raw[2];
             float rad[2];
             int64_t g[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 g[u] = seg_g0 + (it0 + u) * 16 + wave * 4 + sub;
-                const int64_t gc = g[u] < a.n_groups ? g[u] : a.n_groups - 1;
+                const int64_t gc = g[u] < n_groups ? g[u] : n_groups - 1;
                 lvr_load_raw(Cb, gc, li, raw[u]);
-                rad[u] = Rb[gc * a.S + (li & (a.S - 1))];   // lanes li >= S multiply it by zero below
+                rad[u] = Rb[gc * S + (li & (S - 1))];   // lanes li >= S multiply it by zero below
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -103,7 +101,7 @@ query_f32_kernel(const FusedF32Args a) {
                     for (int e = 0; e < 8; ++e) p += qv[h][e] * x[e];
                     alive |= (lvr_row16_sum(p) >= taue[h]);
                 }
-                const uint64_t bal = __ballot(alive && g[u] < a.n_groups && it0 + u < trips && li == 0);
+                const uint64_t bal = __ballot(alive && g[u] < n_groups && it0 + u < trips && li == 0);
                 const uint32_t mask4 = (uint32_t)(bal & 1u) | (uint32_t)((bal >> 15) & 2u) | (uint32_t)((bal >> 30) & 4u) |
                                        (uint32_t)((bal >> 45) & 8u);
                 if (lane == it0 + u) mybits = mask4;
@@ -215,13 +213,9 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
                                 hipStream_t st, const void *k_new, const void *v_new, int64_t m_new) {
     if (ix->cfg.kv_dtype != LVR_F32) return hipErrorInvalidValue;
     FusedF32Args a;
-    a.centres = ix->centres;
-    a.radii = ix->radii;
     a.K = ix->K;
     a.V = ix->V;
     a.slot_pos = ix->slot_pos;
-    a.q = q;
-    a.tau = tau;
     a.k_new = k_new;
     a.v_new = v_new;
     a.m_new = (int)m_new;
@@ -240,7 +234,6 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     a.n_total = ix->n_total + m_new;
     a.log2r = 0;
     while ((1 << a.log2r) < ix->cfg.group_size) ++a.log2r;
-    a.S = ix->cfg.n_subspaces;
     a.buffer_dense = (ix->cfg.flags & LVR_ATTEND_BUFFER_DENSE) ? 1 : 0;
     const int n_bh = lvr_n_bh(ix);
     // segments of a multiple of 16 groups (a trip of the four waves); aim at the workgroups that are resident at once (three
@@ -254,18 +247,17 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     seg = (seg + 15) & ~(int64_t)15;
     if (seg < LVR_MIN_SEG_GROUPS) seg = LVR_MIN_SEG_GROUPS;
     if (seg > F32_SEG_MAX) seg = F32_SEG_MAX;
-    a.seg_groups = (int)seg;
-    a.n_segs = (int)((a.n_groups + seg - 1) / seg);
+    const int seg_groups = (int)seg, n_segs = (int)((a.n_groups + seg - 1) / seg);
     const int has_buffer = a.n_total > ix->n_indexed ? 1 : 0;
-    ix->seg_groups = a.seg_groups;
-    ix->n_segs = a.n_segs;
-    if (a.n_segs + has_buffer == 0) return hipSuccess;
-    const dim3 grid((unsigned)(a.n_segs + has_buffer), (unsigned)n_bh);
+    ix->seg_groups = seg_groups;
+    ix->n_segs = n_segs;
+    if (n_segs + has_buffer == 0) return hipSuccess;
+    const dim3 grid((unsigned)(n_segs + has_buffer), (unsigned)n_bh);
     switch (ix->G) {
-        case 1: hipLaunchKernelGGL(query_f32_kernel<1>, grid, dim3(256), 0, st, a); break;
-        case 2: hipLaunchKernelGGL(query_f32_kernel<2>, grid, dim3(256), 0, st, a); break;
-        case 4: hipLaunchKernelGGL(query_f32_kernel<4>, grid, dim3(256), 0, st, a); break;
-        case 8: hipLaunchKernelGGL(query_f32_kernel<8>, grid, dim3(256), 0, st, a); break;
+        case 1: hipLaunchKernelGGL(query_f32_kernel<1>, grid, dim3(256), 0, st, q, ix->centres, tau, ix->radii, (int)a.n_groups, (int)a.max_groups, seg_groups, n_segs, ix->cfg.n_subspaces, a); break;
+        case 2: hipLaunchKernelGGL(query_f32_kernel<2>, grid, dim3(256), 0, st, q, ix->centres, tau, ix->radii, (int)a.n_groups, (int)a.max_groups, seg_groups, n_segs, ix->cfg.n_subspaces, a); break;
+        case 4: hipLaunchKernelGGL(query_f32_kernel<4>, grid, dim3(256), 0, st, q, ix->centres, tau, ix->radii, (int)a.n_groups, (int)a.max_groups, seg_groups, n_segs, ix->cfg.n_subspaces, a); break;
+        case 8: hipLaunchKernelGGL(query_f32_kernel<8>, grid, dim3(256), 0, st, q, ix->centres, tau, ix->radii, (int)a.n_groups, (int)a.max_groups, seg_groups, n_segs, ix->cfg.n_subspaces, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
