@@ -293,14 +293,13 @@ sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ 
 //           softmax update over them.
 // sparse_attention_wg_kernel pays count -> positions -> one trip per batch: five in a row for 656 keys per head.
 // Lists longer than 1024 entries take further rounds of two trips each.
-template <typename KT>
-__global__ void __launch_bounds__(1024)
+template <typename KT, int NW>
+__global__ void __launch_bounds__(64 * NW)
 sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count: not restrict
                                  const int32_t *__restrict__ idx, const float *__restrict__ scores, const void *__restrict__ V,
                                  int64_t cap, int count_stride, int cap_rows, int n_total, int G,
                                  const int32_t *__restrict__ pos_slot, float *__restrict__ out, float qscale, int32_t *head_count,
                                  int32_t *__restrict__ head_stat, int32_t *__restrict__ publish_count) {
-    constexpr int NW = 16;
     __shared__ float s_m[NW], s_l[NW];
     __shared__ float s_o[NW][LVR_D];
     const int64_t hq = blockIdx.x;
@@ -926,45 +925,51 @@ hipError_t lvr_launch_sparse_attention_wg(lvr_index *ix, const float *q, const i
     const float qscale = ix->sigma * LOG2E;
     // a pair of events handed in by the caller goes into the dispatch itself (they then read the kernel's own start and end)
     hipEvent_t ev0 = ix->launch_start, ev1 = ix->launch_stop;
-#define LVR_AT_LAUNCH(KERNEL, GRID, ...)                                                                    \
+#define LVR_AT_LAUNCH_N(KERNEL, GRID, THREADS, ...)                                                         \
     do {                                                                                                    \
-        if (ev0) hipExtLaunchKernelGGL(KERNEL, GRID, dim3(1024), 0, st, ev0, ev1, 0, __VA_ARGS__);           \
-        else hipLaunchKernelGGL(KERNEL, GRID, dim3(1024), 0, st, __VA_ARGS__);                              \
+        if (ev0) hipExtLaunchKernelGGL(KERNEL, GRID, dim3(THREADS), 0, st, ev0, ev1, 0, __VA_ARGS__);        \
+        else hipLaunchKernelGGL(KERNEL, GRID, dim3(THREADS), 0, st, __VA_ARGS__);                           \
     } while (0)
+#define LVR_AT_LAUNCH(KERNEL, GRID, ...) LVR_AT_LAUNCH_N(KERNEL, GRID, 1024, __VA_ARGS__)
 #define LVR_WG_LAUNCH(KT, CARRY)                                                                                         \
     LVR_AT_LAUNCH((sparse_attention_wg_kernel<KT, CARRY>), dim3((unsigned)n_bhq), ix->K, ix->V,                          \
                   ix->pos_slot, q, idx, scores, ix->cap_rows, count, count_stride, cap, out, ix->cap_rows,               \
                   ix->n_total, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale, lvr_head_count(ix),                 \
                   lvr_head_stat(ix), publish_count)
     if (ix->cfg.kv_dtype == LVR_BF16) {
-        // With more heads than compute units the workgroups queue up behind each other and the lighter kernel wins
-        // (512 heads: 24.0 against 26.0 us); with one workgroup per unit the shorter chain of trips does (32 heads:
-        // 8.4 against 8.7 us at 328 keys per head, 10.5 against 10.9 us at 656).
+        // With more heads than compute units a workgroup of eight waves serves a head: its waves hold up to 64 rows each in
+        // flight as the sixteen of the wide form do, and two such workgroups share a compute unit instead of queueing
+        // up behind each other (512 heads of 655 keys: 126.5 us per step against 128.2 with sixteen light waves that take a
+        // trip per 16 rows; 384 heads of 18 to 105 keys: 15.4 against 18.4, 34.2 against 37.2).
         // Up to 128 heads two workgroups can share a head (one per half of the channels) and every workgroup still
         // has a compute unit of its own.  That pays where a head's list is long (656 keys per head at 128k keys of
         // context: 9.1 against 9.7 us); short lists lose more to the extra barrier and the ticket than they gain
         // (3.6 keys per head: 7.6 against 6.9 us), and the list lengths are not known on the host, so the context
         // length stands in as it does for the launch form.
-        if (scores && n_bhq > 256) LVR_WG_LAUNCH(lvr_bf16_t, true);
+        if (scores && n_bhq > 256)
+            LVR_AT_LAUNCH_N((sparse_attention_wg_carry_kernel<lvr_bf16_t, 8>), dim3((unsigned)n_bhq), 512, count, idx, scores, ix->V, cap,
+                            count_stride, (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
+                            lvr_head_stat(ix), publish_count);
         else if (scores && n_bhq <= 128 && publish_count && ix->n_total > 65536)
             LVR_AT_LAUNCH((sparse_attention_wg_carry_split_kernel<lvr_bf16_t, 2>), dim3((unsigned)n_bhq * 2),
                                count, idx, scores, ix->V, cap, count_stride, (int)ix->cap_rows, (int)ix->n_total, ix->G,
                                ix->pos_slot, out, qscale, lvr_head_count(ix), lvr_head_stat(ix), publish_count, lvr_head_ticket(ix));
         else if (scores)
-            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_bf16_t>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
+            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_bf16_t, 16>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
                                (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
                                lvr_head_stat(ix), publish_count);
         else LVR_WG_LAUNCH(lvr_bf16_t, false);
     } else {
         if (scores && n_bhq > 256) LVR_WG_LAUNCH(lvr_f32_t, true);   // as above: more heads than compute units
         else if (scores)
-            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_f32_t>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
+            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_f32_t, 16>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
                                (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
                                lvr_head_stat(ix), publish_count);
         else LVR_WG_LAUNCH(lvr_f32_t, false);
     }
 #undef LVR_WG_LAUNCH
 #undef LVR_AT_LAUNCH
+#undef LVR_AT_LAUNCH_N
     return hipGetLastError();
 }
 
