@@ -425,7 +425,9 @@ int lvr_build(lvr_index *ix, const void *K, const void *V, int64_t n, const int6
     ix->n_indexed = 0;
     const int r = ix->cfg.group_size;
     const int64_t n_groups = n / r;
-    LVR_HIP(lvr_launch_channel_scales(ix, K, ks, n, st));   // before any group is formed
+    // the exponents of a 6-bit index come before any group is formed; contiguous groups copy V in the same launches below
+    const bool contiguous = !ix->per_subspace && ix->cfg.grouping != LVR_GROUP_TREE;
+    if (!contiguous) LVR_HIP(lvr_launch_channel_scales(ix, K, ks, n, st));
     if (n > 0 && ix->per_subspace) {
         // rows stay in arrival order; every coordinate block gets the tree order of its own coordinates,
         // and from it the block's balls and the keys' labels (Alg. 1: one BalancedPCATree call per subspace)
@@ -453,7 +455,8 @@ int lvr_build(lvr_index *ix, const void *K, const void *V, int64_t n, const int6
         // contiguous groups: V and the ungrouped tail of K are copied here, the grouped key rows by the
         // build kernel below, which reads them from the caller's K anyway
         Timed t(ix, LVR_K_COPY, st);
-        LVR_HIP(lvr_launch_copy_kv(ix, K, ks, V, vs, 0, n, st, n_groups * r));
+        if (ix->chan_scaled) LVR_HIP(lvr_launch_channel_scales(ix, K, ks, n, st, V, vs, n_groups * r));
+        else LVR_HIP(lvr_launch_copy_kv(ix, K, ks, V, vs, 0, n, st, n_groups * r));
     }
     if (!ix->per_subspace) {
         Timed t(ix, LVR_K_BUILD, st);

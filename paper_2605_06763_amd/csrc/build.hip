@@ -16,10 +16,7 @@ namespace {
 
 typedef uint32_t lvr_u32x4 __attribute__((ext_vector_type(4)));
 
-// 16 bytes per thread, arbitrary source strides (in elements) for (batch, head, token).
-// blockIdx.z = 0 copies keys, 1 copies values, so an append is one launch.  The rows are streamed past the caches, here
-// and where the 6-bit build copies the key rows: they are larger than the caches and the next launch reads the index
-// (build and step at 8 x 131072 keys: 262 us, 277 with ordinary stores).
+// One side of a copy of rows into the arena: arbitrary source strides (in elements) for (batch, head, token).
 struct CopySide {
     const char *src;
     char *dst;
@@ -36,20 +33,42 @@ struct BuildSrc {
     int n_kv_heads;
 };
 
-__global__ void copy_rows_kernel(CopySide k, CopySide v, int n_kv_heads, int64_t cap_rows, int64_t dst_row0,
-                                 int64_t rows, int row_bytes, int elt) {
-    const CopySide c = blockIdx.z == 0 ? k : v;
-    const int chunks = row_bytes / 16;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= rows * chunks) return;
-    int bh = blockIdx.y;
-    int b = bh / n_kv_heads, h = bh % n_kv_heads;
-    int64_t row = i / chunks;
-    if (row < c.first) return;
-    int ch = (int)(i % chunks);
-    const uint4 *s = reinterpret_cast<const uint4 *>(c.src + (b * c.sb + h * c.sh + row * c.st) * elt) + ch;
-    uint4 *d = reinterpret_cast<uint4 *>(c.dst + ((int64_t)bh * cap_rows + dst_row0 + row) * row_bytes) + ch;
-    __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const lvr_u32x4 *>(s)), reinterpret_cast<lvr_u32x4 *>(d));
+constexpr int COPY_PIECES = 4;   // 16-byte pieces per thread
+
+// Block `block` (256 threads) of the copy of rows [c.first, rows), 2^SH pieces each, to arena row dst_row0 on.  All of a
+// thread's pieces are in flight before the first is stored; the rows are streamed past the caches, here and where the 6-bit
+// build copies the key rows (they are larger than the caches and the next launch reads the index: build and step at
+// 8 x 131072 keys 262 us against 277 with ordinary accesses, one piece per thread; four pieces and no division by the row
+// length bring the copy itself from 103 to 90 us, 6 TB/s).
+template <int SH>
+__device__ __forceinline__ void copy_block(const CopySide &c, int bh, int n_kv_heads, int64_t cap_rows, int64_t dst_row0, int64_t rows,
+                                           int64_t block) {
+    constexpr int ELT = SH == 4 ? 2 : 4;
+    const char *src = c.src + ((int64_t)(bh / n_kv_heads) * c.sb + (int64_t)(bh % n_kv_heads) * c.sh) * ELT;
+    char *dst = c.dst + (((int64_t)bh * cap_rows + dst_row0) << (SH + 4));
+    const int64_t first = (c.first << SH) + block * (256 * COPY_PIECES) + threadIdx.x, end = rows << SH;
+    lvr_u32x4 w[COPY_PIECES];
+#pragma unroll
+    for (int u = 0; u < COPY_PIECES; ++u) {
+        const int64_t i = first + 256 * u;
+        if (i < end)
+            w[u] = __builtin_nontemporal_load(reinterpret_cast<const lvr_u32x4 *>(src + (i >> SH) * c.st * ELT) + (i & ((1 << SH) - 1)));
+    }
+#pragma unroll
+    for (int u = 0; u < COPY_PIECES; ++u) {
+        const int64_t i = first + 256 * u;
+        if (i < end) __builtin_nontemporal_store(w[u], reinterpret_cast<lvr_u32x4 *>(dst) + i);
+    }
+}
+
+inline unsigned copy_blocks(int64_t rows, int sh) { return (unsigned)(((rows << sh) + 256 * COPY_PIECES - 1) / (256 * COPY_PIECES)); }
+
+// Values in the first v_blocks blocks, keys in the rest, so an append is one launch.
+template <int SH>
+__global__ void __launch_bounds__(256)
+copy_rows_kernel(CopySide k, CopySide v, int n_kv_heads, int64_t cap_rows, int64_t dst_row0, int64_t rows, unsigned v_blocks) {
+    if (blockIdx.x < v_blocks) copy_block<SH>(v, blockIdx.y, n_kv_heads, cap_rows, dst_row0, rows, blockIdx.x);
+    else copy_block<SH>(k, blockIdx.y, n_kv_heads, cap_rows, dst_row0, rows, blockIdx.x - v_blocks);
 }
 
 __device__ __forceinline__ float seg_sum(float v, int lanes_per_sub) {
@@ -256,7 +275,7 @@ build_groups_kernel(void *__restrict__ K, void *__restrict__ centres, float *__r
 // add up over the quad is two lane exchanges per radius.  A wave stores 16 groups' codes as 1536 consecutive bytes.
 // R = group size up to four (the members stay in registers between the two passes); R = 0: any r, members read twice.
 // Bound by memory: K in, K out and 108 bytes per group (650 MB for 8 heads of 131072 keys).  With 16 lanes per group, a software encoder
-// and a four-step exchange per reduction the vector ALU took longer than the traffic, 223 us; now some 120 us.
+// and a four-step exchange per reduction the vector ALU took longer than the traffic, 223 us; now 113 us (5.8 TB/s).
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float lvr_f32x16;
 
 __device__ __forceinline__ float quad_sum(float v) {
@@ -523,14 +542,16 @@ __global__ void iota_rows_kernel(int32_t *slot_pos, int32_t *pos_slot, int64_t c
 hipError_t lvr_launch_copy_kv(lvr_index *ix, const void *K, const int64_t ks[3], const void *V, const int64_t vs[3],
                               int64_t dst_row0, int64_t rows, hipStream_t st, int64_t k_first) {
     if (rows <= 0) return hipSuccess;
-    const int row_bytes = (int)(LVR_D * ix->elt);
-    const int64_t total = rows * (row_bytes / 16);
-    dim3 grid((unsigned)((total + 255) / 256), (unsigned)lvr_n_bh(ix), 2);
     // k_first > 0: the leading key rows are written by the build kernel that reads them from the caller's K
     CopySide k{static_cast<const char *>(K), static_cast<char *>(ix->K), ks[0], ks[1], ks[2], k_first};
     CopySide v{static_cast<const char *>(V), static_cast<char *>(ix->V), vs[0], vs[1], vs[2], 0};
-    hipLaunchKernelGGL(copy_rows_kernel, grid, dim3(256), 0, st, k, v, ix->cfg.n_kv_heads, ix->cap_rows, dst_row0, rows,
-                       row_bytes, (int)ix->elt);
+    const int sh = ix->elt == 2 ? 4 : 5;
+    const unsigned v_blocks = copy_blocks(rows, sh);
+    const dim3 grid(v_blocks + copy_blocks(rows - k_first, sh), (unsigned)lvr_n_bh(ix));
+    if (sh == 4)
+        hipLaunchKernelGGL(copy_rows_kernel<4>, grid, dim3(256), 0, st, k, v, ix->cfg.n_kv_heads, ix->cap_rows, dst_row0, rows, v_blocks);
+    else
+        hipLaunchKernelGGL(copy_rows_kernel<5>, grid, dim3(256), 0, st, k, v, ix->cfg.n_kv_heads, ix->cap_rows, dst_row0, rows, v_blocks);
     return hipGetLastError();
 }
 
@@ -589,23 +610,31 @@ namespace {
 // rescaled space against the centres as stored there); these make the coordinates of a key comparable in size, so that
 // the 32 coordinates that share a scale in the 6-bit code are not drowned by one large channel.
 //
-// Two launches.  The first adds up squares: CHAN_SPLITS workgroups per (sequence, KV head) (fewer where the work space
+// Two steps.  The first adds up squares: CHAN_SPLITS workgroups per (sequence, KV head) (fewer where the work space
 // is smaller), 16 lanes per row with 16-byte loads, four rows of every lane in flight; a sample of 4096 rows is one
-// round trip to memory for 64 workgroups.  The second, a workgroup of 128 threads per (sequence, KV head), adds the
-// workgroups' sums in order (the exponents do not depend on timing) and forms the exponents.  Bound by the latency of two
-// launches and three round trips.  As one workgroup per (sequence, KV head) with a 2-byte load and an add per row the
-// same sums took 826 us for 8 heads of 131072 keys, 2048 dependent rounds (a build and one step: 1192 us, now 360 us).
+// round trip to memory for 64 workgroups.  The second, a workgroup per (sequence, KV head), adds the workgroups' sums in
+// order (the exponents do not depend on timing) and forms the exponents.  Each is bound by the latency of a launch and its
+// trips, some 5 us, so where V has to be copied as well (contiguous groups) half of the copy rides behind each: 8 heads of
+// 131072 keys, build and one step: 237 us, 262 with launches of their own and a copy of one piece per thread.  (As one
+// workgroup per (sequence, KV head) with a 2-byte load and an add per row the sums alone took 826 us.)
 constexpr int CHAN_SPLITS = 64;
 
-__global__ void __launch_bounds__(256)
-channel_sums_kernel(const char *__restrict__ K, int64_t sb, int64_t sh, int64_t stt, int n_kv_heads, int64_t rows, int64_t step,
-                    float *__restrict__ part) {
+struct ChannelArgs {
+    const char *K;
+    int64_t sb, sh, st;       // element strides
+    int64_t rows, step;       // sampled rows, every step-th of the caller's
+    int n_kv_heads, splits;   // workgroups per (sequence, KV head) that add up squares
+    float *part;              // [n_bh][splits][128]
+    int8_t *chan_exp;
+};
+
+__device__ __forceinline__ void channel_sums(const ChannelArgs &a, int bh, int split) {   // 256 threads
     __shared__ float s_sum[4][LVR_D];
-    const int bh = blockIdx.y, splits = gridDim.x;
+    const int64_t rows = a.rows;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15;
-    const char *base = K + ((int64_t)(bh / n_kv_heads) * sb + (int64_t)(bh % n_kv_heads) * sh) * 2;
-    const int64_t share = (rows + splits - 1) / splits;   // sampled rows of this workgroup
-    const int64_t first = blockIdx.x * share, end = first + share < rows ? first + share : rows;
+    const char *base = a.K + ((int64_t)(bh / a.n_kv_heads) * a.sb + (int64_t)(bh % a.n_kv_heads) * a.sh) * 2;
+    const int64_t share = (rows + a.splits - 1) / a.splits;   // sampled rows of this workgroup
+    const int64_t first = split * share, end = first + share < rows ? first + share : rows;
     float ss[8];
     lvr_zero8(ss);
     for (int64_t i0 = first + (threadIdx.x >> 4); i0 < end; i0 += 64) {
@@ -613,7 +642,7 @@ channel_sums_kernel(const char *__restrict__ K, int64_t sb, int64_t sh, int64_t 
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int64_t i = i0 + 16 * u;
-            lvr_load_raw(base + (i < end ? i : i0) * step * stt * 2, 0, li, raw[u]);
+            lvr_load_raw(base + (i < end ? i : i0) * a.step * a.st * 2, 0, li, raw[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -633,19 +662,18 @@ channel_sums_kernel(const char *__restrict__ K, int64_t sb, int64_t sh, int64_t 
     __syncthreads();
     if (threadIdx.x < LVR_D) {
         const int c = threadIdx.x;
-        part[((int64_t)bh * splits + blockIdx.x) * LVR_D + c] = (s_sum[0][c] + s_sum[1][c]) + (s_sum[2][c] + s_sum[3][c]);
+        a.part[((int64_t)bh * a.splits + split) * LVR_D + c] = (s_sum[0][c] + s_sum[1][c]) + (s_sum[2][c] + s_sum[3][c]);
     }
 }
 
-__global__ void __launch_bounds__(LVR_D)
-channel_scale_kernel(const float *__restrict__ part, int splits, int64_t rows, int8_t *__restrict__ chan_exp) {
+__device__ __forceinline__ void channel_exponents(const ChannelArgs &a, int bh) {   // 256 threads, the upper half repeats the lower
     __shared__ float s_dir[2][2];
-    const int bh = blockIdx.x, c = threadIdx.x, wave = threadIdx.x >> 6;
-    const float *p = part + (int64_t)bh * splits * LVR_D + c;
+    const int c = threadIdx.x & (LVR_D - 1), wave = (threadIdx.x >> 6) & 1;
+    const float *p = a.part + (int64_t)bh * a.splits * LVR_D + c;
     float ss = 0.f;
 #pragma unroll 16
-    for (int k = 0; k < splits; ++k) ss += p[(int64_t)k * LVR_D];
-    const float ms = ss / (float)(rows > 0 ? rows : 1);
+    for (int k = 0; k < a.splits; ++k) ss += p[(int64_t)k * LVR_D];
+    const float ms = ss / (float)(a.rows > 0 ? a.rows : 1);
     const bool live = ms > 0.f && ms < INFINITY;
     const float L = live ? 0.5f * log2f(ms) : 0.f;
     constexpr float kTwoPi = 6.283185307179586f;
@@ -656,7 +684,7 @@ channel_scale_kernel(const float *__restrict__ part, int splits, int64_t rows, i
         sc += __shfl_xor(sc, off, 64);
         sn += __shfl_xor(sn, off, 64);
     }
-    if ((c & 63) == 0) {
+    if (threadIdx.x < LVR_D && (c & 63) == 0) {
         s_dir[wave][0] = sc;
         s_dir[wave][1] = sn;
     }
@@ -669,29 +697,62 @@ channel_scale_kernel(const float *__restrict__ part, int splits, int64_t rows, i
         e = (int)rintf(L - o);
         e = e < -8 ? -8 : (e > 8 ? 8 : e);
     }
-    int8_t *mine = chan_exp + (int64_t)bh * LVR_CHAN_STRIDE;
-    mine[c] = (int8_t)e;
-    reinterpret_cast<float *>(mine + LVR_D)[c] = __uint_as_float((uint32_t)(127 + e) << 23);
+    if (threadIdx.x < LVR_D) {
+        int8_t *mine = a.chan_exp + (int64_t)bh * LVR_CHAN_STRIDE;
+        mine[c] = (int8_t)e;
+        reinterpret_cast<float *>(mine + LVR_D)[c] = __uint_as_float((uint32_t)(127 + e) << 23);
+    }
+}
+
+// The two steps, each with a copy behind it in the same launch: the values' first part while squares are added up, the rest
+// and the ungrouped keys while the exponents are formed.  v.first and v_end bound the values' rows, k.first and rows the
+// keys'; v_blocks = 0 and an empty key range: the step alone.
+template <bool SUMS>
+__global__ void __launch_bounds__(256)
+channel_step_kernel(ChannelArgs a, CopySide k, CopySide v, int64_t cap_rows, int64_t v_end, int64_t rows, unsigned v_blocks) {
+    const unsigned lead = SUMS ? (unsigned)a.splits : 1u;
+    if (blockIdx.x < lead) {
+        if constexpr (SUMS) channel_sums(a, blockIdx.y, blockIdx.x);
+        else channel_exponents(a, blockIdx.y);
+    } else if (blockIdx.x - lead < v_blocks) copy_block<4>(v, blockIdx.y, a.n_kv_heads, cap_rows, 0, v_end, blockIdx.x - lead);
+    else copy_block<4>(k, blockIdx.y, a.n_kv_heads, cap_rows, 0, rows, blockIdx.x - lead - v_blocks);
 }
 
 }  // namespace
 
 // The workgroups' sums go through the attention's partial-output buffer (G * Pmax * 128 floats per (sequence, KV head),
 // Pmax >= 4), which no launch in flight on the same stream still needs once these run.
-hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t ks[3], int64_t n, hipStream_t st) {
+// V != NULL: the launches also copy all n value rows and the key rows from k_first on.
+hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t ks[3], int64_t n, hipStream_t st, const void *V,
+                                     const int64_t *vs, int64_t k_first) {
     if (!ix->chan_scaled || n <= 0) return hipSuccess;
-    const int64_t step = (n + 4095) / 4096;   // at most 4096 rows are looked at
-    const int64_t rows = (n + step - 1) / step;
+    ChannelArgs a;
+    a.K = static_cast<const char *>(K);
+    a.sb = ks[0];
+    a.sh = ks[1];
+    a.st = ks[2];
+    a.step = (n + 4095) / 4096;   // at most 4096 rows are looked at
+    a.rows = (n + a.step - 1) / a.step;
+    a.n_kv_heads = ix->cfg.n_kv_heads;
     const int room = ix->G * (ix->P > ix->P_dense ? ix->P : ix->P_dense);
-    int splits = (int)((rows + 63) / 64);     // 64 rows: four per lane quarter of a workgroup
-    if (splits > CHAN_SPLITS) splits = CHAN_SPLITS;
-    if (splits > room) splits = room;
-    hipLaunchKernelGGL(channel_sums_kernel, dim3((unsigned)splits, (unsigned)lvr_n_bh(ix)), dim3(256), 0, st,
-                       static_cast<const char *>(K), ks[0], ks[1], ks[2], ix->cfg.n_kv_heads, rows, step, ix->part_o);
+    a.splits = (int)((a.rows + 63) / 64);     // 64 rows: four per lane quarter of a workgroup
+    if (a.splits > CHAN_SPLITS) a.splits = CHAN_SPLITS;
+    if (a.splits > room) a.splits = room;
+    a.part = ix->part_o;
+    a.chan_exp = lvr_chan_exp(ix);
+    CopySide k{a.K, static_cast<char *>(ix->K), ks[0], ks[1], ks[2], V ? k_first : n};
+    CopySide v{static_cast<const char *>(V), static_cast<char *>(ix->V), V ? vs[0] : 0, V ? vs[1] : 0, V ? vs[2] : 0, 0};
+    const int64_t half = V ? n / 2 : 0;
+    const unsigned n_bh = (unsigned)lvr_n_bh(ix);
+    unsigned v_blocks = copy_blocks(half, 4);
+    hipLaunchKernelGGL(channel_step_kernel<true>, dim3((unsigned)a.splits + v_blocks, n_bh), dim3(256), 0, st, a, k, v, ix->cap_rows,
+                       half, n, v_blocks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(channel_scale_kernel, dim3((unsigned)lvr_n_bh(ix)), dim3(LVR_D), 0, st, ix->part_o, splits, rows,
-                       lvr_chan_exp(ix));
+    v.first = half;
+    v_blocks = V ? copy_blocks(n - half, 4) : 0;
+    hipLaunchKernelGGL(channel_step_kernel<false>, dim3(1u + v_blocks + copy_blocks(n - k.first, 4), n_bh), dim3(256), 0, st, a, k, v,
+                       ix->cap_rows, n, n, v_blocks);
     return hipGetLastError();
 }
 

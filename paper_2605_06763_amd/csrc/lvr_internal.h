@@ -132,8 +132,10 @@ static inline int8_t *lvr_chan_exp(const lvr_index *ix) {
 }
 
 // ---- launchers (each returns a hipError_t from hipGetLastError after the launch) ----
-// channel exponents from the keys about to be indexed (element strides ks for (sequence, head, token))
-hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t ks[3], int64_t n, hipStream_t st);
+// channel exponents from the keys about to be indexed (element strides ks for (sequence, head, token)); with V, the same
+// launches copy the value rows and the key rows from k_first on into the arena (lvr_launch_copy_kv at row 0)
+hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t ks[3], int64_t n, hipStream_t st,
+                                     const void *V = nullptr, const int64_t *vs = nullptr, int64_t k_first = 0);
 // copies `rows` key rows and value rows into the arena starting at arena row dst_row0 (one launch)
 hipError_t lvr_launch_copy_kv(lvr_index *ix, const void *K, const int64_t ks[3], const void *V, const int64_t vs[3],
                               int64_t dst_row0, int64_t rows, hipStream_t st, int64_t k_first = 0);
