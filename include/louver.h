@@ -145,9 +145,9 @@ typedef struct lvr_config {
                              * lvr_threshold (appendix "Threshold Oracle Comparison"); 0 = none         */
     uint64_t seed;          /* seed of the counter-based generator behind the reservoir              */
     int32_t index_dtype;    /* lvr_index_dtype: storage of the centres                               */
-    int32_t query_workgroups; /* workgroups a range-query launch aims at (its segment size follows from it);
-                               * 0 = the default, 1024 (four per compute unit); a tuning knob, results do not
-                               * depend on it                                                        */
+    int32_t query_workgroups; /* workgroups a range-query launch aims at (its segment size, a power of two times
+                               * 64 groups, follows from it); 0 = the default, a segment size chosen for how the
+                               * workgroups fill the device; a tuning knob, results do not depend on it */
 } lvr_config;
 
 /* Counters of the most recent lvr_query / lvr_decode_step, summed over batch and heads. */

@@ -56,11 +56,10 @@ struct FusedArgs {
 // Four waves per SIMD (four workgroups per compute unit) are asked for wherever the kernel fits 128 registers: one
 // head block of balls with at most four coordinate blocks, and the eight-head operand.  Left to itself the compiler
 // has filled 128 vector registers and then needed four accumulator registers more, which costs a quarter of the waves.
-// And no more than four: the launches aim at 1024 workgroups (four per compute unit) and larger batches run as whole
-// rounds of 1024; a fifth resident workgroup makes the rounds uneven (1280 + 768 for 2048 workgroups: 1.2 % slower at
-// 16 sequences of 32k keys).  The launcher sees to that with unused dynamic LDS (a fifth of a compute unit's LDS and a
+// And no more than four for a launch of several rounds: larger batches run as whole rounds of 1024; a fifth resident
+// workgroup makes the rounds uneven (1280 + 768 for 2048 workgroups: 1.2 % slower at 16 sequences of 32k keys).  The launcher sees to that with unused dynamic LDS (a fifth of a compute unit's LDS and a
 // little more per workgroup) whenever a launch has more workgroups than fit at once; a launch that fits takes whatever
-// residency the registers allow, which is where the few workgroups beyond 1024 (the buffer's) find room.
+// residency the registers allow.
 // What the first loads need comes as scalar arguments ahead of the struct: 14 words of them are in registers when a wave
 // starts, so the loads of q and the first centres do not wait for a read of the argument block (32.9 against 33.4 us per
 // step at 128k keys, 11.7 against 12.1 at 16k; the attention kernels order their arguments the same way).
@@ -815,6 +814,37 @@ struct LaunchEvents {
         else hipLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, a.q, a.chan_exp, a.centres, a.radii, a.tau, a.G, a.tiles_per_wave, (int)a.max_groups, (int)a.n_groups, a);                                            \
     } while (0)
 
+// Tiles per wave of a launch.  All workgroups start together and the launch ends with the compute unit that holds the most of
+// them, so what counts is k (tiles + fixed part), k = workgroups on the fullest of 256 compute units; the fixed part (entry,
+// operand, barriers, lists) is about two tiles of one-key groups, and a tile's work grows with the keys of a group.  With
+// one or two workgroups per unit too few loads are in flight (factors 2 and 1.25), a fifth costs more than its share where
+// the index is most of the traffic (one key per group: 1.125), a trip reads two tiles (odd counts read one for nothing,
+// which matters in the same place), and what does not fit at once is a round of its own: beyond four per unit with eight
+// heads, beyond 1280 workgroups otherwise.  The constants are fitted to sweeps of 1 to 64 tiles at 17 sizes (contexts of
+// 5000 to 131072 keys, batches up to 16, 2 to 128 (sequence, KV head) pairs): within 3 % of the best count at most of them.
+// The former rule, 1024 workgroups in powers of two, put 1032 on the device as soon as a buffer joined 1024 segments, and
+// 520 just behind a power of two.  us per step, then and now: 32768 keys and a buffer 16.0 / 14.5, with 64 heads 28.1 / 22.2;
+// 131072 keys and a buffer 36.3 / 34.2; 67530 keys 21.7 / 20.4, in groups of four 41.2 / 37.6; 16 sequences of 32768 keys and
+// buffers 121.4 / 113.3; eight sequences of 20000 keys and buffers went the other way, 41.4 / 42.7.
+int tiles_for_launch(int64_t n_groups, int n_bh, int has_buffer, int r, bool wide) {
+    const uint32_t n64 = (uint32_t)((n_groups + 63) / 64);   // segments of one tile per wave
+    int best = 1;
+    int64_t best_cost = 0;
+    for (int tpw = 1; tpw <= SEG_MAX_TILES; ++tpw) {
+        if (r == 1 && tpw > 1 && (tpw & 1)) continue;
+        const int64_t wgs = (int64_t)n_bh * ((n64 + (uint32_t)tpw - 1) / (uint32_t)tpw + (uint32_t)has_buffer);
+        int64_t k = (wgs + 255) / 256;
+        if (wgs > 1280 || (wide && wgs > 1024)) k = 4 * ((wgs + 1023) / 1024);
+        const int64_t cost = (k == 1 ? 16 : (k == 2 ? 10 : (k == 5 && r == 1 ? 9 : 8))) * k * (tpw * r + 2);
+        if (best_cost == 0 || cost < best_cost) {   // equal: the more workgroups
+            best = tpw;
+            best_cost = cost;
+        }
+        if ((uint32_t)tpw >= n64) break;   // one segment: a longer one changes nothing
+    }
+    return best;
+}
+
 template <int UA, int W>
 void launch_s(dim3 grid, unsigned dyn_lds, hipStream_t st, const FusedArgs &a, int S, const LaunchEvents &ev) {
     switch (S) {
@@ -867,15 +897,17 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     a.buffer_dense = (ix->cfg.flags & LVR_ATTEND_BUFFER_DENSE) ? 1 : 0;
     a.skip_bounds = (ix->skip_bounds && !tau_s) ? 1 : 0;
     const int n_bh = lvr_n_bh(ix);
-    // segment = 4 waves x tiles_per_wave tiles x 16 groups; aim at a fixed number of workgroups per launch
-    const int64_t target_wgs = ix->cfg.query_workgroups > 0 ? ix->cfg.query_workgroups : 1024;
-    const int64_t want = a.n_groups * n_bh / target_wgs;
+    // segment = 4 waves x tiles_per_wave tiles x 16 groups
+    const int has_buffer = a.n_total > ix->n_indexed ? 1 : 0;
     int tpw = 1;
-    while (tpw < SEG_MAX_TILES && (int64_t)tpw * 64 < want) tpw *= 2;
+    if (ix->cfg.query_workgroups > 0) {   // the caller's number of workgroups
+        const int64_t want = a.n_groups * n_bh / ix->cfg.query_workgroups;
+        while (tpw < SEG_MAX_TILES && (int64_t)tpw * 64 < want) tpw *= 2;
+    } else
+        tpw = tiles_for_launch(a.n_groups, n_bh, has_buffer, ix->cfg.group_size, ix->G > 4);
     a.tiles_per_wave = tpw;
     const int seg_groups = tpw * 64;
     a.n_segs = (int)((a.n_groups + seg_groups - 1) / seg_groups);
-    const int has_buffer = a.n_total > ix->n_indexed ? 1 : 0;
     ix->seg_groups = seg_groups;
     ix->n_segs = a.n_segs;
     if (a.n_segs + has_buffer == 0) return hipSuccess;

@@ -223,3 +223,26 @@ def test_fp32_one_launch_query_is_the_two_launch_one(G, oracle, hq, hkv, n, r, S
         if o1 is not None:
             # weights of logits of magnitude below 60, each good to 128 * 2^-24 of the sum of its terms' magnitudes
             assert np.abs(o1 - o2).max() <= 1e-4
+
+
+@pytest.mark.parametrize("index_dtype", ["auto", "same"])
+@pytest.mark.parametrize("hq,hkv,n,r,tail", [
+    (32, 32, 2000, 1, 3), (8, 8, 9001, 1, 0), (64, 8, 20000, 1, 5), (8, 8, 34001, 1, 7), (8, 8, 50007, 1, 1),
+    (16, 16, 34003, 4, 0), (16, 16, 50001, 4, 2), (8, 2, 40001, 1, 0), (24, 12, 12288, 2, 9)])
+def test_segments_chosen_by_the_launch(G, oracle, hq, hkv, n, r, tail, index_dtype):
+    """The tiles per wave that a launch picks by itself, powers of two, other even counts and (groups of several keys) odd
+    ones, with and without the buffer's workgroups, four and eight heads per pass: the oracle's sets and outputs."""
+    L = G.L
+    g = np.random.default_rng(n + hkv)
+    # bf16 values, as the cache holds them (a value off the grid is half an ulp, 2^-9 = 2.0e-3, from what is attended)
+    K, V = (torch.from_numpy(g.standard_normal((1, hkv, n + tail, 128)).astype(np.float32)).bfloat16().float().numpy()
+            for _ in range(2))
+    q = g.standard_normal((1, hq, 128)).astype(np.float32)
+    dt = {"auto": L.LVR_INDEX_AUTO, "same": L.LVR_INDEX_SAME}[index_dtype]
+    with G.Index(K[:, :, :n], V[:, :, :n], "bf16", hq, capacity=n + tail, group_size=r, buffer_size=64, index_dtype=dt) as ix:
+        if tail:
+            ix.append(K[:, :, n:], V[:, :, n:])
+        for frac in (0.004, 0.05):
+            tau = G.oracle_taus(oracle, ix, q, frac=frac)
+            idx, cnt, out = ix.query(q, tau, fused=True)
+            G.check_step(oracle, ix, q, tau, idx, cnt, out, tag=f"segments n={n} r={r} hkv={hkv} {index_dtype}")
