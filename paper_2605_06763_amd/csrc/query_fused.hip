@@ -57,9 +57,9 @@ struct FusedArgs {
 // head block of balls with at most four coordinate blocks, and the eight-head operand.  Left to itself the compiler
 // has filled 128 vector registers and then needed four accumulator registers more, which costs a quarter of the waves.
 // And no more than four for a launch of several rounds: larger batches run as whole rounds of 1024; a fifth resident
-// workgroup makes the rounds uneven (1280 + 768 for 2048 workgroups: 1.2 % slower at 16 sequences of 32k keys).  The launcher sees to that with unused dynamic LDS (a fifth of a compute unit's LDS and a
-// little more per workgroup) whenever a launch has more workgroups than fit at once; a launch that fits takes whatever
-// residency the registers allow.
+// workgroup makes the rounds uneven (1280 + 768 for 2048 workgroups: 1.2 % slower at 16 sequences of 32k keys).  The
+// launcher sees to that with unused dynamic LDS (a fifth of a compute unit's LDS and a little more per workgroup)
+// whenever a launch has more workgroups than fit at once; a launch that fits takes whatever residency the registers allow.
 // What the first loads need comes as scalar arguments ahead of the struct: 14 words of them are in registers when a wave
 // starts, so the loads of q and the first centres do not wait for a read of the argument block (32.9 against 33.4 us per
 // step at 128k keys, 11.7 against 12.1 at 16k; the attention kernels order their arguments the same way).
