@@ -246,3 +246,29 @@ def test_segments_chosen_by_the_launch(G, oracle, hq, hkv, n, r, tail, index_dty
             tau = G.oracle_taus(oracle, ix, q, frac=frac)
             idx, cnt, out = ix.query(q, tau, fused=True)
             G.check_step(oracle, ix, q, tau, idx, cnt, out, tag=f"segments n={n} r={r} hkv={hkv} {index_dtype}")
+
+
+@pytest.mark.parametrize("dtype,batch,hq,hkv,n,splits", [
+    ("f32", 1, 4, 2, 3000, -1), ("f32", 1, 4, 2, 3000, 64), ("f32", 9, 32, 8, 300, 0), ("bf16", 1, 4, 2, 3000, -1),
+    ("bf16", 1, 4, 2, 3000, 64), ("bf16", 9, 32, 8, 300, 0), ("bf16", 1, 2, 1, 65600, 0)])
+def test_carried_scores_are_not_rounded_at_the_size_of_the_logit(G, dtype, batch, hq, hkv, n, splits):
+    """Every attention form over carried scores, on integers: each score is 2^20 plus a small exact integer, so the difference
+    of two scores is exact and a softmax weight is off by the roundings of that difference times the scale alone.  (Scaled
+    first, a logit of 2^17 base-2 units is rounded by up to 2^-7, a weight by half a percent.)"""
+    g = np.random.default_rng(n + hq)
+    K = g.integers(-4, 5, size=(batch, hkv, n, 128)).astype(np.float32)
+    V = W.round_to_bf16(g.uniform(-1.0, 1.0, size=(batch, hkv, n, 128)).astype(np.float32))
+    q = g.integers(-4, 5, size=(batch, hq, 128)).astype(np.float32)
+    K[..., 0] = q[..., 0] = 1024.0
+    with G.Index(K, V, dtype, hq, capacity=n, group_size=4, attn_splits=splits) as ix:
+        _, cnt, out = ix.query(q, np.full((batch, hq), -np.inf, dtype=np.float32), fused=True)
+    assert (cnt == n).all()
+    for b in range(batch):
+        for h in range(hq):
+            kv = h * hkv // hq
+            s = K[b, kv].astype(np.float64) @ q[b, h].astype(np.float64)
+            p = np.exp((s - s.max()) / math.sqrt(128))
+            want = (p / p.sum()) @ V[b, kv].astype(np.float64)
+            # weights above 2^-30 of the largest: 30 ln 2 * 3 * 2^-24 (scale, difference, product) plus two ulps of the
+            # exponential; values below 1; the fp32 sums add at most 2^-24 for each of the lists' rounds
+            assert np.abs(out[b, h] - want).max() <= 2e-5, (b, h, np.abs(out[b, h] - want).max())
