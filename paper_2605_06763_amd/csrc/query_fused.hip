@@ -814,33 +814,51 @@ struct LaunchEvents {
         else hipLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, a.q, a.chan_exp, a.centres, a.radii, a.tau, a.G, a.tiles_per_wave, (int)a.max_groups, (int)a.n_groups, a);                                            \
     } while (0)
 
-// Tiles per wave of a launch.  All workgroups start together and the launch ends with the compute unit that holds the most of
-// them, so what counts is k (tiles + fixed part), k = workgroups on the fullest of 256 compute units; the fixed part (entry,
-// operand, barriers, lists) is about two tiles of one-key groups, and a tile's work grows with the keys of a group.  With
-// one or two workgroups per unit too few loads are in flight (factors 2 and 1.25), a fifth costs more than its share where
-// the index is most of the traffic (one key per group: 1.125), a trip reads two tiles (odd counts read one for nothing,
-// which matters in the same place), and what does not fit at once is a round of its own: beyond four per unit with eight
-// heads, beyond 1280 workgroups otherwise.  The constants are fitted to sweeps of 1 to 64 tiles at 17 sizes (contexts of
-// 5000 to 131072 keys, batches up to 16, 2 to 128 (sequence, KV head) pairs): within 3 % of the best count at most of them.
-// The former rule, 1024 workgroups in powers of two, put 1032 on the device as soon as a buffer joined 1024 segments, and
-// 520 just behind a power of two.  us per step, then and now: 32768 keys and a buffer 16.0 / 14.5, with 64 heads 28.1 / 22.2;
-// 131072 keys and a buffer 36.3 / 34.2; 67530 keys 21.7 / 20.4, in groups of four 41.2 / 37.6; 16 sequences of 32768 keys and
-// buffers 121.4 / 113.3; eight sequences of 20000 keys and buffers went the other way, 41.4 / 42.7.
-int tiles_for_launch(int64_t n_groups, int n_bh, int has_buffer, int r, bool wide) {
-    const uint32_t n64 = (uint32_t)((n_groups + 63) / 64);   // segments of one tile per wave
-    int best = 1;
-    int64_t best_cost = 0;
-    for (int tpw = 1; tpw <= SEG_MAX_TILES; ++tpw) {
+// Tiles per wave of a launch: the power of two that gives about `workgroups` workgroups or fewer.
+int tiles_for_workgroups(int64_t n_groups, int n_bh, int workgroups) {
+    const int64_t want = n_groups * n_bh / workgroups;
+    int tpw = 1;
+    while (tpw < SEG_MAX_TILES && (int64_t)tpw * 64 < want) tpw *= 2;
+    return tpw;
+}
+
+// The default number of tiles per wave.  1024 workgroups in powers of two put 1032 on the device as soon as a buffer joins
+// 1024 segments, and 520 just behind a power of two.  All workgroups start together and the launch ends with the compute unit
+// that holds the most of them, so where another count brings a launch of one round a lower k (tiles + fixed part), k =
+// workgroups on the fullest of 256 compute units, that count is taken: the fixed part (entry, operand, barriers, lists) is
+// about two tiles of one-key groups, a further key in a group adds a quarter of a tile, one or two workgroups per unit have
+// too few loads in flight (factors 2 and 1.15), a trip reads two tiles (odd counts of one-key groups read one for nothing),
+// and `resident` workgroups per unit are a round.  It has to be 6 % lower: the sum does not know how many keys survive.
+// Sweeps of 1 to 64 tiles at 23 sizes (5000 to 131072 keys, batches up to 16, 2 to 128 (sequence, KV head) pairs, with and
+// without a buffer, keys with and without locality) say where that holds: for eight heads per pass, any format and group
+// size (6 % faster than powers of two over 84 such settings; one is slower by more than 2 %, groups of eight at 65736 keys:
+// 46.5 -> 48.6 us where all balls survive, 30.0 -> 25.7 on local keys), and for four heads on coded centres of one-key groups
+// (1.2 % faster over 78; slower by more than 2 %: local keys at 32845 keys 17.4 -> 18.1 us, and two 8-bit settings by 0.3 and 0.9 us).
+// For boxes, bf16 centres and groups of several keys with four heads the same choice won and lost by up to 23 % (boxes of 16
+// sequences of 9004 keys 84.9 -> 104.5 us), so those keep the powers of two.
+// us per step, powers of two and now: 32768 keys and a buffer 17.2 / 16.3, 65536 and a buffer 23.3 / 21.8, 131072 and a buffer
+// 34.2 / 33.0; with 64 heads 16384 keys and a buffer 24.3 / 18.4, 65536 and a buffer 36.6 / 28.7.
+int tiles_for_launch(int64_t n_groups, int n_bh, int has_buffer, int r, bool fitted, int resident) {
+    const int former = tiles_for_workgroups(n_groups, n_bh, 1024);
+    if (!fitted) return former;
+    const int64_t n64 = (n_groups + 63) / 64;   // segments of one tile per wave
+    const int64_t round = 256 * resident;
+    auto cost = [&](int tpw, int64_t wgs) {
+        const int64_t k = wgs > round ? resident * ((wgs + round - 1) / round) : (wgs + 255) / 256;
+        return (k == 1 ? 40 : (k == 2 ? 23 : 20)) * k * ((tpw < n64 ? tpw : n64) * (r + 3) + 8);
+    };
+    auto workgroups = [&](int tpw) { return n_bh * ((n64 + tpw - 1) / tpw + has_buffer); };
+    int best = former;
+    int64_t best_cost = cost(former, workgroups(former)) * 94 / 100;
+    for (int tpw = 1; tpw <= SEG_MAX_TILES && tpw <= n64; ++tpw) {
         if (r == 1 && tpw > 1 && (tpw & 1)) continue;
-        const int64_t wgs = (int64_t)n_bh * ((n64 + (uint32_t)tpw - 1) / (uint32_t)tpw + (uint32_t)has_buffer);
-        int64_t k = (wgs + 255) / 256;
-        if (wgs > 1280 || (wide && wgs > 1024)) k = 4 * ((wgs + 1023) / 1024);
-        const int64_t cost = (k == 1 ? 16 : (k == 2 ? 10 : (k == 5 && r == 1 ? 9 : 8))) * k * (tpw * r + 2);
-        if (best_cost == 0 || cost < best_cost) {   // equal: the more workgroups
+        const int64_t wgs = workgroups(tpw);
+        if (wgs > round) continue;
+        const int64_t c = cost(tpw, wgs);
+        if (c < best_cost) {   // equal: the more workgroups
             best = tpw;
-            best_cost = cost;
+            best_cost = c;
         }
-        if ((uint32_t)tpw >= n64) break;   // one segment: a longer one changes nothing
     }
     return best;
 }
@@ -899,12 +917,12 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     const int n_bh = lvr_n_bh(ix);
     // segment = 4 waves x tiles_per_wave tiles x 16 groups
     const int has_buffer = a.n_total > ix->n_indexed ? 1 : 0;
-    int tpw = 1;
-    if (ix->cfg.query_workgroups > 0) {   // the caller's number of workgroups
-        const int64_t want = a.n_groups * n_bh / ix->cfg.query_workgroups;
-        while (tpw < SEG_MAX_TILES && (int64_t)tpw * 64 < want) tpw *= 2;
-    } else
-        tpw = tiles_for_launch(a.n_groups, n_bh, has_buffer, ix->cfg.group_size, ix->G > 4);
+    const bool wide = ix->G > 4;
+    const int tpw = ix->cfg.query_workgroups > 0
+                        ? tiles_for_workgroups(a.n_groups, n_bh, ix->cfg.query_workgroups)   // the caller's number
+                        : tiles_for_launch(a.n_groups, n_bh, has_buffer, ix->cfg.group_size,
+                                           !tau_s && (wide || (!ix->box && (ix->cf8 || ix->cf6) && ix->cfg.group_size == 1)),
+                                           wide ? (ix->box ? 3 : 4) : 5);
     a.tiles_per_wave = tpw;
     const int seg_groups = tpw * 64;
     a.n_segs = (int)((a.n_groups + seg_groups - 1) / seg_groups);

@@ -228,10 +228,11 @@ def test_fp32_one_launch_query_is_the_two_launch_one(G, oracle, hq, hkv, n, r, S
 @pytest.mark.parametrize("index_dtype", ["auto", "same"])
 @pytest.mark.parametrize("hq,hkv,n,r,tail", [
     (32, 32, 2000, 1, 3), (8, 8, 9001, 1, 0), (64, 8, 20000, 1, 5), (8, 8, 34001, 1, 7), (8, 8, 50007, 1, 1),
-    (16, 16, 34003, 4, 0), (16, 16, 50001, 4, 2), (8, 2, 40001, 1, 0), (24, 12, 12288, 2, 9)])
+    (16, 16, 34003, 4, 0), (16, 16, 50001, 4, 2), (8, 2, 40001, 1, 0), (24, 12, 12288, 2, 9),
+    (64, 8, 16390, 2, 7), (64, 8, 33001, 4, 3)])
 def test_segments_chosen_by_the_launch(G, oracle, hq, hkv, n, r, tail, index_dtype):
-    """The tiles per wave that a launch picks by itself, powers of two, other even counts and (groups of several keys) odd
-    ones, with and without the buffer's workgroups, four and eight heads per pass: the oracle's sets and outputs."""
+    """The tiles per wave that a launch picks by itself, powers of two, other even counts and (eight heads, groups of several
+    keys) odd ones, with and without the buffer's workgroups, four and eight heads per pass: the oracle's sets and outputs."""
     L = G.L
     g = np.random.default_rng(n + hkv)
     # bf16 values, as the cache holds them (a value off the grid is half an ulp, 2^-9 = 2.0e-3, from what is attended)
