@@ -236,10 +236,13 @@ void prof_free(lvr_index *ix) {
 // at 0.5-1 % retrieved).  The set sizes are not known on the host, so the context length stands in.
 inline bool one_launch_attention(const lvr_index *ix, bool carried = false) {
     if (ix->attn_one_launch >= 0) return ix->attn_one_launch != 0;
-    // lists that carry their scores take the one-launch kernels with two dependent trips (two workgroups per head
+    // bf16 lists that carry their scores take the one-launch kernels with two dependent trips (two workgroups per head
     // beyond 65536 keys), which moves the crossover up: one launch against two, us per step at 0.5 % retrieved,
-    // 32 heads: 39.7 / 41.3 at 196608 keys, 50.2 / 51.3 at 262144, 102.5 / 101.5 at 524288
-    return lvr_n_bhq(ix) >= 128 || ix->n_total <= (carried ? 262144 : 65536);
+    // 32 heads: 39.7 / 41.3 at 196608 keys, 50.2 / 51.3 at 262144, 102.5 / 101.5 at 524288.  fp32 rows are twice as wide
+    // and one workgroup gathers a head's: one launch against two at 1 % and 3 % retrieved, one head of 65536 keys
+    // 18.5 / 18.3 and 27.9 / 21.3, of 131072 30.3 / 27.0 and 46.7 / 29.7, 32 heads on 8 at 131072 138.9 / 132.4 and
+    // 167.5 / 140.3 (at 0.2 % the single launch is some 2 us ahead up to 200000 keys)
+    return lvr_n_bhq(ix) >= 128 || ix->n_total <= (carried && ix->cfg.kv_dtype == LVR_BF16 ? 262144 : 65536);
 }
 
 // One grouping per coordinate block: groups [g0, g0 + ng) are formed from arena rows g0*r .. (g0+ng)*r - 1

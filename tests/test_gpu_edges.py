@@ -273,3 +273,20 @@ def test_carried_scores_are_not_rounded_at_the_size_of_the_logit(G, dtype, batch
             # weights above 2^-30 of the largest: 30 ln 2 * 3 * 2^-24 (scale, difference, product) plus two ulps of the
             # exponential; values below 1; the fp32 sums add at most 2^-24 for each of the lists' rounds
             assert np.abs(out[b, h] - want).max() <= 2e-5, (b, h, np.abs(out[b, h] - want).max())
+
+
+@pytest.mark.parametrize("dtype,n,one_launch", [("f32", 65536, True), ("f32", 65537, False), ("bf16", 65537, True), ("bf16", 262145, False)])
+def test_attention_form_of_a_decode_step(G, oracle, dtype, n, one_launch):
+    """The context length up to which a head's list is attended in one launch, on both sides of it, against the oracle: 65536
+    keys of fp32, 262144 of bf16 (whose rows are half as wide and, beyond 65536, gathered by two workgroups per head)."""
+    L = G.L
+    g = np.random.default_rng(n)
+    K = W.round_to_bf16(g.standard_normal((1, 1, n, 128)).astype(np.float32))
+    q = g.standard_normal((1, 2, 128)).astype(np.float32)
+    with G.Index(K, K, dtype, 2, capacity=n, group_size=1) as ix:
+        L.lvr_profile_enable(ix.h, 64)
+        tau = G.oracle_taus(oracle, ix, q, frac=0.02)
+        idx, cnt, out = ix.query(q, tau, fused=True)
+        launches = L.lvr_profile_read(ix.h)
+        G.check_step(oracle, ix, q, tau, idx, cnt, out, tag=f"{dtype} n={n}")
+    assert launches["attn_partial"][1] == 1 and launches["attn_combine"][1] == (0 if one_launch else 1)
