@@ -166,12 +166,11 @@ sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__rest
 // then the 16 partial triples are merged through LDS, so no partials travel through HBM and no
 // combine launch follows.  Thread 0 also publishes (and clears) the head's internal counter
 // when asked to.
-template <typename KT, bool CARRY>
+template <typename KT>
 __global__ void __launch_bounds__(1024)
 sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ V,
                            const int32_t *__restrict__ pos_slot, const float *__restrict__ q,
-                           const int32_t *__restrict__ idx, const float *__restrict__ scores, int64_t score_stride,
-                           const int32_t *count, int count_stride,   // may alias head_count: not restrict
+                           const int32_t *__restrict__ idx, const int32_t *count, int count_stride,   // may alias head_count: not restrict
                            int64_t cap, float *__restrict__ out, int64_t cap_rows, int64_t n_total, int n_q_heads,
                            int n_kv_heads, int G, float qscale, int32_t *head_count,
                            int32_t *__restrict__ head_stat, int32_t *__restrict__ publish_count) {
@@ -190,7 +189,6 @@ sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ 
     const int64_t start = (int64_t)wave * L;
     const int64_t end = (start + L < cnt) ? start + L : cnt;
 
-    const float unit = CARRY ? qscale : 1.0f;   // carried scores are raw, q below is scaled
     float qv[8];
     {
         const float *qh = q + hq * LVR_D + li * 8;
@@ -207,45 +205,35 @@ sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ 
     for (int64_t c0 = start; c0 < end; c0 += 64) {          // uniform over the wave
         int64_t e = c0 + lane;
         int myslot = -1;
-        float myscore = 0.f;
         if (e < end) {
             const int64_t pos = my_idx[e];
-            if constexpr (CARRY) myscore = e < score_stride ? scores[hq * score_stride + e] : 0.f;
             if (pos >= 0 && pos < n_total) myslot = pslot ? pslot[pos] : (int)pos;
         }
         const int chunk = (int)((end - c0 < 64) ? end - c0 : 64);
         for (int b0 = 0; b0 < chunk; b0 += 16) {
-            lvr_raw8<KT> kr[CARRY ? 1 : 4], vr[4];
+            lvr_raw8<KT> kr[4], vr[4];
             int slot[4];
-            float given[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 slot[i] = __shfl(myslot, (b0 + i * 4 + sub) & 63, 64);
-                if constexpr (CARRY) given[i] = __shfl(myscore, (b0 + i * 4 + sub) & 63, 64);
                 if (b0 + i * 4 + sub >= chunk) slot[i] = -1;
                 const int64_t sl = slot[i] < 0 ? 0 : slot[i];
-                if constexpr (!CARRY) lvr_load_raw(Kb, sl, li, kr[i]);
+                lvr_load_raw(Kb, sl, li, kr[i]);
                 lvr_load_raw(Vb, sl, li, vr[i]);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                float vx[8];
+                float kx[8], vx[8];
+                lvr_unpack(kr[i], kx);
                 lvr_unpack(vr[i], vx);
-                float s;
-                if constexpr (CARRY) {
-                    s = given[i];
-                } else {
-                    float kx[8];
-                    lvr_unpack(kr[i], kx);
-                    float d = 0.f;
+                float d = 0.f;
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) d += qv[c] * kx[c];
-                    s = lvr_row16_sum(d);
-                }
+                for (int c = 0; c < 8; ++c) d += qv[c] * kx[c];
+                float s = lvr_row16_sum(d);
                 s = (slot[i] >= 0) ? s : -INFINITY;
                 const float m_new = fmaxf(m, s);
-                const float alpha = exp2_safe(m, m_new, unit);
-                const float w = exp2_safe(s, m_new, unit);
+                const float alpha = exp2_safe(m, m_new);
+                const float w = exp2_safe(s, m_new);
                 l = l * alpha + w;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) acc[c] = acc[c] * alpha + w * vx[c];
@@ -255,7 +243,7 @@ sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ 
     }
     float m_all = fmaxf(m, __shfl_xor(m, 16, 64));
     m_all = fmaxf(m_all, __shfl_xor(m_all, 32, 64));
-    const float sc = exp2_safe(m, m_all, unit);
+    const float sc = exp2_safe(m, m_all);
     l *= sc;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
@@ -278,7 +266,7 @@ sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ 
         float num = 0.f, den = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float wt = exp2_safe(s_m[w], M, unit);
+            const float wt = exp2_safe(s_m[w], M);
             den += wt * s_l[w];
             num += wt * s_o[w][threadIdx.x];
         }
@@ -291,15 +279,16 @@ sparse_attention_wg_kernel(const void *__restrict__ K, const void *__restrict__ 
     }
 }
 
-// The one-launch form for lists that carry their scores (the decode step on bf16 caches): the same 1024-thread
-// workgroup per head, with the dependent round trips to memory cut to two.
-//   trip 1  the count AND the positions and scores of the first 1024 list entries: which entries a lane asks for
-//           does not depend on the count (lane (quarter s, j) of wave w asks for entry j of batch w + 16 s, a batch
+// The one-launch form for lists that carry their scores (the decode step): a workgroup of NW waves per head, with the
+// dependent round trips to memory cut to two (fp32: three).
+//   trip 1  the count AND the positions and scores of the first 64 NW list entries: which entries a lane asks for
+//           does not depend on the count (lane (quarter s, j) of wave w asks for entry j of batch w + NW s, a batch
 //           being 16 consecutive entries), what lies beyond the count is dropped when it arrives;
 //   trip 2  the V rows of ALL the wave's batches (up to four: 16 rows per lane quarter in flight), then the
-//           softmax update over them.
+//           softmax update over them.  fp32 rows are twice as wide: two batches are in flight and the other two follow
+//           as a third trip.
 // sparse_attention_wg_kernel pays count -> positions -> one trip per batch: five in a row for 656 keys per head.
-// Lists longer than 1024 entries take further rounds of two trips each.
+// Lists longer than 64 NW entries take further rounds of the same trips.
 template <typename KT, int NW>
 __global__ void __launch_bounds__(64 * NW)
 sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count: not restrict
@@ -320,7 +309,7 @@ sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count
     // trip 1 (the count first: it is read through the scalar unit, whose argument loads and the read itself form a
     // chain of their own that should start before the vector loads are set up, not after)
     int64_t cnt = count[hq * count_stride];
-    const int64_t e_rel = (int64_t)(wave + NW * sub) * 16 + li;   // this lane's entry within a round of 1024
+    const int64_t e_rel = (int64_t)(wave + NW * sub) * 16 + li;   // this lane's entry within a round of 64 NW
     int32_t pos = (e_rel < cap) ? my_idx[e_rel] : -1;
     float sc = (e_rel < cap && e_rel < cap_rows) ? my_sc[e_rel] : 0.f;
     const int32_t true_cnt = (int32_t)cnt;
@@ -338,7 +327,7 @@ sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count
         }
         int myslot = -1;
         if (e < cnt && pos >= 0 && pos < n_total) myslot = pslot ? pslot[pos] : (int)pos;
-        // trip 2: batch bq of this wave is entries base + (wave + 16 bq) * 16 ..; row i * 4 + sub of it is held by lane 16 bq + i * 4 + sub.
+        // trip 2: batch bq of this wave is entries base + (wave + NW bq) * 16 ..; row i * 4 + sub of it is held by lane 16 bq + i * 4 + sub.
         // All four batches are in flight; fp32 rows are twice as wide: two batches at a time fit the registers of 16 waves
         constexpr int NB = sizeof(KT) == sizeof(lvr_bf16_t) ? 4 : 2;
         lvr_raw8<KT> vr[NB * 4];
@@ -354,7 +343,7 @@ sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count
                 }
             }
         }
-        if (!have[0]) continue;   // wave-uniform: none of this wave's batches holds an entry in this pass over 1024 entries
+        if (!have[0]) continue;   // wave-uniform: none of this wave's batches holds an entry in this round
         // The scores are here already, so the softmax weights of all 64 entries are formed while the rows travel:
         // one maximum and one sum over the wave, one exponential per lane, instead of a chain of rescalings per row.
         const float s_e = (myslot >= 0) ? sc : -INFINITY;
@@ -504,7 +493,7 @@ sparse_attention_wg_carry_split_kernel(const int32_t *count,   // may alias head
                 lvr_load_raw(Vb, sl < 0 ? 0 : sl, part * LPR + lp, vr[j]);
             }
         }
-        if (!have[0]) continue;   // wave-uniform: none of this wave's batches holds an entry in this pass over 1024 entries
+        if (!have[0]) continue;   // wave-uniform: none of this wave's batches holds an entry in this round
         // The scores are here already, so the softmax weights of all 64 entries are formed while the rows travel:
         // one maximum and one sum over the wave, one exponential per lane, instead of a chain of rescalings per row.
         const float s_e = (myslot >= 0) ? sc : -INFINITY;
@@ -938,42 +927,39 @@ hipError_t lvr_launch_sparse_attention_wg(lvr_index *ix, const float *q, const i
         else hipLaunchKernelGGL(KERNEL, GRID, dim3(THREADS), 0, st, __VA_ARGS__);                           \
     } while (0)
 #define LVR_AT_LAUNCH(KERNEL, GRID, ...) LVR_AT_LAUNCH_N(KERNEL, GRID, 1024, __VA_ARGS__)
-#define LVR_WG_LAUNCH(KT, CARRY)                                                                                         \
-    LVR_AT_LAUNCH((sparse_attention_wg_kernel<KT, CARRY>), dim3((unsigned)n_bhq), ix->K, ix->V,                          \
-                  ix->pos_slot, q, idx, scores, ix->cap_rows, count, count_stride, cap, out, ix->cap_rows,               \
-                  ix->n_total, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale, lvr_head_count(ix),                 \
-                  lvr_head_stat(ix), publish_count)
+#define LVR_WG_LAUNCH(KT)                                                                                                \
+    LVR_AT_LAUNCH(sparse_attention_wg_kernel<KT>, dim3((unsigned)n_bhq), ix->K, ix->V, ix->pos_slot, q, idx, count,       \
+                  count_stride, cap, out, ix->cap_rows, ix->n_total, ix->cfg.n_q_heads, ix->cfg.n_kv_heads, ix->G, qscale, \
+                  lvr_head_count(ix), lvr_head_stat(ix), publish_count)
+#define LVR_CARRY_LAUNCH(KT, WAVES)                                                                                      \
+    LVR_AT_LAUNCH_N((sparse_attention_wg_carry_kernel<KT, WAVES>), dim3((unsigned)n_bhq), 64 * WAVES, count, idx, scores, \
+                    ix->V, cap, count_stride, (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale,      \
+                    lvr_head_count(ix), lvr_head_stat(ix), publish_count)
+    // Lists that carry their scores.  With more heads than compute units a workgroup of eight waves serves a head: its waves
+    // hold up to 64 rows each in flight (fp32: 32) as the sixteen of the wide form do, and two such workgroups share a compute
+    // unit instead of queueing up behind each other (bf16, 512 heads of 655 keys: 126.5 us per step against 128.2 with sixteen
+    // light waves that take a trip per 16 rows; 384 heads of 18 to 105 keys: 15.4 against 18.4, 34.2 against 37.2.  fp32, light
+    // waves and eight: 288 heads of 20 to 100 keys 19.4 / 16.9 and 21.9 / 19.2, 2048 heads of 40 keys 168.1 / 158.0).
+    const bool many_heads = n_bhq > 256;
     if (ix->cfg.kv_dtype == LVR_BF16) {
-        // With more heads than compute units a workgroup of eight waves serves a head: its waves hold up to 64 rows each in
-        // flight as the sixteen of the wide form do, and two such workgroups share a compute unit instead of queueing
-        // up behind each other (512 heads of 655 keys: 126.5 us per step against 128.2 with sixteen light waves that take a
-        // trip per 16 rows; 384 heads of 18 to 105 keys: 15.4 against 18.4, 34.2 against 37.2).
         // Up to 128 heads two workgroups can share a head (one per half of the channels) and every workgroup still
         // has a compute unit of its own.  That pays where a head's list is long (656 keys per head at 128k keys of
         // context: 9.1 against 9.7 us); short lists lose more to the extra barrier and the ticket than they gain
         // (3.6 keys per head: 7.6 against 6.9 us), and the list lengths are not known on the host, so the context
         // length stands in as it does for the launch form.
-        if (scores && n_bhq > 256)
-            LVR_AT_LAUNCH_N((sparse_attention_wg_carry_kernel<lvr_bf16_t, 8>), dim3((unsigned)n_bhq), 512, count, idx, scores, ix->V, cap,
-                            count_stride, (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
-                            lvr_head_stat(ix), publish_count);
+        if (scores && many_heads) LVR_CARRY_LAUNCH(lvr_bf16_t, 8);
         else if (scores && n_bhq <= 128 && publish_count && ix->n_total > 65536)
             LVR_AT_LAUNCH((sparse_attention_wg_carry_split_kernel<lvr_bf16_t, 2>), dim3((unsigned)n_bhq * 2),
                                count, idx, scores, ix->V, cap, count_stride, (int)ix->cap_rows, (int)ix->n_total, ix->G,
                                ix->pos_slot, out, qscale, lvr_head_count(ix), lvr_head_stat(ix), publish_count, lvr_head_ticket(ix));
-        else if (scores)
-            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_bf16_t, 16>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
-                               (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
-                               lvr_head_stat(ix), publish_count);
-        else LVR_WG_LAUNCH(lvr_bf16_t, false);
+        else if (scores) LVR_CARRY_LAUNCH(lvr_bf16_t, 16);
+        else LVR_WG_LAUNCH(lvr_bf16_t);
     } else {
-        if (scores && n_bhq > 256) LVR_WG_LAUNCH(lvr_f32_t, true);   // as above: more heads than compute units
-        else if (scores)
-            LVR_AT_LAUNCH((sparse_attention_wg_carry_kernel<lvr_f32_t, 16>), dim3((unsigned)n_bhq), count, idx, scores, ix->V, cap, count_stride,
-                               (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->pos_slot, out, qscale, lvr_head_count(ix),
-                               lvr_head_stat(ix), publish_count);
-        else LVR_WG_LAUNCH(lvr_f32_t, false);
+        if (scores && many_heads) LVR_CARRY_LAUNCH(lvr_f32_t, 8);
+        else if (scores) LVR_CARRY_LAUNCH(lvr_f32_t, 16);
+        else LVR_WG_LAUNCH(lvr_f32_t);
     }
+#undef LVR_CARRY_LAUNCH
 #undef LVR_WG_LAUNCH
 #undef LVR_AT_LAUNCH
 #undef LVR_AT_LAUNCH_N

@@ -290,3 +290,21 @@ def test_attention_form_of_a_decode_step(G, oracle, dtype, n, one_launch):
         launches = L.lvr_profile_read(ix.h)
         G.check_step(oracle, ix, q, tau, idx, cnt, out, tag=f"{dtype} n={n}")
     assert launches["attn_partial"][1] == 1 and launches["attn_combine"][1] == (0 if one_launch else 1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("batch,hq,hkv,n,r", [(9, 32, 8, 1000, 4), (33, 8, 8, 96, 1)])
+def test_more_heads_than_compute_units(G, oracle, dtype, batch, hq, hkv, n, r):
+    """Decode steps of more than 256 query heads, whose lists are attended by eight waves each: lists of one entry, of less and
+    more than a round of 512 entries, and none, against the oracle."""
+    g = np.random.default_rng(n)
+    K, V = (W.round_to_bf16(g.standard_normal((batch, hkv, n, 128)).astype(np.float32)) for _ in range(2))
+    q = g.standard_normal((batch, hq, 128)).astype(np.float32)
+    with G.Index(K, V, dtype, hq, capacity=n, group_size=r) as ix:
+        taus = [G.oracle_taus(oracle, ix, q, k_count=1), G.oracle_taus(oracle, ix, q, frac=0.1), np.full((batch, hq), -np.inf, np.float32)]
+        taus.append(taus[1].copy())
+        taus[3][:, ::2] = 1e9
+        for tau in taus:
+            idx, cnt, out = ix.query(q, tau, fused=True)
+            G.check_step(oracle, ix, q, tau, idx, cnt, out, tag=f"{dtype} {batch} x {hq} heads")
+        assert (cnt[:, ::2] == 0).all() and (out[:, ::2] == 0).all()
