@@ -238,12 +238,24 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     const int n_bh = lvr_n_bh(ix);
     // segments of a multiple of 16 groups (a trip of the four waves); aim at the workgroups that are resident at once (three
     // per compute unit, two with eight heads: the registers of two tiles of rows and the query) less the buffers', so that
-    // the launch is one round (8 x 16384 keys: 23.6 us per step against 25.2 with 1024, which ran as 768 + 264)
+    // the launch is one round (8 x 16384 keys: 23.6 us per step against 25.2 with 1024, which ran as 768 + 264).  Counted in
+    // whole segments per (sequence, KV head): the same total divided by the workgroups alone put 13 on each of 40, 520 on room
+    // for 512 (five sequences of 16384 keys, 64 heads on 8: 133.5 us, 101.8 with twelve), and a long and a short one on each of 512
+    // (4096 keys: 75.1 us on local keys, 56.9 with one).  What does not fit one round gets several, and four where already
+    // a segment each is more than one.
     const int64_t buffers = a.n_total > ix->n_indexed ? n_bh : 0;
-    int64_t target_wgs = (ix->G == 8 ? 512 : 768) - buffers;
-    if (target_wgs < 256) target_wgs = 256;
-    if (ix->cfg.query_workgroups > 0) target_wgs = ix->cfg.query_workgroups;
-    int64_t seg = (a.n_groups * n_bh + target_wgs - 1) / target_wgs;
+    const int64_t resident = ix->G == 8 ? 512 : 768;
+    int64_t per_head = (a.n_groups + F32_SEG_MAX - 1) / F32_SEG_MAX;   // segments of a (sequence, KV head), at least
+    if (ix->cfg.query_workgroups > 0) {
+        per_head = ix->cfg.query_workgroups / n_bh;
+    } else {
+        int64_t rounds = (per_head * n_bh + buffers + resident - 1) / resident;
+        if (n_bh + buffers > resident && rounds < 4) rounds = 4;
+        if (rounds < 1) rounds = 1;
+        per_head = (rounds * resident - buffers) / n_bh;
+    }
+    if (per_head < 1) per_head = 1;
+    int64_t seg = (a.n_groups + per_head - 1) / per_head;
     seg = (seg + 15) & ~(int64_t)15;
     if (seg < LVR_MIN_SEG_GROUPS) seg = LVR_MIN_SEG_GROUPS;
     if (seg > F32_SEG_MAX) seg = F32_SEG_MAX;
