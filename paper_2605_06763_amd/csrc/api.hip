@@ -648,7 +648,7 @@ int decode_step_impl(lvr_index *ix, const float *q, const float *tau, float *out
     }
     {   // ... and the combine pass hands them to the caller
         Timed t(ix, LVR_K_ATTN_COMBINE, st);
-        LVR_HIP(lvr_launch_combine(ix, out, ix->P, lvr_head_count(ix), LVR_CNT_STRIDE, cap, out_count, st, carried != nullptr));
+        LVR_HIP(lvr_launch_combine(ix, out, ix->P, lvr_head_count(ix), LVR_CNT_STRIDE, cap, out_count, st));
     }
     ix->counters_dirty = 0;
     return LVR_OK;

@@ -9,9 +9,10 @@
 //  combine_kernel         merges the P partial triples (m_p, l_p, o_p) into the output.
 //
 // Logits are taken in base-2 units (sigma * log2 e) so the exponentials are single exp2 instructions; the softmax is
-// unchanged by the change of base.  Where a kernel forms the scores itself, q is pre-multiplied by that factor.  Where raw
-// scores are carried to it, the maximum and the differences stay raw and the factor meets the difference: a product
-// score * factor would be rounded at the size of the logit, the difference is rounded at its own.
+// unchanged by the change of base.  Where a kernel forms the scores itself, q is pre-multiplied by that factor.  A raw score
+// that is carried to it meets the factor and the running maximum in one fused multiply-add: a product of its own would
+// be rounded at the size of the logit, the difference is rounded at its own (and how the maximum is rounded does not
+// matter, all weights share it).
 #include <hip/hip_ext.h>
 
 #include "mfma_score.h"
@@ -23,8 +24,8 @@ constexpr float LOG2E = 1.4426950408889634f;
 __device__ __forceinline__ float exp2_safe(float a, float b) {   // 2^(a-b) with (-inf) - (-inf) -> 0
     return (a == -INFINITY) ? 0.f : exp2f(a - b);
 }
-__device__ __forceinline__ float exp2_safe(float a, float b, float unit) {   // the same for a and b in units of `unit`
-    return (a == -INFINITY) ? 0.f : exp2f((a - b) * unit);
+__device__ __forceinline__ float exp2_carried(float score, float unit, float m) {   // 2^(score * unit - m), 0 for score -inf
+    return (score == -INFINITY) ? 0.f : exp2f(__builtin_fmaf(score, unit, -m));
 }
 
 // Split geometry of the sparse attention: 16 entries per split (one gather batch) while the
@@ -73,7 +74,6 @@ sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__rest
     const int64_t start = (int64_t)p * L;
     const int64_t end = (start + L < cnt) ? start + L : cnt;
 
-    const float unit = CARRY ? qscale : 1.0f;   // carried scores are raw, q below is scaled
     float qv[8];
     {
         const float *qh = q + hq * LVR_D + li * 8;
@@ -126,9 +126,9 @@ sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__rest
                     s = lvr_row16_sum(d);
                 }
                 s = (slot[i] >= 0) ? s : -INFINITY;
-                const float m_new = fmaxf(m, s);
-                const float alpha = exp2_safe(m, m_new, unit);
-                const float w = exp2_safe(s, m_new, unit);
+                const float m_new = fmaxf(m, CARRY ? s * qscale : s);
+                const float alpha = exp2_safe(m, m_new);
+                const float w = CARRY ? exp2_carried(s, qscale, m_new) : exp2_safe(s, m_new);
                 l = l * alpha + w;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) acc[c] = acc[c] * alpha + w * vx[c];
@@ -139,7 +139,7 @@ sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__rest
     // merge the four quarter rows of the wave
     float m_all = fmaxf(m, __shfl_xor(m, 16, 64));
     m_all = fmaxf(m_all, __shfl_xor(m_all, 32, 64));
-    const float sc = exp2_safe(m, m_all, unit);
+    const float sc = exp2_safe(m, m_all);
     l *= sc;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
@@ -350,12 +350,12 @@ sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count
         float mw = s_e;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off, 64));
-        const float m_new = fmaxf(m, mw);
-        const float w_e = exp2_safe(s_e, m_new, qscale);
+        const float m_new = fmaxf(m, mw * qscale);
+        const float w_e = exp2_carried(s_e, qscale, m_new);
         float lw = w_e;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) lw += __shfl_xor(lw, off, 64);
-        const float alpha = exp2_safe(m, m_new, qscale);
+        const float alpha = exp2_safe(m, m_new);
         l = l * alpha + lw;
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[c] *= alpha;
@@ -406,7 +406,7 @@ sparse_attention_wg_carry_kernel(const int32_t *count,   // may alias head_count
         float num = 0.f, den = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float wt = exp2_safe(s_m[w], M, qscale);
+            const float wt = exp2_safe(s_m[w], M);
             den += wt * s_l[w];
             num += wt * s_o[w][threadIdx.x];
         }
@@ -500,12 +500,12 @@ sparse_attention_wg_carry_split_kernel(const int32_t *count,   // may alias head
         float mw = s_e;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off, 64));
-        const float m_new = fmaxf(m, mw);
-        const float w_e = exp2_safe(s_e, m_new, qscale);
+        const float m_new = fmaxf(m, mw * qscale);
+        const float w_e = exp2_carried(s_e, qscale, m_new);
         float lw = w_e;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) lw += __shfl_xor(lw, off, 64);
-        const float alpha = exp2_safe(m, m_new, qscale);
+        const float alpha = exp2_safe(m, m_new);
         l = l * alpha + lw;
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[c] *= alpha;
@@ -541,7 +541,7 @@ sparse_attention_wg_carry_split_kernel(const int32_t *count,   // may alias head
         float num = 0.f, den = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float wt = exp2_safe(s_m[w], M, qscale);
+            const float wt = exp2_safe(s_m[w], M);
             den += wt * s_l[w];
             num += wt * s_o[w][threadIdx.x];
         }
@@ -561,7 +561,7 @@ sparse_attention_wg_carry_split_kernel(const int32_t *count,   // may alias head
 // every fourth partial of channel c; its values are requested first, then the weights
 // w_p = 2^(m_p - M) are computed into LDS, the slices are weighted, and the four slices are
 // added through LDS.  With a count pointer the number of partials in use follows the sparse
-// attention's split geometry; without one all P are merged (dense baseline).  The m_p are in units of `unit`.
+// attention's split geometry; without one all P are merged (dense baseline).
 constexpr int COMBINE_MAX_P = 256;
 
 // `count` and `head_count` may be the same array (the decode step hands the internal counters to
@@ -569,7 +569,7 @@ constexpr int COMBINE_MAX_P = 256;
 // barrier and the counter is cleared only AFTER it.
 __global__ void __launch_bounds__(512)
 combine_kernel(const float *__restrict__ part_o, const float *__restrict__ part_ml, const int32_t *count, int64_t cap,
-               float *__restrict__ out, int P, int count_stride, float unit, int32_t *head_count,
+               float *__restrict__ out, int P, int count_stride, int32_t *head_count,
                int32_t *__restrict__ head_stat, int32_t *__restrict__ publish_count) {
     __shared__ float s_w[COMBINE_MAX_P];
     __shared__ float s_red[8];
@@ -616,7 +616,7 @@ combine_kernel(const float *__restrict__ part_o, const float *__restrict__ part_
 #pragma unroll
     for (int w = 1; w < 8; ++w) M = fmaxf(M, s_red[w]);
     __syncthreads();
-    const float w_p = exp2_safe(m, M, unit);
+    const float w_p = exp2_safe(m, M);
     if (t < COMBINE_MAX_P) s_w[t] = w_p;
     float dn = w_p * l;
 #pragma unroll
@@ -1012,10 +1012,9 @@ hipError_t lvr_launch_dense_partial(lvr_index *ix, const float *q, hipStream_t s
 }
 
 hipError_t lvr_launch_combine(lvr_index *ix, float *out, int P, const int32_t *count, int count_stride, int64_t cap,
-                              int32_t *publish_count, hipStream_t st, bool raw_scores) {
+                              int32_t *publish_count, hipStream_t st) {
     const int n_bhq = lvr_n_bhq(ix);
-    const float unit = raw_scores ? ix->sigma * LOG2E : 1.0f;
     hipLaunchKernelGGL(combine_kernel, dim3((unsigned)n_bhq), dim3(512), 0, st, ix->part_o, ix->part_ml, count, cap, out, P,
-                       count_stride, unit, lvr_head_count(ix), lvr_head_stat(ix), publish_count);
+                       count_stride, lvr_head_count(ix), lvr_head_stat(ix), publish_count);
     return hipGetLastError();
 }

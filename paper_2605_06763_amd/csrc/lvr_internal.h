@@ -169,10 +169,9 @@ hipError_t lvr_launch_sparse_attention_wg(lvr_index *ix, const float *q, const i
 hipError_t lvr_launch_dense_partial(lvr_index *ix, const float *q, hipStream_t st);
 // merge the partials of every head.  count == NULL: all P (dense baseline); otherwise as many as the
 // sparse split geometry uses for that count.  publish_count != NULL: also hands the internal
-// per-head counters to the caller (and to the statistics copy) and clears them.  raw_scores: the partials come from carried
-// scores, their maxima are raw dot products
+// per-head counters to the caller (and to the statistics copy) and clears them
 hipError_t lvr_launch_combine(lvr_index *ix, float *out, int P, const int32_t *count, int count_stride, int64_t cap,
-                              int32_t *publish_count, hipStream_t st, bool raw_scores = false);
+                              int32_t *publish_count, hipStream_t st);
 int lvr_dense_splits(const lvr_index *ix);
 // reservoir of past keys and threshold selection (threshold.hip)
 hipError_t lvr_launch_reservoir_reset(lvr_index *ix, hipStream_t st);
