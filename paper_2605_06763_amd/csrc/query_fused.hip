@@ -841,22 +841,22 @@ int tiles_for_workgroups(int64_t n_groups, int n_bh, int workgroups) {
 int tiles_for_launch(int64_t n_groups, int n_bh, int has_buffer, int r, bool fitted, int resident) {
     const int former = tiles_for_workgroups(n_groups, n_bh, 1024);
     if (!fitted) return former;
-    const int64_t n64 = (n_groups + 63) / 64;   // segments of one tile per wave
+    const uint32_t n64 = (uint32_t)((n_groups + 63) / 64);   // segments of one tile per wave (32-bit division: this runs per call)
     const int64_t round = 256 * resident;
-    auto cost = [&](int tpw, int64_t wgs) {
+    auto workgroups = [&](uint32_t tpw) { return (int64_t)n_bh * ((n64 + tpw - 1) / tpw + (uint32_t)has_buffer); };
+    auto cost = [&](uint32_t tpw, int64_t wgs) {
         const int64_t k = wgs > round ? resident * ((wgs + round - 1) / round) : (wgs + 255) / 256;
         return (k == 1 ? 40 : (k == 2 ? 23 : 20)) * k * ((tpw < n64 ? tpw : n64) * (r + 3) + 8);
     };
-    auto workgroups = [&](int tpw) { return n_bh * ((n64 + tpw - 1) / tpw + has_buffer); };
     int best = former;
     int64_t best_cost = cost(former, workgroups(former)) * 94 / 100;
-    for (int tpw = 1; tpw <= SEG_MAX_TILES && tpw <= n64; ++tpw) {
+    for (uint32_t tpw = 1; tpw <= SEG_MAX_TILES && tpw <= n64; ++tpw) {
         if (r == 1 && tpw > 1 && (tpw & 1)) continue;
         const int64_t wgs = workgroups(tpw);
         if (wgs > round) continue;
         const int64_t c = cost(tpw, wgs);
         if (c < best_cost) {   // equal: the more workgroups
-            best = tpw;
+            best = (int)tpw;
             best_cost = c;
         }
     }
