@@ -33,42 +33,57 @@ struct BuildSrc {
     int n_kv_heads;
 };
 
-constexpr int COPY_PIECES = 4;   // 16-byte pieces per thread
+// Rows that nothing reads again soon are streamed past the caches, but only where they would push out more than they are
+// worth: a copy that fits the caches is faster through them.  `rows` rows of n_bh (sequence, KV head) pairs, each read and
+// written once; with bf16 centres, groups of four: 37 MB of values 17.3 us against 18.9 streamed (build of 8 x 9001 keys), 67 MB
+// 54.4 against 48.7 (8 x 32768), 268 MB 208 against 199.  An append's rows are read again by the next launch.
+constexpr int64_t STREAM_BYTES = 48 << 20;
+inline bool streamed(int64_t rows, int n_bh, size_t row_bytes) { return rows * n_bh * (int64_t)row_bytes >= STREAM_BYTES; }
 
-// Block `block` (256 threads) of the copy of rows [c.first, rows), 2^SH pieces each, to arena row dst_row0 on.  All of a
-// thread's pieces are in flight before the first is stored; the rows are streamed past the caches, here and where the 6-bit
-// build copies the key rows (they are larger than the caches and the next launch reads the index: build and step at
-// 8 x 131072 keys 262 us against 277 with ordinary accesses, one piece per thread; four pieces and no division by the row
-// length bring the copy itself from 103 to 90 us, 6 TB/s).
-template <int SH>
+// Block `block` (256 threads) of the copy of rows [c.first, rows), 2^SH 16-byte pieces each, to arena row dst_row0 on.  All of
+// a thread's pieces are in flight before the first is stored.
+template <int SH, int PIECES, bool STREAM>
 __device__ __forceinline__ void copy_block(const CopySide &c, int bh, int n_kv_heads, int64_t cap_rows, int64_t dst_row0, int64_t rows,
                                            int64_t block) {
     constexpr int ELT = SH == 4 ? 2 : 4;
     const char *src = c.src + ((int64_t)(bh / n_kv_heads) * c.sb + (int64_t)(bh % n_kv_heads) * c.sh) * ELT;
     char *dst = c.dst + (((int64_t)bh * cap_rows + dst_row0) << (SH + 4));
-    const int64_t first = (c.first << SH) + block * (256 * COPY_PIECES) + threadIdx.x, end = rows << SH;
-    lvr_u32x4 w[COPY_PIECES];
+    const int64_t first = (c.first << SH) + block * (256 * PIECES) + threadIdx.x, end = rows << SH;
+    lvr_u32x4 w[PIECES];
 #pragma unroll
-    for (int u = 0; u < COPY_PIECES; ++u) {
+    for (int u = 0; u < PIECES; ++u) {
         const int64_t i = first + 256 * u;
-        if (i < end)
-            w[u] = __builtin_nontemporal_load(reinterpret_cast<const lvr_u32x4 *>(src + (i >> SH) * c.st * ELT) + (i & ((1 << SH) - 1)));
+        if (i < end) {
+            const lvr_u32x4 *from = reinterpret_cast<const lvr_u32x4 *>(src + (i >> SH) * c.st * ELT) + (i & ((1 << SH) - 1));
+            if constexpr (STREAM) w[u] = __builtin_nontemporal_load(from);
+            else w[u] = *from;
+        }
     }
 #pragma unroll
-    for (int u = 0; u < COPY_PIECES; ++u) {
+    for (int u = 0; u < PIECES; ++u) {
         const int64_t i = first + 256 * u;
-        if (i < end) __builtin_nontemporal_store(w[u], reinterpret_cast<lvr_u32x4 *>(dst) + i);
+        if (i < end) {
+            lvr_u32x4 *to = reinterpret_cast<lvr_u32x4 *>(dst) + i;
+            if constexpr (STREAM) __builtin_nontemporal_store(w[u], to);
+            else *to = w[u];
+        }
     }
 }
 
-inline unsigned copy_blocks(int64_t rows, int sh) { return (unsigned)(((rows << sh) + 256 * COPY_PIECES - 1) / (256 * COPY_PIECES)); }
+// One piece per thread where the copy is a launch of its own (four: 17.6 against 17.3 us at 8 x 9001 keys, 208 against 201 at
+// 8 x 131072); four, streamed, where it rides behind another step's few workgroups, as the 6-bit build streams the key rows
+// (build and one step at 8 x 131072 keys: 262 us streamed, 277 with ordinary accesses; the four pieces 237).
+constexpr int COPY_PIECES = 1, STEP_PIECES = 4;
+inline unsigned copy_blocks(int64_t rows, int sh, int pieces) {
+    return (unsigned)(((rows << sh) + 256 * pieces - 1) / (256 * pieces));
+}
 
 // Values in the first v_blocks blocks, keys in the rest, so an append is one launch.
-template <int SH>
+template <int SH, bool STREAM>
 __global__ void __launch_bounds__(256)
 copy_rows_kernel(CopySide k, CopySide v, int n_kv_heads, int64_t cap_rows, int64_t dst_row0, int64_t rows, unsigned v_blocks) {
-    if (blockIdx.x < v_blocks) copy_block<SH>(v, blockIdx.y, n_kv_heads, cap_rows, dst_row0, rows, blockIdx.x);
-    else copy_block<SH>(k, blockIdx.y, n_kv_heads, cap_rows, dst_row0, rows, blockIdx.x - v_blocks);
+    if (blockIdx.x < v_blocks) copy_block<SH, COPY_PIECES, STREAM>(v, blockIdx.y, n_kv_heads, cap_rows, dst_row0, rows, blockIdx.x);
+    else copy_block<SH, COPY_PIECES, STREAM>(k, blockIdx.y, n_kv_heads, cap_rows, dst_row0, rows, blockIdx.x - v_blocks);
 }
 
 __device__ __forceinline__ float seg_sum(float v, int lanes_per_sub) {
@@ -546,12 +561,21 @@ hipError_t lvr_launch_copy_kv(lvr_index *ix, const void *K, const int64_t ks[3],
     CopySide k{static_cast<const char *>(K), static_cast<char *>(ix->K), ks[0], ks[1], ks[2], k_first};
     CopySide v{static_cast<const char *>(V), static_cast<char *>(ix->V), vs[0], vs[1], vs[2], 0};
     const int sh = ix->elt == 2 ? 4 : 5;
-    const unsigned v_blocks = copy_blocks(rows, sh);
-    const dim3 grid(v_blocks + copy_blocks(rows - k_first, sh), (unsigned)lvr_n_bh(ix));
-    if (sh == 4)
-        hipLaunchKernelGGL(copy_rows_kernel<4>, grid, dim3(256), 0, st, k, v, ix->cfg.n_kv_heads, ix->cap_rows, dst_row0, rows, v_blocks);
-    else
-        hipLaunchKernelGGL(copy_rows_kernel<5>, grid, dim3(256), 0, st, k, v, ix->cfg.n_kv_heads, ix->cap_rows, dst_row0, rows, v_blocks);
+    const unsigned v_blocks = copy_blocks(rows, sh, COPY_PIECES);
+    // an append's rows are read again by the next launch; of a build, only the values come this way (and the ungrouped tail)
+    const bool stream = k_first > 0 && streamed(rows, lvr_n_bh(ix), LVR_D * ix->elt);
+    const dim3 grid(v_blocks + copy_blocks(rows - k_first, sh, COPY_PIECES), (unsigned)lvr_n_bh(ix));
+#define LVR_COPY_LAUNCH(SH, STREAM)                                                                                      \
+    hipLaunchKernelGGL((copy_rows_kernel<SH, STREAM>), grid, dim3(256), 0, st, k, v, ix->cfg.n_kv_heads, ix->cap_rows,    \
+                       dst_row0, rows, v_blocks)
+    if (sh == 4) {
+        if (stream) LVR_COPY_LAUNCH(4, true);
+        else LVR_COPY_LAUNCH(4, false);
+    } else {
+        if (stream) LVR_COPY_LAUNCH(5, true);
+        else LVR_COPY_LAUNCH(5, false);
+    }
+#undef LVR_COPY_LAUNCH
     return hipGetLastError();
 }
 
@@ -714,8 +738,8 @@ channel_step_kernel(ChannelArgs a, CopySide k, CopySide v, int64_t cap_rows, int
     if (blockIdx.x < lead) {
         if constexpr (SUMS) channel_sums(a, blockIdx.y, blockIdx.x);
         else channel_exponents(a, blockIdx.y);
-    } else if (blockIdx.x - lead < v_blocks) copy_block<4>(v, blockIdx.y, a.n_kv_heads, cap_rows, 0, v_end, blockIdx.x - lead);
-    else copy_block<4>(k, blockIdx.y, a.n_kv_heads, cap_rows, 0, rows, blockIdx.x - lead - v_blocks);
+    } else if (blockIdx.x - lead < v_blocks) copy_block<4, STEP_PIECES, true>(v, blockIdx.y, a.n_kv_heads, cap_rows, 0, v_end, blockIdx.x - lead);
+    else copy_block<4, STEP_PIECES, true>(k, blockIdx.y, a.n_kv_heads, cap_rows, 0, rows, blockIdx.x - lead - v_blocks);
 }
 
 }  // namespace
@@ -744,14 +768,14 @@ hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t
     CopySide v{static_cast<const char *>(V), static_cast<char *>(ix->V), V ? vs[0] : 0, V ? vs[1] : 0, V ? vs[2] : 0, 0};
     const int64_t half = V ? n / 2 : 0;
     const unsigned n_bh = (unsigned)lvr_n_bh(ix);
-    unsigned v_blocks = copy_blocks(half, 4);
+    unsigned v_blocks = copy_blocks(half, 4, STEP_PIECES);
     hipLaunchKernelGGL(channel_step_kernel<true>, dim3((unsigned)a.splits + v_blocks, n_bh), dim3(256), 0, st, a, k, v, ix->cap_rows,
                        half, n, v_blocks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     v.first = half;
-    v_blocks = V ? copy_blocks(n - half, 4) : 0;
-    hipLaunchKernelGGL(channel_step_kernel<false>, dim3(1u + v_blocks + copy_blocks(n - k.first, 4), n_bh), dim3(256), 0, st, a, k, v,
+    v_blocks = V ? copy_blocks(n - half, 4, STEP_PIECES) : 0;
+    hipLaunchKernelGGL(channel_step_kernel<false>, dim3(1u + v_blocks + copy_blocks(n - k.first, 4, STEP_PIECES), n_bh), dim3(256), 0, st, a, k, v,
                        ix->cap_rows, n, n, v_blocks);
     return hipGetLastError();
 }

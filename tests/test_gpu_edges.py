@@ -309,3 +309,34 @@ def test_more_heads_than_compute_units(G, oracle, dtype, batch, hq, hkv, n, r):
             idx, cnt, out = ix.query(q, tau, fused=True)
             G.check_step(oracle, ix, q, tau, idx, cnt, out, tag=f"{dtype} {batch} x {hq} heads")
         assert (cnt[:, ::2] == 0).all() and (out[:, ::2] == 0).all()
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 98303), ("bf16", 98307), ("f32", 49151), ("f32", 49155), ("f32", 5)])
+def test_rows_of_a_build_and_an_append_arrive(G, dtype, n):
+    """Value rows copied by a build on both sides of the size (48 MiB) from which they are streamed, out of a token-major view,
+    with rows behind the last whole group, and by an append: the attention over a list of one position is that row."""
+    L = G.L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    more, hkv, hq = 300, 2, 8
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K, V = (torch.randn((1, n + more, hkv, 128), generator=g, device="cuda").to(dt).transpose(1, 2) for _ in range(2))
+    cfg = L.make_config(batch=1, n_q_heads=hq, n_kv_heads=hkv, kv_dtype=L.LVR_BF16 if dtype == "bf16" else L.LVR_F32, capacity=n + more,
+                        group_size=4, index_dtype=L.LVR_INDEX_SAME)
+    h = L.lvr_create(cfg)
+    try:
+        L.lvr_build(h, K[:, :, :n], V[:, :, :n])
+        L.lvr_append(h, K[:, :, n:].contiguous(), V[:, :, n:].contiguous())
+        keys = L.lvr_export_index(h, cfg)[3]
+        q = torch.randn((1, hq, 128), generator=g, device="cuda")
+        count = torch.ones((1, hq), dtype=torch.int32, device="cuda")
+        out = torch.empty((1, hq, 128), device="cuda")
+        edges = torch.tensor([0, n - 1, n - 2, n, n + more - 1, n // 2, n + 1, n // 4 * 4 - 1], device="cuda")
+        for picks in [edges] + [torch.randint(0, n + more, (hq,), generator=g, device="cuda") for _ in range(8)]:
+            L.lvr_sparse_attention(h, q, picks.to(torch.int32).reshape(1, hq, 1).contiguous(), count, out)
+            want = V[0, torch.arange(hq, device="cuda") * hkv // hq, picks].float()
+            assert torch.equal(out[0], want), (out[0] != want).any(dim=1)
+    finally:
+        L.lvr_destroy(h)
+    bits = keys.view(np.int16) if dtype == "bf16" else keys.view(np.int32)
+    assert np.array_equal(bits, K.contiguous().view(torch.int16 if dtype == "bf16" else torch.int32).cpu().numpy().reshape(bits.shape))
