@@ -45,7 +45,9 @@ __global__ void reservoir_update_kernel(int32_t *res, int R, uint64_t seed, int6
 // with a quarter of the 256 each (16 broadcast reads of LDS), and the score goes to the place its rank says.
 // With four waves, a dependent load of position and row per four keys, a bitonic sort (36 barriers) and a serial count of
 // the valid scores the launch took 28 us for 32 heads, with rows in flight and ranks but four waves 12.9; now 7.0 (threshold and step:
-// 50.0, 33.6, 27.7 us).
+// 50.0, 33.6, 27.7 us).  The gaps and the mean are taken by
+// all threads: by one thread, 4096 heads, of which only two workgroups of 16 waves fit a compute unit, took 99.3 and 76.9 us
+// where four waves each had taken 80.3 and 74.7; now 67.7 and 69.3.
 template <typename KT>
 __global__ void __launch_bounds__(1024)
 threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slot, const int32_t *__restrict__ res,
@@ -54,6 +56,9 @@ threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slo
     __shared__ __align__(16) uint32_t s_key[256];
     __shared__ int s_rank[4][256];
     __shared__ float s[256];
+    __shared__ float s_gap[4];
+    __shared__ int s_at[4];
+    __shared__ double s_sum[4];
     const int64_t hq = blockIdx.x;
     const int b = (int)(hq / n_q_heads), h = (int)(hq % n_q_heads);
     const int bh = b * n_kv_heads + h / G;
@@ -111,22 +116,42 @@ threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slo
     const int m = __syncthreads_count(t < 256 && score != -INFINITY);   // valid scores come first
     if (t < 256) s[s_rank[0][t] + s_rank[1][t] + s_rank[2][t] + s_rank[3][t]] = score;
     __syncthreads();
+    if (mode == LVR_TAU_SAMPLE_GAP) {   // uniform: the first of the largest gaps of every wave of 64 (a gap that is no number counts for none)
+        float gap = -1.0f;
+        if (t < 256 && t + 1 < m) {
+            const float g = s[t] - s[t + 1];
+            if (g > gap) gap = g;
+        }
+        float most = gap;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, 64));
+        const int at = __builtin_ctzll(__ballot(gap == most));   // some lane holds the maximum
+        if (lane == 0 && wave < 4) {
+            s_gap[wave] = most;
+            s_at[wave] = wave * 64 + at;
+        }
+        __syncthreads();
+    } else if (mode == LVR_TAU_SAMPLE_MEAN_MAX) {
+        double sum = (t < 256 && t < m) ? (double)s[t] : 0.0;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        if (lane == 0 && wave < 4) s_sum[wave] = sum;
+        __syncthreads();
+    }
     if (t == 0) {
         float tau = -INFINITY;
         if (m > 0) {
             tau = s[0];
             if (mode == LVR_TAU_SAMPLE_MEAN_MAX) {
-                double mean = 0.0;
-                for (int i = 0; i < m; ++i) mean += (double)s[i];
-                tau = (float)(0.5 * ((double)s[0] + mean / (double)m));
+                const double sum = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+                tau = (float)(0.5 * ((double)s[0] + sum / (double)m));
             } else if (mode == LVR_TAU_SAMPLE_GAP) {
                 int best = 0;
                 float gap = -1.0f;
-                for (int i = 0; i + 1 < m; ++i) {
-                    const float g = s[i] - s[i + 1];
-                    if (g > gap) {
-                        gap = g;
-                        best = i;
+                for (int w = 0; w < 4; ++w) {
+                    if (s_gap[w] > gap) {
+                        gap = s_gap[w];
+                        best = s_at[w];
                     }
                 }
                 tau = s[best];

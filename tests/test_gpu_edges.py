@@ -340,3 +340,25 @@ def test_rows_of_a_build_and_an_append_arrive(G, dtype, n):
         L.lvr_destroy(h)
     bits = keys.view(np.int16) if dtype == "bf16" else keys.view(np.int32)
     assert np.array_equal(bits, K.contiguous().view(torch.int16 if dtype == "bf16" else torch.int32).cpu().numpy().reshape(bits.shape))
+
+
+@pytest.mark.parametrize("R,n", [(256, 5000), (255, 255), (65, 900), (64, 900), (2, 2), (1, 1)])
+def test_threshold_gap_and_mean(G, R, n):
+    """The rules that look at all scores, on integers (exact scores, many equal gaps of which the first counts), for
+    reservoirs that end within, at and just behind a wave."""
+    g = np.random.default_rng(R)
+    K = np.zeros((1, 2, n, 128), dtype=np.float32)
+    K[..., 0] = g.integers(-100, 100, size=(1, 2, n)) * 3
+    K[..., 1] = g.integers(0, 2, size=(1, 2, n))
+    q = np.zeros((1, 4, 128), dtype=np.float32)
+    q[0, :, 0] = [1, -2, 5, 0]
+    q[0, :, 1] = [1, 1, 0, 0]
+    with G.Index(K, K, "f32", 4, capacity=n, reservoir_size=R, seed=3) as ix:
+        res = ix.reservoir()
+        gap, mean = ix.threshold(q, "sample-gap"), ix.threshold(q, "sample-mean-max")
+    for h in range(4):
+        pos = res[0, h // 2]
+        s = np.sort(K[0, h // 2, pos[pos >= 0]].astype(np.float64) @ q[0, h].astype(np.float64))[::-1]
+        d = s[:-1] - s[1:]
+        assert gap[0, h] == (s[int(np.argmax(d))] if d.size else s[0]), h
+        assert mean[0, h] == np.float32(0.5 * (s[0] + s.sum() / s.size)), h
