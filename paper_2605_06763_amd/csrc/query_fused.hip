@@ -27,24 +27,31 @@ namespace {
 constexpr int SEG_MAX_TILES = 64;                          // tiles per wave (at most 64: lane `it` of a wave keeps the mask of its tile `it`)
 constexpr int SEG_MAX_GROUPS = 4 * SEG_MAX_TILES * 16;     // 4 waves x 64 tiles x 16 groups; the survivor list holds 16-bit offsets into the segment
 
+// What the kernel needs after its first loads (those come as scalar arguments ahead of it, see LeadArgs).
 struct FusedArgs {
-    const void *centres;
-    const float *radii;
     const void *K;
     const int32_t *slot_pos;
-    const float *q;
-    const float *tau;
     const float *tau_s;      // Query 1: [batch][H_q][S] per-block thresholds; NULL: Query 2
-    const int8_t *chan_exp;  // per (sequence, KV head) LVR_CHAN_STRIDE bytes: channel exponents of a 6-bit index in a rescaled
-                             // space (else all zero), then the factors 2^e_c as floats (else all 1)
     const void *k_new, *v_new;   // rows appended by this launch ([batch][H_kv][m_new][d]), or NULL
     void *V;
     int m_new;               // n_total already counts them
     int32_t *seg_count;      // survivors per segment, for statistics only
     lvr_emit_target emit;
-    int64_t n_groups, max_groups, max_segs, cap_rows, n_indexed, n_total;
-    int log2r, n_q_heads, n_kv_heads, G, buffer_dense, n_segs, tiles_per_wave;
+    int64_t max_segs, cap_rows, n_indexed, n_total;
+    int log2r, buffer_dense, n_segs;
     int skip_bounds;         // 1: no bound test, every group of the segment goes to the exact check
+};
+
+// The scalar arguments, and the pair of events that the dispatch carries if there is one (they read the kernel's own start and end).
+struct LeadArgs {
+    const float *q;
+    const int8_t *chan_exp;  // per (sequence, KV head) LVR_CHAN_STRIDE bytes: channel exponents of a 6-bit index in a rescaled
+                             // space (else all zero), then the factors 2^e_c as floats (else all 1)
+    const void *centres;
+    const float *radii;
+    const float *tau;
+    int G, tiles_per_wave, max_groups, n_groups;
+    hipEvent_t start, stop;
 };
 
 // UA = centre tiles per phase-A trip; ENC = 1: boxes instead of balls; Q1 = 1: per-block thresholds (S <= 4);
@@ -803,15 +810,12 @@ query_fused_kernel(const float *__restrict__ q_in, const int8_t *__restrict__ ch
     }
 }
 
-// One launch of an instantiation.  With a pair of events in `ev` the dispatch itself carries them (they read the kernel's
-// own start and end); without, a plain launch.
-struct LaunchEvents {
-    hipEvent_t start, stop;
-};
+// One launch of an instantiation.
+#define LVR_QF_ARGS lead.q, lead.chan_exp, lead.centres, lead.radii, lead.tau, lead.G, lead.tiles_per_wave, lead.max_groups, lead.n_groups, a
 #define LVR_QF_LAUNCH(KERNEL)                                                                                        \
     do {                                                                                                             \
-        if (ev.start) hipExtLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, ev.start, ev.stop, 0, a.q, a.chan_exp, a.centres, a.radii, a.tau, a.G, a.tiles_per_wave, (int)a.max_groups, (int)a.n_groups, a);           \
-        else hipLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, a.q, a.chan_exp, a.centres, a.radii, a.tau, a.G, a.tiles_per_wave, (int)a.max_groups, (int)a.n_groups, a);                                            \
+        if (lead.start) hipExtLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, lead.start, lead.stop, 0, LVR_QF_ARGS); \
+        else hipLaunchKernelGGL(KERNEL, grid, dim3(256), dyn_lds, st, LVR_QF_ARGS);                                  \
     } while (0)
 
 // Tiles per wave of a launch: the power of two that gives about `workgroups` workgroups or fewer.
@@ -864,7 +868,7 @@ int tiles_for_launch(int64_t n_groups, int n_bh, int has_buffer, int r, bool fit
 }
 
 template <int UA, int W>
-void launch_s(dim3 grid, unsigned dyn_lds, hipStream_t st, const FusedArgs &a, int S, const LaunchEvents &ev) {
+void launch_s(dim3 grid, unsigned dyn_lds, hipStream_t st, const FusedArgs &a, int S, const LeadArgs &lead) {
     switch (S) {
         case 1: LVR_QF_LAUNCH((query_fused_kernel<1, 1, UA, 0, 0, 0, W>)); break;
         case 2: LVR_QF_LAUNCH((query_fused_kernel<1, 2, UA, 0, 0, 0, W>)); break;
@@ -881,19 +885,25 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
                                   int64_t m_new) {
     if (ix->cfg.kv_dtype != LVR_BF16) return hipErrorInvalidValue;
     if (tau_s && ((ix->box || ix->cf8 || ix->cf6) && ix->cfg.n_subspaces > 4)) return hipErrorInvalidValue;
+    LeadArgs lead;
+    lead.q = q;
+    lead.chan_exp = lvr_chan_exp(ix);   // exponents 0 and factors 1 unless the index is a rescaled one
+    lead.centres = ix->centres;
+    lead.radii = ix->radii;
+    lead.tau = tau;
+    lead.G = ix->G;
+    lead.max_groups = (int)ix->max_groups;
+    lead.n_groups = (int)(ix->n_indexed / ix->cfg.group_size);
+    lead.start = ix->launch_start;
+    lead.stop = ix->launch_stop;
     FusedArgs a;
     a.tau_s = tau_s;
-    a.chan_exp = lvr_chan_exp(ix);   // exponents 0 and factors 1 unless the index is a rescaled one
     a.k_new = k_new;
     a.v_new = v_new;
     a.V = ix->V;
     a.m_new = (int)m_new;
-    a.centres = ix->centres;
-    a.radii = ix->radii;
     a.K = ix->K;
     a.slot_pos = ix->slot_pos;
-    a.q = q;
-    a.tau = tau;
     a.seg_count = lvr_seg_count(ix);
     a.emit.out_idx = out_idx;
     a.emit.head_count = lvr_head_count(ix);
@@ -901,17 +911,12 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     a.emit.cap = cap;
     a.emit.out_score = ix->scores;
     a.emit.score_stride = ix->cap_rows;
-    a.n_groups = ix->n_indexed / ix->cfg.group_size;
-    a.max_groups = ix->max_groups;
     a.max_segs = lvr_max_segs(ix->max_groups);
     a.cap_rows = ix->cap_rows;
     a.n_indexed = ix->n_indexed;
     a.n_total = ix->n_total + m_new;
     a.log2r = 0;
     while ((1 << a.log2r) < ix->cfg.group_size) ++a.log2r;
-    a.n_q_heads = ix->cfg.n_q_heads;
-    a.n_kv_heads = ix->cfg.n_kv_heads;
-    a.G = ix->G;
     a.buffer_dense = (ix->cfg.flags & LVR_ATTEND_BUFFER_DENSE) ? 1 : 0;
     a.skip_bounds = (ix->skip_bounds && !tau_s) ? 1 : 0;
     const int n_bh = lvr_n_bh(ix);
@@ -919,20 +924,19 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     const int has_buffer = a.n_total > ix->n_indexed ? 1 : 0;
     const bool wide = ix->G > 4;
     const int tpw = ix->cfg.query_workgroups > 0
-                        ? tiles_for_workgroups(a.n_groups, n_bh, ix->cfg.query_workgroups)   // the caller's number
-                        : tiles_for_launch(a.n_groups, n_bh, has_buffer, ix->cfg.group_size,
+                        ? tiles_for_workgroups(lead.n_groups, n_bh, ix->cfg.query_workgroups)   // the caller's number
+                        : tiles_for_launch(lead.n_groups, n_bh, has_buffer, ix->cfg.group_size,
                                            !tau_s && (wide || (!ix->box && (ix->cf8 || ix->cf6) && ix->cfg.group_size == 1)),
                                            wide ? (ix->box ? 3 : 4) : 5);
-    a.tiles_per_wave = tpw;
+    lead.tiles_per_wave = tpw;
     const int seg_groups = tpw * 64;
-    a.n_segs = (int)((a.n_groups + seg_groups - 1) / seg_groups);
+    a.n_segs = (int)(((int64_t)lead.n_groups + seg_groups - 1) / seg_groups);
     ix->seg_groups = seg_groups;
     ix->n_segs = a.n_segs;
     if (a.n_segs + has_buffer == 0) return hipSuccess;
     dim3 grid((unsigned)(a.n_segs + has_buffer), (unsigned)n_bh);
     // more workgroups than 5 x 256: hold the residency at four per compute unit, so that the rounds are whole
     const unsigned dyn_lds = (int64_t)grid.x * grid.y > 1280 ? 20480u : 0u;
-    const LaunchEvents ev = {ix->launch_start, ix->launch_stop};
     // one centre tile per trip for the small segments of short contexts, two per trip for long ones
     // (measured crossover between 32k and 128k keys); four per trip costs a wave per SIMD and 12 us
     const bool one = tpw == 1;
@@ -1013,11 +1017,11 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
         return hipGetLastError();
     }
     if (ix->G <= 4) {
-        if (one) launch_s<1, 4>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, ev);
-        else launch_s<2, 4>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, ev);
+        if (one) launch_s<1, 4>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, lead);
+        else launch_s<2, 4>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, lead);
     } else {   // up to eight heads in one operand
-        if (one) launch_s<1, 8>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, ev);
-        else launch_s<2, 8>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, ev);
+        if (one) launch_s<1, 8>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, lead);
+        else launch_s<2, 8>(grid, dyn_lds, st, a, ix->cfg.n_subspaces, lead);
     }
     return hipGetLastError();
 }
