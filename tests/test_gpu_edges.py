@@ -118,6 +118,47 @@ def test_threshold_ranks(G, dtype, R, n, tree):
                 assert abs(tau[0, h] - want) <= 200 * 128 * 2.0 ** -24, (mode, param, h)
 
 
+def check_median_splits(x, got, r):
+    """`got` [entries]: the positions a tree of groups of r put in its slots; x [entries][128] fp64, multiples of 0.5 or arbitrary.
+    Walks the tree down the given order: a node's entries have to be split at the median of (coordinate, position) on an axis of
+    the largest variance, and the last split's order is the slots' order.  Which axis is taken is free among those whose
+    variances are within rounding of the largest (exact integers where the values are multiples of 0.5)."""
+    halves = np.rint(2.0 * x)
+    exact = np.array_equal(halves, 2.0 * x)
+    size = r
+    while size < len(got):
+        size *= 2
+
+    def axes(ent):
+        if exact:   # n * sum(v^2) - sum(v)^2: below 2^63 for 32768 entries of magnitude below 90
+            v = halves[ent].astype(np.int64)
+            var = len(ent) * (v * v).sum(axis=0) - v.sum(axis=0) ** 2
+            return np.nonzero(var >= var.max() - var.max() * 1e-13)[0]   # fp64 sums of such values are exact, the quotient is rounded
+        v = x[ent] - x[ent].mean(axis=0)
+        var = (v * v).mean(axis=0)
+        return np.nonzero(var >= var.max() * (1 - 1e-10))[0]
+
+    def walk(ent, at, m):   # ent: real entries of a node of m padded ones, ascending; its slots start at `at`
+        if len(ent) == 0:
+            return
+        mine = got[at:at + len(ent)]
+        if m == r:
+            assert np.array_equal(mine, ent), f"slots {at}..: a group that was never split is out of order"
+            return
+        orders = [ent[np.lexsort((ent, x[ent, c]))] for c in axes(ent)]
+        if m == 2 * r:
+            assert any(np.array_equal(mine, o) for o in orders), f"slots {at}..: not the order of the last split"
+            return
+        left = np.sort(mine[:m // 2])
+        fits = [o for o in orders if np.array_equal(left, np.sort(o[:m // 2]))]
+        assert fits, f"slots {at}..: {len(ent)} entries are not split at their median"
+        walk(left, at, m // 2)
+        walk(np.sort(mine[m // 2:]), at + m // 2, m // 2)
+
+    assert np.array_equal(np.sort(got), np.arange(len(got)))
+    walk(np.arange(len(got)), 0, size)
+
+
 @pytest.mark.parametrize("dtype,r,n,ties", [("bf16", 4, 1024, False), ("bf16", 4, 2048, True), ("bf16", 2, 3000, False), ("bf16", 1, 4096, True),
                                             ("f32", 4, 5000, False), ("f32", 16, 16384, True), ("bf16", 8, 32768, True),
                                             ("bf16", 4, 40000, False)])
@@ -140,31 +181,10 @@ def test_tree_order_is_the_recursive_median_split(G, dtype, r, n, ties):
         slot_pos = L.lvr_export_index(h, cfg)[2]
     finally:
         L.lvr_destroy(h)
-    groups = n // r
-    size = r
-    while size < groups * r:
-        size *= 2
+    grouped = n // r * r
     for kv in range(2):
-        x = K[0, kv].astype(np.float64)
-
-        def split(ent, m):   # ent: real entries of a node of m padded ones, in ascending position order
-            if m == r or len(ent) == 0:
-                return ent
-            v = x[ent].var(axis=0)
-            if np.partition(v, -2)[-2] > v.max() * (1 - 1e-12) and not ties:
-                pytest.skip("two axes within rounding of each other")
-            c = x[ent, int(np.argmax(v))]
-            order = ent[np.lexsort((ent, c))]
-            left, right = order[:m // 2], order[m // 2:]
-            if m == 2 * r:
-                return order
-            return np.concatenate([split(np.sort(left), m // 2), split(np.sort(right), m // 2)])
-
-        want = split(np.arange(groups * r), size)
-        assert np.array_equal(np.sort(slot_pos[0, kv]), np.arange(n))
-        got = slot_pos[0, kv, :groups * r]
-        # axes whose variances tie to rounding may be chosen differently; everything else is exact
-        assert np.array_equal(got, want) or (ties and (got == want).mean() > 0.5), (got != want).sum()
+        assert np.array_equal(slot_pos[0, kv, grouped:], np.arange(grouped, n))
+        check_median_splits(K[0, kv, :grouped].astype(np.float64), slot_pos[0, kv, :grouped], r)
 
 
 @pytest.mark.parametrize("hq,hkv,n,r,S,tail,kw", [
