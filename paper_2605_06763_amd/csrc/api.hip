@@ -257,7 +257,7 @@ int build_subspace_groups(lvr_index *ix, int64_t g0, int64_t ng, hipStream_t st)
     for (int sb = 0; sb < S; ++sb) {
         lvr_tree_perm perm;
         hipError_t e = lvr_tree_order(ix, src, as, ng * r, st, &perm, sb * (LVR_D / S), (sb + 1) * (LVR_D / S));
-        if (e == hipErrorInvalidValue) return LVR_E_UNSUPPORTED;   // sort key wider than 64 bits
+        if (e == hipErrorInvalidValue) return LVR_E_UNSUPPORTED;   // beyond lvr_tree_feasible
         LVR_HIP(e);
         LVR_HIP(lvr_launch_subspace_groups(ix, &perm, sb, row0, g0, ng, st));
     }
@@ -446,7 +446,7 @@ int lvr_build(lvr_index *ix, const void *K, const void *V, int64_t n, const int6
         Timed t(ix, LVR_K_COPY, st);
         const int64_t n_tree = n_groups * r;
         hipError_t e = lvr_tree_group(ix, K, ks, V, vs, n_tree, 0, st);
-        if (e == hipErrorInvalidValue) return LVR_E_UNSUPPORTED;   // sort key wider than 64 bits
+        if (e == hipErrorInvalidValue) return LVR_E_UNSUPPORTED;   // beyond lvr_tree_feasible
         LVR_HIP(e);
         if (n > n_tree) {
             const char *Kt = static_cast<const char *>(K) + n_tree * ks[2] * (int64_t)ix->elt;
@@ -484,7 +484,7 @@ int lvr_append(lvr_index *ix, const void *k_new, const void *v_new, int64_t m, v
     hipStream_t st = static_cast<hipStream_t>(stream);
     // Everything that can refuse the call is settled before a row is stored, so a call that returns
     // LVR_E_UNSUPPORTED has changed nothing and may be repeated differently: whether a chunk can be
-    // grouped by the tree (the width of its sort key), and the side stream of the two-stream update.
+    // grouped by the tree (lvr_tree_feasible), and the side stream of the two-stream update.
     if ((ix->cfg.grouping == LVR_GROUP_TREE || ix->per_subspace) &&
         ix->n_total + m - ix->n_indexed >= ix->cfg.buffer_size && !lvr_tree_feasible(ix, ix->cfg.buffer_size))
         return LVR_E_UNSUPPORTED;

@@ -106,7 +106,10 @@ __device__ __forceinline__ int wave_argmax(double v0, double v1, int lane, int c
     const uint64_t b0 = __ballot(v0 == best), b1 = __ballot(v1 == best);
     const int a0 = b0 ? 2 * __builtin_ctzll(b0) : 2 * 64, a1 = b1 ? 2 * __builtin_ctzll(b1) + 1 : 2 * 64;
     const int a = a0 < a1 ? a0 : a1;
-    return a < 2 * 64 ? a : c_lo;   // no variance compares equal to the maximum (NaN keys): any axis of the block
+    // Keys with NaN or overflowing coordinates: where no variance of the block is a number the masked coordinates' -1 is the
+    // maximum and the first of them is taken (c_lo where nothing is masked); the split is then on that coordinate, the set a
+    // query returns does not depend on it
+    return a < 2 * 64 ? a : c_lo;
 }
 
 // Sums of the 64 consecutive entries whose positions the lanes hold, relative to the row (p0, p1): sixteen rows in flight.
@@ -570,8 +573,10 @@ hipError_t tree_order_t(lvr_index *ix, const TreeSrc &src, int64_t n_real, int64
 
 }  // namespace
 
-// Whether lvr_tree_order can handle n_real keys per (sequence, KV head): the sort key
-// [node | coordinate | position] has to fit 64 bits and the work space the padded entries.
+// Which inputs the tree takes: node number, coordinate code and position together have to fit 64 bits, and the work space the
+// padded entries.  Only the second is a need of the kernels above, which keep codes and positions apart; the first is the
+// limit of the entry points (LVR_E_UNSUPPORTED beyond it) since the construction sorted one 64-bit key per entry, and stands
+// so that the same calls are refused.
 bool lvr_tree_feasible(const lvr_index *ix, int64_t n_real) {
     if (n_real <= 0) return true;
     const int r = ix->cfg.group_size;
