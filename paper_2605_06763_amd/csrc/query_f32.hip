@@ -244,13 +244,16 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     // (4096 keys: 75.1 us on local keys, 56.9 with one).  What does not fit one round gets several, and four where already
     // a segment each is more than one.
     const int64_t buffers = a.n_total > ix->n_indexed ? n_bh : 0;
-    const int64_t resident = ix->G == 8 ? 512 : 768;
+    // Rows behind the host link come no faster for more requests: 96 workgroups (8 x 4096 keys, all balls survive: 332 us per step,
+    // 392 with 512, 361 with a launch per stage; 64 and 128: 333 and 360).
+    const bool on_host = (ix->cfg.flags & LVR_KV_IN_HOST_MEMORY) != 0;
+    const int64_t resident = on_host ? 96 : (ix->G == 8 ? 512 : 768);
     int64_t per_head = (a.n_groups + F32_SEG_MAX - 1) / F32_SEG_MAX;   // segments of a (sequence, KV head), at least
     if (ix->cfg.query_workgroups > 0) {
         per_head = ix->cfg.query_workgroups / n_bh;
     } else {
         int64_t rounds = (per_head * n_bh + buffers + resident - 1) / resident;
-        if (n_bh + buffers > resident && rounds < 4) rounds = 4;
+        if (n_bh + buffers > resident && rounds < 4 && !on_host) rounds = 4;
         if (rounds < 1) rounds = 1;
         per_head = (rounds * resident - buffers) / n_bh;
     }

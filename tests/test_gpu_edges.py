@@ -191,19 +191,21 @@ def test_tree_order_is_the_recursive_median_split(G, dtype, r, n, ties):
     (1, 1, 64, 4, 4, 0, {}), (1, 1, 4096, 4, 4, 0, {}), (2, 1, 1000, 2, 1, 3, {}), (8, 2, 4095, 4, 16, 131, {}),
     (8, 1, 8192, 1, 2, 255, dict(query_workgroups=16)), (4, 4, 5000, 16, 8, 17, dict(buffer_size=32)),
     (8, 2, 2048, 4, 4, 40, dict(tree=True)), (4, 1, 3, 4, 4, 5, {}), (4, 2, 700, 4, 4, 100, dict(dense_buffer=True)),
-    (4, 2, 700, 4, 4, 300, dict(concurrent=True)), (320, 40, 700, 2, 4, 5, {}), (800, 800, 40, 1, 1, 3, {})])
+    (4, 2, 700, 4, 4, 300, dict(concurrent=True)), (320, 40, 700, 2, 4, 5, {}), (800, 800, 40, 1, 1, 3, {}),
+    (8, 2, 2050, 4, 4, 40, dict(offload=True)), (4, 4, 3000, 2, 1, 0, dict(offload=True, tree=True)), (120, 120, 50, 1, 4, 7, dict(offload=True))])
 def test_fp32_one_launch_query_is_the_two_launch_one(G, oracle, hq, hkv, n, r, S, tail, kw):
     """The fused fp32 query against the separate bound test and filter (LVR_SEPARATE_KERNELS): the same sets and counts for
     every head count, block count, group size, segment remainder, buffer content and option, with thresholds that keep
     few keys, everything and nothing, room for fewer entries than there are, and an append that rides in the launch; as many
-    (sequence, KV head) pairs as give each a few segments, and more than fit the device at once; the attention over the lists
-    against the oracle."""
+    (sequence, KV head) pairs as give each a few segments, and more than fit the device at once; rows in host memory; the
+    attention over the lists against the oracle."""
     L = G.L
     g = np.random.default_rng(n + hq)
     K = g.standard_normal((1, hkv, n + tail + 2, 128)).astype(np.float32)
     V = g.standard_normal((1, hkv, n + tail + 2, 128)).astype(np.float32)
     q = g.standard_normal((1, hq, 128)).astype(np.float32)
     flags = (L.LVR_ATTEND_BUFFER_DENSE if kw.get("dense_buffer") else 0) | (L.LVR_CONCURRENT_UPDATE if kw.get("concurrent") else 0)
+    flags |= L.LVR_KV_IN_HOST_MEMORY if kw.get("offload") else 0
     opt = {k: v for k, v in kw.items() if k in ("query_workgroups", "buffer_size")}
     if kw.get("tree"):
         opt["grouping"] = L.LVR_GROUP_TREE
