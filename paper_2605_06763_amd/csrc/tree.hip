@@ -15,24 +15,36 @@
 //   2. the node is split at the median of (coordinate on that axis, position): the coordinate is
 //      mapped to an order-preserving unsigned code, and equal coordinates are ordered by position
 //      (Alg. 2 is silent; this is the rule the CPU reference uses).
-// Only which entries go left matters above the last level, so nodes of more than 1024 entries are
-// not sorted: a workgroup per node finds the median code by counting digits and moves the
+// Only which entries go left matters above the last level, so nodes larger than tree_small_kernel takes (512 entries of bf16
+// keys, 256 of fp32 ones) are not sorted: their workgroups find the median code by counting digits and move the
 // entries to the two halves in the order they had.  Every node's entries therefore stay in ascending
-// position order, which is what breaks ties and keeps the padding at a node's end.  The levels of
-// nodes of at most 1024 entries are finished by tree_small_kernel in one launch, a workgroup per
-// node, an entry per thread; it sorts, so a finished group's rows are in the order of the last split.
+// position order, which is what breaks ties and keeps the padding at a node's end.  The levels below are
+// finished by tree_small_kernel in one launch, a workgroup per node, which sorts, so a finished group's rows are in the
+// order of the last split.
 //
-// A build of 8 x 32768 bf16 keys in groups of four (five levels above 1024 entries, eight below) took
-// 2.5 ms with one wave per SIMD on the statistics, a device-wide 64-bit radix sort per level and
-// four waves per small node; this construction takes 0.33 ms (tree build and one step: 2321 -> 424 us).
+// Variances come from sums and sums of squares in fp64, and only the left half of a node's rows is added up for the level below:
+// the right half's sums are the node's less those.
+//
+// A build of 8 x 32768 bf16 keys in groups of four and one step, us: 2321 with one wave per SIMD on the statistics, a device-wide radix
+// sort per level and four waves per small node; 424 with a workgroup per node that splits, statistics over all rows in a launch per
+// level, and small nodes of 1024 entries whose rows came from memory at every level; 300 now.  Builds alone, that form and this one: 2048
+// keys 176 / 81 (4 x 4 heads), 9000 keys 276 / 157 (2 heads), 32768 fp32 keys 553 / 417, 131072 keys 1574 / 1245; one tree per coordinate block,
+// S = 16, 32768 keys 5514 / 3761.
 #include <type_traits>
 
 #include "lvr_internal.h"
 
 namespace {
 
-constexpr int PIECE = 1024;         // entries per partial-statistics piece of a large node
-constexpr int TREE_WG_MAX = 1024;   // entries of a node that one workgroup finishes
+constexpr int PIECE = 1024;          // entries whose rows a workgroup adds up
+// entries of a node whose workgroups each fetch the codes of all of it: every further time that all codes are fetched costs some 5 us (a line per
+// coordinate: 33 MB for 8 x 32768 keys), a launch of its own with the fetch 8.8 us.  A level of 8 x 32768 keys, us: nodes of 4096 32.5 gathered by
+// their four workgroups, 23.6 with the codes in a launch of their own; nodes of 2048 21.5 and 24
+constexpr int GATHER_MAX = 2048;
+template <int ELT>
+constexpr int SMALL_NODE = ELT == 2 ? 512 : 256;   // entries of a node that one workgroup finishes: 128 KB of rows
+template <int ELT>
+using code_t = typename std::conditional<ELT == 2, uint16_t, uint32_t>::type;
 
 struct TreeSrc {
     const char *K;             // source key rows
@@ -49,16 +61,20 @@ __device__ __forceinline__ int64_t key_pos(uint64_t k, int pos_bits) { return (i
 
 // lane owns channels 2*lane, 2*lane+1 of a row
 template <int ELT>
-__device__ __forceinline__ void lane_pair(const char *row, int lane, float &x0, float &x1) {
+using row_piece = typename std::conditional<ELT == 2, uint32_t, float2>::type;
+template <int ELT>
+__device__ __forceinline__ void unpack_pair(const row_piece<ELT> &w, float &x0, float &x1) {
     if constexpr (ELT == 2) {
-        const uint32_t w = reinterpret_cast<const uint32_t *>(row)[lane];
-        x0 = __uint_as_float(w << 16);
-        x1 = __uint_as_float(w & 0xffff0000u);
+        x0 = lvr_bf16_lo(w);
+        x1 = lvr_bf16_hi(w);
     } else {
-        const float2 v = reinterpret_cast<const float2 *>(row)[lane];
-        x0 = v.x;
-        x1 = v.y;
+        x0 = w.x;
+        x1 = w.y;
     }
+}
+template <int ELT>
+__device__ __forceinline__ void lane_pair(const char *row, int lane, float &x0, float &x1) {
+    unpack_pair<ELT>(reinterpret_cast<const row_piece<ELT> *>(row)[lane], x0, x1);
 }
 
 // order-preserving unsigned code of coordinate c of a row (16 or 32 bits); padding takes the largest code
@@ -77,233 +93,432 @@ __device__ __forceinline__ uint32_t coord_code(const char *row, int c) {
 template <int ELT>
 constexpr uint32_t PAD_CODE = ELT == 2 ? 0xffffu : 0xffffffffu;
 
-// one step of a wave maximum: the value DPP moves here, or this lane's own where nothing arrives
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_max(double v) {
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const int lo = (int)(uint32_t)u, hi = (int)(uint32_t)(u >> 32);
-    const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
-    const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
-    return fmax(v, __longlong_as_double((long long)(((uint64_t)h2 << 32) | l2)));
+// Largest of a wave's values (lane 63 holds it, every lane gets it).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    auto with = [&](auto ctrl, auto rows) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+        v = v > o ? v : o;
+    };
+    with(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr:1, 2, 4, 8: lane 15 of a row
+    with(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});   // holds the row's maximum
+    with(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+    with(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+    with(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15, row_bcast:31
+    with(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// argmax over 128 channel variances held as (v0, v1) per lane; lowest channel wins ties
-// [c_lo, c_hi): the coordinates that may be chosen (a tree over one coordinate block looks at that block only)
+// argmax over 128 channel variances (>= 0) held as (v0, v1) per lane; lowest channel wins ties.
+// [c_lo, c_hi): the coordinates that may be chosen (a tree over one coordinate block looks at that block only).
+// Non-negative doubles are ordered as their bits are: the upper words decide, the lower ones only where those tie.
 __device__ __forceinline__ int wave_argmax(double v0, double v1, int lane, int c_lo, int c_hi) {
-    if (2 * lane < c_lo || 2 * lane >= c_hi) v0 = -1.0;           // variances are >= 0
-    if (2 * lane + 1 < c_lo || 2 * lane + 1 >= c_hi) v1 = -1.0;
-    double m = fmax(v0, v1);
-    m = dpp_max<0x111, 0xf>(m);   // row_shr:1, 2, 4, 8: lane 15 of a row holds the row's maximum
-    m = dpp_max<0x112, 0xf>(m);
-    m = dpp_max<0x114, 0xf>(m);
-    m = dpp_max<0x118, 0xf>(m);
-    m = dpp_max<0x142, 0xa>(m);   // row_bcast:15, row_bcast:31: lane 63 holds the wave's
-    m = dpp_max<0x143, 0xc>(m);
-    const uint64_t u = (uint64_t)__double_as_longlong(m);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
-    const double best = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-    const uint64_t b0 = __ballot(v0 == best), b1 = __ballot(v1 == best);
+    const bool may0 = 2 * lane >= c_lo && 2 * lane < c_hi, may1 = 2 * lane + 1 >= c_lo && 2 * lane + 1 < c_hi;
+    const uint64_t u0 = (uint64_t)__double_as_longlong(v0), u1 = (uint64_t)__double_as_longlong(v1);
+    const uint32_t h0 = may0 ? (uint32_t)(u0 >> 32) + 1u : 0u, h1 = may1 ? (uint32_t)(u1 >> 32) + 1u : 0u;
+    const uint32_t best = wave_max(h0 > h1 ? h0 : h1);
+    uint64_t b0 = __ballot(h0 == best), b1 = __ballot(h1 == best);
+    if ((int)__popcll(b0) + (int)__popcll(b1) > 1) {   // uniform
+        const uint32_t l0 = h0 == best ? (uint32_t)u0 : 0u, l1 = h1 == best ? (uint32_t)u1 : 0u;
+        const uint32_t low = wave_max(l0 > l1 ? l0 : l1);
+        b0 = __ballot(h0 == best && (uint32_t)u0 == low);
+        b1 = __ballot(h1 == best && (uint32_t)u1 == low);
+    }
     const int a0 = b0 ? 2 * __builtin_ctzll(b0) : 2 * 64, a1 = b1 ? 2 * __builtin_ctzll(b1) + 1 : 2 * 64;
-    const int a = a0 < a1 ? a0 : a1;
-    // Keys with NaN or overflowing coordinates: where no variance of the block is a number the masked coordinates' -1 is the
-    // maximum and the first of them is taken (c_lo where nothing is masked); the split is then on that coordinate, the set a
-    // query returns does not depend on it
-    return a < 2 * 64 ? a : c_lo;
+    return a0 < a1 ? a0 : a1;
 }
 
-// Sums of the 64 consecutive entries whose positions the lanes hold, relative to the row (p0, p1): sixteen rows in flight.
-// `real`: ballot of the lanes whose entry is no padding; `any`: a position that may be read in the place of padding.
+// Variances of a node's 128 channels from its sums, times the square of the number of keys (the same factor for all of them):
+// n q - s^2, with the rounding of the product carried along, so that sums that are exact (bf16 keys, whole numbers) give variances that
+// are equal where they should be.  Never negative; what is no number counts as zero.
+__device__ __forceinline__ double spread(double s, double q, double n) {
+    const double p = s * s;
+    return fmax(fma(n, q, -p) - fma(s, s, -p), 0.0);
+}
+
+// What is taken off every coordinate before it is squared: nothing for bf16 keys, whose sums are exact in fp64 wherever squares
+// of the mean cancel (eight significant bits); a key of the tree for fp32 ones.
+struct Shift {
+    double p0, p1;
+};
+
+// Adds the rows held in (x0, x1) to the sums.
+template <int ELT, int N>
+__device__ __forceinline__ void add_rows(const float (&x0)[N], const float (&x1)[N], const Shift &p, double &s0, double &s1, double &q0,
+                                         double &q1) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        double d0 = (double)x0[u], d1 = (double)x1[u];
+        if constexpr (ELT == 4) {
+            d0 -= p.p0;
+            d1 -= p.p1;
+        }
+        s0 += d0; s1 += d1; q0 = fma(d0, d0, q0); q1 = fma(d1, d1, q1);
+    }
+}
+
+// Sums of the up to 64 entries whose positions the lanes hold; the next sixteen rows are requested before sixteen are added up.
+// `real`: ballot of the lanes whose entry is no padding, a prefix of them.
 template <int ELT>
-__device__ __forceinline__ void sum_rows64(const TreeSrc &src, int bh, int lane, int mypos, uint64_t real, int any, float p0, float p1,
-                                           double &s0, double &s1, double &q0, double &q1) {
+__device__ __forceinline__ void sum_rows64(const TreeSrc &src, int bh, int lane, int mypos, uint64_t real, const Shift &p, double &s0,
+                                           double &s1, double &q0, double &q1) {
     const char *base = src.row(bh, 0);
     const int64_t row_bytes = src.st * ELT;
-    for (int j0 = 0; j0 < 64; j0 += 16) {
-        if (!((real >> j0) & 1ull)) break;   // padding is at the end: nothing real follows (uniform)
-        float x0[16], x1[16];
+    const int n = (int)__popcll(real);
+    row_piece<ELT> w[2][16];
+    auto fetch = [&](int j0, row_piece<ELT>(&x)[16]) {
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int pos = __builtin_amdgcn_readlane(mypos, j0 + u);
-            const bool in = (real >> (j0 + u)) & 1ull;   // uniform
-            lane_pair<ELT>(base + (int64_t)(in ? pos : any) * row_bytes, lane, x0[u], x1[u]);
+            x[u] = reinterpret_cast<const row_piece<ELT> *>(base + (int64_t)(j0 + u < n ? pos : 0) * row_bytes)[lane];
         }
-        if (((real >> j0) & 0xffffull) == 0xffffull) {   // uniform: no padding among them
+        __builtin_amdgcn_sched_barrier(0);   // requested here, not next to their use
+    };
+    auto add = [&](int j0, const row_piece<ELT>(&x)[16]) {
+        float x0[16], x1[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) unpack_pair<ELT>(x[u], x0[u], x1[u]);
+        if (j0 + 16 > n) {   // uniform: what is masked adds nothing
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                const double d0 = (double)x0[u] - (double)p0, d1 = (double)x1[u] - (double)p1;
-                s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const bool in = (real >> (j0 + u)) & 1ull;
-                const double d0 = in ? (double)x0[u] - (double)p0 : 0., d1 = in ? (double)x1[u] - (double)p1 : 0.;
-                s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
+                x0[u] = j0 + u < n ? x0[u] : (float)p.p0;   // (the shift is a key's coordinate: exact)
+                x1[u] = j0 + u < n ? x1[u] : (float)p.p1;
             }
         }
+        add_rows<ELT>(x0, x1, p, s0, s1, q0, q1);
+    };
+    if (n > 0) fetch(0, w[0]);   // uniform conditions throughout
+#pragma unroll
+    for (int j0 = 0; j0 < 64; j0 += 16) {
+        if (j0 + 16 < 64 && n > j0 + 16) fetch(j0 + 16, w[(j0 / 16 + 1) & 1]);
+        if (n > j0) add(j0, w[(j0 / 16) & 1]);
     }
 }
 
-// Statistics of a piece of a large node: 16 waves, 64 entries each; sums are relative to the node's first key (the variance
-// does not depend on the shift; the shift removes the cancellation).  order == NULL: entry i holds position i.
-// Bound by the fp64 adds and the row reads about alike.
+// The tree's first key (position 0), the shift of every node above the small ones.
 template <int ELT>
-__global__ void __launch_bounds__(1024)
-tree_stats_piece_kernel(TreeSrc src, const uint32_t *__restrict__ order, double *__restrict__ partial, int64_t np,
-                        int64_t n_real, int64_t m) {
-    __shared__ double sm[16][256];
-    __shared__ int sc[16];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int bh = blockIdx.y;
-    const int64_t piece = blockIdx.x;
-    const int64_t node0 = (piece * PIECE / m) * m;
-    const int64_t i = piece * PIECE + threadIdx.x;
-    const uint32_t *ord = order + (int64_t)bh * np;
-    const int mypos = order ? (int)ord[i] : (int)i;
-    const int ppos = order ? (int)ord[node0] : (int)node0;   // first entry of the node; real unless the node is all padding
-    const uint64_t real = __ballot(mypos < n_real);
-    double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-    if (real) {   // uniform: then the node's first entry is real too
-        float p0, p1;
-        lane_pair<ELT>(src.row(bh, ppos), lane, p0, p1);
-        sum_rows64<ELT>(src, bh, lane, mypos, real, ppos, p0, p1, s0, s1, q0, q1);
+__device__ __forceinline__ Shift tree_shift(const TreeSrc &src, int bh, int lane) {
+    Shift p = {0.0, 0.0};
+    if constexpr (ELT == 4) {
+        float x0, x1;
+        lane_pair<ELT>(src.row(bh, 0), lane, x0, x1);
+        p.p0 = (double)x0;
+        p.p1 = (double)x1;
     }
+    return p;
+}
+
+// The waves' sums of a workgroup, added in order and stored as 256 doubles: 128 sums, 128 sums of squares.
+template <int NW>
+__device__ __forceinline__ void store_partial(double (*sm)[256], int lane, int wave, int waves, double s0, double s1, double q0, double q1,
+                                              double *out) {
     sm[wave][2 * lane] = s0; sm[wave][2 * lane + 1] = s1;
     sm[wave][128 + 2 * lane] = q0; sm[wave][128 + 2 * lane + 1] = q1;
-    if (lane == 0) sc[wave] = __popcll(real);
     __syncthreads();
     const int t = threadIdx.x;
-    double *out = partial + ((int64_t)bh * (np / PIECE) + piece) * 258;
     if (t < 256) {
         double a = 0.;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) a += sm[w][t];
+        for (int w = 0; w < NW; ++w) a += w < waves ? sm[w][t] : 0.;
         out[t] = a;
-    }
-    if (t == 256) {
-        int c = 0;
-        for (int w = 0; w < 16; ++w) c += sc[w];
-        out[256] = (double)c;
     }
 }
 
-// Adds the pieces of a node (eight slices of them side by side, 1024 threads) and picks the axis; every thread gets it.
-__device__ __forceinline__ int node_axis(const double *__restrict__ partial, int bh, int64_t np, int64_t m, int64_t node, int c_lo, int c_hi) {
-    __shared__ double sm[8][2][128];
-    __shared__ double sc[8];
+// Sums of whole pieces of PIECE entries: the root, and the nodes below one that was split by a single workgroup.  order == NULL:
+// entry i holds position i.  (Everywhere else the launch that splits a node adds up the rows that go left, see below.)
+template <int ELT>
+__global__ void __launch_bounds__(1024)
+tree_stats_piece_kernel(TreeSrc src, const uint32_t *__restrict__ order, double *__restrict__ partial, int64_t np, int64_t n_real) {
+    __shared__ double sm[16][256];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int bh = blockIdx.y;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t *ord = order + (int64_t)bh * np;
+    const int mypos = order ? (int)ord[i] : (int)i;
+    const uint64_t real = __ballot(mypos < n_real);
+    double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
+    if (real) sum_rows64<ELT>(src, bh, lane, mypos, real, tree_shift<ELT>(src, bh, lane), s0, s1, q0, q1);   // uniform
+    store_partial<16>(sm, lane, wave, (int)(blockDim.x >> 6), s0, s1, q0, q1, partial + ((int64_t)bh * gridDim.x + blockIdx.x) * 256);
+}
+
+// The sums a level starts from.  `whole`: the pieces' sums cover their entries; else they cover the rows of the parents' level that
+// went left, so a left node adds up its parent's pieces and a right one takes them off its parent's sums.
+struct LevelSums {
+    const double *pieces;   // [n_bh][pieces of the tree][256]
+    const double *parent;   // [n_bh][nodes of the level above][256]
+    double *own;            // [n_bh][nodes of this level][256], or NULL where no level below needs them (then there may be more nodes than room)
+    int64_t n_pieces;
+    int whole;
+};
+
+// The axis of a node (every thread gets it); the first workgroup of a node also stores its sums for the level below.  NT threads.
+template <int NT>
+__device__ __forceinline__ int node_axis(const LevelSums &a, int bh, int64_t m, int64_t node, int64_t n_nodes, int64_t n_real, bool store,
+                                         int c_lo, int c_hi) {
+    constexpr int SL = NT / 128;   // slices of the pieces side by side
+    __shared__ double sm[SL][256];
     __shared__ int s_axis;
     const int t = threadIdx.x, c = t & 127, sl = t >> 7;
-    const int64_t pieces = m / PIECE;
-    const double *pp = partial + ((int64_t)bh * (np / PIECE) + node * pieces) * 258;
-    double s = 0.0, q = 0.0, cnt = 0.0;
-#pragma unroll 4
-    for (int64_t p = sl; p < pieces; p += 8) {
-        s += pp[p * 258 + c];
-        q += pp[p * 258 + 128 + c];
-        cnt += pp[p * 258 + 256];
+    const int64_t up = a.whole ? m : 2 * m;   // entries the pieces to be added cover
+    const int64_t count = up > PIECE ? up / PIECE : 1, first = (a.whole ? node : node >> 1) * count;
+    const double *pp = a.pieces + ((int64_t)bh * a.n_pieces + first) * 256;
+    const bool right = !a.whole && (node & 1);
+    double e0 = 0., e1 = 0., f0 = 0., f1 = 0.;
+    if (right && t < 64) {
+        const double *e = a.parent + ((int64_t)bh * (n_nodes >> 1) + (node >> 1)) * 256;
+        e0 = e[2 * t]; e1 = e[2 * t + 1];
+        f0 = e[128 + 2 * t]; f1 = e[128 + 2 * t + 1];
     }
-    sm[sl][0][c] = s;
-    sm[sl][1][c] = q;
-    if (c == 0) sc[sl] = cnt;
+    double s = 0.0, q = 0.0;
+#pragma unroll 4
+    for (int64_t p = sl; p < count; p += SL) {
+        s += pp[p * 256 + c];
+        q += pp[p * 256 + 128 + c];
+    }
+    sm[sl][c] = s;
+    sm[sl][128 + c] = q;
     __syncthreads();
     if (t < 64) {
-        double s0 = 0., s1 = 0., q0 = 0., q1 = 0., n = 0.;
-        for (int k = 0; k < 8; ++k) {
-            s0 += sm[k][0][2 * t]; s1 += sm[k][0][2 * t + 1];
-            q0 += sm[k][1][2 * t]; q1 += sm[k][1][2 * t + 1];
-            n += sc[k];
+        double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            s0 += sm[k][2 * t]; s1 += sm[k][2 * t + 1];
+            q0 += sm[k][128 + 2 * t]; q1 += sm[k][128 + 2 * t + 1];
         }
-        const double v0 = n > 0 ? (q0 - s0 * s0 / n) / n : 0., v1 = n > 0 ? (q1 - s1 * s1 / n) / n : 0.;
-        const int a = wave_argmax(v0, v1, t, c_lo, c_hi);
-        if (t == 0) s_axis = a;
+        if (right) {
+            s0 = e0 - s0; s1 = e1 - s1;
+            q0 = f0 - q0; q1 = f1 - q1;
+        }
+        if (store && a.own) {
+            double *o = a.own + ((int64_t)bh * n_nodes + node) * 256;
+            o[2 * t] = s0; o[2 * t + 1] = s1;
+            o[128 + 2 * t] = q0; o[128 + 2 * t + 1] = q1;
+        }
+        int64_t n = n_real - node * m;   // real keys fill a prefix of the entries
+        n = n < 0 ? 0 : (n > m ? m : n);
+        const int ax = wave_argmax(spread(s0, q0, (double)n), spread(s1, q1, (double)n), t, c_lo, c_hi);
+        if (t == 0) s_axis = ax;
     }
     __syncthreads();
     return s_axis;
 }
 
-// The axis of every node whose codes are fetched by a launch of their own.
+// The axis of every node that a single workgroup splits.
 __global__ void __launch_bounds__(1024)
-tree_axis_kernel(const double *__restrict__ partial, int32_t *__restrict__ axis, int64_t np, int64_t m, int64_t n_nodes,
-                 int c_lo, int c_hi) {
-    const int a = node_axis(partial, blockIdx.y, np, m, blockIdx.x, c_lo, c_hi);
+tree_axis_kernel(LevelSums sums, int32_t *__restrict__ axis, int64_t m, int64_t n_nodes, int64_t n_real, int c_lo, int c_hi) {
+    const int a = node_axis<1024>(sums, blockIdx.y, m, blockIdx.x, n_nodes, n_real, false, c_lo, c_hi);
     if (threadIdx.x == 0) axis[(int64_t)blockIdx.y * n_nodes + blockIdx.x] = a;
 }
 
-// Code of every entry on its node's axis (nodes large enough that the whole device should fetch them).
+// Code of every entry on its node's axis, and how often each value of a code's upper eight bits occurs in every piece, for nodes
+// so large that the whole device should fetch the coordinates (a workgroup fetches a coordinate of 64 different rows at
+// about one row per clock).  axis == NULL: the workgroup picks it from the sums itself.
 template <int ELT>
-__global__ void __launch_bounds__(256)
-tree_codes_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__restrict__ codes, const int32_t *__restrict__ axis,
-                  int64_t np, int64_t n_real, int64_t m, int64_t n_nodes) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // np is a multiple of 256 here
-    const int bh = blockIdx.y;
-    const int64_t at = (int64_t)bh * np + i;
+__global__ void __launch_bounds__(1024)
+tree_codes_kernel(TreeSrc src, const uint32_t *__restrict__ order, code_t<ELT> *__restrict__ codes, uint32_t *__restrict__ hist,
+                  const int32_t *__restrict__ axis, LevelSums sums, int64_t np, int64_t n_real, int64_t m, int64_t n_nodes, int c_lo, int c_hi) {
+    __shared__ uint32_t s_hist[256];
+    const int t = threadIdx.x, bh = blockIdx.y;
+    const int64_t i = (int64_t)blockIdx.x * PIECE + t, at = (int64_t)bh * np + i;
+    const int64_t node = i / m;   // the same in every thread
+    if (t < 256) s_hist[t] = 0;
     const int64_t pos = order ? (int64_t)order[at] : i;
-    codes[at] = pos < n_real ? coord_code<ELT>(src.row(bh, pos), axis[(int64_t)bh * n_nodes + i / m]) : PAD_CODE<ELT>;
+    const int ax = axis ? axis[(int64_t)bh * n_nodes + node]
+                        : node_axis<1024>(sums, bh, m, node, n_nodes, n_real, (int64_t)blockIdx.x * PIECE == node * m, c_lo, c_hi);
+    const uint32_t c = pos < n_real ? coord_code<ELT>(src.row(bh, pos), ax) : PAD_CODE<ELT>;
+    codes[at] = (code_t<ELT>)c;
+    if (axis) return;   // uniform
+    atomicAdd(&s_hist[c >> (ELT * 8 - 8)], 1u);   // (cleared before the barriers of node_axis)
+    __syncthreads();
+    if (t < 256) hist[((int64_t)bh * (np / PIECE) + blockIdx.x) * 256 + t] = s_hist[t];
 }
 
-// Splits a node of m entries (a multiple of 2048) at its median: one workgroup per node, wave w takes the entries
-// [w m/16, (w+1) m/16).  The code of the m/2-th smallest entry is found digit by digit (11 bits at a time: the leading
-// digit of a bf16 code holds sign, exponent and two bits of the fraction, enough that the counters of one LDS pass are not
-// all the same), then entries below it, and as many entries equal to it as the half still needs, in order, go left.
-// STEPS: entries per thread that are held in registers with their codes (m <= 1024 STEPS); 0: any m, both re-read per pass.
-// GATHER: the workgroup picks the axis from the partial statistics and fetches the codes from the rows itself (small nodes:
-// there are many workgroups); else the codes are given.
-// Bound by latency: the fetch of the entries, a pass over LDS counters per digit, the stores: 18 us for 8 nodes of 32768
-// entries (22 with the codes read again in every pass), 20, 13 and 11 us for 32 to 128 nodes down to 2048 entries (with the
-// axis in a launch of its own 27, 19 and 16).
-template <int ELT, int STEPS, bool GATHER>
-__global__ void __launch_bounds__(1024)
-tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__restrict__ out, const uint32_t *__restrict__ codes,
-                  const double *__restrict__ partial, int64_t np, int64_t n_real, int64_t m, int c_lo, int c_hi) {
-    static_assert(!GATHER || STEPS > 0, "fetched codes are held in registers");
-    __shared__ uint32_t s_hist[2048];
-    __shared__ int s_tot[16], s_eq[16];
+// One digit of the search for the code of a node's median: s_hist holds how often each of 2048 values of the digit occurs among the
+// entries looked at, `rank` (from 1) counts among them.  Returns the digit and leaves the rank among the entries that have it.
+template <int NT>
+__device__ __forceinline__ uint32_t pick_digit(uint32_t (&s_hist)[2048], int lane, int wave, int &rank) {
+    constexpr int BPT = 2048 / NT;   // values per thread
+    __shared__ int s_tot[NT / 64], s_rank;
     __shared__ uint32_t s_digit;
-    __shared__ int s_rank;
+    const int t = threadIdx.x;
+    int h[BPT], sum = 0;
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) {
+        h[j] = (int)s_hist[BPT * t + j];
+        sum += h[j];
+    }
+    const int incl = lvr_wave_inclusive_sum(sum);
+    if (lane == 63) s_tot[wave] = incl;
+    __syncthreads();
+    int before = incl - sum;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) before += w < wave ? s_tot[w] : 0;
+    if (before < rank && rank <= before + sum) {   // exactly one thread
+#pragma unroll
+        for (int j = 0; j < BPT; ++j) {
+            if (before < rank && rank <= before + h[j]) {
+                s_digit = (uint32_t)(BPT * t + j);
+                s_rank = rank - before;
+            }
+            before += h[j];
+        }
+    }
+    __syncthreads();
+    rank = s_rank;
+    return s_digit;
+}
+
+// Splits nodes of m entries (NT to 32768) at their median, a workgroup of NT threads per NT entries.  Every workgroup of a node
+// finds the node's median code for itself, from all the node's codes (digit by digit, in registers and LDS counters),
+// and then sends its own entries left or right: entries below the median, and as many equal to it as the half still needs, in
+// order, go left.  The rows that go left are added up on the way (part_out, unless NULL): a level's statistics take half of the rows, and
+// no launch of their own.
+// GATHER: the codes are fetched from the rows of the whole node by each of its workgroups, and the axis is picked from the sums
+// (nodes of up to STEPS workgroups, where that costs less than a launch); else codes and the counts of their upper eight bits
+// come from tree_codes_kernel.
+// Bound by a chain of short stretches (8 x 32768 keys, nodes of 16384, from timestamps): codes 0.9 us, two digits 2.5 and 2.1, the partition 1.9,
+// the rows 5 (2.8 of them fp64 instructions), the sums' way out 3; a workgroup per 1024 entries, so one round of the device.
+template <int ELT, int STEPS, bool GATHER, int NT>
+__global__ void __launch_bounds__(NT)
+tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__restrict__ out, const code_t<ELT> *__restrict__ codes,
+                  const uint32_t *__restrict__ hist, LevelSums sums, double *__restrict__ part_out, int64_t np, int64_t n_real, int64_t m,
+                  int64_t n_nodes, int c_lo, int c_hi) {
+    constexpr int NW = NT / 64, BITS = ELT * 8;
+    __shared__ uint32_t s_hist[2048];
+    __shared__ int s_lt[NW], s_eq[NW], s_plt[NW], s_peq[NW];   // entries below / equal to the median: the workgroup's own, those of the workgroups before it
+    __shared__ uint32_t s_left[NT];
+    __shared__ double s_part[NW][256];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int bh = blockIdx.y;
+    const int parts = (int)(m / NT);   // workgroups of a node
+    const int node = (int)blockIdx.x / parts, mine = (int)blockIdx.x % parts;
+    const int64_t node0 = (int64_t)node * m, at0 = (int64_t)bh * np + node0;
+    auto pos_of = [&](int i) { return order ? order[at0 + i] : (uint32_t)(node0 + i); };
+    uint32_t code[STEPS], entry = 0, own = 0;   // code[k]: entry k NT + t of the node
+    if constexpr (GATHER) {
+        uint32_t e[STEPS];
+#pragma unroll
+        for (int k = 0; k < STEPS; ++k)
+            if (k < parts) e[k] = pos_of(k * NT + t);   // uniform conditions throughout
+        const int ax = node_axis<NT>(sums, bh, m, node, n_nodes, n_real, mine == 0, c_lo, c_hi);
+#pragma unroll
+        for (int k = 0; k < STEPS; ++k)
+            if (k < parts) {
+                code[k] = e[k] < n_real ? coord_code<ELT>(src.row(bh, e[k]), ax) : PAD_CODE<ELT>;
+                if (k == mine) entry = e[k];
+            }
+    } else {
+#pragma unroll
+        for (int k = 0; k < STEPS; ++k)
+            if (k < parts) code[k] = codes[at0 + k * NT + t];
+        entry = pos_of(mine * NT + t);
+    }
+    int rank = (int)(m / 2);   // the entry looked for is the rank-th smallest (from 1) of those that share `known`
+    uint32_t known = 0, known_mask = 0;
+    int top = BITS;   // bits not known yet
+    if constexpr (!GATHER) {
+        static_assert(GATHER || NT == 1024, "four slices of 256 counts");
+        const uint32_t *h = hist + ((int64_t)bh * (np / PIECE) + (int64_t)node * parts) * 256;
+        uint32_t n = 0;
+#pragma unroll 8
+        for (int p = t >> 8; p < parts; p += 4) n += h[p * 256 + (t & 255)];
+        s_hist[t] = 0;
+        s_hist[t + 1024] = 0;
+        __syncthreads();
+        if (n) atomicAdd(&s_hist[t & 255], n);
+        __syncthreads();
+        top -= 8;
+        known = pick_digit<NT>(s_hist, lane, wave, rank) << top;
+        known_mask = 0xffu << top;
+    }
+    while (top > 0) {
+        const int width = top > 11 ? 11 : top, shift = top - width;
+        for (int i = t; i < 2048; i += NT) s_hist[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < STEPS; ++k)
+            if (k < parts && (code[k] & known_mask) == known) atomicAdd(&s_hist[(code[k] >> shift) & ((1u << width) - 1u)], 1u);
+        __syncthreads();
+        known |= pick_digit<NT>(s_hist, lane, wave, rank) << shift;
+        known_mask |= ((1u << width) - 1u) << shift;
+        top = shift;
+    }
+    // `known` is the median code, `rank` (>= 1) the number of entries equal to it that go left
+    int plt = 0, peq = 0;
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k)
+        if (k < parts) {
+            if (k < mine) {
+                plt += (int)__popcll(__ballot(code[k] < known));
+                peq += (int)__popcll(__ballot(code[k] == known));
+            } else if (k == mine) own = code[k];
+        }
+    const uint64_t lts = __ballot(own < known), eqs = __ballot(own == known);
+    if (lane == 0) {
+        s_plt[wave] = plt;
+        s_peq[wave] = peq;
+        s_lt[wave] = (int)__popcll(lts);
+        s_eq[wave] = (int)__popcll(eqs);
+    }
+    __syncthreads();
+    int lt0 = 0, eq0 = 0, lt_w = 0, eq_w = 0, lt_all = 0, eq_all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        lt0 += s_plt[w];
+        eq0 += s_peq[w];
+        lt_w += w < wave ? s_lt[w] : 0;
+        eq_w += w < wave ? s_eq[w] : 0;
+        lt_all += s_lt[w];
+        eq_all += s_eq[w];
+    }
+    auto lefts_before = [&](int lt, int eq) { return lt + (eq < rank ? eq : rank); };
+    const int left0 = lefts_before(lt0, eq0);                                  // entries of the node before this workgroup's that go left
+    const int n_left = lefts_before(lt0 + lt_all, eq0 + eq_all) - left0;       // of this workgroup's
+    const uint64_t below = (1ull << lane) - 1ull;
+    const int eq_before = eq0 + eq_w + (int)__popcll(eqs & below);
+    const int lt = lefts_before(lt0 + lt_w + (int)__popcll(lts & below), eq_before);   // entries before this one that go left
+    const bool left = own < known || (own == known && eq_before < rank);
+    out[at0 + (left ? lt : (int)(m / 2) + mine * NT + t - lt)] = entry;
+    if (!part_out) return;   // uniform
+    if (left) s_left[lt - left0] = entry;
+    __syncthreads();
+    const int share = ((n_left + NW - 1) / NW + 15) & ~15;   // rows of a wave, at most 64
+    const int idx = wave * share + lane;
+    const int mypos = (lane < share && idx < n_left) ? (int)s_left[idx] : 0x7fffffff;
+    const uint64_t real = __ballot(mypos < n_real);
+    double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
+    if (real) sum_rows64<ELT>(src, bh, lane, mypos, real, tree_shift<ELT>(src, bh, lane), s0, s1, q0, q1);   // uniform
+    store_partial<NW>(s_part, lane, wave, NW, s0, s1, q0, q1, part_out + ((int64_t)bh * sums.n_pieces + blockIdx.x) * 256);
+}
+
+// Splits a node of more than 32768 entries: one workgroup per node, wave w takes the entries [w m/16, (w+1) m/16), eight codes per
+// thread in flight, the codes read again for every digit.
+template <int ELT>
+__global__ void __launch_bounds__(1024)
+tree_split_large_kernel(const uint32_t *__restrict__ order, uint32_t *__restrict__ out, const code_t<ELT> *__restrict__ codes, int64_t np,
+                        int64_t m) {
+    __shared__ uint32_t s_hist[2048];
+    __shared__ int s_lt[16], s_eq[16];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int bh = blockIdx.y;
     const int64_t node0 = (int64_t)blockIdx.x * m, at0 = (int64_t)bh * np + node0;
     const int steps = (int)(m / 1024), first = wave * steps * 64 + lane;   // this thread's entries: first + 64 k, k < steps
     auto pos_of = [&](int i) { return order ? order[at0 + i] : (uint32_t)(node0 + i); };
-    uint32_t code[STEPS ? STEPS : 1], entry[STEPS ? STEPS : 1];
-    if constexpr (STEPS > 0) {
-#pragma unroll
-        for (int k = 0; k < STEPS; ++k)
-            if (k < steps) entry[k] = pos_of(first + 64 * k);   // uniform conditions throughout
-        if constexpr (GATHER) {
-            const int ax = node_axis(partial, bh, np, m, blockIdx.x, c_lo, c_hi);
-#pragma unroll
-            for (int k = 0; k < STEPS; ++k)
-                if (k < steps) code[k] = entry[k] < n_real ? coord_code<ELT>(src.row(bh, entry[k]), ax) : PAD_CODE<ELT>;
-        } else {
-#pragma unroll
-            for (int k = 0; k < STEPS; ++k)
-                if (k < steps) code[k] = codes[at0 + first + 64 * k];
-        }
-    }
     // f(i, code, entry) for this thread's entries; the conditions are the same in every lane, so f may use ballots
     auto for_codes = [&](bool entries, auto f) {
-        if constexpr (STEPS > 0) {
+        for (int b = 0; b < steps; b += 8) {   // eight at a time
+            uint32_t c[8], p[8];
 #pragma unroll
-            for (int k = 0; k < STEPS; ++k)
-                if (k < steps) f(first + 64 * k, code[k], entry[k]);
-        } else {
-            for (int b = 0; b < steps; b += 8) {   // eight at a time
-                uint32_t c[8], p[8];
+            for (int u = 0; u < 8; ++u)
+                if (b + u < steps) {
+                    c[u] = codes[at0 + first + 64 * (b + u)];
+                    p[u] = entries ? pos_of(first + 64 * (b + u)) : 0u;
+                }
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (b + u < steps) {
-                        c[u] = codes[at0 + first + 64 * (b + u)];
-                        p[u] = entries ? pos_of(first + 64 * (b + u)) : 0u;
-                    }
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (b + u < steps) f(first + 64 * (b + u), c[u], p[u]);
-            }
+            for (int u = 0; u < 8; ++u)
+                if (b + u < steps) f(first + 64 * (b + u), c[u], p[u]);
         }
     };
-    int rank = (int)(m / 2);   // the entry looked for is the rank-th smallest (from 1) of those that share `known`
+    int rank = (int)(m / 2);
     uint32_t known = 0, known_mask = 0;
     constexpr int BITS = ELT * 8;
 #pragma unroll
@@ -316,36 +531,22 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
             if ((c & known_mask) == known) atomicAdd(&s_hist[(c >> shift) & ((1u << width) - 1u)], 1u);
         });
         __syncthreads();
-        const int h0 = (int)s_hist[2 * t], h1 = (int)s_hist[2 * t + 1];
-        const int incl = lvr_wave_inclusive_sum(h0 + h1);
-        if (lane == 63) s_tot[wave] = incl;
-        __syncthreads();
-        int before = incl - (h0 + h1);
-        for (int w = 0; w < wave; ++w) before += s_tot[w];
-        if (before < rank && rank <= before + h0 + h1) {   // exactly one thread
-            const bool second = rank > before + h0;
-            s_digit = 2 * t + (second ? 1 : 0);
-            s_rank = rank - before - (second ? h0 : 0);
-        }
-        __syncthreads();
-        rank = s_rank;
-        known |= s_digit << shift;
+        known |= pick_digit<1024>(s_hist, lane, wave, rank) << shift;
         known_mask |= ((1u << width) - 1u) << shift;
     }
-    // `known` is the median code, `rank` (>= 1) the number of entries equal to it that go left
     int n_lt = 0, n_eq = 0;
     for_codes(false, [&](int, uint32_t c, uint32_t) {
         n_lt += (int)__popcll(__ballot(c < known));
         n_eq += (int)__popcll(__ballot(c == known));
     });
     if (lane == 0) {
-        s_tot[wave] = n_lt;
+        s_lt[wave] = n_lt;
         s_eq[wave] = n_eq;
     }
     __syncthreads();
     int eq_before = 0, left_at = 0;
     for (int w = 0; w < wave; ++w) {
-        left_at += s_tot[w];
+        left_at += s_lt[w];
         eq_before += s_eq[w];
     }
     left_at += eq_before < rank ? eq_before : rank;
@@ -364,11 +565,11 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
     });
 }
 
-// Rows into the arena in tree order, and the two position maps.  pos_base is added to the
-// positions (a chunk's positions are relative to its first row).
+// Rows into the arena in tree order, and with the key rows the two position maps (row0 is added to the
+// positions: a chunk's positions are relative to its first row).  blockIdx.z = 0: keys, 1: values; z0 is added to it.
 __global__ void tree_gather_kernel(TreeSrc ksrc, TreeSrc vsrc, const uint64_t *__restrict__ keys, char *Kdst,
                                    char *Vdst, int32_t *slot_pos, int32_t *pos_slot, int64_t np, int64_t n_real,
-                                   int pos_bits, int64_t cap_rows, int64_t row0, int row_bytes) {
+                                   int pos_bits, int64_t cap_rows, int64_t row0, int row_bytes, int z0) {
     const int chunks = row_bytes / 16;
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_real * chunks) return;
@@ -376,151 +577,340 @@ __global__ void tree_gather_kernel(TreeSrc ksrc, TreeSrc vsrc, const uint64_t *_
     const int64_t slot = i / chunks;
     const int ch = (int)(i % chunks);
     const int64_t pos = key_pos(keys[(int64_t)bh * np + slot], pos_bits);
-    const TreeSrc &s = blockIdx.z == 0 ? ksrc : vsrc;
-    char *dst = blockIdx.z == 0 ? Kdst : Vdst;
+    const bool keys_too = blockIdx.z + z0 == 0;
+    const TreeSrc &s = keys_too ? ksrc : vsrc;
+    char *dst = keys_too ? Kdst : Vdst;
     reinterpret_cast<uint4 *>(dst + ((int64_t)bh * cap_rows + row0 + slot) * row_bytes)[ch] =
         reinterpret_cast<const uint4 *>(s.row(bh, pos))[ch];
-    if (blockIdx.z == 0 && ch == 0) {
+    if (keys_too && ch == 0) {
         slot_pos[(int64_t)bh * cap_rows + row0 + slot] = (int32_t)(row0 + pos);
         pos_slot[(int64_t)bh * cap_rows + row0 + pos] = (int32_t)(row0 + slot);
     }
 }
 
-// All the remaining levels of a node of at most TREE_WG_MAX padded entries in ONE launch, an entry per thread.  Either the
-// whole tree of a small input (a buffer chunk of B keys: order == NULL, one workgroup per (sequence, KV head)), or
-// every node of the level at which the kernels above have brought the nodes down to TREE_WG_MAX entries (the node's
-// entries are np consecutive ones of `order`, in ascending position order).  Per level: statistics (a wave per 64
-// entries, sixteen rows in flight), the code on the axis, and a bitonic sort of [ code | index of the entry in the node's
-// initial order ] inside every node, in registers where the exchange stays inside a wave.
-// Bound by the fp64 adds of the statistics and the row reads from L2, eight passes over 256 KB per workgroup at 1024
-// entries and groups of four.
+// Lanes whose number has the bit J.
+template <int J>
+constexpr uint64_t LANES = J == 1 ? 0xaaaaaaaaaaaaaaaaull : J == 2 ? 0xccccccccccccccccull : J == 4 ? 0xf0f0f0f0f0f0f0f0ull
+                         : J == 8 ? 0xff00ff00ff00ff00ull : J == 16 ? 0xffff0000ffff0000ull : 0xffffffff00000000ull;
+
+// One compare-exchange of a bitonic sort with the lane J away; the lanes of `flip` stand in a descending run.  Data-parallel moves up
+// to J = 8, row and half swaps beyond (these put the two values of a pair side by side), so no step makes a trip through LDS.
+template <int J>
+__device__ __forceinline__ uint32_t exchanged(uint32_t key, uint64_t flip) {
+    auto dpp = [](uint32_t x, auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xf, 0xf, true); };
+    uint32_t a = key, b;
+    if constexpr (J == 1) b = dpp(key, std::integral_constant<int, 0xB1>{});        // quad_perm [1,0,3,2]
+    else if constexpr (J == 2) b = dpp(key, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+    else if constexpr (J == 4)                                                      // 7 - i within 8, then 3 - i within 4
+        b = dpp(dpp(key, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+    else if constexpr (J == 8) b = dpp(key, std::integral_constant<int, 0x128>{});  // row_ror:8
+    else if constexpr (J == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(key, key, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(key, key, false, false);
+        a = r[0];
+        b = r[1];
+    }
+    const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
+    return __builtin_amdgcn_inverse_ballot_w64(~LANES<J> ^ flip) ? lo : hi;
+}
+template <int J>
+__device__ __forceinline__ uint64_t exchanged(uint64_t key, uint64_t flip) {
+    auto word = [](uint32_t v, uint32_t &a, uint32_t &b) {   // the pair's two values, in either order but the same one for both words
+        auto dpp = [](uint32_t x, auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xf, 0xf, true); };
+        a = v;
+        if constexpr (J == 1) b = dpp(v, std::integral_constant<int, 0xB1>{});
+        else if constexpr (J == 2) b = dpp(v, std::integral_constant<int, 0x4E>{});
+        else if constexpr (J == 4) b = dpp(dpp(v, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+        else if constexpr (J == 8) b = dpp(v, std::integral_constant<int, 0x128>{});
+        else if constexpr (J == 16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+            a = r[0];
+            b = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+            a = r[0];
+            b = r[1];
+        }
+    };
+    uint32_t a0, a1, b0, b1;
+    word((uint32_t)key, a0, b0);
+    word((uint32_t)(key >> 32), a1, b1);
+    const uint64_t a = ((uint64_t)a1 << 32) | a0, b = ((uint64_t)b1 << 32) | b0;
+    const bool less = a < b;
+    return (__builtin_amdgcn_inverse_ballot_w64(~LANES<J> ^ flip) == less) ? a : b;
+}
+
+// The merge of runs of K entries as far as it stays inside a wave.
+template <int K, typename KEY>
+__device__ __forceinline__ KEY merged(KEY key, uint64_t flip) {
+    if constexpr (K >= 64) key = exchanged<32>(key, flip);
+    if constexpr (K >= 32) key = exchanged<16>(key, flip);
+    if constexpr (K >= 16) key = exchanged<8>(key, flip);
+    if constexpr (K >= 8) key = exchanged<4>(key, flip);
+    if constexpr (K >= 4) key = exchanged<2>(key, flip);
+    return exchanged<1>(key, flip);
+}
+
+// The merges of up to 32 entries of a sort of every aligned run of m (a merge of m entries ends in ascending order, the ones
+// before it alternate).  The upper half of a wave may repeat the lower.
+template <typename KEY>
+__device__ __forceinline__ KEY sort_in_wave(KEY key, int m) {
+    key = merged<2>(key, m == 2 ? 0ull : LANES<2>);
+    if (m > 2) key = merged<4>(key, m == 4 ? 0ull : LANES<4>);   // uniform
+    if (m > 4) key = merged<8>(key, m == 8 ? 0ull : LANES<8>);
+    if (m > 8) key = merged<16>(key, m == 16 ? 0ull : LANES<16>);
+    if (m > 16) key = merged<32>(key, m == 32 ? 0ull : LANES<32>);
+    return key;
+}
+
+// Where a finished node's rows go in the same launch (K == NULL: only the order is wanted).
+struct TreeRows {
+    char *K;
+    int32_t *slot_pos, *pos_slot;
+    int64_t cap_rows, row0;
+};
+
+// All the remaining levels of a node of np <= SMALL_NODE padded entries in one launch, a workgroup per node.  Either the whole
+// tree of a small input (a buffer chunk of B keys: order == NULL, one workgroup per (sequence, KV head)), or every node of
+// the level at which the kernels above have brought the nodes down to that size (the node's entries are np consecutive ones of
+// `order`, in ascending position order).
+// The node's rows are fetched once, 128 KB that stay in LDS: all levels read them there, and the finished node's key rows go to the
+// arena from there.  A wave per 32 entries.  Per level a wave adds up 16 rows: nodes of 32 entries and more share the rows of the left
+// child out among the waves of the parent, the sums meet in LDS, and the right child's sums are the parent's less the left child's (a wave holds
+// its own node's in registers); below that a node belongs to one wave and no barrier is left.  Nodes of 64 and more are sorted by
+// [ code | index of the entry in the node's initial order ], an entry per thread, exchanged through LDS only between waves.
+// Bound by instructions: 8 per row and two channels (conversion, add, multiply-add in fp64), then the searches for the largest
+// variance and the exchanges.  A round of one workgroup per compute unit takes 36 us (8 x 32768 keys are two): 7.4 to fetch the rows, 3.2 for the first
+// sums, 3.3 to 4.3 per level of 512 to 64 entries, 8 for the levels of one wave, 2 for the rows' way out; 77 us in all.  (Nodes of 1024 entries
+// whose rows were fetched from memory at every level: 160 us, and 19 more to gather the key rows.)
 template <int ELT>
 __global__ void __launch_bounds__(1024)
 tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__restrict__ keys_out, int64_t np_total,
-                  int np, int64_t n_real, int levels, int c_lo, int c_hi) {
+                  int np, int64_t n_real, int levels, int c_lo, int c_hi, TreeRows dst) {
     typedef typename std::conditional<ELT == 2, uint32_t, uint64_t>::type key_t;
-    constexpr int ENT_BITS = 10;   // TREE_WG_MAX entries
-    __shared__ key_t s_key[TREE_WG_MAX];
-    __shared__ int32_t s_pos[TREE_WG_MAX];    // position of an entry
-    __shared__ uint16_t s_ent[TREE_WG_MAX];   // the current order: entry in every place
-    __shared__ int32_t s_axis[TREE_WG_MAX / 2];
-    __shared__ double s_part[16][256];   // per wave: 128 sums, 128 sums of squares
-    __shared__ int s_cnt[16];
-    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    constexpr int NODE = SMALL_NODE<ELT>, ROW = LVR_D * ELT, PIECES = ROW / 16;
+    constexpr int ENT_BITS = ELT == 2 ? 9 : 8;
+    static_assert((1 << ENT_BITS) == NODE, "an entry's index fills its bits of a key");
+    __shared__ __align__(16) char s_rows[NODE * ROW];
+    __shared__ double2 s_part[NODE / 64][2][64];   // sums of a pair of waves: lane's two channels, their squares
+    __shared__ key_t s_key[2][NODE];
+    __shared__ int32_t s_pos[NODE];      // position of an entry
+    __shared__ uint16_t s_ent[NODE];     // the current order: entry in every place
+    __shared__ int32_t s_axis[NODE / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), waves = (int)(blockDim.x >> 6);
     const int bh = blockIdx.y;
-    const int64_t base = (int64_t)bh * np_total + (int64_t)blockIdx.x * np;   // this node's entries
-    const bool mine = t < np;
-    if (mine) {
-        s_pos[t] = order ? (int32_t)order[base + t] : t;
-        s_ent[t] = (uint16_t)t;
-    }
-    __syncthreads();
+    const int64_t node0 = (int64_t)blockIdx.x * np, base = (int64_t)bh * np_total + node0;
+    const int nr = n_real - node0 < np ? (int)(n_real - node0) : np;   // real entries: a prefix of the node's
+    if (nr <= 0) return;   // uniform: all padding, which nothing reads
+    auto pos_of = [&](int e) { return order ? (int)order[base + e] : (int)(node0 + e); };
     const char *rows = src.row(bh, 0);
     const int64_t row_bytes = src.st * ELT;
-    for (int L = 0; L < levels; ++L) {
-        const int m = np >> L;
-        // 1. split axis of every node: sums relative to the node's first key (padding sorts last: it is real unless the
-        // whole node is padding)
-        const int mypos = mine ? s_pos[s_ent[t]] : 0x7fffffff;
-        const uint64_t real = __ballot(mine && mypos < n_real);
-        if (m >= 64) {
-            double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-            if (real) {   // uniform
-                const int ppos = s_pos[s_ent[wave * 64 / m * m]];
-                float p0, p1;
-                lane_pair<ELT>(rows + ppos * row_bytes, lane, p0, p1);
-                sum_rows64<ELT>(src, bh, lane, mypos, real, ppos, p0, p1, s0, s1, q0, q1);
+    const int held = np < 32 ? 32 : np;   // rows a wave may look at: those past nr add nothing to any sum
+    {
+        const int c = t % PIECES, step = (int)blockDim.x / PIECES;
+        for (int e0 = t / PIECES; e0 < held; e0 += 8 * step) {
+            uint4 w[8];
+            int p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int e = e0 + u * step;
+                p[u] = pos_of(e < nr ? e : 0);
             }
-            double *o = s_part[wave];
-            o[2 * lane] = s0; o[2 * lane + 1] = s1;
-            o[128 + 2 * lane] = q0; o[128 + 2 * lane + 1] = q1;
-            if (lane == 0) s_cnt[wave] = __popcll(real);
-            __syncthreads();
-            if (wave < (1 << L)) {   // wave w adds the runs of node w in order
-                const int runs = m / 64;
-                s0 = s1 = q0 = q1 = 0.;
-                int cnt = 0;
-                for (int k = wave * runs; k < (wave + 1) * runs; ++k) {
-                    s0 += s_part[k][2 * lane]; s1 += s_part[k][2 * lane + 1];
-                    q0 += s_part[k][128 + 2 * lane]; q1 += s_part[k][128 + 2 * lane + 1];
-                    cnt += s_cnt[k];
-                }
-                const double inv = cnt > 0 ? 1.0 / (double)cnt : 0.;
-                const int arg = wave_argmax((q0 - s0 * s0 * inv) * inv, (q1 - s1 * s1 * inv) * inv, lane, c_lo, c_hi);
-                if (lane == 0) s_axis[wave] = arg;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = reinterpret_cast<const uint4 *>(rows + (int64_t)p[u] * row_bytes)[c];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int e = e0 + u * step;
+                // padding: zeros for bf16, the first row (the shift of the sums) for fp32
+                if (e < held) reinterpret_cast<uint4 *>(s_rows + e * ROW)[c] = (e < nr || ELT == 4) ? w[u] : make_uint4(0, 0, 0, 0);
             }
-        } else if (real) {   // several nodes per wave, one after the other; sixteen rows in flight whatever the node's size
-            auto nodes = [&](auto rows_c) {   // rows_c = entries of a node within a batch of sixteen
-                constexpr int RW = decltype(rows_c)::value;
-                double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-                float p0 = 0.f, p1 = 0.f;
-                int cnt = 0;
-                const int some = __builtin_amdgcn_readlane(mypos, 0);   // real: the wave's first entry
-                for (int j0 = 0; j0 < 64 && wave * 64 + j0 < np; j0 += 16) {
-                    float x0[16], x1[16];
+        }
+    }
+    if (t < held) {
+        s_ent[t] = (uint16_t)t;
+        s_pos[t] = t < np ? pos_of(t) : 0;
+    }
+    __syncthreads();
+    Shift shift = {0.0, 0.0};
+    if constexpr (ELT == 4) {
+        float x0, x1;
+        lane_pair<ELT>(s_rows, lane, x0, x1);
+        shift.p0 = (double)x0;
+        shift.p1 = (double)x1;
+    }
+    double s0, s1, q0, q1;   // sums of this wave's node
+    // sums of N rows: the entries that lanes `first` .. `first` + N - 1 hold in `ent`
+    auto sum = [&](auto n_c, int ent, int first, double &a0, double &a1, double &b0, double &b1) {
+        constexpr int N = decltype(n_c)::value;
+        float x0[N], x1[N];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) {
-                        const int pos = __builtin_amdgcn_readlane(mypos, j0 + u);
-                        const bool in = (real >> (j0 + u)) & 1ull;
-                        lane_pair<ELT>(rows + (int64_t)(in ? pos : some) * row_bytes, lane, x0[u], x1[u]);
-                    }
-#pragma unroll
-                    for (int k = 0; k < 16 / RW; ++k) {
-                        const int at = j0 + k * RW;   // first entry of this part of a node
-                        if ((at & (m - 1)) == 0) {
-                            p0 = x0[k * RW]; p1 = x1[k * RW];
-                            s0 = s1 = q0 = q1 = 0.;
-                            cnt = 0;
-                        }
-#pragma unroll
-                        for (int u = 0; u < RW; ++u) {
-                            const bool in = (real >> (at + u)) & 1ull;
-                            const double d0 = in ? (double)x0[k * RW + u] - (double)p0 : 0.;
-                            const double d1 = in ? (double)x1[k * RW + u] - (double)p1 : 0.;
-                            s0 += d0; s1 += d1; q0 += d0 * d0; q1 += d1 * d1;
-                            cnt += in ? 1 : 0;
-                        }
-                        if (((at + RW) & (m - 1)) == 0 && wave * 64 + at < np) {   // the node's last part
-                            const double inv = cnt > 0 ? 1.0 / (double)cnt : 0.;
-                            const int arg = wave_argmax((q0 - s0 * s0 * inv) * inv, (q1 - s1 * s1 * inv) * inv, lane, c_lo, c_hi);
-                            if (lane == 0) s_axis[(wave * 64 + at) / m] = arg;
-                        }
-                    }
-                }
-            };
-            if (m == 2) nodes(std::integral_constant<int, 2>{});
-            else if (m == 4) nodes(std::integral_constant<int, 4>{});
-            else if (m == 8) nodes(std::integral_constant<int, 8>{});
-            else nodes(std::integral_constant<int, 16>{});
+        for (int u = 0; u < N; ++u) lane_pair<ELT>(s_rows + __builtin_amdgcn_readlane(ent, first + u) * ROW, lane, x0[u], x1[u]);
+        a0 = a1 = b0 = b1 = 0.;
+        add_rows<ELT>(x0, x1, shift, a0, a1, b0, b1);
+    };
+    typedef std::integral_constant<int, 16> N16;
+    typedef std::integral_constant<int, 8> N8;
+    typedef std::integral_constant<int, 4> N4;
+    typedef std::integral_constant<int, 2> N2;
+    // the sums of `group` consecutive waves (a power of two, at least 2), the same in each of them
+    auto add_waves = [&](int group, double &a0, double &a1, double &b0, double &b1) {
+        double2(&pair)[2][64] = s_part[wave >> 1];
+        if (wave & 1) {
+            pair[0][lane] = make_double2(a0, a1);
+            pair[1][lane] = make_double2(b0, b1);
         }
         __syncthreads();
-        // 2. this thread's entry: [ code on its node's axis | entry ]
+        if (!(wave & 1)) {
+            const double2 a = pair[0][lane], b = pair[1][lane];
+            pair[0][lane] = make_double2(a0 + a.x, a1 + a.y);
+            pair[1][lane] = make_double2(b0 + b.x, b1 + b.y);
+        }
+        __syncthreads();
+        const int first = (wave & ~(group - 1)) >> 1;
+        a0 = a1 = b0 = b1 = 0.;
+        for (int i = 0; i < group >> 1; ++i) {
+            const double2 a = s_part[first + i][0][lane], b = s_part[first + i][1][lane];
+            a0 += a.x; a1 += a.y; b0 += b.x; b1 += b.y;
+        }
+    };
+    auto real_of = [&](int first, int m) { return nr <= first ? 0. : (nr - first < m ? (double)(nr - first) : (double)m); };
+    auto axis_of = [&](double a0, double a1, double b0, double b1, double n) {
+        return wave_argmax(spread(a0, b0, n), spread(a1, b1, n), lane, c_lo, c_hi);
+    };
+    auto code_of = [&](int e, int axis) { return e < nr ? coord_code<ELT>(s_rows + e * ROW, axis) : PAD_CODE<ELT>; };
+    const int groups_of = np >> levels;   // entries of a finished node
+    int m = np;
+    int ent = s_ent[wave * 32 + (lane & 31)];
+    {
+        double a0, a1, b0, b1;
+        sum(N16{}, ent, 0, s0, s1, q0, q1);
+        sum(N16{}, ent, 16, a0, a1, b0, b1);
+        s0 += a0; s1 += a1; q0 += b0; q1 += b1;
+    }
+    if (waves > 1) add_waves(waves, s0, s1, q0, q1);
+    for (; m >= 64 && m > groups_of; m >>= 1) {   // uniform
+        if (m < np) {   // the sums of this wave's node out of its parent's
+            const int group = m / 16, parent = wave & ~(group - 1);   // the parent's waves
+            const int e = s_ent[parent * 32 + (wave - parent) * 16 + (lane & 15)];
+            double a0, a1, b0, b1;
+            sum(N16{}, e, 0, a0, a1, b0, b1);
+            add_waves(group, a0, a1, b0, b1);
+            const bool right = (wave & (group >> 1)) != 0;
+            s0 = right ? s0 - a0 : a0; s1 = right ? s1 - a1 : a1;
+            q0 = right ? q0 - b0 : b0; q1 = right ? q1 - b1 : b1;
+        }
+        const int ax = axis_of(s0, s1, q0, q1, real_of(wave * 32 & ~(m - 1), m));
+        if (lane == 0 && (wave & (m / 32 - 1)) == 0) s_axis[wave / (m / 32)] = ax;
+        __syncthreads();
+        const bool sorts = wave * 64 < np;   // an entry per thread: the waves that hold one
         key_t key = ~(key_t)0;
-        if (mine) {
-            const uint32_t code = mypos < n_real ? coord_code<ELT>(rows + (int64_t)mypos * row_bytes, s_axis[t / m]) : PAD_CODE<ELT>;
-            key = ((key_t)code << ENT_BITS) | (key_t)s_ent[t];
+        if (sorts) {
+            const int e = s_ent[t];
+            key = ((key_t)code_of(e, s_axis[t / m]) << ENT_BITS) | (key_t)e;
         }
-        // 3. ascending bitonic sort inside every node (nodes are aligned runs of m = 2^x entries)
-        for (int k = 2; k <= m; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                key_t other;
-                if (j >= 64) {
-                    __syncthreads();
-                    s_key[t] = key;
-                    __syncthreads();
-                    other = s_key[t ^ j];
-                } else {
-                    other = __shfl_xor(key, j, 64);
+        int buf = 0;
+        if (sorts) key = sort_in_wave(key, m);
+        for (int k = 64; k <= m; k <<= 1) {
+            const bool up = k == m || (wave * 64 & k) == 0;   // the same in the whole wave
+            for (int j = k >> 1; j >= 64; j >>= 1) {
+                if (sorts) s_key[buf][t] = key;
+                __syncthreads();
+                if (sorts) {
+                    const key_t other = s_key[buf][t ^ j];
+                    key = ((wave * 64 & j) == 0) == up ? (key < other ? key : other) : (key < other ? other : key);
                 }
-                const bool up = k == m || (t & k) == 0;   // the last merge of every node ascends
-                const bool low = (t & j) == 0;
-                key = (low == up) ? (key < other ? key : other) : (key < other ? other : key);
+                buf ^= 1;
             }
+            if (sorts) key = merged<64>(key, up ? 0ull : ~0ull);
         }
-        if (mine) s_ent[t] = (uint16_t)(key & (key_t)(TREE_WG_MAX - 1));
+        if (sorts) s_ent[t] = (uint16_t)(key & (key_t)(NODE - 1));
         __syncthreads();
     }
-    if (mine) keys_out[base + t] = (uint64_t)(uint32_t)s_pos[s_ent[t]];
+    if (m > groups_of) {   // uniform: nodes of 32 entries and less, each of one wave
+        const int i = lane & 31, place = wave * 32;
+        if (np > 32) {   // this wave's node of 32 out of the node of 64 it shares with its neighbour
+            const int e = s_ent[(wave & ~1) * 32 + (wave & 1) * 16 + (lane & 15)];
+            double a0, a1, b0, b1;
+            sum(N16{}, e, 0, a0, a1, b0, b1);
+            add_waves(2, a0, a1, b0, b1);
+            const bool right = (wave & 1) != 0;
+            s0 = right ? s0 - a0 : a0; s1 = right ? s1 - a1 : a1;
+            q0 = right ? q0 - b0 : b0; q1 = right ? q1 - b1 : b1;
+            ent = s_ent[place + i];
+        }
+        auto split = [&](int axis, int size) {
+            const key_t key = ((key_t)code_of(ent, axis) << ENT_BITS) | (key_t)ent;
+            ent = (int)(sort_in_wave(key, size) & (key_t)(NODE - 1));
+        };
+        if (m == 32) {
+            split(axis_of(s0, s1, q0, q1, real_of(place, 32)), 32);
+            m = 16;
+        }
+        double a[2][4];   // the nodes of 16 (where the whole tree is smaller than 32 entries the second is empty)
+        if (m > groups_of) {
+            sum(N16{}, ent, 0, a[0][0], a[0][1], a[0][2], a[0][3]);
+            a[1][0] = s0 - a[0][0]; a[1][1] = s1 - a[0][1]; a[1][2] = q0 - a[0][2]; a[1][3] = q1 - a[0][3];
+            if (m == 16) {
+                const int x0 = axis_of(a[0][0], a[0][1], a[0][2], a[0][3], real_of(place, 16));
+                const int x1 = axis_of(a[1][0], a[1][1], a[1][2], a[1][3], real_of(place + 16, 16));
+                split((i & 16) ? x1 : x0, 16);
+                m = 8;
+            }
+        }
+        if (m > groups_of) {
+            int axis = 0;
+            if (m == 8) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    double b[4];
+                    sum(N8{}, ent, 16 * h, b[0], b[1], b[2], b[3]);
+                    const int x0 = axis_of(b[0], b[1], b[2], b[3], real_of(place + 16 * h, 8));
+                    const int x1 = axis_of(a[h][0] - b[0], a[h][1] - b[1], a[h][2] - b[2], a[h][3] - b[3], real_of(place + 16 * h + 8, 8));
+                    if ((i >> 4) == h) axis = (i & 8) ? x1 : x0;
+                }
+                split(axis, 8);
+                m = 4;
+            }
+        }
+        if (m == 4 && m > groups_of) {
+            int axis = 0;
+            for (int h = 0; h < 8; ++h) {
+                double b[4];
+                sum(N4{}, ent, 4 * h, b[0], b[1], b[2], b[3]);
+                const int x = axis_of(b[0], b[1], b[2], b[3], real_of(place + 4 * h, 4));
+                if ((i >> 2) == h) axis = x;
+            }
+            split(axis, 4);
+            m = 2;
+        }
+        if (m == 2 && m > groups_of) {
+            int axis = 0;
+            for (int h = 0; h < 16; ++h) {
+                double b[4];
+                sum(N2{}, ent, 2 * h, b[0], b[1], b[2], b[3]);
+                const int x = axis_of(b[0], b[1], b[2], b[3], real_of(place + 2 * h, 2));
+                if ((i >> 1) == h) axis = x;
+            }
+            split(axis, 2);
+        }
+        if (lane < 32) s_ent[place + i] = (uint16_t)ent;
+        __syncthreads();
+    }
+    if (t < np) keys_out[base + t] = (uint64_t)(uint32_t)s_pos[s_ent[t]];
+    if (!dst.K) return;   // uniform
+    const int64_t slot0 = (int64_t)bh * dst.cap_rows + dst.row0 + node0;
+    for (int x = t; x < nr * PIECES; x += (int)blockDim.x) {
+        const int j = x / PIECES, c = x % PIECES;
+        reinterpret_cast<uint4 *>(dst.K + (slot0 + j) * ROW)[c] = reinterpret_cast<const uint4 *>(s_rows + s_ent[j] * ROW)[c];
+    }
+    if (t < nr) {
+        const int pos = s_pos[s_ent[t]];
+        dst.slot_pos[slot0 + t] = (int32_t)(dst.row0 + pos);
+        dst.pos_slot[(int64_t)bh * dst.cap_rows + dst.row0 + pos] = (int32_t)(dst.row0 + node0 + t);
+    }
 }
 
 int bits_for(int64_t v) {   // bits needed to hold values 0 .. v-1
@@ -529,45 +919,62 @@ int bits_for(int64_t v) {   // bits needed to hold values 0 .. v-1
     return b;
 }
 
-// The two work arrays: a = the order before and after a split (32-bit positions, two halves), b = the codes of a level
-// (32 bits each), at the end the finished order as 64-bit keys.
+// The two work arrays: a = the order before and after a split (32-bit positions, two halves), b = the codes of a level and, behind
+// room for 32-bit codes, the counts of their upper eight bits, at the end the finished order as 64-bit keys.
 template <int ELT>
 hipError_t tree_order_t(lvr_index *ix, const TreeSrc &src, int64_t n_real, int64_t np, int levels, int c_lo, int c_hi,
-                        hipStream_t st) {
+                        hipStream_t st, const TreeRows &dst) {
     const int n_bh = lvr_n_bh(ix);
     uint32_t *cur = nullptr;   // the order at the start: entry i holds position i
     uint32_t *half[2] = {reinterpret_cast<uint32_t *>(ix->tree_keys_a),
                          reinterpret_cast<uint32_t *>(ix->tree_keys_a) + ix->tree_cap_keys};
-    uint32_t *codes = reinterpret_cast<uint32_t *>(ix->tree_keys_b);
+    code_t<ELT> *codes = reinterpret_cast<code_t<ELT> *>(ix->tree_keys_b);
+    uint32_t *hist = reinterpret_cast<uint32_t *>(ix->tree_keys_b) + ix->tree_cap_keys;
+    // sums of pieces and of nodes, of two levels each
+    const int64_t n_pieces = np > PIECE ? np / PIECE : 1;
+    double *pieces[2], *node_sums[2];
+    for (int i = 0; i < 2; ++i) {
+        pieces[i] = ix->tree_partial + (int64_t)i * n_bh * n_pieces * 256;
+        node_sums[i] = ix->tree_partial + (int64_t)(2 + i) * n_bh * n_pieces * 256;
+    }
+    int whole = 1;   // the next level's pieces are added up by a launch of their own
     int L = 0;
-    for (; (np >> L) > TREE_WG_MAX; ++L) {   // np is a power of two: every node here holds a multiple of 2048 entries
+    for (; (np >> L) > SMALL_NODE<ELT>; ++L) {   // np is a power of two
         const int64_t n_nodes = (int64_t)1 << L, m = np >> L;
-        hipLaunchKernelGGL(tree_stats_piece_kernel<ELT>, dim3((unsigned)(np / PIECE), (unsigned)n_bh), dim3(1024), 0, st, src,
-                           cur, ix->tree_partial, np, n_real, m);
+        const bool last = m / 2 <= SMALL_NODE<ELT>;   // small nodes take their own sums
+        // (fp32: the last level's nodes of 512 entries are twice as many as there are pieces)
+        LevelSums sums{pieces[L & 1], node_sums[(L & 1) ^ 1], last ? nullptr : node_sums[L & 1], n_pieces, whole};
+        if (whole)
+            hipLaunchKernelGGL(tree_stats_piece_kernel<ELT>, dim3((unsigned)n_pieces, (unsigned)n_bh),
+                               dim3(np < PIECE ? (unsigned)np : (unsigned)PIECE), 0, st, src, cur, pieces[L & 1], np, n_real);
         uint32_t *next = half[L & 1];
-        const dim3 nodes((unsigned)n_nodes, (unsigned)n_bh);
-        // nodes of more than 8192 entries leave most of the device idle in the split launch (a workgroup fetches a
-        // coordinate of 64 different rows at about one row per clock): there the codes are a launch of their own
-        if (m > 8192) {
-            hipLaunchKernelGGL(tree_axis_kernel, nodes, dim3(1024), 0, st, ix->tree_partial, ix->tree_axis, np, m, n_nodes, c_lo, c_hi);
-            hipLaunchKernelGGL(tree_codes_kernel<ELT>, dim3((unsigned)(np / 256), (unsigned)n_bh), dim3(256), 0, st, src, cur,
-                               codes, ix->tree_axis, np, n_real, m, n_nodes);
-            if (m <= 32768)
-                hipLaunchKernelGGL((tree_split_kernel<ELT, 32, false>), nodes, dim3(1024), 0, st, src, cur, next, codes,
-                                   ix->tree_partial, np, n_real, m, c_lo, c_hi);
-            else
-                hipLaunchKernelGGL((tree_split_kernel<ELT, 0, false>), nodes, dim3(1024), 0, st, src, cur, next, codes,
-                                   ix->tree_partial, np, n_real, m, c_lo, c_hi);
+        double *part_out = last ? nullptr : pieces[(L & 1) ^ 1];
+        const dim3 per_piece((unsigned)n_pieces, (unsigned)n_bh), per_node((unsigned)n_nodes, (unsigned)n_bh);
+#define LVR_SPLIT_LAUNCH(STEPS, GATHER, NT)                                                                                        \
+    hipLaunchKernelGGL((tree_split_kernel<ELT, STEPS, GATHER, NT>), dim3((unsigned)(np / NT), (unsigned)n_bh), dim3(NT), 0, st, src, \
+                       cur, next, codes, hist, sums, part_out, np, n_real, m, n_nodes, c_lo, c_hi)
+        if (m > 32768) {   // more codes than the threads of a workgroup hold
+            hipLaunchKernelGGL(tree_axis_kernel, per_node, dim3(1024), 0, st, sums, ix->tree_axis, m, n_nodes, n_real, c_lo, c_hi);
+            hipLaunchKernelGGL(tree_codes_kernel<ELT>, per_piece, dim3(1024), 0, st, src, cur, codes, hist, ix->tree_axis, sums, np, n_real,
+                               m, n_nodes, c_lo, c_hi);
+            hipLaunchKernelGGL(tree_split_large_kernel<ELT>, per_node, dim3(1024), 0, st, cur, next, codes, np, m);
+            whole = 1;
         } else {
-            hipLaunchKernelGGL((tree_split_kernel<ELT, 8, true>), nodes, dim3(1024), 0, st, src, cur, next, codes,
-                               ix->tree_partial, np, n_real, m, c_lo, c_hi);
+            if (m > GATHER_MAX) {
+                hipLaunchKernelGGL(tree_codes_kernel<ELT>, per_piece, dim3(1024), 0, st, src, cur, codes, hist, (const int32_t *)nullptr, sums,
+                                   np, n_real, m, n_nodes, c_lo, c_hi);
+                LVR_SPLIT_LAUNCH(32, false, 1024);
+            } else if (m >= 1024) LVR_SPLIT_LAUNCH(GATHER_MAX / 1024, true, 1024);
+            else LVR_SPLIT_LAUNCH(1, true, 512);   // fp32: nodes of 512
+            whole = 0;
         }
+#undef LVR_SPLIT_LAUNCH
         cur = next;
     }
     const int64_t m0 = np >> L;   // entries of a node that one workgroup finishes
-    const unsigned threads = m0 <= 64 ? 64u : (unsigned)m0;
+    const unsigned threads = m0 <= 32 ? 64u : (unsigned)(2 * m0);
     hipLaunchKernelGGL(tree_small_kernel<ELT>, dim3((unsigned)(np / m0), (unsigned)n_bh), dim3(threads), 0, st, src, cur,
-                       ix->tree_keys_b, np, (int)m0, n_real, levels - L, c_lo, c_hi);
+                       ix->tree_keys_b, np, (int)m0, n_real, levels - L, c_lo, c_hi, dst);
     return hipGetLastError();
 }
 
@@ -592,10 +999,10 @@ bool lvr_tree_feasible(const lvr_index *ix, int64_t n_real) {
     return pos_bits + coord_bits + node_bits <= 64 && (int64_t)n_bh * np <= ix->tree_cap_keys;
 }
 
-// Orders n_real = groups*r keys (positions 0..n_real-1 of the given source rows) by the tree; perm->keys then holds, per
-// (sequence, KV head), the position stored in every slot.  Returns hipErrorInvalidValue if lvr_tree_feasible says no.
-hipError_t lvr_tree_order(lvr_index *ix, const void *Ksrc, const int64_t ks[3], int64_t n_real, hipStream_t st,
-                          lvr_tree_perm *perm, int c_lo, int c_hi) {
+namespace {
+
+hipError_t tree_order(lvr_index *ix, const void *Ksrc, const int64_t ks[3], int64_t n_real, hipStream_t st, lvr_tree_perm *perm, int c_lo,
+                      int c_hi, const TreeRows &dst) {
     perm->keys = nullptr;
     if (n_real <= 0) return hipSuccess;
     if (!lvr_tree_feasible(ix, n_real)) return hipErrorInvalidValue;
@@ -606,8 +1013,8 @@ hipError_t lvr_tree_order(lvr_index *ix, const void *Ksrc, const int64_t ks[3], 
     int levels = 0;
     while (((int64_t)1 << levels) < gp) ++levels;       // nodes of r entries after `levels` splits
     const TreeSrc src{static_cast<const char *>(Ksrc), ks[0], ks[1], ks[2], (int)ix->elt, ix->cfg.n_kv_heads};
-    const hipError_t e = ix->elt == 2 ? tree_order_t<2>(ix, src, n_real, np, levels, c_lo, c_hi, st)
-                                      : tree_order_t<4>(ix, src, n_real, np, levels, c_lo, c_hi, st);
+    const hipError_t e = ix->elt == 2 ? tree_order_t<2>(ix, src, n_real, np, levels, c_lo, c_hi, st, dst)
+                                      : tree_order_t<4>(ix, src, n_real, np, levels, c_lo, c_hi, st, dst);
     if (e != hipSuccess) return e;
     perm->keys = ix->tree_keys_b;
     perm->np = np;
@@ -615,24 +1022,41 @@ hipError_t lvr_tree_order(lvr_index *ix, const void *Ksrc, const int64_t ks[3], 
     return hipSuccess;
 }
 
-hipError_t lvr_tree_gather(lvr_index *ix, const void *Ksrc, const int64_t ks[3], const void *Vsrc, const int64_t vs[3],
-                           const lvr_tree_perm *perm, int64_t n_real, int64_t row0, hipStream_t st) {
+// Rows `from` keys (z0 = 0) or values (z0 = 1) on into the arena, in the order of perm.
+hipError_t gather_rows(lvr_index *ix, const void *Ksrc, const int64_t ks[3], const void *Vsrc, const int64_t vs[3], const lvr_tree_perm *perm,
+                       int64_t n_real, int64_t row0, hipStream_t st, int z0) {
     if (n_real <= 0 || !perm->keys) return hipSuccess;
     const int n_bh = lvr_n_bh(ix);
     TreeSrc ksrc{static_cast<const char *>(Ksrc), ks[0], ks[1], ks[2], (int)ix->elt, ix->cfg.n_kv_heads};
     TreeSrc vsrc{static_cast<const char *>(Vsrc), vs[0], vs[1], vs[2], (int)ix->elt, ix->cfg.n_kv_heads};
     const int row_bytes = (int)(LVR_D * ix->elt);
     const int64_t total = n_real * (row_bytes / 16);
-    hipLaunchKernelGGL(tree_gather_kernel, dim3((unsigned)((total + 255) / 256), (unsigned)n_bh, 2), dim3(256), 0, st,
+    hipLaunchKernelGGL(tree_gather_kernel, dim3((unsigned)((total + 255) / 256), (unsigned)n_bh, 2u - z0), dim3(256), 0, st,
                        ksrc, vsrc, perm->keys, static_cast<char *>(ix->K), static_cast<char *>(ix->V), ix->slot_pos,
-                       ix->pos_slot, perm->np, n_real, perm->pos_bits, ix->cap_rows, row0, row_bytes);
+                       ix->pos_slot, perm->np, n_real, perm->pos_bits, ix->cap_rows, row0, row_bytes, z0);
     return hipGetLastError();
 }
 
+}  // namespace
+
+// Orders n_real = groups*r keys (positions 0..n_real-1 of the given source rows) by the tree; perm->keys then holds, per
+// (sequence, KV head), the position stored in every slot.  Returns hipErrorInvalidValue if lvr_tree_feasible says no.
+hipError_t lvr_tree_order(lvr_index *ix, const void *Ksrc, const int64_t ks[3], int64_t n_real, hipStream_t st,
+                          lvr_tree_perm *perm, int c_lo, int c_hi) {
+    return tree_order(ix, Ksrc, ks, n_real, st, perm, c_lo, c_hi, TreeRows{nullptr, nullptr, nullptr, 0, 0});
+}
+
+hipError_t lvr_tree_gather(lvr_index *ix, const void *Ksrc, const int64_t ks[3], const void *Vsrc, const int64_t vs[3],
+                           const lvr_tree_perm *perm, int64_t n_real, int64_t row0, hipStream_t st) {
+    return gather_rows(ix, Ksrc, ks, Vsrc, vs, perm, n_real, row0, st, 0);
+}
+
+// Order and rows at once: the launch that finishes the order writes the key rows and the position maps.
 hipError_t lvr_tree_group(lvr_index *ix, const void *Ksrc, const int64_t ks[3], const void *Vsrc, const int64_t vs[3],
                           int64_t n_real, int64_t row0, hipStream_t st) {
     lvr_tree_perm perm;
-    hipError_t e = lvr_tree_order(ix, Ksrc, ks, n_real, st, &perm);
+    hipError_t e = tree_order(ix, Ksrc, ks, n_real, st, &perm, 0, LVR_D,
+                              TreeRows{static_cast<char *>(ix->K), ix->slot_pos, ix->pos_slot, ix->cap_rows, row0});
     if (e != hipSuccess) return e;
-    return lvr_tree_gather(ix, Ksrc, ks, Vsrc, vs, &perm, n_real, row0, st);
+    return gather_rows(ix, Ksrc, ks, Vsrc, vs, &perm, n_real, row0, st, 1);
 }

@@ -187,6 +187,54 @@ def test_tree_order_is_the_recursive_median_split(G, dtype, r, n, ties):
         check_median_splits(K[0, kv, :grouped].astype(np.float64), slot_pos[0, kv, :grouped], r)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("r,n,kind", [(1, 2, "normal"), (1, 33, "normal"), (2, 7, "few"), (4, 17, "normal"), (16, 32, "few"), (8, 64, "normal"),
+                                      (4, 65, "few"), (2, 130, "equal"), (4, 257, "normal"), (16, 512, "outlier"), (4, 513, "normal"),
+                                      (4, 900, "few"), (8, 1025, "outlier"), (2, 2049, "few"), (4, 4097, "normal"), (4, 8193, "mean"),
+                                      (8, 16500, "few"), (4, 33000, "few")])
+def test_tree_order_at_the_edges_of_its_launches(G, dtype, r, n, kind):
+    """Sizes around every size of a node that changes hands (one wave, one workgroup, codes fetched by the split, by a launch of
+    their own, more than one workgroup's registers hold), as a build from token-major keys and as a buffer chunk of the same keys:
+    the order is the recursive median split, the arena holds the keys in that order, and the right half's sums, which are
+    differences, stand up to a few large keys and to a common offset."""
+    L = G.L
+    g = np.random.default_rng(n * 17 + r)
+    K = g.standard_normal((1, 2, n, 128))
+    if kind == "few":
+        K = np.rint(K)
+    elif kind == "equal":
+        K[:] = K[:, :, :1]
+    elif kind == "outlier":
+        K[:, :, :: max(n // 3, 1), :5] *= 1000.0
+    elif kind == "mean":
+        K += 300.0
+    K = W.round_to_bf16(K.astype(np.float32)) if dtype == "bf16" else K.astype(np.float32)
+    chunk = n // (16 * r) * 16 * r if n <= 4097 else 0   # a buffer the keys fill at once
+    cfg = L.make_config(batch=1, n_q_heads=2, n_kv_heads=2, kv_dtype=L.LVR_BF16 if dtype == "bf16" else L.LVR_F32, capacity=n + chunk,
+                        group_size=r, grouping=L.LVR_GROUP_TREE, buffer_size=chunk if chunk else 16 * r)
+    grouped = n // r * r
+    h = L.lvr_create(cfg)
+    try:
+        Kd = G.to_device(K, dtype)
+        Kt = Kd.transpose(1, 2).contiguous().transpose(1, 2)
+        L.lvr_build(h, Kt, Kt)
+        _, _, slot_pos, keys = L.lvr_export_index(h, cfg)
+        if chunk:   # nothing indexed, then one chunk
+            L.lvr_build(h, Kd[:, :, :0], Kd[:, :, :0])
+            L.lvr_append(h, Kd[:, :, :chunk].contiguous(), Kd[:, :, :chunk].contiguous())
+            assert L.lvr_length(h) == (chunk, chunk)
+            chunk_pos = L.lvr_export_index(h, cfg)[2]
+    finally:
+        L.lvr_destroy(h)
+    bits = (K.view(np.uint32) >> 16).astype(np.uint16) if dtype == "bf16" else K
+    for kv in range(2):
+        assert np.array_equal(slot_pos[0, kv, grouped:], np.arange(grouped, n))
+        assert np.array_equal(keys[0, kv], bits[0, kv][slot_pos[0, kv]])
+        check_median_splits(K[0, kv, :grouped].astype(np.float64), slot_pos[0, kv, :grouped], r)
+        if chunk:
+            check_median_splits(K[0, kv, :chunk].astype(np.float64), chunk_pos[0, kv], r)
+
+
 @pytest.mark.parametrize("hq,hkv,n,r,S,tail,kw", [
     (1, 1, 64, 4, 4, 0, {}), (1, 1, 4096, 4, 4, 0, {}), (2, 1, 1000, 2, 1, 3, {}), (8, 2, 4095, 4, 16, 131, {}),
     (8, 1, 8192, 1, 2, 255, dict(query_workgroups=16)), (4, 4, 5000, 16, 8, 17, dict(buffer_size=32)),
