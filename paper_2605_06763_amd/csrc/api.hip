@@ -580,10 +580,10 @@ int lvr_publish(lvr_index *ix, void *stream) {
 
 namespace {
 
-// bound test + exact filter; leaves the set sizes in the internal per-head counters
+// bound test + exact filter; leaves the set sizes in the internal per-head counters, or, with out_count, hands them over there
 int enqueue_query(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx, int64_t cap, hipStream_t st,
                   const float *tau_s = nullptr, const void *k_new = nullptr, const void *v_new = nullptr,
-                  int64_t m_new = 0) {
+                  int64_t m_new = 0, int32_t *out_count = nullptr) {
     const bool fused = !(ix->cfg.flags & LVR_SEPARATE_KERNELS);
     const bool bf16 = ix->cfg.kv_dtype == LVR_BF16;
     if (ix->counters_dirty) {   // an earlier query never published its counts: start from zero again
@@ -600,11 +600,11 @@ int enqueue_query(lvr_index *ix, const float *q, const float *tau, int32_t *out_
         LVR_HIP(lvr_launch_label_filter(ix, q, tau, out_idx, cap, st));
     } else if (fused && !bf16) {
         Timed t(ix, LVR_K_FILTER, st);
-        LVR_HIP(lvr_launch_query_f32(ix, q, tau, out_idx, cap, st, k_new, v_new, m_new));
+        LVR_HIP(lvr_launch_query_f32(ix, q, tau, out_idx, cap, st, k_new, v_new, m_new, out_count));
         ix->n_total += m_new;
     } else if (fused) {
         Timed t(ix, LVR_K_FILTER, st, true);
-        LVR_HIP(lvr_launch_query_fused(ix, q, tau, tau_s, out_idx, cap, st, k_new, v_new, m_new));
+        LVR_HIP(lvr_launch_query_fused(ix, q, tau, tau_s, out_idx, cap, st, k_new, v_new, m_new, out_count));
         ix->n_total += m_new;
     } else {
         if (ix->n_indexed > 0) {
@@ -615,6 +615,13 @@ int enqueue_query(lvr_index *ix, const float *q, const float *tau, int32_t *out_
         }
         Timed t(ix, LVR_K_FILTER, st);
         LVR_HIP(lvr_launch_filter(ix, q, tau, out_idx, cap, st));
+    }
+    if (out_count) {
+        if (!fused || ix->per_subspace) {
+            Timed t(ix, LVR_K_RESET, st);
+            LVR_HIP(lvr_launch_publish_counts(ix, out_count, st));
+        }
+        ix->counters_dirty = 0;
     }
     ix->last_buffer_rows = ix->n_total - ix->n_indexed;
     ix->last_indexed = ix->n_indexed;
@@ -665,14 +672,7 @@ int lvr_query(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx,
     if (!on_home_device(ix)) return LVR_E_STATE;
     if (!aligned4(q) || !aligned4(tau) || !aligned4(out_idx) || !aligned4(out_count)) return LVR_E_INVALID;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int rc = enqueue_query(ix, q, tau, out_idx, cap, st);
-    if (rc != LVR_OK) return rc;
-    {
-        Timed t(ix, LVR_K_RESET, st);
-        LVR_HIP(lvr_launch_publish_counts(ix, out_count, st));
-    }
-    ix->counters_dirty = 0;
-    return LVR_OK;
+    return enqueue_query(ix, q, tau, out_idx, cap, st, nullptr, nullptr, nullptr, 0, out_count);
 }
 
 int lvr_query1(lvr_index *ix, const float *q, const float *tau_s, const float *tau, int32_t *out_idx,
@@ -685,14 +685,7 @@ int lvr_query1(lvr_index *ix, const float *q, const float *tau_s, const float *t
         ix->per_subspace)
         return LVR_E_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int rc = enqueue_query(ix, q, tau, out_idx, cap, st, tau_s);
-    if (rc != LVR_OK) return rc;
-    {
-        Timed t(ix, LVR_K_RESET, st);
-        LVR_HIP(lvr_launch_publish_counts(ix, out_count, st));
-    }
-    ix->counters_dirty = 0;
-    return LVR_OK;
+    return enqueue_query(ix, q, tau, out_idx, cap, st, tau_s, nullptr, nullptr, 0, out_count);
 }
 
 int lvr_subspace_thresholds(lvr_index *ix, const float *q, const float *tau, float *tau_s_out, void *stream) {

@@ -17,7 +17,28 @@ struct lvr_emit_target {
     int64_t cap;
     float *out_score;        // [n_bhq][score_stride] raw scores of the emitted keys (emitters that carry them), or NULL
     int64_t score_stride;
+    int32_t *out_count;      // the caller's set sizes, written by the launch itself (lvr_reserve_last), or NULL: a later launch does that
+    int32_t *head_stat;
 };
+
+// Range of a workgroup's last `tot` entries of a head, reserved once per workgroup by every workgroup of the head (`wgs` of them).
+// Where the launch hands the set sizes over itself, the same atomic counts the workgroups in the upper word of the head's slot: the one that
+// finds all the others there knows the whole size, stores it and clears the slot for the next query (every other addition to the
+// slot had returned before its workgroup was counted).  That takes the place of a launch that copied the counters:
+// 64 heads, 65736 keys, query and attention over its lists 29.3 -> 27.4 us.
+__device__ __forceinline__ int lvr_reserve_last(const lvr_emit_target &a, int64_t hq, int tot, unsigned wgs) {
+    int32_t *slot = &a.head_count[hq * LVR_CNT_STRIDE];
+    if (!a.out_count) return tot > 0 ? atomicAdd(slot, tot) : 0;   // uniform
+    unsigned long long *both = reinterpret_cast<unsigned long long *>(slot);   // slots start on a line of their own
+    const unsigned long long old = atomicAdd(both, (1ull << 32) | (unsigned)tot);
+    if ((unsigned)(old >> 32) == wgs - 1) {
+        const int32_t all = (int32_t)(unsigned)old + tot;
+        a.out_count[hq] = all;
+        a.head_stat[hq] = all;
+        *both = 0ull;
+    }
+    return (int)(unsigned)old;
+}
 
 // The lanes with (lane % 16) in [rep_base, rep_base+NH) report head (lane % 16) - rep_base; the
 // four lanes (one per quarter of the wave) that report the same head keep identical counts.

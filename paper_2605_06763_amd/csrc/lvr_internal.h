@@ -149,13 +149,15 @@ hipError_t lvr_launch_prune(lvr_index *ix, const float *q, const float *tau, hip
 // exact check on survivors and buffer; fills out_idx and the internal per-head counters
 hipError_t lvr_launch_filter(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx, int64_t cap,
                              hipStream_t st);
-// bf16 caches: bound test + exact check in one launch (per-head counters must be zero on entry)
+// bf16 caches: bound test + exact check in one launch (per-head counters must be zero on entry).
+// out_count != NULL: the set sizes are handed over too and the counters cleared (lvr_launch_publish_counts)
 hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *tau, const float *tau_s, int32_t *out_idx,
                                   int64_t cap, hipStream_t st, const void *k_new = nullptr, const void *v_new = nullptr,
-                                  int64_t m_new = 0);
+                                  int64_t m_new = 0, int32_t *out_count = nullptr);
 // the same for fp32 caches (Query 2 only)
 hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx, int64_t cap,
-                                hipStream_t st, const void *k_new = nullptr, const void *v_new = nullptr, int64_t m_new = 0);
+                                hipStream_t st, const void *k_new = nullptr, const void *v_new = nullptr, int64_t m_new = 0,
+                                int32_t *out_count = nullptr);
 // internal per-head counters -> caller's array and the statistics copy; clears the counters
 hipError_t lvr_launch_publish_counts(lvr_index *ix, int32_t *out_count, hipStream_t st);
 // partial softmax per (head, split); count is read with the given stride (1 = caller's array)

@@ -41,7 +41,10 @@ struct PruneArgs {
 
 __global__ void reset_kernel(int32_t *head_count, int n_bhq) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_bhq) head_count[(size_t)i * LVR_CNT_STRIDE] = 0;
+    if (i < n_bhq) {
+        head_count[(size_t)i * LVR_CNT_STRIDE] = 0;
+        head_count[(size_t)i * LVR_CNT_STRIDE + 1] = 0;   // workgroups counted by a query that publishes its counts itself
+    }
 }
 
 __device__ __forceinline__ void clear_query_counters(const PruneArgs &a, int64_t hq0) {

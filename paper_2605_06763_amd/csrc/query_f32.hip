@@ -196,7 +196,7 @@ query_f32_kernel(const float *__restrict__ q_in, const void *__restrict__ centre
     __syncthreads();
     if (wave == 0 && rep && sub == 0) {
         const int tot = s_wcnt[0][li] + s_wcnt[1][li] + s_wcnt[2][li] + s_wcnt[3][li];
-        s_wbase[li] = tot > 0 ? atomicAdd(&a.emit.head_count[(hq0 + li) * LVR_CNT_STRIDE], tot) : 0;
+        s_wbase[li] = lvr_reserve_last(a.emit, hq0 + li, tot, gridDim.x);
     }
     __syncthreads();
     int base = 0;
@@ -210,7 +210,7 @@ query_f32_kernel(const float *__restrict__ q_in, const void *__restrict__ centre
 }  // namespace
 
 hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau, int32_t *out_idx, int64_t cap,
-                                hipStream_t st, const void *k_new, const void *v_new, int64_t m_new) {
+                                hipStream_t st, const void *k_new, const void *v_new, int64_t m_new, int32_t *out_count) {
     if (ix->cfg.kv_dtype != LVR_F32) return hipErrorInvalidValue;
     FusedF32Args a;
     a.K = ix->K;
@@ -226,6 +226,8 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     a.emit.cap = cap;
     a.emit.out_score = ix->scores;
     a.emit.score_stride = ix->cap_rows;
+    a.emit.out_count = out_count;
+    a.emit.head_stat = lvr_head_stat(ix);
     a.n_groups = ix->n_indexed / ix->cfg.group_size;
     a.max_groups = ix->max_groups;
     a.max_segs = lvr_max_segs(ix->max_groups);
@@ -266,7 +268,7 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     const int has_buffer = a.n_total > ix->n_indexed ? 1 : 0;
     ix->seg_groups = seg_groups;
     ix->n_segs = n_segs;
-    if (n_segs + has_buffer == 0) return hipSuccess;
+    if (n_segs + has_buffer == 0) return out_count ? lvr_launch_publish_counts(ix, out_count, st) : hipSuccess;
     const dim3 grid((unsigned)(n_segs + has_buffer), (unsigned)n_bh);
     switch (ix->G) {
         case 1: hipLaunchKernelGGL(query_f32_kernel<1>, grid, dim3(256), 0, st, q, ix->centres, tau, ix->radii, (int)a.n_groups, (int)a.max_groups, seg_groups, n_segs, ix->cfg.n_subspaces, a); break;

@@ -792,7 +792,7 @@ query_fused_kernel(const float *__restrict__ q_in, const int8_t *__restrict__ ch
             if (rep[hb] && kq == 0) {
                 const int h = hb * W + n - 8;
                 const int tot = s_wcnt[0][h] + s_wcnt[1][h] + s_wcnt[2][h] + s_wcnt[3][h];
-                s_wbase[h] = tot > 0 ? atomicAdd(&a.emit.head_count[(hq0 + h) * LVR_CNT_STRIDE], tot) : 0;
+                s_wbase[h] = lvr_reserve_last(a.emit, hq0 + h, tot, gridDim.x);
             }
         }
     }
@@ -882,7 +882,7 @@ void launch_s(dim3 grid, unsigned dyn_lds, hipStream_t st, const FusedArgs &a, i
 
 hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *tau, const float *tau_s,
                                   int32_t *out_idx, int64_t cap, hipStream_t st, const void *k_new, const void *v_new,
-                                  int64_t m_new) {
+                                  int64_t m_new, int32_t *out_count) {
     if (ix->cfg.kv_dtype != LVR_BF16) return hipErrorInvalidValue;
     if (tau_s && ((ix->box || ix->cf8 || ix->cf6) && ix->cfg.n_subspaces > 4)) return hipErrorInvalidValue;
     LeadArgs lead;
@@ -911,6 +911,8 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     a.emit.cap = cap;
     a.emit.out_score = ix->scores;
     a.emit.score_stride = ix->cap_rows;
+    a.emit.out_count = out_count;
+    a.emit.head_stat = lvr_head_stat(ix);
     a.max_segs = lvr_max_segs(ix->max_groups);
     a.cap_rows = ix->cap_rows;
     a.n_indexed = ix->n_indexed;
@@ -933,7 +935,7 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     a.n_segs = (int)(((int64_t)lead.n_groups + seg_groups - 1) / seg_groups);
     ix->seg_groups = seg_groups;
     ix->n_segs = a.n_segs;
-    if (a.n_segs + has_buffer == 0) return hipSuccess;
+    if (a.n_segs + has_buffer == 0) return out_count ? lvr_launch_publish_counts(ix, out_count, st) : hipSuccess;
     dim3 grid((unsigned)(a.n_segs + has_buffer), (unsigned)n_bh);
     // more workgroups than 5 x 256: hold the residency at four per compute unit, so that the rounds are whole
     const unsigned dyn_lds = (int64_t)grid.x * grid.y > 1280 ? 20480u : 0u;
