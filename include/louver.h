@@ -137,10 +137,11 @@ typedef struct lvr_config {
     uint32_t flags;      /* lvr_flags                                                            */
     int64_t capacity;    /* max keys per (sequence, KV head): the arena is sized once (App. "GPU Update") */
     float scale;         /* sigma; 0 means 1/sqrt(head_dim)  (Sec. 2, "Attention")               */
-    int32_t attn_splits; /* P > 0: up to P partial-softmax splits per head, then a combine launch;
-                          * -1: one workgroup per head, 16 splits merged in LDS, a single launch;
-                          * 0: chosen per call: the single launch for batches of 128 heads or more
-                          *    and for contexts up to 65536 keys, else 64 splits + combine      */
+    int32_t attn_splits; /* P > 0: up to P partial-softmax splits per head, merged by the last of them to end
+                          *    (lists that carry their scores: by a combine launch);
+                          * -1: one workgroup per head, 16 splits merged in LDS;
+                          * 0: chosen per call: one workgroup per head for batches of 128 heads or more
+                          *    and for contexts up to 65536 keys, else up to 64 splits              */
     int32_t reservoir_size; /* R <= 256 past keys kept per (sequence, KV head) by reservoir sampling for
                              * lvr_threshold (appendix "Threshold Oracle Comparison"); 0 = none         */
     uint64_t seed;          /* seed of the counter-based generator behind the reservoir              */
@@ -241,7 +242,7 @@ int lvr_subspace_thresholds(lvr_index *ix, const float *q_dev, const float *tau_
                             void *stream);
 
 /* Attention over given index lists (Sec. 2 "Sparse Attention"; App. "GPU Sparse Attention
- * Kernel": P splits with partial (m, l, o), then a combine pass).  Softmax is normalised over
+ * Kernel": P splits with partial (m, l, o), merged by the last split of a head to end).  Softmax is normalised over
  * the listed keys only.  idx_dev / count_dev as produced by lvr_query (count is clamped to
  * cap; positions outside [0, n) are skipped).  out_dev [batch][n_q_heads][head_dim] fp32;
  * an empty list gives zeros. */
@@ -252,16 +253,16 @@ int lvr_sparse_attention(lvr_index *ix, const float *q_dev, const int32_t *idx_d
  * capture, tight serving loops, harnesses that forbid hipMalloc.  No lvr_index is needed and
  * nothing is allocated or freed, by this call or by anything it uses: K_dev and V_dev are the
  * caller's own cache, contiguous [batch][n_kv_heads][n][128] of kv_dtype (rows 16-byte aligned),
- * positions in idx_dev are row numbers 0 .. n-1, and the split pass keeps its partial (m, l, o)
- * triples in a static device array inside the library (8.1 MiB per GPU, held until the process
+ * positions in idx_dev are row numbers 0 .. n-1, and the splits keep their partial (m, l, o)
+ * triples in a static device array inside the library (2.1 MiB per GPU, held until the process
  * ends) whose per-device address is looked up on the first call on that device.
- * Same kernels and same results as lvr_sparse_attention with attn_splits = 64 (64 splits per
- * head, then the combine pass).  scale = 0 means 1/sqrt(128).
+ * Same kernel and same results as lvr_sparse_attention with attn_splits = 64 (up to 64 splits per
+ * head).  scale = 0 means 1/sqrt(128).
  * Limits: batch * n_q_heads <= 256 and n <= 2^30, else LVR_E_CAPACITY.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
  * streams, two threads) race on it and must be ordered by the caller.  The array keeps the last
- * call's partials; none of it has to start at zero, since a call reads only what its own split
- * pass has just written. */
+ * call's partials; a call reads only those its own splits have just written.  The tickets its splits draw
+ * are zero after every call. */
 int lvr_sparse_attention_static(const void *K_dev, const void *V_dev, int64_t n, int32_t kv_dtype, int32_t batch,
                                 int32_t n_q_heads, int32_t n_kv_heads, float scale, const float *q_dev,
                                 const int32_t *idx_dev, const int32_t *count_dev, int64_t cap, float *out_dev,

@@ -649,9 +649,15 @@ int decode_step_impl(lvr_index *ix, const float *q, const float *tau, float *out
         ix->counters_dirty = 0;
         return LVR_OK;
     }
+    if (!carried) {   // the same, by several workgroups per head
+        Timed t(ix, LVR_K_ATTN_PARTIAL, st);
+        LVR_HIP(lvr_launch_sparse_splits(ix, q, out_idx, lvr_head_count(ix), LVR_CNT_STRIDE, cap, out, out_count, st));
+        ix->counters_dirty = 0;
+        return LVR_OK;
+    }
     {   // the attention reads the set sizes straight from the internal counters ...
         Timed t(ix, LVR_K_ATTN_PARTIAL, st);
-        LVR_HIP(lvr_launch_sparse_partial(ix, q, out_idx, carried, lvr_head_count(ix), LVR_CNT_STRIDE, cap, st));
+        LVR_HIP(lvr_launch_carried_splits(ix, out_idx, carried, lvr_head_count(ix), LVR_CNT_STRIDE, cap, st));
     }
     {   // ... and the combine pass hands them to the caller
         Timed t(ix, LVR_K_ATTN_COMBINE, st);
@@ -711,14 +717,8 @@ int lvr_sparse_attention(lvr_index *ix, const float *q, const int32_t *idx, cons
         LVR_HIP(lvr_launch_sparse_attention_wg(ix, q, idx, nullptr, count, 1, cap, out, nullptr, st));
         return LVR_OK;
     }
-    {
-        Timed t(ix, LVR_K_ATTN_PARTIAL, st);
-        LVR_HIP(lvr_launch_sparse_partial(ix, q, idx, nullptr, count, 1, cap, st));
-    }
-    {
-        Timed t(ix, LVR_K_ATTN_COMBINE, st);
-        LVR_HIP(lvr_launch_combine(ix, out, ix->P, count, 1, cap, nullptr, st));
-    }
+    Timed t(ix, LVR_K_ATTN_PARTIAL, st);
+    LVR_HIP(lvr_launch_sparse_splits(ix, q, idx, count, 1, cap, out, nullptr, st));
     return LVR_OK;
 }
 

@@ -3,9 +3,11 @@
 //  sparse_attention_kernel attention restricted to a per-head index list (Sec. 2 "Sparse
 //                         Attention"; App. "GPU Sparse Attention Kernel"): the list is cut into
 //                         P splits, each wave gathers its K and V rows (256 B each for bf16),
-//                         keeps running softmax statistics (m, l) and an fp32 accumulator o.
+//                         keeps running softmax statistics (m, l) and an fp32 accumulator o, and the
+//                         last workgroup of a head merges the partial triples into the output.
 //  dense_partial_kernel   the dense baseline (Sec. 2 "Attention"): every held key, contiguous
 //                         streaming, the G query heads of a KV head served from one read.
+//  carried_split_kernel   the same over lists that carry their scores, partials only.
 //  combine_kernel         merges the P partial triples (m_p, l_p, o_p) into the output.
 //
 // Logits are taken in base-2 units (sigma * log2 e) so the exponentials are single exp2 instructions; the softmax is
@@ -30,7 +32,7 @@ __device__ __forceinline__ float exp2_carried(float score, float unit, float m) 
 
 // Split geometry of the sparse attention: 16 entries per split (one gather batch) while the
 // list fits in P_max splits, longer splits otherwise.  Returns the split length; *used = splits
-// that hold entries.  The partial and the combine kernel derive it from the same count.
+// that hold entries.  carried_split_kernel and combine_kernel derive it from the same count.
 __device__ __forceinline__ int64_t split_length(int64_t cnt, int P_max, int *used) {
     int64_t L = (((cnt + P_max - 1) / P_max) + 15) & ~(int64_t)15;
     if (L < 16) L = 16;
@@ -38,21 +40,32 @@ __device__ __forceinline__ int64_t split_length(int64_t cnt, int P_max, int *use
     return L;
 }
 
-// One wave per (query head, split).  The split's positions are fetched with one coalesced load,
-// then rows are gathered 16 at a time (K and V of four row-quads in flight together).  The
-// partials are merged by combine_kernel in a launch of its own: making them visible to a
-// "last wave" inside this launch would take a device-scope fence per wave, which costs more
-// on this multi-die part than the extra launch does.
-// CARRY: the raw scores of the listed keys are given (written by the query kernel that made the
-// list), so only V rows are gathered.
-template <typename KT, bool CARRY>
-__global__ void __launch_bounds__(64)
-sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__restrict__ idx, const float *__restrict__ scores,
+// One wave per split of a head's list, four waves to a workgroup, up to 256 splits.  The split's positions are fetched with one
+// coalesced load, then rows are gathered 16 at a time (K and V of four row-quads in flight together).  A workgroup merges
+// its waves in LDS; where a list fills more than one workgroup each of them stores its (m, l, o) and takes a ticket, and the one that
+// draws the last merges them all, which saves the launch that used to do it.  A fence per workgroup that makes everything written so far visible would cost
+// more than that launch on this multi-die part; here only the partials cross from one die to another: they are stored and
+// read with accesses of device scope, and a workgroup waits for its own stores before it takes the ticket.  Every workgroup of
+// a head takes one, whatever its share, and the counter wraps at their number (every number has a word of its own): it is back at zero
+// after every launch, and after any set of launches that overlapped against the rules.
+// us per call, a launch per stage and now, 80 / 330 / 1300 entries per head: 32 bf16 heads 7.4 / 7.8 / 9.6 and 5.7 / 6.1 / 8.4, 64 fp32 heads 8.9 /
+// 11.0 / 20.3 and 7.8 / 8.8 / 19.6, 256 bf16 heads 14.0 / 16.3 / - and 8.2 / 13.3 / -.  (Workgroups of 16 waves: 32 bf16 heads 5.0 / 7.8 / 10.9.)
+// publish_count != NULL: the ticket's last also hands the head's counter over and clears it.
+constexpr int SPLIT_WAVES = 4, SPLIT_WGS_MAX = 16;
+
+template <typename KT>
+__global__ void __launch_bounds__(64 * SPLIT_WAVES)
+sparse_attention_kernel(const int32_t *count, const int32_t *__restrict__ idx,   // count may alias head_count: not restrict
                         const float *__restrict__ q, const void *__restrict__ V, int64_t cap, int count_stride, int P,
                         int cap_rows, int n_total, int G, float qscale, const void *__restrict__ K,
-                        const int32_t *__restrict__ pos_slot, float *__restrict__ part_ml, float *__restrict__ part_o) {
+                        const int32_t *__restrict__ pos_slot, float *part_ml, float *part_o, int32_t *ticket, float *__restrict__ out,
+                        int32_t *head_count, int32_t *__restrict__ head_stat, int32_t *__restrict__ publish_count) {
+    __shared__ float s_m[SPLIT_WAVES], s_l[SPLIT_WAVES];
+    __shared__ float s_o[SPLIT_WAVES][LVR_D];
+    __shared__ unsigned s_arrived;
     const int64_t hq = blockIdx.y;
-    const int p = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int p = blockIdx.x * SPLIT_WAVES + wave;   // this wave's split
     const int bh = (int)((uint32_t)hq / (uint32_t)G);   // (hq / H_q) * H_kv + (hq % H_q) / G with H_q = H_kv * G: one 32-bit division
     const int lane = threadIdx.x & 63, sub = lane >> 4, li = lane & 15;
 
@@ -62,17 +75,14 @@ sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__rest
     // speculative load of the positions that goes out together with the count.
     const int64_t e_spec = (int64_t)p * 16 + lane;
     const int32_t pos_spec = (lane < 16 && e_spec < cap) ? my_idx[e_spec] : -1;
-    const float *my_sc = CARRY ? scores + hq * (int64_t)cap_rows : nullptr;
-    float sc_spec = 0.f;
-    if constexpr (CARRY) sc_spec = (lane < 16 && e_spec < cap && e_spec < cap_rows) ? my_sc[e_spec] : 0.f;
     int64_t cnt = count[hq * count_stride];
+    const int32_t true_cnt = (int32_t)cnt;
     if (cnt > cap) cnt = cap;
     if (cnt < 0) cnt = 0;
     int used;
     const int64_t L = split_length(cnt, P, &used);
-    if (p >= used) return;     // the combine pass reads only the `used` partials
     const int64_t start = (int64_t)p * L;
-    const int64_t end = (start + L < cnt) ? start + L : cnt;
+    const int64_t end = (start + L < cnt) ? start + L : cnt;   // past the splits in use: nothing
 
     float qv[8];
     {
@@ -90,45 +100,192 @@ sparse_attention_kernel(const int32_t *__restrict__ count, const int32_t *__rest
         // positions of up to 64 entries, validated and mapped to arena rows once
         int64_t e = c0 + lane;
         int myslot = -1;
-        float myscore = 0.f;
         if (e < end) {
             const int64_t pos = (L == 16) ? (int64_t)pos_spec : (int64_t)my_idx[e];
-            if constexpr (CARRY) myscore = (L == 16) ? sc_spec : my_sc[e];
             if (pos >= 0 && pos < n_total) myslot = pslot ? pslot[pos] : (int)pos;
         }
         const int chunk = (int)((end - c0 < 64) ? end - c0 : 64);
         for (int b0 = 0; b0 < chunk; b0 += 16) {
-            lvr_raw8<KT> kr[CARRY ? 1 : 4], vr[4];
+            lvr_raw8<KT> kr[4], vr[4];
             int slot[4];
-            float given[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 slot[i] = __shfl(myslot, (b0 + i * 4 + sub) & 63, 64);
-                if constexpr (CARRY) given[i] = __shfl(myscore, (b0 + i * 4 + sub) & 63, 64);
                 if (b0 + i * 4 + sub >= chunk) slot[i] = -1;
                 const int64_t sl = slot[i] < 0 ? 0 : slot[i];
-                if constexpr (!CARRY) lvr_load_raw(Kb, sl, li, kr[i]);
+                lvr_load_raw(Kb, sl, li, kr[i]);
                 lvr_load_raw(Vb, sl, li, vr[i]);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float vx[8];
                 lvr_unpack(vr[i], vx);
-                float s;
-                if constexpr (CARRY) {
-                    s = given[i];
-                } else {
-                    float kx[8];
-                    lvr_unpack(kr[i], kx);
-                    float d = 0.f;
+                float kx[8];
+                lvr_unpack(kr[i], kx);
+                float d = 0.f;
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) d += qv[c] * kx[c];
-                    s = lvr_row16_sum(d);
-                }
+                for (int c = 0; c < 8; ++c) d += qv[c] * kx[c];
+                float s = lvr_row16_sum(d);
                 s = (slot[i] >= 0) ? s : -INFINITY;
-                const float m_new = fmaxf(m, CARRY ? s * qscale : s);
+                const float m_new = fmaxf(m, s);
                 const float alpha = exp2_safe(m, m_new);
-                const float w = CARRY ? exp2_carried(s, qscale, m_new) : exp2_safe(s, m_new);
+                const float w = exp2_safe(s, m_new);
+                l = l * alpha + w;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[c] = acc[c] * alpha + w * vx[c];
+                m = m_new;
+            }
+        }
+    }
+    // merge the four quarter rows of the wave, then the waves
+    float m_all = fmaxf(m, __shfl_xor(m, 16, 64));
+    m_all = fmaxf(m_all, __shfl_xor(m_all, 32, 64));
+    const float sc = exp2_safe(m, m_all);
+    l *= sc;
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        float a = acc[c] * sc;
+        a += __shfl_xor(a, 16, 64);
+        a += __shfl_xor(a, 32, 64);
+        if (sub == 0) s_o[wave][li * 8 + c] = a;
+    }
+    if (lane == 0) {
+        s_m[wave] = m_all;
+        s_l[wave] = l;
+    }
+    __syncthreads();
+    const int wgs = (int)gridDim.x, used_wgs = (used + SPLIT_WAVES - 1) / SPLIT_WAVES;
+    const int ch = threadIdx.x & (LVR_D - 1), slice = threadIdx.x >> 7;
+    float M = -INFINITY, num = 0.f, den = 0.f;
+    if (slice == 0) {
+#pragma unroll
+        for (int w = 0; w < SPLIT_WAVES; ++w) M = fmaxf(M, s_m[w]);
+#pragma unroll
+        for (int w = 0; w < SPLIT_WAVES; ++w) {
+            const float wt = exp2_safe(s_m[w], M);
+            den += wt * s_l[w];
+            num += wt * s_o[w][ch];
+        }
+    }
+    if (used_wgs <= 1) {   // uniform over the head's workgroups: the first one holds all of the list
+        if (blockIdx.x == 0 && slice == 0) out[hq * LVR_D + ch] = (den > 0.f && M != -INFINITY) ? num / den : 0.f;
+        if (!publish_count) return;
+    } else if ((int)blockIdx.x < used_wgs && slice == 0) {
+        __hip_atomic_store(&part_o[(hq * wgs + blockIdx.x) * LVR_D + ch], num, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ch == 0) {
+            __hip_atomic_store(&part_ml[(hq * wgs + blockIdx.x) * 2], M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&part_ml[(hq * wgs + blockIdx.x) * 2 + 1], den, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's stores have reached the memory all compute units share
+    __syncthreads();
+    if (threadIdx.x == 0) s_arrived = atomicInc(reinterpret_cast<unsigned *>(&ticket[hq * LVR_CNT_STRIDE]), (unsigned)wgs - 1u);
+    __syncthreads();
+    if (s_arrived != (unsigned)wgs - 1u) return;
+    // every workgroup of the head has its partial in memory and has read the count
+    if (publish_count && threadIdx.x == 0) {
+        publish_count[hq] = true_cnt;
+        head_stat[hq] = true_cnt;
+        head_count[hq * LVR_CNT_STRIDE] = 0;
+    }
+    if (used_wgs <= 1) return;
+    auto load = [](const float *x) { return __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // at most 16 workgroups: lane p of every wave holds the weight of partial p
+    const float m_p = lane < used_wgs ? load(&part_ml[(hq * wgs + lane) * 2]) : -INFINITY;
+    const float l_p = lane < used_wgs ? load(&part_ml[(hq * wgs + lane) * 2 + 1]) : 0.f;
+    const float *po = part_o + hq * wgs * LVR_D + ch;
+    constexpr int SLICES = SPLIT_WAVES / 2;
+    constexpr int EACH = SPLIT_WGS_MAX / SLICES;
+    float pv[EACH];
+#pragma unroll
+    for (int i = 0; i < EACH; ++i) pv[i] = SLICES * i + slice < used_wgs ? load(&po[(SLICES * i + slice) * LVR_D]) : 0.f;
+    M = m_p;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+    const float w_p = exp2_safe(m_p, M);
+    den = w_p * l_p;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off, 64);
+    num = 0.f;
+#pragma unroll
+    for (int i = 0; i < EACH; ++i) num += __shfl(w_p, SLICES * i + slice, 64) * pv[i];   // past the partials in use: zero times zero
+    s_o[slice][ch] = num;
+    __syncthreads();
+    if (slice == 0) {
+#pragma unroll
+        for (int i = 1; i < SLICES; ++i) num += s_o[i][ch];
+        out[hq * LVR_D + ch] = (den > 0.f && M != -INFINITY) ? num / den : 0.f;
+    }
+}
+
+// Lists that carry their raw scores (written by the query kernel that made them) and are too long for the one-launch forms
+// below: one wave per (query head, split), the partials merged by combine_kernel.  The split's positions and scores are fetched with
+// one coalesced load each, then V rows are gathered 16 at a time.
+template <typename KT>
+__global__ void __launch_bounds__(64)
+carried_split_kernel(const int32_t *__restrict__ count, const int32_t *__restrict__ idx, const float *__restrict__ scores,
+                        const void *__restrict__ V, int64_t cap, int count_stride, int P,
+                        int cap_rows, int n_total, int G, float qscale, const int32_t *__restrict__ pos_slot, float *__restrict__ part_ml, float *__restrict__ part_o) {
+    const int64_t hq = blockIdx.y;
+    const int p = blockIdx.x;
+    const int bh = (int)((uint32_t)hq / (uint32_t)G);   // (hq / H_q) * H_kv + (hq % H_q) / G with H_q = H_kv * G: one 32-bit division
+    const int lane = threadIdx.x & 63, sub = lane >> 4, li = lane & 15;
+
+    const int32_t *my_idx = idx + hq * cap;
+    // The split geometry depends on the count, and the positions on the geometry: two dependent
+    // loads before the first gather.  The common geometry (16 entries per split) is assumed for a
+    // speculative load of the positions that goes out together with the count.
+    const int64_t e_spec = (int64_t)p * 16 + lane;
+    const int32_t pos_spec = (lane < 16 && e_spec < cap) ? my_idx[e_spec] : -1;
+    const float *my_sc = scores + hq * (int64_t)cap_rows;
+    const float sc_spec = (lane < 16 && e_spec < cap && e_spec < cap_rows) ? my_sc[e_spec] : 0.f;
+    int64_t cnt = count[hq * count_stride];
+    if (cnt > cap) cnt = cap;
+    if (cnt < 0) cnt = 0;
+    int used;
+    const int64_t L = split_length(cnt, P, &used);
+    if (p >= used) return;     // the combine pass reads only the `used` partials
+    const int64_t start = (int64_t)p * L;
+    const int64_t end = (start + L < cnt) ? start + L : cnt;
+
+    const char *Vb = static_cast<const char *>(V) + (int64_t)bh * cap_rows * LVR_D * sizeof(KT);
+    const int32_t *pslot = pos_slot ? pos_slot + (int64_t)bh * cap_rows : nullptr;
+
+    float m = -INFINITY, l = 0.f, acc[8];
+    lvr_zero8(acc);
+    for (int64_t c0 = start; c0 < end; c0 += 64) {          // uniform over the wave
+        // positions of up to 64 entries, validated and mapped to arena rows once
+        int64_t e = c0 + lane;
+        int myslot = -1;
+        float myscore = 0.f;
+        if (e < end) {
+            const int64_t pos = (L == 16) ? (int64_t)pos_spec : (int64_t)my_idx[e];
+            myscore = (L == 16) ? sc_spec : my_sc[e];
+            if (pos >= 0 && pos < n_total) myslot = pslot ? pslot[pos] : (int)pos;
+        }
+        const int chunk = (int)((end - c0 < 64) ? end - c0 : 64);
+        for (int b0 = 0; b0 < chunk; b0 += 16) {
+            lvr_raw8<KT> vr[4];
+            int slot[4];
+            float given[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                slot[i] = __shfl(myslot, (b0 + i * 4 + sub) & 63, 64);
+                given[i] = __shfl(myscore, (b0 + i * 4 + sub) & 63, 64);
+                if (b0 + i * 4 + sub >= chunk) slot[i] = -1;
+                const int64_t sl = slot[i] < 0 ? 0 : slot[i];
+                lvr_load_raw(Vb, sl, li, vr[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float vx[8];
+                lvr_unpack(vr[i], vx);
+                const float s = (slot[i] >= 0) ? given[i] : -INFINITY;
+                const float m_new = fmaxf(m, s * qscale);
+                const float alpha = exp2_safe(m, m_new);
+                const float w = exp2_carried(s, qscale, m_new);
                 l = l * alpha + w;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) acc[c] = acc[c] * alpha + w * vx[c];
@@ -966,24 +1123,40 @@ hipError_t lvr_launch_sparse_attention_wg(lvr_index *ix, const float *q, const i
     return hipGetLastError();
 }
 
-hipError_t lvr_launch_sparse_partial(lvr_index *ix, const float *q, const int32_t *idx, const float *scores,
-                                     const int32_t *count, int count_stride, int64_t cap, hipStream_t st) {
+hipError_t lvr_launch_sparse_splits(lvr_index *ix, const float *q, const int32_t *idx, const int32_t *count, int count_stride,
+                                    int64_t cap, float *out, int32_t *publish_count, hipStream_t st) {
     const int n_bhq = lvr_n_bhq(ix);
-    const int P = ix->P;
-    dim3 grid((unsigned)P, (unsigned)n_bhq);
-    const float qscale = ix->sigma * LOG2E;
-#define LVR_PART_LAUNCH(KT, CARRY)                                                                                       \
-    hipLaunchKernelGGL((sparse_attention_kernel<KT, CARRY>), grid, dim3(64), 0, st, count, idx, scores, q, ix->V, cap,     \
-                       count_stride, P, (int)ix->cap_rows, (int)ix->n_total, ix->G, qscale, ix->K, ix->pos_slot,         \
-                       ix->part_ml, ix->part_o)
-    if (ix->cfg.kv_dtype == LVR_BF16) {
-        if (scores) LVR_PART_LAUNCH(lvr_bf16_t, true);
-        else LVR_PART_LAUNCH(lvr_bf16_t, false);
-    } else {
-        if (scores) LVR_PART_LAUNCH(lvr_f32_t, true);
-        else LVR_PART_LAUNCH(lvr_f32_t, false);
-    }
-#undef LVR_PART_LAUNCH
+    // Every workgroup of a head costs a read of the count and a ticket whether the list reaches it or not, and the list lengths
+    // are not known here: as many as keep the device at about one workgroup per compute unit (80 / 330 / 1300 entries per head, us: 32
+    // bf16 heads 6.1 / 6.5 / 8.5 with 16 workgroups, 5.7 / 6.1 / 8.4 with 8; 64 fp32 heads 9.5 / 10.0 / 20.2 with 16, 7.8 / 8.8 / 19.6 with 8,
+    // 6.1 / 10.1 / 21.3 with 4; 128 bf16 heads 7.9 / 9.2 / 20.1 with 8, 6.3 / 8.7 / 17.9 with 4).
+    int wgs = n_bhq <= 16 ? SPLIT_WGS_MAX : (n_bhq <= 64 ? 8 : 4);
+    const int most = (ix->P + SPLIT_WAVES - 1) / SPLIT_WAVES;   // the caller's number of splits is an upper bound
+    if (wgs > most) wgs = most;
+    const int P = wgs * SPLIT_WAVES < ix->P ? wgs * SPLIT_WAVES : ix->P;
+    int32_t *ticket = lvr_split_ticket(ix) + (n_bhq <= 16 ? 0 : (n_bhq <= 64 ? 1 : 2));   // a word per number it counts modulo
+    dim3 grid((unsigned)wgs, (unsigned)n_bhq);
+#define LVR_SPLIT_LAUNCH(KT)                                                                                              \
+    hipLaunchKernelGGL(sparse_attention_kernel<KT>, grid, dim3(64 * SPLIT_WAVES), 0, st, count, idx, q, ix->V, cap,         \
+                       count_stride, P, (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->sigma * LOG2E, ix->K,              \
+                       ix->pos_slot, ix->part_ml, ix->part_o, ticket, out, lvr_head_count(ix),               \
+                       lvr_head_stat(ix), publish_count)
+    if (ix->cfg.kv_dtype == LVR_BF16) LVR_SPLIT_LAUNCH(lvr_bf16_t);
+    else LVR_SPLIT_LAUNCH(lvr_f32_t);
+#undef LVR_SPLIT_LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t lvr_launch_carried_splits(lvr_index *ix, const int32_t *idx, const float *scores, const int32_t *count, int count_stride,
+                                     int64_t cap, hipStream_t st) {
+    dim3 grid((unsigned)ix->P, (unsigned)lvr_n_bhq(ix));
+#define LVR_SPLIT_LAUNCH(KT)                                                                                              \
+    hipLaunchKernelGGL(carried_split_kernel<KT>, grid, dim3(64), 0, st, count, idx, scores, ix->V, cap, count_stride,      \
+                       ix->P, (int)ix->cap_rows, (int)ix->n_total, ix->G, ix->sigma * LOG2E, ix->pos_slot, ix->part_ml,    \
+                       ix->part_o)
+    if (ix->cfg.kv_dtype == LVR_BF16) LVR_SPLIT_LAUNCH(lvr_bf16_t);
+    else LVR_SPLIT_LAUNCH(lvr_f32_t);
+#undef LVR_SPLIT_LAUNCH
     return hipGetLastError();
 }
 

@@ -107,6 +107,9 @@ static inline int lvr_n_bhq(const lvr_index *ix) { return ix->cfg.batch * ix->cf
 // per query head: size of the retrieved set of the running query (padded).  Zero between
 // queries: the kernel that publishes the counts clears them.
 static inline int32_t *lvr_head_count(const lvr_index *ix) { return ix->counters; }
+// in the same line as a head's counter (words 0 and 1, see lvr_reserve_last): three words of tickets of the workgroups that share the
+// head's list, LVR_CNT_STRIDE apart per head, zero between launches
+static inline int32_t *lvr_split_ticket(const lvr_index *ix) { return ix->counters + 2; }
 static inline int32_t *lvr_overflow_flag(const lvr_index *ix) { return ix->counters + (size_t)lvr_n_bhq(ix) * LVR_CNT_STRIDE; }
 // per query head: set size of the last finished query (kept for statistics)
 static inline int32_t *lvr_head_stat(const lvr_index *ix) { return ix->counters + ((size_t)lvr_n_bhq(ix) + 1) * LVR_CNT_STRIDE; }
@@ -160,10 +163,13 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
                                 int32_t *out_count = nullptr);
 // internal per-head counters -> caller's array and the statistics copy; clears the counters
 hipError_t lvr_launch_publish_counts(lvr_index *ix, int32_t *out_count, hipStream_t st);
-// partial softmax per (head, split); count is read with the given stride (1 = caller's array)
-// scores: raw <q,k> of the listed keys, [n_bhq][cap_rows] (then no key row is read), or NULL
-hipError_t lvr_launch_sparse_partial(lvr_index *ix, const float *q, const int32_t *idx, const float *scores,
-                                     const int32_t *count, int count_stride, int64_t cap, hipStream_t st);
+// sparse attention of a head by ix->P waves, merged by the last workgroup; count is read with the given stride (1 = caller's array)
+// publish_count != NULL: also hands the internal per-head counters to the caller (and to the statistics copy) and clears them
+hipError_t lvr_launch_sparse_splits(lvr_index *ix, const float *q, const int32_t *idx, const int32_t *count, int count_stride,
+                                    int64_t cap, float *out, int32_t *publish_count, hipStream_t st);
+// partial softmax per (head, split) of lists with scores: raw <q,k> of the listed keys, [n_bhq][cap_rows]
+hipError_t lvr_launch_carried_splits(lvr_index *ix, const int32_t *idx, const float *scores, const int32_t *count, int count_stride,
+                                     int64_t cap, hipStream_t st);
 // whole sparse attention of a head in one workgroup (16 splits merged through LDS), one launch
 hipError_t lvr_launch_sparse_attention_wg(lvr_index *ix, const float *q, const int32_t *idx, const float *scores,
                                           const int32_t *count, int count_stride, int64_t cap, float *out,

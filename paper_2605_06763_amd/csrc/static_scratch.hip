@@ -2,11 +2,10 @@
 // cannot allocate (HIP graph capture, serving loops, harnesses that forbid hipMalloc).
 //
 // It needs no index object: K and V are the caller's own contiguous cache, and the partial
-// softmax triples of the split pass (the only device memory the attention kernels use beyond
-// their inputs and outputs) live in a file-scope device array instead of an arena that
-// lvr_create would have allocated.  The kernels are the ones lvr_sparse_attention launches in its
-// two-launch form (64 splits per head, then the combine pass); they take the array's device
-// address as an argument exactly as they take the arena's.
+// softmax triples and tickets of the splits (the only device memory the attention kernel uses beyond
+// its inputs and outputs) live in a file-scope device array instead of an arena that
+// lvr_create would have allocated.  The kernel is the one lvr_sparse_attention launches
+// for 64 splits per head; it takes the array's device address as an argument exactly as it takes the arena's.
 //
 // Every GPU holds its own copy of the array at its own address.  That address is looked up once
 // per device (hipGetSymbolAddress with that device current) and cached; host code never passes
@@ -18,15 +17,18 @@
 namespace {
 
 constexpr int STATIC_MAX_HEADS = 256;   // batch * n_q_heads
-constexpr int STATIC_SPLITS = 64;       // P of the two-launch form
+constexpr int STATIC_SPLITS = 64;       // P: splits per head, one wave each
+constexpr int STATIC_PARTIALS = 16;      // workgroups of a head, at most
 constexpr int STATIC_MAX_DEVICES = 64;
-constexpr size_t ML_FLOATS = (size_t)STATIC_MAX_HEADS * STATIC_SPLITS * 2;
-constexpr size_t O_FLOATS = (size_t)STATIC_MAX_HEADS * STATIC_SPLITS * LVR_D;
+constexpr size_t TICKET_FLOATS = (size_t)STATIC_MAX_HEADS * LVR_CNT_STRIDE;   // a line per head, as in an index
+constexpr size_t ML_FLOATS = (size_t)STATIC_MAX_HEADS * STATIC_PARTIALS * 2;
+constexpr size_t O_FLOATS = (size_t)STATIC_MAX_HEADS * STATIC_PARTIALS * LVR_D;
 
-// (m, l) pairs first, then the o vectors: 64 KiB + 8 MiB per GPU, held until the process ends.
-// Contents are whatever the last call left; nothing here has to start at zero, because a call
-// reads only the partials its own split pass has just written.
-static __device__ __align__(256) float scratch[ML_FLOATS + O_FLOATS];
+// The tickets, (m, l) pairs, then the o vectors: 32 KiB + 32 KiB + 2 MiB per GPU, held until the process ends.
+// The tickets start at zero with the process and count modulo the workgroups of a head, with a word for each such number, so they
+// are zero again after any set of calls, also of calls that overlapped.  Of the rest a call reads only the partials it has
+// just written.
+static __device__ __align__(256) float scratch[TICKET_FLOATS + ML_FLOATS + O_FLOATS];
 
 std::mutex g_mu;
 float *g_scratch_ptr[STATIC_MAX_DEVICES];   // device address of `scratch` on each GPU, once known
@@ -85,11 +87,10 @@ extern "C" int lvr_sparse_attention_static(const void *K, const void *V, int64_t
     view.cap_rows = n;        // contiguous [batch][n_kv_heads][n][128]
     view.n_total = n;
     view.P = STATIC_SPLITS;
-    view.part_ml = base;
-    view.part_o = base + ML_FLOATS;
-    view.counters = reinterpret_cast<int32_t *>(base);   // handed to the combine pass, which never touches it here
+    view.counters = reinterpret_cast<int32_t *>(base);
+    view.part_ml = base + TICKET_FLOATS;
+    view.part_o = view.part_ml + ML_FLOATS;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (lvr_launch_sparse_partial(&view, q, idx, nullptr, count, 1, cap, st) != hipSuccess) return LVR_E_HIP;
-    if (lvr_launch_combine(&view, out, STATIC_SPLITS, count, 1, cap, nullptr, st) != hipSuccess) return LVR_E_HIP;
+    if (lvr_launch_sparse_splits(&view, q, idx, count, 1, cap, out, nullptr, st) != hipSuccess) return LVR_E_HIP;
     return LVR_OK;
 }

@@ -363,6 +363,57 @@ def test_attention_form_of_a_decode_step(G, oracle, dtype, n, one_launch):
     assert launches["attn_partial"][1] == 1 and launches["attn_combine"][1] == (0 if one_launch else 1)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("batch,hq,hkv,splits", [(1, 4, 1, 64), (1, 16, 2, 256), (1, 32, 8, 64), (1, 64, 8, 9), (3, 32, 8, 64), (1, 8, 4, 1)])
+def test_attention_of_lists_by_several_workgroups(G, dtype, batch, hq, hkv, splits):
+    """List lengths around the entries of a wave, of a workgroup and of all of a head's workgroups, whose last to end merges the
+    others: a length per head, three calls in a row (tickets back at zero, the last one from a graph replayed twice), and the query
+    that hands its counts over followed by the attention over its lists."""
+    L = G.L
+    g = np.random.default_rng(hq + splits)
+    n = 4200
+    lens = [0, 1, 15, 16, 17, 63, 64, 65, 128, 129, 255, 256, 257, 511, 513, 1024, 1025, 2049, 4096, 4200]
+    K = W.round_to_bf16(g.standard_normal((batch, hkv, n, 128)).astype(np.float32))
+    V = W.round_to_bf16(g.standard_normal((batch, hkv, n, 128)).astype(np.float32))
+    q = g.standard_normal((batch, hq, 128)).astype(np.float32)
+    with G.Index(K, V, dtype, hq, capacity=n, group_size=4, attn_splits=splits) as ix:
+        qd = torch.from_numpy(q).cuda()
+        stream = torch.cuda.Stream()
+        for call in range(3):
+            cnt = np.array([[lens[(7 * h + 3 * b + call) % len(lens)] for h in range(hq)] for b in range(batch)], dtype=np.int32)
+            idx = np.stack([[g.permutation(n) for _ in range(hq)] for _ in range(batch)]).astype(np.int32)
+            idx_d, cnt_d, out = torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda(), torch.full((batch, hq, 128), np.nan, device="cuda")
+            torch.cuda.synchronize()
+            if call < 2:
+                L.lvr_sparse_attention(ix.h, qd, idx_d, cnt_d, out)
+            else:
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=stream):
+                    L.lvr_sparse_attention(ix.h, qd, idx_d, cnt_d, out, stream)
+                for _ in range(2):
+                    out.fill_(float("nan"))
+                    graph.replay()
+            torch.cuda.synchronize()
+            got = out.cpu().numpy()
+            for b in range(batch):
+                for h in range(hq):
+                    l = idx[b, h, :cnt[b, h]]
+                    s = K[b, h * hkv // hq][l].astype(np.float64) @ q[b, h].astype(np.float64) / math.sqrt(128)
+                    p = np.exp(s - s.max()) if len(l) else s
+                    want = (p / max(p.sum(), 1e-300)) @ V[b, h * hkv // hq][l].astype(np.float64)
+                    # logits below 6: d + 1 products and 7 levels of fp32 sums (2^-24 * 6 * 136), the exponential's and the sums' few ulps
+                    # of weights that add up to one, values below 5
+                    assert np.abs(got[b, h] - want).max() <= 3e-4, (call, b, h, len(l), np.abs(got[b, h] - want).max())
+        tau = np.sort(np.einsum("bhd,bhnd->bhn", q, np.repeat(K, hq // hkv, axis=1)), axis=-1)
+        tau = np.stack([[0.5 * (tau[b, h, -m] + tau[b, h, -m - 1]) for h, m in enumerate(np.resize([3, 60, 70, 300], hq))] for b in range(batch)])
+        for _ in range(2):
+            idx, cnt, out = ix.query(q, tau.astype(np.float32))
+            s = np.einsum("bhd,bhnd->bhn", q.astype(np.float64), np.repeat(K, hq // hkv, axis=1).astype(np.float64))
+            slack = 1e-4 * np.abs(tau)
+            assert ((s >= tau[..., None]).sum(-1) <= cnt).all() and (cnt <= (s >= (tau - slack)[..., None]).sum(-1)).all()
+            assert ix.stats()["keys_emitted"] == int(cnt.sum()) and np.isfinite(out).all()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("batch,hq,hkv,n,r", [(9, 32, 8, 1000, 4), (33, 8, 8, 96, 1)])
 def test_more_heads_than_compute_units(G, oracle, dtype, batch, hq, hkv, n, r):
