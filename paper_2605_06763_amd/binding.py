@@ -11,7 +11,14 @@ import os
 
 import torch
 
-from .build import LIB_PATH
+from .build import CALL_PATH, LIB_PATH
+
+try:
+    from . import _call   # the decode loop's calls without the interpreter's share (csrc/pycall.cpp)
+except ImportError:
+    if os.path.exists(CALL_PATH):
+        raise
+    _call = None          # nothing is built yet: this import is the build's own
 
 LVR_BF16, LVR_F32 = 0, 1
 LVR_GROUP_CONTIGUOUS, LVR_GROUP_TREE, LVR_GROUP_SUBSPACE_TREE = 0, 1, 2
@@ -117,6 +124,10 @@ def lib():
     L.lvr_strerror.argtypes = [C.c_int]
     L.lvr_strerror.restype = C.c_char_p
     L.lvr_last_hip_error.restype = C.c_int
+    if _call is not None:
+        for name in ("lvr_decode_step", "lvr_append_decode_step", "lvr_query", "lvr_sparse_attention", "lvr_sparse_attention_static",
+                     "lvr_dense_attention"):
+            _call.bind(name, C.cast(getattr(L, name), vp).value)
     _lib = L
     return L
 
@@ -129,8 +140,9 @@ def _check(code: int, where: str):
 def _stream(stream=None):
     if type(stream) is C.c_void_p:      # already marshalled (stream_arg)
         return stream
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is None:                  # torch.cuda.current_stream().cuda_stream without the Stream object around it
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return C.c_void_p(stream.cuda_stream)
 
 
 def stream_arg(stream=None) -> C.c_void_p:
@@ -138,16 +150,24 @@ def stream_arg(stream=None) -> C.c_void_p:
     return _stream(stream)
 
 
-class DeviceArg:
-    """A device tensor checked and marshalled once (tensor_arg); the tensor is kept alive."""
+class _Arg:
+    """What _call.Arg is, before that is built."""
     __slots__ = ("tensor", "ptr", "dtype", "shape")
+
+    def __init__(self, t: torch.Tensor, ptr: C.c_void_p):
+        self.tensor, self.ptr, self.dtype, self.shape = t, ptr, t.dtype, tuple(t.shape)
+
+
+class DeviceArg(_Arg if _call is None else _call.Arg):
+    """A device tensor checked and marshalled once (tensor_arg); the tensor is kept alive."""
+    __slots__ = ()
 
     def __init__(self, t: torch.Tensor):
         if not t.is_cuda:
             raise ValueError("tensor must be a device tensor")
         if not t.is_contiguous():
             raise ValueError("tensor must be contiguous")
-        self.tensor, self.ptr, self.dtype, self.shape = t, C.c_void_p(t.data_ptr()), t.dtype, tuple(t.shape)
+        super().__init__(t, C.c_void_p(t.data_ptr()))
 
 
 def tensor_arg(t: torch.Tensor) -> DeviceArg:
@@ -214,10 +234,14 @@ def lvr_append(h, k_new: torch.Tensor, v_new: torch.Tensor, stream=None) -> None
 
 
 def lvr_query(h, q, tau, out_idx, out_count, stream=None) -> None:
-    cap = out_idx.shape[-1]
-    _check(lib().lvr_query(h, _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
-                           _dev(out_idx, torch.int32, "out_idx"), _dev(out_count, torch.int32, "out_count"),
-                           cap, _stream(stream)), "lvr_query")
+    st = _stream(stream)
+    code = _call.query(h, q, tau, out_idx, out_count, st) if _lib is not None and _call is not None else None
+    if code is None:   # not all plain tensors of the right type, or the first call
+        code = lib().lvr_query(h, _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
+                               _dev(out_idx, torch.int32, "out_idx"), _dev(out_count, torch.int32, "out_count"),
+                               out_idx.shape[-1], st)
+    if code != LVR_OK:
+        raise LouverError(code, "lvr_query")
 
 
 def lvr_query1(h, q, tau_s, tau, out_idx, out_count, stream=None) -> None:
@@ -234,47 +258,64 @@ def lvr_subspace_thresholds(h, q, tau, tau_s_out, stream=None) -> None:
 
 
 def lvr_sparse_attention(h, q, idx, count, out, stream=None) -> None:
-    cap = idx.shape[-1]
-    _check(lib().lvr_sparse_attention(h, _dev(q, torch.float32, "q"), _dev(idx, torch.int32, "idx"),
-                                      _dev(count, torch.int32, "count"), cap, _dev(out, torch.float32, "out"),
-                                      _stream(stream)), "lvr_sparse_attention")
+    st = _stream(stream)
+    code = _call.sparse_attention(h, q, idx, count, out, st) if _lib is not None and _call is not None else None
+    if code is None:   # not all plain tensors of the right type, or the first call
+        code = lib().lvr_sparse_attention(h, _dev(q, torch.float32, "q"), _dev(idx, torch.int32, "idx"),
+                                          _dev(count, torch.int32, "count"), idx.shape[-1],
+                                          _dev(out, torch.float32, "out"), st)
+    if code != LVR_OK:
+        raise LouverError(code, "lvr_sparse_attention")
 
 
 def lvr_sparse_attention_static(K, V, q, idx, count, out, scale=0.0, stream=None) -> None:
     """K, V: contiguous device tensors [batch][n_kv_heads][n][128] (bf16 or fp32); no index object."""
-    if K.dim() != 4 or V.shape != K.shape or K.dtype != V.dtype:
-        raise ValueError("K and V must be [batch][n_kv_heads][n][head_dim] of one dtype")
-    if K.dtype not in (torch.bfloat16, torch.float32):
-        raise ValueError("K and V must be bf16 or fp32")
-    cap = idx.shape[-1]
-    _check(lib().lvr_sparse_attention_static(_dev(K, name="K"), _dev(V, name="V"), K.shape[2],
-                                             LVR_BF16 if K.dtype == torch.bfloat16 else LVR_F32, K.shape[0],
-                                             q.shape[1], K.shape[1], float(scale), _dev(q, torch.float32, "q"),
-                                             _dev(idx, torch.int32, "idx"), _dev(count, torch.int32, "count"), cap,
-                                             _dev(out, torch.float32, "out"), _stream(stream)),
-           "lvr_sparse_attention_static")
+    st = _stream(stream)
+    code = _call.sparse_attention_static(K, V, q, idx, count, out, scale, st) if _lib is not None and _call is not None else None
+    if code is None:   # not all plain tensors of the right type, or the first call
+        if K.dim() != 4 or V.shape != K.shape or K.dtype != V.dtype:
+            raise ValueError("K and V must be [batch][n_kv_heads][n][head_dim] of one dtype")
+        if K.dtype not in (torch.bfloat16, torch.float32):
+            raise ValueError("K and V must be bf16 or fp32")
+        code = lib().lvr_sparse_attention_static(_dev(K, name="K"), _dev(V, name="V"), K.shape[2],
+                                                 LVR_BF16 if K.dtype == torch.bfloat16 else LVR_F32, K.shape[0],
+                                                 q.shape[1], K.shape[1], float(scale), _dev(q, torch.float32, "q"),
+                                                 _dev(idx, torch.int32, "idx"), _dev(count, torch.int32, "count"),
+                                                 idx.shape[-1], _dev(out, torch.float32, "out"), st)
+    if code != LVR_OK:
+        raise LouverError(code, "lvr_sparse_attention_static")
 
 
 def lvr_decode_step(h, q, tau, out, out_idx, out_count, stream=None) -> None:
-    cap = out_idx.shape[-1]
-    _check(lib().lvr_decode_step(h, _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
-                                 _dev(out, torch.float32, "out"), _dev(out_idx, torch.int32, "out_idx"),
-                                 _dev(out_count, torch.int32, "out_count"), cap, _stream(stream)),
-           "lvr_decode_step")
+    st = _stream(stream)
+    code = _call.decode_step(h, q, tau, out, out_idx, out_count, st) if _lib is not None and _call is not None else None
+    if code is None:   # not all plain tensors of the right type, or the first call
+        code = lib().lvr_decode_step(h, _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
+                                     _dev(out, torch.float32, "out"), _dev(out_idx, torch.int32, "out_idx"),
+                                     _dev(out_count, torch.int32, "out_count"), out_idx.shape[-1], st)
+    if code != LVR_OK:
+        raise LouverError(code, "lvr_decode_step")
 
 
 def lvr_append_decode_step(h, k_new, v_new, q, tau, out, out_idx, out_count, stream=None) -> None:
-    cap = out_idx.shape[-1]
-    _check(lib().lvr_append_decode_step(h, _dev(k_new, name="k_new"), _dev(v_new, name="v_new"), k_new.shape[2],
-                                        _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
-                                        _dev(out, torch.float32, "out"), _dev(out_idx, torch.int32, "out_idx"),
-                                        _dev(out_count, torch.int32, "out_count"), cap, _stream(stream)),
-           "lvr_append_decode_step")
+    st = _stream(stream)
+    code = _call.append_decode_step(h, k_new, v_new, q, tau, out, out_idx, out_count, st) if _lib is not None and _call is not None else None
+    if code is None:   # not all plain tensors of the right type, or the first call
+        code = lib().lvr_append_decode_step(h, _dev(k_new, name="k_new"), _dev(v_new, name="v_new"), k_new.shape[2],
+                                            _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
+                                            _dev(out, torch.float32, "out"), _dev(out_idx, torch.int32, "out_idx"),
+                                            _dev(out_count, torch.int32, "out_count"), out_idx.shape[-1], st)
+    if code != LVR_OK:
+        raise LouverError(code, "lvr_append_decode_step")
 
 
 def lvr_dense_attention(h, q, out, stream=None) -> None:
-    _check(lib().lvr_dense_attention(h, _dev(q, torch.float32, "q"), _dev(out, torch.float32, "out"),
-                                     _stream(stream)), "lvr_dense_attention")
+    st = _stream(stream)
+    code = _call.dense_attention(h, q, out, st) if _lib is not None and _call is not None else None
+    if code is None:   # not all plain tensors of the right type, or the first call
+        code = lib().lvr_dense_attention(h, _dev(q, torch.float32, "q"), _dev(out, torch.float32, "out"), st)
+    if code != LVR_OK:
+        raise LouverError(code, "lvr_dense_attention")
 
 
 def lvr_get_stats(h, raise_on_overflow: bool = True) -> dict:

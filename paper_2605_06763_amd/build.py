@@ -1,4 +1,4 @@
-"""Compile the HIP sources under csrc/ into one in-tree shared library for gfx950."""
+"""Compile the HIP sources under csrc/ into one in-tree shared library for gfx950, and the Python module that calls it."""
 from __future__ import annotations
 
 import glob
@@ -9,6 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "liblouver.so")
+CALL_PATH = os.path.join(_HERE, "_call.so")   # the Python module of the decode loop's calls (csrc/pycall.cpp, host code only)
 OBJ_DIR = os.path.join(_HERE, "_build")
 
 HIPCC_FLAGS = [
@@ -28,8 +29,21 @@ def sources() -> list[str]:
 def _run(cmd: list[str]) -> str:
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + res.stdout + res.stderr)
+        raise RuntimeError("compiler failed: " + " ".join(cmd) + "\n" + res.stdout + res.stderr)
     return res.stderr
+
+
+def _call_command() -> list[str]:
+    """The host compiler's line for the Python module: torch's headers, nothing of the GPU."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"]]
+    cmd += ["-isystem" + p for p in cpp_extension.include_paths()]
+    cmd += [os.path.join(CSRC, "pycall.cpp"), "-o", CALL_PATH]
+    return cmd + ["-L" + p for p in cpp_extension.library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"]
 
 
 def build_library(verbose: bool = False, jobs: int | None = None) -> str:
@@ -40,7 +54,9 @@ def build_library(verbose: bool = False, jobs: int | None = None) -> str:
     objs = [os.path.join(OBJ_DIR, os.path.basename(s)[:-4] + ".o") for s in srcs]
     jobs = jobs or min(len(srcs), os.cpu_count() or 1, 16)
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        call = pool.submit(_run, _call_command())
         logs = list(pool.map(lambda so: _run([hipcc, *HIPCC_FLAGS, "-c", so[0], "-o", so[1]]), zip(srcs, objs)))
+        logs.append(call.result())
     logs.append(_run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]))
     if verbose:
         # the host pass does not know the packed-fp32 feature name and says so; that is expected

@@ -100,3 +100,19 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_calls_of_the_decode_loop_refuse_what_the_general_binding_refuses(L):
+    """Arguments that are no plain device tensors of the right type go to the general binding, which raises as it always did."""
+    import torch
+    h, st = C.c_void_p(0), C.c_void_p(0)
+    f, i = torch.zeros(1, 2, 128), torch.zeros(1, 2, 8, dtype=torch.int32)
+    K = torch.zeros(1, 1, 4, 128)
+    for call in (lambda: L.lvr_query(h, f, f, i, i, st), lambda: L.lvr_decode_step(h, f, f, f, i, i, st),
+                 lambda: L.lvr_append_decode_step(h, K, K, f, f, f, i, i, st), lambda: L.lvr_sparse_attention(h, f, i, i, f, st),
+                 lambda: L.lvr_dense_attention(h, f, f, st), lambda: L.lvr_sparse_attention_static(K, K, f, i, i, f, 0.0, st),
+                 lambda: L.tensor_arg(f)):
+        with pytest.raises(ValueError, match="must be a device tensor"):
+            call()
+    with pytest.raises(ValueError, match="of one dtype"):
+        L.lvr_sparse_attention_static(K, K.bfloat16(), f, i, i, f, 0.0, st)

@@ -483,3 +483,50 @@ def test_threshold_gap_and_mean(G, R, n):
         d = s[:-1] - s[1:]
         assert gap[0, h] == (s[int(np.argmax(d))] if d.size else s[0]), h
         assert mean[0, h] == np.float32(0.5 * (s[0] + s.sum() / s.size)), h
+
+
+def test_marshalled_and_plain_arguments_are_the_same_call(G, oracle):
+    """Every entry point of a decode loop with tensors, with arguments marshalled once, and with both; on a stream given as an object,
+    as a handle and not at all; wrong types and strides are refused either way."""
+    L = G.L
+    g = np.random.default_rng(5)
+    n = 700
+    K = W.round_to_bf16(g.standard_normal((1, 2, n, 128)).astype(np.float32))
+    q = g.standard_normal((1, 8, 128)).astype(np.float32)
+    with G.Index(K, K, "bf16", 8, capacity=n + 8, group_size=1) as ix:
+        tau = torch.from_numpy(G.oracle_taus(oracle, ix, q, frac=0.05).astype(np.float32)).cuda()
+        qd = torch.from_numpy(q).cuda()
+        out, idx, cnt = torch.empty(1, 8, 128, device="cuda"), torch.zeros(1, 8, n + 8, dtype=torch.int32, device="cuda"), torch.zeros(1, 8, dtype=torch.int32, device="cuda")
+        k = G.to_device(K[:, :, :1].copy(), "bf16")
+        other = torch.cuda.Stream()
+        A = L.tensor_arg
+        results = []
+        for form in range(4):
+            w = (lambda t: t) if form == 0 else (A if form == 1 else (lambda t: A(t) if t.dtype == torch.int32 else t))
+            st = (None, L.stream_arg(), other, torch.cuda.current_stream())[form]
+            out.fill_(float("nan"))
+            torch.cuda.synchronize()
+            L.lvr_query(ix.h, w(qd), w(tau), w(idx), w(cnt), st)
+            L.lvr_sparse_attention(ix.h, w(qd), w(idx), w(cnt), w(out), st)
+            torch.cuda.synchronize()
+            listed = out.clone()
+            L.lvr_sparse_attention_static(ix.Kd, ix.Vd, w(qd), w(idx), w(cnt), w(out), 0.0, st)
+            torch.cuda.synchronize()
+            static = out.clone()
+            L.lvr_decode_step(ix.h, w(qd), w(tau), w(out), w(idx), w(cnt), st)
+            torch.cuda.synchronize()
+            step = out.clone()
+            L.lvr_dense_attention(ix.h, w(qd), w(out), st)
+            torch.cuda.synchronize()
+            results.append((listed, static, step, out.clone(), cnt.clone()))
+        for r in results[1:]:
+            for a, b in zip(results[0], r):
+                assert torch.allclose(a.float(), b.float(), rtol=0, atol=1e-5)   # lists come in another order
+        L.lvr_append_decode_step(ix.h, A(k), k, A(qd), tau, out, A(idx), cnt)
+        torch.cuda.synchronize()
+        assert L.lvr_length(ix.h)[0] == n + 1
+        for bad in (qd.double(), qd.transpose(1, 2), qd.cpu()):
+            with pytest.raises(ValueError):
+                L.lvr_decode_step(ix.h, bad, tau, out, idx, cnt)
+        with pytest.raises(ValueError):
+            L.lvr_query(ix.h, A(qd), A(tau), A(tau), cnt)
