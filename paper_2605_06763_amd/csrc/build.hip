@@ -304,6 +304,8 @@ __global__ void __launch_bounds__(256)
 build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__restrict__ radii, int64_t cap_rows,
                      int64_t max_groups, int64_t g0, int64_t g1, int r, const BuildSrc src, const int8_t *__restrict__ chan) {
     constexpr int KEEP = R ? R : 1;
+    __shared__ uint4 s_codes[64 * 6];    // 96 bytes of codes per group
+    __shared__ uint32_t s_rec[64 * 3];   // 12 bytes of radii and scales
     const int bh = blockIdx.y;
     const int b = threadIdx.x & 3;
     int64_t g = g0 + (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2);
@@ -390,8 +392,8 @@ build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__
     const lvr_u32x6 code = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, scale);
     // from here on: the centre as stored (decoded by the conversion the query kernel uses, in its fp32 form)
     const lvr_f32x32 dec = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(code, scale);
-    if (valid) {
-        uint2 *dst = reinterpret_cast<uint2 *>(static_cast<char *>(centres) + ((int64_t)bh * max_groups + g) * (LVR_D * 3 / 4) + b * 24);
+    {
+        uint2 *dst = reinterpret_cast<uint2 *>(s_codes) + (threadIdx.x >> 2) * 12 + b * 3;
         dst[0] = make_uint2(code[0], code[1]);
         dst[1] = make_uint2(code[2], code[3]);
         dst[2] = make_uint2(code[4], code[5]);
@@ -442,10 +444,16 @@ build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__
     uint32_t scales = (uint32_t)(E + 127) << (8 * b);
     scales |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)scales, 0xB1, 0xf, 0xf, false);
     scales |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)scales, 0x4E, 0xf, 0xf, false);
-    if (valid && b != 3) {   // 12-byte record: two words of radii (lanes 0 and 2 hold them), then the scale bytes
-        uint32_t *rec = reinterpret_cast<uint32_t *>(radii) + ((int64_t)bh * max_groups + g) * 3;
-        rec[b == 0 ? 0 : (b == 2 ? 1 : 2)] = b == 1 ? scales : mine | (next << 16);
-    }
+    if (b != 3)   // 12-byte record: two words of radii (lanes 0 and 2 hold them), then the scale bytes
+        s_rec[(threadIdx.x >> 2) * 3 + (b == 0 ? 0 : (b == 2 ? 1 : 2))] = b == 1 ? scales : mine | (next << 16);
+    // out in whole lines: the pieces of the lanes side by side wrote 10 % more bytes to memory than they held
+    __syncthreads();
+    const int64_t first = g0 + (int64_t)blockIdx.x * 64;
+    const int groups = g1 - first < 64 ? (int)(g1 - first) : 64;
+    uint4 *out = reinterpret_cast<uint4 *>(static_cast<char *>(centres) + ((int64_t)bh * max_groups + first) * (LVR_D * 3 / 4));
+    for (int i = threadIdx.x; i < groups * 6; i += 256) out[i] = s_codes[i];
+    uint32_t *rec = reinterpret_cast<uint32_t *>(radii) + ((int64_t)bh * max_groups + first) * 3;
+    if ((int)threadIdx.x < groups * 3) rec[threadIdx.x] = s_rec[threadIdx.x];
 }
 
 // Axis-aligned box of every group (appendix "Ablation on Index Design", Def. 1): per coordinate the
