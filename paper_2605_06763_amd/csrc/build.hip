@@ -290,7 +290,10 @@ build_groups_kernel(void *__restrict__ K, void *__restrict__ centres, float *__r
 // add up over the quad is two lane exchanges per radius.  A wave stores 16 groups' codes as 1536 consecutive bytes.
 // R = group size up to four (the members stay in registers between the two passes); R = 0: any r, members read twice.
 // Bound by memory: K in, K out and 108 bytes per group (650 MB for 8 heads of 131072 keys).  With 16 lanes per group, a software encoder
-// and a four-step exchange per reduction the vector ALU took longer than the traffic, 223 us; now 113 us (5.8 TB/s).
+// and a four-step exchange per reduction the vector ALU took longer than the traffic, 223 us; with four lanes 113-119 us.  Now 106 us: a lane's
+// pieces of a row are 64 bytes apart, so what a wave stored at once were halves of lines, and the codes and records partial ones (420 MB
+// written for 381 MB).  Rows (group sizes up to four), codes and records go through LDS and leave in whole lines.  Builds, us, before and after: 8 x 32768 keys
+// 59.5 / 53.9, 128 x 32768 843 / 793, 8 x 131072 in groups of 1 (token-major), 2, 4: 221 / 209, 208 / 193, 206 / 185.
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float lvr_f32x16;
 
 __device__ __forceinline__ float quad_sum(float v) {
@@ -306,6 +309,8 @@ build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__
     constexpr int KEEP = R ? R : 1;
     __shared__ uint4 s_codes[64 * 6];    // 96 bytes of codes per group
     __shared__ uint32_t s_rec[64 * 3];   // 12 bytes of radii and scales
+    constexpr bool STAGED = R != 0;      // the rows stay until the whole workgroup writes them
+    __shared__ uint4 s_row[STAGED ? 64 * R * 16 : 1];
     const int bh = blockIdx.y;
     const int b = threadIdx.x & 3;
     int64_t g = g0 + (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2);
@@ -323,6 +328,11 @@ build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__
         for (int kk = 0; kk < 4; ++kk) w[kk] = p[kk * 4];
     };
     auto keep_row = [&](int m, const uint4 (&w)[4]) {   // the arena's copy of the row
+        if constexpr (STAGED) {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) s_row[((threadIdx.x >> 2) * R + m) * 16 + b + kk * 4] = w[kk];
+            return;
+        }
         uint4 *p = reinterpret_cast<uint4 *>(Kb + (g * members + m) * (LVR_D * 2)) + b;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
@@ -446,10 +456,19 @@ build_groups6_kernel(void *__restrict__ K, void *__restrict__ centres, float *__
     scales |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)scales, 0x4E, 0xf, 0xf, false);
     if (b != 3)   // 12-byte record: two words of radii (lanes 0 and 2 hold them), then the scale bytes
         s_rec[(threadIdx.x >> 2) * 3 + (b == 0 ? 0 : (b == 2 ? 1 : 2))] = b == 1 ? scales : mine | (next << 16);
-    // out in whole lines: the pieces of the lanes side by side wrote 10 % more bytes to memory than they held
     __syncthreads();
     const int64_t first = g0 + (int64_t)blockIdx.x * 64;
     const int groups = g1 - first < 64 ? (int)(g1 - first) : 64;
+    if constexpr (STAGED) {
+        if (from_src) {
+            lvr_u32x4 *rows = reinterpret_cast<lvr_u32x4 *>(Kb + first * R * (LVR_D * 2));
+#pragma unroll
+            for (int u = 0; u < 4 * R; ++u) {
+                const int i = threadIdx.x + 256 * u;
+                if (i < groups * R * 16) __builtin_nontemporal_store(__builtin_bit_cast(lvr_u32x4, s_row[i]), rows + i);
+            }
+        }
+    }
     uint4 *out = reinterpret_cast<uint4 *>(static_cast<char *>(centres) + ((int64_t)bh * max_groups + first) * (LVR_D * 3 / 4));
     for (int i = threadIdx.x; i < groups * 6; i += 256) out[i] = s_codes[i];
     uint32_t *rec = reinterpret_cast<uint32_t *>(radii) + ((int64_t)bh * max_groups + first) * 3;
