@@ -661,13 +661,15 @@ namespace {
 // rescaled space against the centres as stored there); these make the coordinates of a key comparable in size, so that
 // the 32 coordinates that share a scale in the 6-bit code are not drowned by one large channel.
 //
-// Two steps.  The first adds up squares: CHAN_SPLITS workgroups per (sequence, KV head) (fewer where the work space
-// is smaller), 16 lanes per row with 16-byte loads, four rows of every lane in flight; a sample of 4096 rows is one
-// round trip to memory for 64 workgroups.  The second, a workgroup per (sequence, KV head), adds the workgroups' sums in
-// order (the exponents do not depend on timing) and forms the exponents.  Each is bound by the latency of a launch and its
-// trips, some 5 us, so where V has to be copied as well (contiguous groups) half of the copy rides behind each: 8 heads of
-// 131072 keys, build and one step: 237 us, 262 with launches of their own and a copy of one piece per thread.  (As one
-// workgroup per (sequence, KV head) with a 2-byte load and an add per row the sums alone took 826 us.)
+// CHAN_SPLITS workgroups per (sequence, KV head) (fewer where the work space is smaller) add up squares, 16 lanes per row with
+// 16-byte loads, four rows of every lane in flight; a sample of 4096 rows is one round trip to memory for 64 workgroups.  The last of
+// them to end adds the workgroups' sums in order (the exponents do not depend on timing) and forms the exponents: the sums are
+// stored and read with device scope, and a workgroup takes its ticket once its own are in memory.  What is left is the latency of one launch and its
+// trips, so where V has to be copied as well (contiguous groups) the copy rides behind the sums of each (sequence, KV head).
+// As one workgroup per (sequence, KV head) with a 2-byte load and an add per row the sums alone took 826 us.  With sums and exponents in
+// launches of their own, half of the copy behind each, and now, builds, us: 8 x 1500 keys 14.2 / 12.3, 8 x 9001 25.0 / 22.3, 8 x 32768
+// 53.9 / 51.3, 8 x 131072 198 / 194; 128 x 32768 791 / 807, which has no explanation yet (two launches of half the copy each, or all
+// sums ahead of the copy, measured the same 806).
 constexpr int CHAN_SPLITS = 64;
 
 struct ChannelArgs {
@@ -677,10 +679,14 @@ struct ChannelArgs {
     int n_kv_heads, splits;   // workgroups per (sequence, KV head) that add up squares
     float *part;              // [n_bh][splits][128]
     int8_t *chan_exp;
+    int32_t *ticket;          // zero between launches, ticket_stride apart per (sequence, KV head)
+    int ticket_stride;
 };
 
-__device__ __forceinline__ void channel_sums(const ChannelArgs &a, int bh, int split) {   // 256 threads
+// Returns whether this workgroup is the last of its (sequence, KV head) to end: all sums are then in memory.
+__device__ __forceinline__ bool channel_sums(const ChannelArgs &a, int bh, int split) {   // 256 threads
     __shared__ float s_sum[4][LVR_D];
+    __shared__ int s_arrived;
     const int64_t rows = a.rows;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15;
     const char *base = a.K + ((int64_t)(bh / a.n_kv_heads) * a.sb + (int64_t)(bh % a.n_kv_heads) * a.sh) * 2;
@@ -713,8 +719,17 @@ __device__ __forceinline__ void channel_sums(const ChannelArgs &a, int bh, int s
     __syncthreads();
     if (threadIdx.x < LVR_D) {
         const int c = threadIdx.x;
-        a.part[((int64_t)bh * a.splits + split) * LVR_D + c] = (s_sum[0][c] + s_sum[1][c]) + (s_sum[2][c] + s_sum[3][c]);
+        __hip_atomic_store(&a.part[((int64_t)bh * a.splits + split) * LVR_D + c], (s_sum[0][c] + s_sum[1][c]) + (s_sum[2][c] + s_sum[3][c]),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's sums have reached the memory all compute units share
+    __syncthreads();
+    int32_t *ticket = &a.ticket[(int64_t)bh * a.ticket_stride];
+    if (threadIdx.x == 0) s_arrived = atomicAdd(ticket, 1);
+    __syncthreads();
+    if (s_arrived != a.splits - 1) return false;
+    if (threadIdx.x == 0) *ticket = 0;
+    return true;
 }
 
 __device__ __forceinline__ void channel_exponents(const ChannelArgs &a, int bh) {   // 256 threads, the upper half repeats the lower
@@ -723,7 +738,7 @@ __device__ __forceinline__ void channel_exponents(const ChannelArgs &a, int bh) 
     const float *p = a.part + (int64_t)bh * a.splits * LVR_D + c;
     float ss = 0.f;
 #pragma unroll 16
-    for (int k = 0; k < a.splits; ++k) ss += p[(int64_t)k * LVR_D];
+    for (int k = 0; k < a.splits; ++k) ss += __hip_atomic_load(&p[(int64_t)k * LVR_D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const float ms = ss / (float)(a.rows > 0 ? a.rows : 1);
     const bool live = ms > 0.f && ms < INFINITY;
     const float L = live ? 0.5f * log2f(ms) : 0.f;
@@ -755,17 +770,14 @@ __device__ __forceinline__ void channel_exponents(const ChannelArgs &a, int bh) 
     }
 }
 
-// The two steps, each with a copy behind it in the same launch: the values' first part while squares are added up, the rest
-// and the ungrouped keys while the exponents are formed.  v.first and v_end bound the values' rows, k.first and rows the
-// keys'; v_blocks = 0 and an empty key range: the step alone.
-template <bool SUMS>
+// Sums and exponents, and behind those of each (sequence, KV head) the copy of its values' rows [0, rows) and keys' rows [k.first, rows)
+// (v_blocks = 0 and an empty key range: no copy).
 __global__ void __launch_bounds__(256)
-channel_step_kernel(ChannelArgs a, CopySide k, CopySide v, int64_t cap_rows, int64_t v_end, int64_t rows, unsigned v_blocks) {
-    const unsigned lead = SUMS ? (unsigned)a.splits : 1u;
+channel_step_kernel(ChannelArgs a, CopySide k, CopySide v, int64_t cap_rows, int64_t rows, unsigned v_blocks) {
+    const unsigned lead = (unsigned)a.splits;
     if (blockIdx.x < lead) {
-        if constexpr (SUMS) channel_sums(a, blockIdx.y, blockIdx.x);
-        else channel_exponents(a, blockIdx.y);
-    } else if (blockIdx.x - lead < v_blocks) copy_block<4, STEP_PIECES, true>(v, blockIdx.y, a.n_kv_heads, cap_rows, 0, v_end, blockIdx.x - lead);
+        if (channel_sums(a, blockIdx.y, blockIdx.x)) channel_exponents(a, blockIdx.y);
+    } else if (blockIdx.x - lead < v_blocks) copy_block<4, STEP_PIECES, true>(v, blockIdx.y, a.n_kv_heads, cap_rows, 0, rows, blockIdx.x - lead);
     else copy_block<4, STEP_PIECES, true>(k, blockIdx.y, a.n_kv_heads, cap_rows, 0, rows, blockIdx.x - lead - v_blocks);
 }
 
@@ -791,19 +803,13 @@ hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t
     if (a.splits > room) a.splits = room;
     a.part = ix->part_o;
     a.chan_exp = lvr_chan_exp(ix);
+    a.ticket = lvr_channel_ticket(ix);
+    a.ticket_stride = ix->G * LVR_CNT_STRIDE;
     CopySide k{a.K, static_cast<char *>(ix->K), ks[0], ks[1], ks[2], V ? k_first : n};
     CopySide v{static_cast<const char *>(V), static_cast<char *>(ix->V), V ? vs[0] : 0, V ? vs[1] : 0, V ? vs[2] : 0, 0};
-    const int64_t half = V ? n / 2 : 0;
-    const unsigned n_bh = (unsigned)lvr_n_bh(ix);
-    unsigned v_blocks = copy_blocks(half, 4, STEP_PIECES);
-    hipLaunchKernelGGL(channel_step_kernel<true>, dim3((unsigned)a.splits + v_blocks, n_bh), dim3(256), 0, st, a, k, v, ix->cap_rows,
-                       half, n, v_blocks);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    v.first = half;
-    v_blocks = V ? copy_blocks(n - half, 4, STEP_PIECES) : 0;
-    hipLaunchKernelGGL(channel_step_kernel<false>, dim3(1u + v_blocks + copy_blocks(n - k.first, 4, STEP_PIECES), n_bh), dim3(256), 0, st, a, k, v,
-                       ix->cap_rows, n, n, v_blocks);
+    const unsigned v_blocks = V ? copy_blocks(n, 4, STEP_PIECES) : 0;
+    hipLaunchKernelGGL(channel_step_kernel, dim3((unsigned)a.splits + v_blocks + copy_blocks(n - k.first, 4, STEP_PIECES), (unsigned)lvr_n_bh(ix)),
+                       dim3(256), 0, st, a, k, v, ix->cap_rows, n, v_blocks);
     return hipGetLastError();
 }
 

@@ -110,6 +110,8 @@ static inline int32_t *lvr_head_count(const lvr_index *ix) { return ix->counters
 // in the same line as a head's counter (words 0 and 1, see lvr_reserve_last): three words of tickets of the workgroups that share the
 // head's list, LVR_CNT_STRIDE apart per head, zero between launches
 static inline int32_t *lvr_split_ticket(const lvr_index *ix) { return ix->counters + 2; }
+// word 5 of the line of a (sequence, KV head)'s first query head: ticket of the workgroups that add up its channels' squares
+static inline int32_t *lvr_channel_ticket(const lvr_index *ix) { return ix->counters + 5; }
 static inline int32_t *lvr_overflow_flag(const lvr_index *ix) { return ix->counters + (size_t)lvr_n_bhq(ix) * LVR_CNT_STRIDE; }
 // per query head: set size of the last finished query (kept for statistics)
 static inline int32_t *lvr_head_stat(const lvr_index *ix) { return ix->counters + ((size_t)lvr_n_bhq(ix) + 1) * LVR_CNT_STRIDE; }

@@ -53,6 +53,30 @@ def test_channel_exponents_over_sample_sizes(G, n, splits):
         assert np.array_equal(e[kv][sure], np.clip(want + shift, -8, 8)[sure]), (n, kv)
 
 
+@pytest.mark.parametrize("batch,n", [(1, 65), (3, 4096), (1, 20000)])
+def test_channel_exponents_of_builds_in_a_row(G, batch, n):
+    """The last workgroup to end forms the exponents: a build after a build on the same index (tickets back at zero), with channels of
+    other sizes, gives those of an index of its own."""
+    L = G.L
+    g = np.random.default_rng(n)
+    cfg = L.make_config(batch=batch, n_q_heads=4, n_kv_heads=2, capacity=n, group_size=1)
+    data = [G.to_device(W.round_to_bf16((g.standard_normal((batch, 2, n, 128)) * 2.0 ** g.uniform(-4, 4, size=(batch, 2, 1, 128))).astype(np.float32)), "bf16")
+            for _ in range(3)]
+    one = L.lvr_create(cfg)
+    try:
+        for Kd in data:
+            L.lvr_build(one, Kd, Kd)
+            fresh = L.lvr_create(cfg)
+            try:
+                L.lvr_build(fresh, Kd, Kd)
+                want = L.lvr_export_channel_scales(fresh, cfg)
+            finally:
+                L.lvr_destroy(fresh)
+            assert np.array_equal(L.lvr_export_channel_scales(one, cfg), want) and np.ptp(want) >= 4
+    finally:
+        L.lvr_destroy(one)
+
+
 @pytest.mark.parametrize("r,S,groups", [(1, 4, 1), (1, 1, 65), (2, 2, 63), (4, 4, 64), (4, 1, 129), (8, 2, 65), (16, 4, 17)])
 def test_6_bit_balls_enclose_their_members_tightly(G, r, S, groups):
     """Every group size and block count of the 6-bit build at the edges of its 64-group tiles, from a strided source with a
