@@ -44,8 +44,8 @@ __global__ void reservoir_update_kernel(int32_t *res, int R, uint64_t seed, int6
 // with one load and their rows are in flight together.  The order is found by counting: four threads per score compare it
 // with a quarter of the 256 each (16 broadcast reads of LDS), and the score goes to the place its rank says.
 // With four waves, a dependent load of position and row per four keys, a bitonic sort (36 barriers) and a serial count of
-// the valid scores the launch took 28 us for 32 heads, with rows in flight and ranks but four waves 12.9; now 7.0 (threshold and step:
-// 50.0, 33.6, 27.7 us).  The gaps and the mean are taken by
+// the valid scores the launch took 28 us for 32 heads, with rows in flight and ranks but four waves 12.9; then 7.0 (threshold and step:
+// 50.0, 33.6, 27.7 us), and with two instructions per compared pair instead of five 0.4 less (27.24 -> 26.81).  The gaps and the mean are taken by
 // all threads: by one thread, 4096 heads, of which only two workgroups of 16 waves fit a compute unit, took 99.3 and 76.9 us
 // where four waves each had taken 80.3 and 74.7; now 67.7 and 69.3.
 template <typename KT>
@@ -98,18 +98,25 @@ threshold_kernel(const void *__restrict__ K, const int32_t *__restrict__ pos_slo
     }
     __syncthreads();
     // descending order, equal scores in the order of their slots
-    const int j = t & 255, quarter = t >> 8;
+    const int j = t & 255, quarter = __builtin_amdgcn_readfirstlane(t >> 8);
     const uint32_t key = s_key[j];
     {
         int rank = 0;
+        auto count = [&](auto before) {   // before(o, i): score i comes before this thread's
 #pragma unroll
-        for (int i = quarter * 64; i < quarter * 64 + 64; i += 4) {
-            const uint4 o = *reinterpret_cast<const uint4 *>(&s_key[i]);
-            rank += (o.x > key || (o.x == key && i < j)) ? 1 : 0;
-            rank += (o.y > key || (o.y == key && i + 1 < j)) ? 1 : 0;
-            rank += (o.z > key || (o.z == key && i + 2 < j)) ? 1 : 0;
-            rank += (o.w > key || (o.w == key && i + 3 < j)) ? 1 : 0;
-        }
+            for (int i = quarter * 64; i < quarter * 64 + 64; i += 4) {
+                const uint4 o = *reinterpret_cast<const uint4 *>(&s_key[i]);
+                rank += before(o.x, i) ? 1 : 0;
+                rank += before(o.y, i + 1) ? 1 : 0;
+                rank += before(o.z, i + 2) ? 1 : 0;
+                rank += before(o.w, i + 3) ? 1 : 0;
+            }
+        };
+        // the slots of a quarter lie all below, all above or among those of a wave's threads: two instructions per pair instead of five
+        const int mine = __builtin_amdgcn_readfirstlane(j >> 6);
+        if (quarter < mine) count([&](uint32_t o, int) { return o >= key; });
+        else if (quarter > mine) count([&](uint32_t o, int) { return o > key; });
+        else count([&](uint32_t o, int i) { return o > key || (o == key && i < j); });
         s_rank[quarter][j] = rank;
     }
     const float score = __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xffffffffu));
