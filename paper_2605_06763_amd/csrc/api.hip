@@ -229,11 +229,11 @@ void prof_free(lvr_index *ix) {
     ix->prof_cap = ix->prof_used = ix->prof_on = 0;
 }
 
-// Sparse attention as one launch (a workgroup per head merges its splits in LDS) or as partials plus
-// a combine launch.  One launch wins whenever there are many heads in the batch or few keys per head;
-// with one sequence's 32 heads and several hundred retrieved keys each, 32 workgroups cannot gather
-// fast enough and the two-launch form wins (measured crossover: between 32k and 128k keys of context
-// at 0.5-1 % retrieved).  The set sizes are not known on the host, so the context length stands in.
+// Sparse attention with one workgroup per head (which merges its splits in LDS) or with P splits per head: partials and a
+// combine launch for lists that carry their scores, several workgroups per head that merge behind a ticket for the others.
+// One workgroup wins whenever there are many heads in the batch or few keys per head; with one sequence's 32 heads and several
+// hundred retrieved keys each, 32 workgroups cannot gather fast enough (measured crossover with the combine launch: between 32k
+// and 128k keys of context at 0.5-1 % retrieved).  The set sizes are not known on the host, so the context length stands in.
 inline bool one_launch_attention(const lvr_index *ix, bool carried = false) {
     if (ix->attn_one_launch >= 0) return ix->attn_one_launch != 0;
     // bf16 lists that carry their scores take the one-launch kernels with two dependent trips (two workgroups per head

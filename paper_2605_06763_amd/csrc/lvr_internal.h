@@ -33,8 +33,8 @@ struct lvr_index {
     int64_t n_total;       // keys held
     int64_t n_indexed;     // keys inside groups (multiple of r)
     int built;
-    int attn_one_launch;   // sparse attention as one workgroup per head (default) or partials + combine
-    int P;                 // attention splits of the two-launch form
+    int attn_one_launch;   // sparse attention as one workgroup per head (1), as P splits per head (0), or as the call decides (-1)
+    int P;                 // attention splits per head at most, where one workgroup does not take a head
     int P_dense;           // splits of the dense baseline
     float sigma;
     size_t elt;            // bytes per K/V element
@@ -137,8 +137,8 @@ static inline int8_t *lvr_chan_exp(const lvr_index *ix) {
 }
 
 // ---- launchers (each returns a hipError_t from hipGetLastError after the launch) ----
-// channel exponents from the keys about to be indexed (element strides ks for (sequence, head, token)); with V, the same
-// launches copy the value rows and the key rows from k_first on into the arena (lvr_launch_copy_kv at row 0)
+// channel exponents from the keys about to be indexed (element strides ks for (sequence, head, token)); one launch; with V it also
+// copies the value rows and the key rows from k_first on into the arena (lvr_launch_copy_kv at row 0)
 hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t ks[3], int64_t n, hipStream_t st,
                                      const void *V = nullptr, const int64_t *vs = nullptr, int64_t k_first = 0);
 // copies `rows` key rows and value rows into the arena starting at arena row dst_row0 (one launch)

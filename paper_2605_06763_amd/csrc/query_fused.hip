@@ -13,8 +13,8 @@
 //
 // Compared with two launches this keeps the survivor list on chip, builds the query operand
 // once per segment instead of twice, and removes one kernel tail from the step.
-// The per-head counters must be zero when the kernel starts; the kernels that publish the
-// counts (publish_counts_kernel, combine_kernel) clear them for the next query.
+// The per-head counters must be zero when the kernel starts; whatever publishes the counts clears them for the
+// next query: the head's last reservation (lvr_reserve_last) where a query hands the counts over itself, else the attention.
 #include <type_traits>
 
 #include <hip/hip_ext.h>

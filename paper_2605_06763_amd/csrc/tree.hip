@@ -27,7 +27,7 @@
 //
 // A build of 8 x 32768 bf16 keys in groups of four and one step, us: 2321 with one wave per SIMD on the statistics, a device-wide radix
 // sort per level and four waves per small node; 424 with a workgroup per node that splits, statistics over all rows in a launch per
-// level, and small nodes of 1024 entries whose rows came from memory at every level; 300 now.  Builds alone, that form and this one: 2048
+// level, and small nodes of 1024 entries whose rows came from memory at every level; 302 now.  Builds alone, that form and this one: 2048
 // keys 176 / 81 (4 x 4 heads), 9000 keys 276 / 157 (2 heads), 32768 fp32 keys 553 / 417, 131072 keys 1574 / 1245; one tree per coordinate block,
 // S = 16, 32768 keys 5514 / 3761.
 #include <type_traits>
