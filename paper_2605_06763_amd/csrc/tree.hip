@@ -23,7 +23,7 @@
 // order of the last split.
 //
 // Variances come from sums and sums of squares in fp64, and only the left half of a node's rows is added up for the level below:
-// the right half's sums are the node's less those.
+// the right half's sums are the node's less those, unless so little is left of them that the node's own rows are asked (unsure).
 //
 // A build of 8 x 32768 bf16 keys in groups of four and one step, us: 2321 with one wave per SIMD on the statistics, a device-wide radix
 // sort per level and four waves per small node; 424 with a workgroup per node that splits, statistics over all rows in a launch per
@@ -110,12 +110,13 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 
 // argmax over 128 channel variances (>= 0) held as (v0, v1) per lane; lowest channel wins ties.
 // [c_lo, c_hi): the coordinates that may be chosen (a tree over one coordinate block looks at that block only).
-// Non-negative doubles are ordered as their bits are: the upper words decide, the lower ones only where those tie.
-__device__ __forceinline__ int wave_argmax(double v0, double v1, int lane, int c_lo, int c_hi) {
+// Non-negative doubles are ordered as their bits are: the upper words decide, the lower ones only where those tie.  `top`: the largest's upper word.
+__device__ __forceinline__ int wave_argmax(double v0, double v1, int lane, int c_lo, int c_hi, int &top) {
     const bool may0 = 2 * lane >= c_lo && 2 * lane < c_hi, may1 = 2 * lane + 1 >= c_lo && 2 * lane + 1 < c_hi;
     const uint64_t u0 = (uint64_t)__double_as_longlong(v0), u1 = (uint64_t)__double_as_longlong(v1);
     const uint32_t h0 = may0 ? (uint32_t)(u0 >> 32) + 1u : 0u, h1 = may1 ? (uint32_t)(u1 >> 32) + 1u : 0u;
     const uint32_t best = wave_max(h0 > h1 ? h0 : h1);
+    top = (int)best - 1;
     uint64_t b0 = __ballot(h0 == best), b1 = __ballot(h1 == best);
     if ((int)__popcll(b0) + (int)__popcll(b1) > 1) {   // uniform
         const uint32_t l0 = h0 == best ? (uint32_t)u0 : 0u, l1 = h1 == best ? (uint32_t)u1 : 0u;
@@ -135,11 +136,35 @@ __device__ __forceinline__ double spread(double s, double q, double n) {
     return fmax(fma(n, q, -p) - fma(s, s, -p), 0.0);
 }
 
-// What is taken off every coordinate before it is squared: nothing for bf16 keys, whose sums are exact in fp64 wherever squares
-// of the mean cancel (eight significant bits); a key of the tree for fp32 ones.
+// Upper word of the largest of a node's sums of squares over the coordinates that may be chosen (beyond every number where one of them
+// is no number).
+__device__ __forceinline__ int largest_square(double q0, double q1, int lane, int c_lo, int c_hi) {
+    const bool may0 = 2 * lane >= c_lo && 2 * lane < c_hi, may1 = 2 * lane + 1 >= c_lo && 2 * lane + 1 < c_hi;
+    const uint32_t h0 = may0 ? (uint32_t)((uint64_t)__double_as_longlong(q0) >> 32) & 0x7fffffffu : 0u;
+    const uint32_t h1 = may1 ? (uint32_t)((uint64_t)__double_as_longlong(q1) >> 32) & 0x7fffffffu : 0u;
+    return (int)wave_max(h0 > h1 ? h0 : h1);
+}
+
+// Whether the largest spread of a node of m = 2^log_m keys (its upper word: top) may be made of rounding errors.  They are some 2^-53 m times
+// the sum of squares that the node's sums descend from, its own or, for differences, that of the last node above it whose rows were added up (`mag`:
+// the upper word of the largest).  22 binades between spread and square leave the largest variance good to about 1e-9.  Keys whose mean is 16 times
+// their deviation, seven right halves below the last rows added up, need 15 of them.  Where there are more, a key far off went left (its square, or
+// its infinity, is still in the difference), all keys are the same, or the shift is far from all of them: then the
+// node's own rows are added up, relative to its own first key.
+__device__ __forceinline__ bool unsure(int top, int mag, int log_m) { return top < mag + ((log_m - 22) << 20); }
+
+// What is taken off every coordinate before it is squared: nothing for bf16 keys, whose rows' sums are exact in fp64 wherever squares
+// of the mean cancel (eight significant bits); for fp32 ones a value among the tree's keys.
 struct Shift {
     double p0, p1;
 };
+
+// Sums relative to `from`, of n keys, as sums relative to `to`.
+__device__ __forceinline__ void shift_sums(double &s, double &q, double n, double from, double to) {
+    const double d = from - to;
+    q += d * (2.0 * s + n * d);
+    s += n * d;
+}
 
 // Adds the rows held in (x0, x1) to the sums.
 template <int ELT, int N>
@@ -194,15 +219,26 @@ __device__ __forceinline__ void sum_rows64(const TreeSrc &src, int bh, int lane,
     }
 }
 
-// The tree's first key (position 0), the shift of every node above the small ones.
+// A row of keys as a shift, where there is one.
 template <int ELT>
-__device__ __forceinline__ Shift tree_shift(const TreeSrc &src, int bh, int lane) {
+__device__ __forceinline__ Shift shift_of(const char *row, int lane) {
+    float x0 = 0.f, x1 = 0.f;
+    if constexpr (ELT == 4) lane_pair<ELT>(row, lane, x0, x1);
+    return Shift{(double)x0, (double)x1};
+}
+
+// The shift of every node above the small ones: in every channel the middle one of the first, a middle and the last key's values,
+// so that one key far from the others (often the first) does not move it.
+template <int ELT>
+__device__ __forceinline__ Shift tree_shift(const TreeSrc &src, int bh, int lane, int64_t n_real) {
     Shift p = {0.0, 0.0};
     if constexpr (ELT == 4) {
-        float x0, x1;
-        lane_pair<ELT>(src.row(bh, 0), lane, x0, x1);
-        p.p0 = (double)x0;
-        p.p1 = (double)x1;
+        float a0, a1, b0, b1, c0, c1;
+        lane_pair<ELT>(src.row(bh, 0), lane, a0, a1);
+        lane_pair<ELT>(src.row(bh, n_real >> 1), lane, b0, b1);
+        lane_pair<ELT>(src.row(bh, n_real - 1), lane, c0, c1);
+        p.p0 = (double)fmaxf(fminf(a0, b0), fminf(fmaxf(a0, b0), c0));   // (a NaN among them is passed over)
+        p.p1 = (double)fmaxf(fminf(a1, b1), fminf(fmaxf(a1, b1), c1));
     }
     return p;
 }
@@ -236,7 +272,7 @@ tree_stats_piece_kernel(TreeSrc src, const uint32_t *__restrict__ order, double 
     const int mypos = order ? (int)ord[i] : (int)i;
     const uint64_t real = __ballot(mypos < n_real);
     double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-    if (real) sum_rows64<ELT>(src, bh, lane, mypos, real, tree_shift<ELT>(src, bh, lane), s0, s1, q0, q1);   // uniform
+    if (real) sum_rows64<ELT>(src, bh, lane, mypos, real, tree_shift<ELT>(src, bh, lane, n_real), s0, s1, q0, q1);   // uniform
     store_partial<16>(sm, lane, wave, (int)(blockDim.x >> 6), s0, s1, q0, q1, partial + ((int64_t)bh * gridDim.x + blockIdx.x) * 256);
 }
 
@@ -246,14 +282,69 @@ struct LevelSums {
     const double *pieces;   // [n_bh][pieces of the tree][256]
     const double *parent;   // [n_bh][nodes of the level above][256]
     double *own;            // [n_bh][nodes of this level][256], or NULL where no level below needs them (then there may be more nodes than room)
+    const int *parent_mag;  // [n_bh][nodes of the level above]: what the rounding errors of their sums are measured by (unsure)
+    int *own_mag;
     int64_t n_pieces;
     int whole;
 };
 
+// Sums of the n real entries of a node (`order`: theirs, or NULL where entry i holds position node0 + i), relative to p, by a workgroup of NT threads;
+// threads 0 to 63 get those of their two channels.  Sixteen rows of every wave in flight.
+template <int ELT, int NT>
+__device__ __forceinline__ void own_sums(const TreeSrc &src, int bh, const uint32_t *__restrict__ order, int64_t node0, int64_t n, const Shift &p,
+                                         double (&sm)[NT / 128][256], double &s0, double &s1, double &q0, double &q1) {
+    constexpr int SL = NT / 128;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const char *base = src.row(bh, 0);
+    const int64_t row_bytes = src.st * ELT;
+    s0 = s1 = q0 = q1 = 0.;
+    for (int64_t e0 = wave * 64; e0 < n; e0 += NT) {   // uniform over the wave
+        const int rows = n - e0 < 64 ? (int)(n - e0) : 64;
+        const int mypos = lane < rows ? (order ? (int)order[e0 + lane] : (int)(node0 + e0 + lane)) : 0;
+        for (int j0 = 0; j0 < rows; j0 += 16) {
+            row_piece<ELT> w[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                w[u] = reinterpret_cast<const row_piece<ELT> *>(base + (int64_t)__builtin_amdgcn_readlane(mypos, j0 + u < rows ? j0 + u : 0) * row_bytes)[lane];
+            __builtin_amdgcn_sched_barrier(0);   // all of them requested before the first is used
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                float x0[1], x1[1];
+                unpack_pair<ELT>(w[u], x0[0], x1[0]);
+                if (j0 + u < rows) add_rows<ELT>(x0, x1, p, s0, s1, q0, q1);   // uniform
+            }
+        }
+    }
+    double *mine = sm[wave % SL];   // SL slices, twice as many waves
+    __syncthreads();
+    if (wave < SL) {
+        mine[2 * lane] = s0; mine[2 * lane + 1] = s1;
+        mine[128 + 2 * lane] = q0; mine[128 + 2 * lane + 1] = q1;
+    }
+    __syncthreads();
+    if (wave >= SL) {
+        mine[2 * lane] += s0; mine[2 * lane + 1] += s1;
+        mine[128 + 2 * lane] += q0; mine[128 + 2 * lane + 1] += q1;
+    }
+    __syncthreads();
+    if (t < 64) {
+        s0 = s1 = q0 = q1 = 0.;
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            s0 += sm[k][2 * t]; s1 += sm[k][2 * t + 1];
+            q0 += sm[k][128 + 2 * t]; q1 += sm[k][128 + 2 * t + 1];
+        }
+    }
+}
+
 // The axis of a node (every thread gets it); the first workgroup of a node also stores its sums for the level below.  NT threads.
-template <int NT>
-__device__ __forceinline__ int node_axis(const LevelSums &a, int bh, int64_t m, int64_t node, int64_t n_nodes, int64_t n_real, bool store,
-                                         int c_lo, int c_hi) {
+// Where the sums do not tell (unsure), each of the node's workgroups adds up all of its rows: no launch and no trip more where they do.  Builds of
+// 8 x 32768 bf16 keys, us: 270, with a key of -1e8 in every head 584 (its right-hand siblings ask, one node per level), all keys the same 700
+// (every right half asks).  Statistics over all rows at every level: 388, 388 and 489; differences without the question: 268, 269 and 338,
+// and in 73 of 126 builds with a key far off nodes that were not split on their widest axis.
+template <int ELT, int NT>
+__device__ __forceinline__ int node_axis(const LevelSums &a, const TreeSrc &src, const uint32_t *__restrict__ order, int bh, int64_t np, int64_t m,
+                                         int64_t node, int64_t n_nodes, int64_t n_real, bool store, int c_lo, int c_hi) {
     constexpr int SL = NT / 128;   // slices of the pieces side by side
     __shared__ double sm[SL][256];
     __shared__ int s_axis;
@@ -263,7 +354,9 @@ __device__ __forceinline__ int node_axis(const LevelSums &a, int bh, int64_t m, 
     const double *pp = a.pieces + ((int64_t)bh * a.n_pieces + first) * 256;
     const bool right = !a.whole && (node & 1);
     double e0 = 0., e1 = 0., f0 = 0., f1 = 0.;
+    int mag = 0;
     if (right && t < 64) {
+        mag = a.parent_mag[(int64_t)bh * (n_nodes >> 1) + (node >> 1)];
         const double *e = a.parent + ((int64_t)bh * (n_nodes >> 1) + (node >> 1)) * 256;
         e0 = e[2 * t]; e1 = e[2 * t + 1];
         f0 = e[128 + 2 * t]; f1 = e[128 + 2 * t + 1];
@@ -277,6 +370,16 @@ __device__ __forceinline__ int node_axis(const LevelSums &a, int bh, int64_t m, 
     sm[sl][c] = s;
     sm[sl][128 + c] = q;
     __syncthreads();
+    int64_t n = n_real - node * m;   // real keys fill a prefix of the entries
+    n = n < 0 ? 0 : (n > m ? m : n);
+    auto finish = [&](double s0, double s1, double q0, double q1, int mag, int axis) {   // threads 0 to 63
+        if (t == 0) s_axis = axis;
+        if (!store || !a.own) return;
+        double *o = a.own + ((int64_t)bh * n_nodes + node) * 256;
+        o[2 * t] = s0; o[2 * t + 1] = s1;
+        o[128 + 2 * t] = q0; o[128 + 2 * t + 1] = q1;
+        if (t == 0) a.own_mag[(int64_t)bh * n_nodes + node] = mag;
+    };
     if (t < 64) {
         double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
 #pragma unroll
@@ -288,24 +391,43 @@ __device__ __forceinline__ int node_axis(const LevelSums &a, int bh, int64_t m, 
             s0 = e0 - s0; s1 = e1 - s1;
             q0 = f0 - q0; q1 = f1 - q1;
         }
-        if (store && a.own) {
-            double *o = a.own + ((int64_t)bh * n_nodes + node) * 256;
-            o[2 * t] = s0; o[2 * t + 1] = s1;
-            o[128 + 2 * t] = q0; o[128 + 2 * t + 1] = q1;
-        }
-        int64_t n = n_real - node * m;   // real keys fill a prefix of the entries
-        n = n < 0 ? 0 : (n > m ? m : n);
-        const int ax = wave_argmax(spread(s0, q0, (double)n), spread(s1, q1, (double)n), t, c_lo, c_hi);
-        if (t == 0) s_axis = ax;
+        int top;
+        const int ax = wave_argmax(spread(s0, q0, (double)n), spread(s1, q1, (double)n), t, c_lo, c_hi, top);
+        if (!right) mag = largest_square(q0, q1, t, c_lo, c_hi);
+        // (one key has no axis; sums of bf16 rows are as good as sums relative to one of them)
+        const bool ask = n > 1 && (ELT == 4 || right) && unsure(top, mag, __builtin_ctzll(m));
+        finish(s0, s1, q0, q1, mag, ask ? -1 : ax);
     }
     __syncthreads();
-    return s_axis;
+    int axis = s_axis;
+    if (axis < 0) {   // uniform
+        const uint32_t *ord = order ? order + (int64_t)bh * np + node * m : nullptr;
+        const int lane = t & 63;
+        const Shift p = shift_of<ELT>(src.row(bh, ord ? (int64_t)ord[0] : node * m), lane);
+        double s0, s1, q0, q1;
+        own_sums<ELT, NT>(src, bh, ord, node * m, n, p, sm, s0, s1, q0, q1);
+        if (t < 64) {
+            int top;
+            const int ax = wave_argmax(spread(s0, q0, (double)n), spread(s1, q1, (double)n), t, c_lo, c_hi, top);
+            if constexpr (ELT == 4) {
+                const Shift to = tree_shift<ELT>(src, bh, lane, n_real);
+                shift_sums(s0, q0, (double)n, p.p0, to.p0);
+                shift_sums(s1, q1, (double)n, p.p1, to.p1);
+            }
+            finish(s0, s1, q0, q1, largest_square(q0, q1, t, c_lo, c_hi), ax);
+        }
+        __syncthreads();
+        axis = s_axis;
+    }
+    return axis;
 }
 
 // The axis of every node that a single workgroup splits.
+template <int ELT>
 __global__ void __launch_bounds__(1024)
-tree_axis_kernel(LevelSums sums, int32_t *__restrict__ axis, int64_t m, int64_t n_nodes, int64_t n_real, int c_lo, int c_hi) {
-    const int a = node_axis<1024>(sums, blockIdx.y, m, blockIdx.x, n_nodes, n_real, false, c_lo, c_hi);
+tree_axis_kernel(TreeSrc src, const uint32_t *__restrict__ order, LevelSums sums, int32_t *__restrict__ axis, int64_t np, int64_t m, int64_t n_nodes,
+                 int64_t n_real, int c_lo, int c_hi) {
+    const int a = node_axis<ELT, 1024>(sums, src, order, blockIdx.y, np, m, blockIdx.x, n_nodes, n_real, false, c_lo, c_hi);
     if (threadIdx.x == 0) axis[(int64_t)blockIdx.y * n_nodes + blockIdx.x] = a;
 }
 
@@ -323,7 +445,7 @@ tree_codes_kernel(TreeSrc src, const uint32_t *__restrict__ order, code_t<ELT> *
     if (t < 256) s_hist[t] = 0;
     const int64_t pos = order ? (int64_t)order[at] : i;
     const int ax = axis ? axis[(int64_t)bh * n_nodes + node]
-                        : node_axis<1024>(sums, bh, m, node, n_nodes, n_real, (int64_t)blockIdx.x * PIECE == node * m, c_lo, c_hi);
+                        : node_axis<ELT, 1024>(sums, src, order, bh, np, m, node, n_nodes, n_real, (int64_t)blockIdx.x * PIECE == node * m, c_lo, c_hi);
     const uint32_t c = pos < n_real ? coord_code<ELT>(src.row(bh, pos), ax) : PAD_CODE<ELT>;
     codes[at] = (code_t<ELT>)c;
     if (axis) return;   // uniform
@@ -399,7 +521,7 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
 #pragma unroll
         for (int k = 0; k < STEPS; ++k)
             if (k < parts) e[k] = pos_of(k * NT + t);   // uniform conditions throughout
-        const int ax = node_axis<NT>(sums, bh, m, node, n_nodes, n_real, mine == 0, c_lo, c_hi);
+        const int ax = node_axis<ELT, NT>(sums, src, order, bh, np, m, node, n_nodes, n_real, mine == 0, c_lo, c_hi);
 #pragma unroll
         for (int k = 0; k < STEPS; ++k)
             if (k < parts) {
@@ -486,7 +608,7 @@ tree_split_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint32_t *__r
     const int mypos = (lane < share && idx < n_left) ? (int)s_left[idx] : 0x7fffffff;
     const uint64_t real = __ballot(mypos < n_real);
     double s0 = 0., s1 = 0., q0 = 0., q1 = 0.;
-    if (real) sum_rows64<ELT>(src, bh, lane, mypos, real, tree_shift<ELT>(src, bh, lane), s0, s1, q0, q1);   // uniform
+    if (real) sum_rows64<ELT>(src, bh, lane, mypos, real, tree_shift<ELT>(src, bh, lane, n_real), s0, s1, q0, q1);   // uniform
     store_partial<NW>(s_part, lane, wave, NW, s0, s1, q0, q1, part_out + ((int64_t)bh * sums.n_pieces + blockIdx.x) * 256);
 }
 
@@ -742,6 +864,7 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
         shift.p1 = (double)x1;
     }
     double s0, s1, q0, q1;   // sums of this wave's node
+    int mag;                 // and what their rounding errors are measured by
     // sums of N rows: the entries that lanes `first` .. `first` + N - 1 hold in `ent`
     auto sum = [&](auto n_c, int ent, int first, double &a0, double &a1, double &b0, double &b1) {
         constexpr int N = decltype(n_c)::value;
@@ -776,14 +899,49 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
             a0 += a.x; a1 += a.y; b0 += b.x; b1 += b.y;
         }
     };
+    int ent = s_ent[wave * 32 + (lane & 31)];
     auto real_of = [&](int first, int m) { return nr <= first ? 0. : (nr - first < m ? (double)(nr - first) : (double)m); };
-    auto axis_of = [&](double a0, double a1, double b0, double b1, double n) {
-        return wave_argmax(spread(a0, b0, n), spread(a1, b1, n), lane, c_lo, c_hi);
+    // Axis of the node at entries [first, first + 2^log_m) of the order, from its sums; `difference`: they are one.  Where they do not
+    // tell, they are taken again from the node's real rows, relative to its first: add(shift, ...) adds those up.
+    auto axis_of = [&](double &a0, double &a1, double &b0, double &b1, int first, int log_m, bool difference, int first_ent, auto add) {
+        const double n = real_of(first, 1 << log_m);
+        int top;
+        int ax = wave_argmax(spread(a0, b0, n), spread(a1, b1, n), lane, c_lo, c_hi, top);
+        if (n > 1. && (ELT == 4 || difference) && unsure(top, mag, log_m)) {   // uniform over the wave
+            const Shift p = shift_of<ELT>(s_rows + first_ent * ROW, lane);
+            a0 = a1 = b0 = b1 = 0.;
+            add(p, (int)n);
+            ax = wave_argmax(spread(a0, b0, n), spread(a1, b1, n), lane, c_lo, c_hi, top);
+            if constexpr (ELT == 4) {
+                shift_sums(a0, b0, n, p.p0, shift.p0);
+                shift_sums(a1, b1, n, p.p1, shift.p1);
+            }
+            if (log_m >= 5) mag = largest_square(b0, b1, lane, c_lo, c_hi);   // (the wave's only node)
+        }
+        return ax;
+    };
+    // n rows: the entries that lanes `at` .. hold in `e`
+    auto add_some = [&](int e, int at, int n, const Shift &p, double &a0, double &a1, double &b0, double &b1) {
+for (int j0 = 0; j0 < n; j0 += 4) {
+            float x0[4], x1[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                lane_pair<ELT>(s_rows + __builtin_amdgcn_readlane(e, at + (j0 + u < n ? j0 + u : 0)) * ROW, lane, x0[u], x1[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float y0[1] = {x0[u]}, y1[1] = {x1[u]};
+                if (j0 + u < n) add_rows<ELT>(y0, y1, p, a0, a1, b0, b1);   // uniform
+            }
+        }
+    };
+    // the axis of a node of 32 entries or less that lanes `at` .. of `ent` hold
+    auto axis_in_wave = [&](double &a0, double &a1, double &b0, double &b1, int at, int log_m, bool difference) {
+        return axis_of(a0, a1, b0, b1, wave * 32 + at, log_m, difference, __builtin_amdgcn_readlane(ent, at),
+                       [&](const Shift &p, int n) { add_some(ent, at, n, p, a0, a1, b0, b1); });
     };
     auto code_of = [&](int e, int axis) { return e < nr ? coord_code<ELT>(s_rows + e * ROW, axis) : PAD_CODE<ELT>; };
     const int groups_of = np >> levels;   // entries of a finished node
     int m = np;
-    int ent = s_ent[wave * 32 + (lane & 31)];
     {
         double a0, a1, b0, b1;
         sum(N16{}, ent, 0, s0, s1, q0, q1);
@@ -791,6 +949,7 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
         s0 += a0; s1 += a1; q0 += b0; q1 += b1;
     }
     if (waves > 1) add_waves(waves, s0, s1, q0, q1);
+    mag = largest_square(q0, q1, lane, c_lo, c_hi);
     for (; m >= 64 && m > groups_of; m >>= 1) {   // uniform
         if (m < np) {   // the sums of this wave's node out of its parent's
             const int group = m / 16, parent = wave & ~(group - 1);   // the parent's waves
@@ -802,7 +961,11 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
             s0 = right ? s0 - a0 : a0; s1 = right ? s1 - a1 : a1;
             q0 = right ? q0 - b0 : b0; q1 = right ? q1 - b1 : b1;
         }
-        const int ax = axis_of(s0, s1, q0, q1, real_of(wave * 32 & ~(m - 1), m));
+        const int place = wave * 32 & ~(m - 1);
+        const bool difference = m < np && (place & m) != 0;
+        const int ax = axis_of(s0, s1, q0, q1, place, __builtin_ctz(m), difference, s_ent[place], [&](const Shift &p, int n) {
+            for (int j = 0; j < n; j += 32) add_some(s_ent[place + j + (lane & 31)], 0, n - j < 32 ? n - j : 32, p, s0, s1, q0, q1);
+        });
         if (lane == 0 && (wave & (m / 32 - 1)) == 0) s_axis[wave / (m / 32)] = ax;
         __syncthreads();
         const bool sorts = wave * 64 < np;   // an entry per thread: the waves that hold one
@@ -846,7 +1009,7 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
             ent = (int)(sort_in_wave(key, size) & (key_t)(NODE - 1));
         };
         if (m == 32) {
-            split(axis_of(s0, s1, q0, q1, real_of(place, 32)), 32);
+            split(axis_in_wave(s0, s1, q0, q1, 0, 5, np > 32 && (wave & 1)), 32);
             m = 16;
         }
         double a[2][4];   // the nodes of 16 (where the whole tree is smaller than 32 entries the second is empty)
@@ -854,8 +1017,8 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
             sum(N16{}, ent, 0, a[0][0], a[0][1], a[0][2], a[0][3]);
             a[1][0] = s0 - a[0][0]; a[1][1] = s1 - a[0][1]; a[1][2] = q0 - a[0][2]; a[1][3] = q1 - a[0][3];
             if (m == 16) {
-                const int x0 = axis_of(a[0][0], a[0][1], a[0][2], a[0][3], real_of(place, 16));
-                const int x1 = axis_of(a[1][0], a[1][1], a[1][2], a[1][3], real_of(place + 16, 16));
+                const int x0 = axis_in_wave(a[0][0], a[0][1], a[0][2], a[0][3], 0, 4, false);
+                const int x1 = axis_in_wave(a[1][0], a[1][1], a[1][2], a[1][3], 16, 4, true);
                 split((i & 16) ? x1 : x0, 16);
                 m = 8;
             }
@@ -867,8 +1030,9 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
                 for (int h = 0; h < 2; ++h) {
                     double b[4];
                     sum(N8{}, ent, 16 * h, b[0], b[1], b[2], b[3]);
-                    const int x0 = axis_of(b[0], b[1], b[2], b[3], real_of(place + 16 * h, 8));
-                    const int x1 = axis_of(a[h][0] - b[0], a[h][1] - b[1], a[h][2] - b[2], a[h][3] - b[3], real_of(place + 16 * h + 8, 8));
+                    double d[4] = {a[h][0] - b[0], a[h][1] - b[1], a[h][2] - b[2], a[h][3] - b[3]};
+                    const int x0 = axis_in_wave(b[0], b[1], b[2], b[3], 16 * h, 3, false);
+                    const int x1 = axis_in_wave(d[0], d[1], d[2], d[3], 16 * h + 8, 3, true);
                     if ((i >> 4) == h) axis = (i & 8) ? x1 : x0;
                 }
                 split(axis, 8);
@@ -880,7 +1044,7 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
             for (int h = 0; h < 8; ++h) {
                 double b[4];
                 sum(N4{}, ent, 4 * h, b[0], b[1], b[2], b[3]);
-                const int x = axis_of(b[0], b[1], b[2], b[3], real_of(place + 4 * h, 4));
+                const int x = axis_in_wave(b[0], b[1], b[2], b[3], 4 * h, 2, false);
                 if ((i >> 2) == h) axis = x;
             }
             split(axis, 4);
@@ -891,7 +1055,7 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
             for (int h = 0; h < 16; ++h) {
                 double b[4];
                 sum(N2{}, ent, 2 * h, b[0], b[1], b[2], b[3]);
-                const int x = axis_of(b[0], b[1], b[2], b[3], real_of(place + 2 * h, 2));
+                const int x = axis_in_wave(b[0], b[1], b[2], b[3], 2 * h, 1, false);
                 if ((i >> 1) == h) axis = x;
             }
             split(axis, 2);
@@ -933,7 +1097,9 @@ hipError_t tree_order_t(lvr_index *ix, const TreeSrc &src, int64_t n_real, int64
     // sums of pieces and of nodes, of two levels each
     const int64_t n_pieces = np > PIECE ? np / PIECE : 1;
     double *pieces[2], *node_sums[2];
+    int *node_mag[2];
     for (int i = 0; i < 2; ++i) {
+        node_mag[i] = reinterpret_cast<int *>(ix->tree_partial + (int64_t)4 * n_bh * n_pieces * 256) + (int64_t)i * n_bh * n_pieces;
         pieces[i] = ix->tree_partial + (int64_t)i * n_bh * n_pieces * 256;
         node_sums[i] = ix->tree_partial + (int64_t)(2 + i) * n_bh * n_pieces * 256;
     }
@@ -943,7 +1109,7 @@ hipError_t tree_order_t(lvr_index *ix, const TreeSrc &src, int64_t n_real, int64
         const int64_t n_nodes = (int64_t)1 << L, m = np >> L;
         const bool last = m / 2 <= SMALL_NODE<ELT>;   // small nodes take their own sums
         // (fp32: the last level's nodes of 512 entries are twice as many as there are pieces)
-        LevelSums sums{pieces[L & 1], node_sums[(L & 1) ^ 1], last ? nullptr : node_sums[L & 1], n_pieces, whole};
+        LevelSums sums{pieces[L & 1], node_sums[(L & 1) ^ 1], last ? nullptr : node_sums[L & 1], node_mag[(L & 1) ^ 1], node_mag[L & 1], n_pieces, whole};
         if (whole)
             hipLaunchKernelGGL(tree_stats_piece_kernel<ELT>, dim3((unsigned)n_pieces, (unsigned)n_bh),
                                dim3(np < PIECE ? (unsigned)np : (unsigned)PIECE), 0, st, src, cur, pieces[L & 1], np, n_real);
@@ -954,7 +1120,7 @@ hipError_t tree_order_t(lvr_index *ix, const TreeSrc &src, int64_t n_real, int64
     hipLaunchKernelGGL((tree_split_kernel<ELT, STEPS, GATHER, NT>), dim3((unsigned)(np / NT), (unsigned)n_bh), dim3(NT), 0, st, src, \
                        cur, next, codes, hist, sums, part_out, np, n_real, m, n_nodes, c_lo, c_hi)
         if (m > 32768) {   // more codes than the threads of a workgroup hold
-            hipLaunchKernelGGL(tree_axis_kernel, per_node, dim3(1024), 0, st, sums, ix->tree_axis, m, n_nodes, n_real, c_lo, c_hi);
+            hipLaunchKernelGGL(tree_axis_kernel<ELT>, per_node, dim3(1024), 0, st, src, cur, sums, ix->tree_axis, np, m, n_nodes, n_real, c_lo, c_hi);
             hipLaunchKernelGGL(tree_codes_kernel<ELT>, per_piece, dim3(1024), 0, st, src, cur, codes, hist, ix->tree_axis, sums, np, n_real,
                                m, n_nodes, c_lo, c_hi);
             hipLaunchKernelGGL(tree_split_large_kernel<ELT>, per_node, dim3(1024), 0, st, cur, next, codes, np, m);

@@ -158,8 +158,10 @@ def check_median_splits(x, got, r):
             v = halves[ent].astype(np.int64)
             var = len(ent) * (v * v).sum(axis=0) - v.sum(axis=0) ** 2
             return np.nonzero(var >= var.max() - var.max() * 1e-13)[0]   # fp64 sums of such values are exact, the quotient is rounded
-        v = x[ent] - x[ent].mean(axis=0)
-        var = (v * v).mean(axis=0)
+        with np.errstate(invalid="ignore"):
+            v = x[ent] - x[ent].mean(axis=0)
+            var = (v * v).mean(axis=0)
+        var = np.where(np.isfinite(var), var, 0.0)   # a node is not split on a coordinate that is no number in one of its keys
         return np.nonzero(var >= var.max() * (1 - 1e-10))[0]
 
     def walk(ent, at, m):   # ent: real entries of a node of m padded ones, ascending; its slots start at `at`
@@ -257,6 +259,43 @@ def test_tree_order_at_the_edges_of_its_launches(G, dtype, r, n, kind):
         check_median_splits(K[0, kv, :grouped].astype(np.float64), slot_pos[0, kv, :grouped], r)
         if chunk:
             check_median_splits(K[0, kv, :chunk].astype(np.float64), chunk_pos[0, kv], r)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("far", [-1e6, -1e8, 1e8, -1e30, -np.inf, np.inf, np.nan])
+@pytest.mark.parametrize("r,n,at", [(2, 12, 3), (4, 60, 0), (2, 250, 100), (4, 512, 0), (4, 1000, 700), (4, 2048, 0), (4, 6000, 5000), (8, 20000, 0),
+                                    (8, 36000, 7)])
+def test_a_key_far_off_does_not_blur_the_splits_of_the_others(G, dtype, far, r, n, at):
+    """One key, the first of the cache or another, is far off in the widest channel (or no number there), its neighbour in the next one, the other
+    way: a node's rows' squares reach neither the sums of the nodes beside it, which are differences, nor (fp32) the value that
+    all coordinates are taken relative to, so that every node of the others is still split on its own widest axis.  As a build and as a
+    buffer chunk."""
+    L = G.L
+    g = np.random.default_rng(n + at)
+    K = g.standard_normal((1, 2, n, 128))
+    K[..., :2] *= 3.0
+    other = -far if far == far else far
+    K[:, 0, at, 0] = far
+    K[:, 1, at, 1] = other
+    K[:, :, (at + 1) % n, 1] = other
+    K = W.round_to_bf16(K.astype(np.float32)) if dtype == "bf16" else K.astype(np.float32)
+    chunk = n // (16 * r) * 16 * r if n <= 2048 else 0
+    cfg = L.make_config(batch=1, n_q_heads=2, n_kv_heads=2, kv_dtype=L.LVR_BF16 if dtype == "bf16" else L.LVR_F32, capacity=n + chunk,
+                        group_size=r, grouping=L.LVR_GROUP_TREE, buffer_size=chunk if chunk else 16 * r)
+    h = L.lvr_create(cfg)
+    try:
+        Kd = G.to_device(K, dtype)
+        L.lvr_build(h, Kd, Kd)
+        orders = [L.lvr_export_index(h, cfg)[2][..., :n // r * r]]
+        if chunk:
+            L.lvr_build(h, Kd[:, :, :0], Kd[:, :, :0])
+            L.lvr_append(h, Kd[:, :, :chunk].contiguous(), Kd[:, :, :chunk].contiguous())
+            orders.append(L.lvr_export_index(h, cfg)[2][..., :chunk])
+    finally:
+        L.lvr_destroy(h)
+    for order in orders:
+        for kv in range(2):
+            check_median_splits(K[0, kv, :order.shape[-1]].astype(np.float64), order[0, kv], r)
 
 
 @pytest.mark.parametrize("hq,hkv,n,r,S,tail,kw", [
