@@ -137,8 +137,8 @@ typedef struct lvr_config {
     uint32_t flags;      /* lvr_flags                                                            */
     int64_t capacity;    /* max keys per (sequence, KV head): the arena is sized once (App. "GPU Update") */
     float scale;         /* sigma; 0 means 1/sqrt(head_dim)  (Sec. 2, "Attention")               */
-    int32_t attn_splits; /* P > 0: up to P partial-softmax splits per head, merged by the last of them to end
-                          *    (lists that carry their scores: by a combine launch);
+    int32_t attn_splits; /* P > 0 (at most 256): up to P partial-softmax splits per head, merged by the last of them
+                          *    to end, 64 of them at most (lists that carry their scores: P of them, by a combine launch);
                           * -1: one workgroup per head, 16 splits merged in LDS;
                           * 0: chosen per call: one workgroup per head for batches of 128 heads or more
                           *    and for contexts up to 65536 keys, else up to 64 splits              */
@@ -254,10 +254,9 @@ int lvr_sparse_attention(lvr_index *ix, const float *q_dev, const int32_t *idx_d
  * nothing is allocated or freed, by this call or by anything it uses: K_dev and V_dev are the
  * caller's own cache, contiguous [batch][n_kv_heads][n][128] of kv_dtype (rows 16-byte aligned),
  * positions in idx_dev are row numbers 0 .. n-1, and the splits keep their partial (m, l, o)
- * triples in a static device array inside the library (2.1 MiB per GPU, held until the process
+ * triples in a static device array inside the library (0.6 MiB per GPU, held until the process
  * ends) whose per-device address is looked up on the first call on that device.
- * Same kernel and same results as lvr_sparse_attention with attn_splits = 64 (up to 64 splits per
- * head).  scale = 0 means 1/sqrt(128).
+ * Same kernel and same results as lvr_sparse_attention with attn_splits = 64.  scale = 0 means 1/sqrt(128).
  * Limits: batch * n_q_heads <= 256 and n <= 2^30, else LVR_E_CAPACITY.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
  * streams, two threads) race on it and must be ordered by the caller.  The array keeps the last

@@ -40,7 +40,7 @@ __device__ __forceinline__ int64_t split_length(int64_t cnt, int P_max, int *use
     return L;
 }
 
-// One wave per split of a head's list, four waves to a workgroup, up to 256 splits.  The split's positions are fetched with one
+// One wave per part of a head's list, four waves to a workgroup, up to 64 workgroups.  The split's positions are fetched with one
 // coalesced load, then rows are gathered 16 at a time (K and V of four row-quads in flight together).  A workgroup merges
 // its waves in LDS; where a list fills more than one workgroup each of them stores its (m, l, o) and takes a ticket, and the one that
 // draws the last merges them all, which saves the launch that used to do it.  A fence per workgroup that makes everything written so far visible would cost
@@ -50,8 +50,10 @@ __device__ __forceinline__ int64_t split_length(int64_t cnt, int P_max, int *use
 // after every launch, and after any set of launches that overlapped against the rules.
 // us per call, a launch per stage and now, 80 / 330 / 1300 entries per head: 32 bf16 heads 7.4 / 7.8 / 9.6 and 5.7 / 6.1 / 8.4, 64 fp32 heads 8.9 /
 // 11.0 / 20.3 and 7.8 / 8.8 / 19.6, 256 bf16 heads 14.0 / 16.3 / - and 8.2 / 13.3 / -.  (Workgroups of 16 waves: 32 bf16 heads 5.0 / 7.8 / 10.9.)
+// 4000 / 8000 / 30000 entries, with room for as many: 32 bf16 heads 16.5 / 24.4 / 59.8 and 15.1 / 22.9 / 58.0, 32 fp32 heads 25.5 / 42.8 / 144.3 and
+// 24.1 / 41.7 / 150 (142 to 150), one fp32 head 10.5 / 14.7 / 64.3 and 8.7 / 9.8 / 24.8.
 // publish_count != NULL: the ticket's last also hands the head's counter over and clears it.
-constexpr int SPLIT_WAVES = 4, SPLIT_WGS_MAX = 16;
+constexpr int SPLIT_WAVES = 4, SPLIT_WGS_MAX = 64;   // 64 x 4: as many splits as lvr_create takes; a wave's lanes hold the partials' weights
 
 template <typename KT>
 __global__ void __launch_bounds__(64 * SPLIT_WAVES)
@@ -192,15 +194,20 @@ sparse_attention_kernel(const int32_t *count, const int32_t *__restrict__ idx,  
     }
     if (used_wgs <= 1) return;
     auto load = [](const float *x) { return __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    // at most 16 workgroups: lane p of every wave holds the weight of partial p
+    // lane p of every wave holds the weight of partial p
     const float m_p = lane < used_wgs ? load(&part_ml[(hq * wgs + lane) * 2]) : -INFINITY;
     const float l_p = lane < used_wgs ? load(&part_ml[(hq * wgs + lane) * 2 + 1]) : 0.f;
     const float *po = part_o + hq * wgs * LVR_D + ch;
-    constexpr int SLICES = SPLIT_WAVES / 2;
-    constexpr int EACH = SPLIT_WGS_MAX / SLICES;
+    constexpr int SLICES = SPLIT_WAVES / 2, EACH = 8;   // a slice takes every other partial, eight loads in flight
     float pv[EACH];
+    auto fetch = [&](int p0) {
 #pragma unroll
-    for (int i = 0; i < EACH; ++i) pv[i] = SLICES * i + slice < used_wgs ? load(&po[(SLICES * i + slice) * LVR_D]) : 0.f;
+        for (int i = 0; i < EACH; ++i) {
+            const int p = p0 + SLICES * i + slice;
+            pv[i] = p < used_wgs ? load(&po[(int64_t)p * LVR_D]) : 0.f;
+        }
+    };
+    fetch(0);
     M = m_p;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
@@ -209,8 +216,13 @@ sparse_attention_kernel(const int32_t *count, const int32_t *__restrict__ idx,  
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off, 64);
     num = 0.f;
+    for (int p0 = 0;;) {   // uniform
 #pragma unroll
-    for (int i = 0; i < EACH; ++i) num += __shfl(w_p, SLICES * i + slice, 64) * pv[i];   // past the partials in use: zero times zero
+        for (int i = 0; i < EACH; ++i) num += __shfl(w_p, p0 + SLICES * i + slice, 64) * pv[i];   // past the partials in use: zero times zero
+        p0 += SLICES * EACH;
+        if (p0 >= used_wgs) break;
+        fetch(p0);
+    }
     s_o[slice][ch] = num;
     __syncthreads();
     if (slice == 0) {
@@ -1127,14 +1139,20 @@ hipError_t lvr_launch_sparse_splits(lvr_index *ix, const float *q, const int32_t
                                     int64_t cap, float *out, int32_t *publish_count, hipStream_t st) {
     const int n_bhq = lvr_n_bhq(ix);
     // Every workgroup of a head costs a read of the count and a ticket whether the list reaches it or not, and the list lengths
-    // are not known here: as many as keep the device at about one workgroup per compute unit (80 / 330 / 1300 entries per head, us: 32
-    // bf16 heads 6.1 / 6.5 / 8.5 with 16 workgroups, 5.7 / 6.1 / 8.4 with 8; 64 fp32 heads 9.5 / 10.0 / 20.2 with 16, 7.8 / 8.8 / 19.6 with 8,
-    // 6.1 / 10.1 / 21.3 with 4; 128 bf16 heads 7.9 / 9.2 / 20.1 with 8, 6.3 / 8.7 / 17.9 with 4).
-    int wgs = n_bhq <= 16 ? SPLIT_WGS_MAX : (n_bhq <= 64 ? 8 : 4);
-    const int most = (ix->P + SPLIT_WAVES - 1) / SPLIT_WAVES;   // the caller's number of splits is an upper bound
-    if (wgs > most) wgs = most;
-    const int P = wgs * SPLIT_WAVES < ix->P ? wgs * SPLIT_WAVES : ix->P;
-    int32_t *ticket = lvr_split_ticket(ix) + (n_bhq <= 16 ? 0 : (n_bhq <= 64 ? 1 : 2));   // a word per number it counts modulo
+    // are not known here, only the room for them.  Up to 2048 entries: 16 workgroups up to 16 heads, 8 up to 64, then 4 (80 / 330 / 1300 entries per
+    // head, us: 32 bf16 heads 6.4 / 6.8 / 8.9 with 16 workgroups, 6.0 / 6.3 / 8.8 with 8; 64 fp32 heads 9.9 / 10.5 / 20.9 with 16, 8.2 / 8.8 / 18.9
+    // with 8, 6.9 / 10.4 / 21.5 with 4; 128 bf16 heads 8.7 / 9.2 / 20.3 with 8, 6.6 / 9.0 / 18.2 with 4).  Where there is more room, two per
+    // compute unit, with which the longest lists are read fastest (4000 / 16000 entries per head: 32 fp32 heads 27.1 / 123.3 with 8, 23.9 / 79.4
+    // with 16, 25.9 / 79.4 with 32; 8 fp32 heads 14.5 / 43.6 with 16, 11.0 / 26.7 with 32, 10.6 / 23.4 with 64; 64 bf16 heads 23.0 / 61.3 with 8,
+    // 23.7 / 66.4 with 16), and of short ones there 0.4 us slower (32 bf16 heads of 80 entries).
+    int wgs = n_bhq <= 16 ? 16 : (n_bhq <= 64 ? 8 : 4);
+    if (cap > 2048)
+        while (wgs < SPLIT_WGS_MAX && 2 * wgs * n_bhq <= 512) wgs *= 2;
+    if (wgs > ix->P) wgs = ix->P;   // the caller's number of splits is an upper bound
+    const int P = wgs * SPLIT_WAVES;
+    int word = 0;   // a word per number it counts modulo: an index meets two powers of two, or its P in the place of those above
+    while ((1 << word) < wgs) ++word;
+    int32_t *ticket = lvr_split_ticket(ix) + word;
     dim3 grid((unsigned)wgs, (unsigned)n_bhq);
 #define LVR_SPLIT_LAUNCH(KT)                                                                                              \
     hipLaunchKernelGGL(sparse_attention_kernel<KT>, grid, dim3(64 * SPLIT_WAVES), 0, st, count, idx, q, ix->V, cap,         \

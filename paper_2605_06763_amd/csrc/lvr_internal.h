@@ -34,7 +34,7 @@ struct lvr_index {
     int64_t n_indexed;     // keys inside groups (multiple of r)
     int built;
     int attn_one_launch;   // sparse attention as one workgroup per head (1), as P splits per head (0), or as the call decides (-1)
-    int P;                 // attention splits per head at most, where one workgroup does not take a head
+    int P;                 // attention splits per head at most (partial results in memory), where one workgroup does not take a head
     int P_dense;           // splits of the dense baseline
     float sigma;
     size_t elt;            // bytes per K/V element
@@ -107,9 +107,9 @@ static inline int lvr_n_bhq(const lvr_index *ix) { return ix->cfg.batch * ix->cf
 // per query head: size of the retrieved set of the running query (padded).  Zero between
 // queries: the kernel that publishes the counts clears them.
 static inline int32_t *lvr_head_count(const lvr_index *ix) { return ix->counters; }
-// in the same line as a head's counter (words 0 and 1, see lvr_reserve_last): three words of tickets of the workgroups that share the
-// head's list, LVR_CNT_STRIDE apart per head, zero between launches
-static inline int32_t *lvr_split_ticket(const lvr_index *ix) { return ix->counters + 2; }
+// in the same line as a head's counter (words 0 and 1, see lvr_reserve_last): seven words of tickets of the workgroups that share the
+// head's list (up to 1, 2, 4 .. 64 of them), LVR_CNT_STRIDE apart per head, zero between launches
+static inline int32_t *lvr_split_ticket(const lvr_index *ix) { return ix->counters + 8; }
 // word 5 of the line of a (sequence, KV head)'s first query head: ticket of the workgroups that add up its channels' squares
 static inline int32_t *lvr_channel_ticket(const lvr_index *ix) { return ix->counters + 5; }
 static inline int32_t *lvr_overflow_flag(const lvr_index *ix) { return ix->counters + (size_t)lvr_n_bhq(ix) * LVR_CNT_STRIDE; }

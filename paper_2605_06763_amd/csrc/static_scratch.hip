@@ -17,14 +17,14 @@
 namespace {
 
 constexpr int STATIC_MAX_HEADS = 256;   // batch * n_q_heads
-constexpr int STATIC_SPLITS = 64;       // P: splits per head, one wave each
-constexpr int STATIC_PARTIALS = 16;      // workgroups of a head, at most
+constexpr int STATIC_SPLITS = 64;       // P: splits per head, at most
+constexpr int STATIC_PARTIALS = 1024;   // heads times splits, at most: 4 splits of 256 heads, or 512 where there are more splits
 constexpr int STATIC_MAX_DEVICES = 64;
 constexpr size_t TICKET_FLOATS = (size_t)STATIC_MAX_HEADS * LVR_CNT_STRIDE;   // a line per head, as in an index
-constexpr size_t ML_FLOATS = (size_t)STATIC_MAX_HEADS * STATIC_PARTIALS * 2;
-constexpr size_t O_FLOATS = (size_t)STATIC_MAX_HEADS * STATIC_PARTIALS * LVR_D;
+constexpr size_t ML_FLOATS = (size_t)STATIC_PARTIALS * 2;
+constexpr size_t O_FLOATS = (size_t)STATIC_PARTIALS * LVR_D;
 
-// The tickets, (m, l) pairs, then the o vectors: 32 KiB + 32 KiB + 2 MiB per GPU, held until the process ends.
+// The tickets, (m, l) pairs, then the o vectors: 32 KiB + 8 KiB + 512 KiB per GPU, held until the process ends.
 // The tickets start at zero with the process and count modulo the workgroups of a head, with a word for each such number, so they
 // are zero again after any set of calls, also of calls that overlapped.  Of the rest a call reads only the partials it has
 // just written.

@@ -443,8 +443,9 @@ def test_attention_of_lists_by_several_workgroups(G, dtype, batch, hq, hkv, spli
         qd = torch.from_numpy(q).cuda()
         stream = torch.cuda.Stream()
         for call in range(3):
+            cap = n if call != 1 else 2048   # room for more entries, and for as many as take fewer workgroups
             cnt = np.array([[lens[(7 * h + 3 * b + call) % len(lens)] for h in range(hq)] for b in range(batch)], dtype=np.int32)
-            idx = np.stack([[g.permutation(n) for _ in range(hq)] for _ in range(batch)]).astype(np.int32)
+            idx = np.stack([[g.permutation(n)[:cap] for _ in range(hq)] for _ in range(batch)]).astype(np.int32)
             idx_d, cnt_d, out = torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda(), torch.full((batch, hq, 128), np.nan, device="cuda")
             torch.cuda.synchronize()
             if call < 2:
@@ -475,6 +476,41 @@ def test_attention_of_lists_by_several_workgroups(G, dtype, batch, hq, hkv, spli
             slack = 1e-4 * np.abs(tau)
             assert ((s >= tau[..., None]).sum(-1) <= cnt).all() and (cnt <= (s >= (tau - slack)[..., None]).sum(-1)).all()
             assert ix.stats()["keys_emitted"] == int(cnt.sum()) and np.isfinite(out).all()
+
+
+@pytest.mark.parametrize("hq,hkv,splits,factor", [(1, 1, 256, 7.0), (1, 1, 64, 7.0), (32, 8, 64, 28.0)])
+def test_long_lists_are_shared_by_more_workgroups(G, hq, hkv, splits, factor):
+    """fp32 lists of 30000 entries against lists of 300 in room for as many, by the clock: one head 25 against 6 us (69 by 16
+    workgroups), 32 heads 150 against 7 (223 by 8 workgroups each)."""
+    L = G.L
+    n = 65536
+    K = torch.randn((1, hkv, n, 128), device="cuda")
+    q, out = torch.randn((1, hq, 128), device="cuda"), torch.empty((1, hq, 128), device="cuda")
+    idx = torch.rand((hq, n), device="cuda").topk(30000, dim=1).indices.sort(dim=1).values.to(torch.int32).reshape(1, hq, -1).contiguous()
+    cfg = L.make_config(batch=1, n_q_heads=hq, n_kv_heads=hkv, kv_dtype=L.LVR_F32, capacity=n, group_size=4, attn_splits=splits)
+    h = L.lvr_create(cfg)
+    try:
+        L.lvr_build(h, K, K)
+        took = []
+        for entries in (300, 30000):
+            count = torch.full((1, hq), entries, dtype=torch.int32, device="cuda")
+            stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+            L.lvr_sparse_attention(h, q, idx, count, out)
+            torch.cuda.synchronize()
+            with torch.cuda.graph(graph, stream=stream):
+                for _ in range(20):
+                    L.lvr_sparse_attention(h, q, idx, count, out, stream)
+            took.append(math.inf)
+            for _ in range(10):
+                start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                start.record()
+                graph.replay()
+                end.record()
+                torch.cuda.synchronize()
+                took[-1] = min(took[-1], start.elapsed_time(end))
+    finally:
+        L.lvr_destroy(h)
+    assert took[1] < factor * took[0], took
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
