@@ -60,6 +60,9 @@ struct LeadArgs {
 // W = heads per head block: 4 (three exact bf16 terms of four heads in the 16 operand columns; HB blocks) or
 //     8 (two terms of eight heads fill the columns, the rarely non-zero third term has an operand of its own:
 //     one pass per tile for up to eight heads; balls with one threshold per head, HB = 1)
+// Three waves per SIMD are asked for with boxes of 8-bit corners and two head blocks, which take 157 to 161 registers
+// then.  Left alone the form with four thresholds per head took 170: 35.3 us instead of 30.6 (Query 1 of 64 heads on 8,
+// 32768 keys in groups of four; 32.3 before the launch handed the set sizes over, with a launch for that behind it).
 // Four waves per SIMD (four workgroups per compute unit) are asked for wherever the kernel fits 128 registers: one
 // head block of balls with at most four coordinate blocks, and the eight-head operand.  Left to itself the compiler
 // has filled 128 vector registers and then needed four accumulator registers more, which costs a quarter of the waves.
@@ -71,7 +74,7 @@ struct LeadArgs {
 // starts, so the loads of q and the first centres do not wait for a read of the argument block (32.9 against 33.4 us per
 // step at 128k keys, 11.7 against 12.1 at 16k; the attention kernels order their arguments the same way).
 template <int HB, int S, int UA, int ENC, int Q1 = 0, int CF = 0, int W = 4>
-__global__ void __launch_bounds__(256, ((HB == 1 && !ENC && S <= 4) || W == 8) ? 4 : 1)
+__global__ void __launch_bounds__(256, ((HB == 1 && !ENC && S <= 4) || W == 8) ? 4 : (HB == 2 && ENC && CF == 1 ? 3 : 1))
 query_fused_kernel(const float *__restrict__ q_in, const int8_t *__restrict__ chan_exp, const void *__restrict__ centres,
                    const float *__restrict__ radii, const float *__restrict__ tau_in, const int G, const int tiles_per_wave,
                    const int max_groups, const int n_groups, const FusedArgs a) {
@@ -912,7 +915,6 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     a.emit.out_score = ix->scores;
     a.emit.score_stride = ix->cap_rows;
     a.emit.out_count = out_count;
-    a.emit.head_stat = lvr_head_stat(ix);
     a.max_segs = lvr_max_segs(ix->max_groups);
     a.cap_rows = ix->cap_rows;
     a.n_indexed = ix->n_indexed;
