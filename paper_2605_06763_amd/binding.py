@@ -8,17 +8,23 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import re
+import warnings
 
 import torch
 
 from .build import CALL_PATH, LIB_PATH
 
-try:
-    from . import _call   # the decode loop's calls without the interpreter's share (csrc/pycall.cpp)
-except ImportError:
-    if os.path.exists(CALL_PATH):
-        raise
-    _call = None          # nothing is built yet: this import is the build's own
+_call = None   # the decode loop's calls without the interpreter's share (csrc/pycall.cpp); None: all calls go through ctypes
+if os.path.exists(CALL_PATH):
+    try:
+        from . import _call
+        if _call.TORCH_VERSION != re.match(r"[\d.]*\d", torch.__version__).group():
+            raise ImportError(f"built for torch {_call.TORCH_VERSION}, this is {torch.__version__}")
+    except ImportError as e:
+        _call = None
+        warnings.warn(f"{os.path.basename(CALL_PATH)} does not load, calls go through ctypes; build it again "
+                      f"(python -m paper_2605_06763_amd.build): {e}")
 
 LVR_BF16, LVR_F32 = 0, 1
 LVR_GROUP_CONTIGUOUS, LVR_GROUP_TREE, LVR_GROUP_SUBSPACE_TREE = 0, 1, 2

@@ -4,12 +4,15 @@ from __future__ import annotations
 import glob
 import os
 import subprocess
+import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "liblouver.so")
-CALL_PATH = os.path.join(_HERE, "_call.so")   # the Python module of the decode loop's calls (csrc/pycall.cpp, host code only)
+# the Python module of the decode loop's calls (csrc/pycall.cpp, host code only); another Python does not find it by this name
+CALL_PATH = os.path.join(_HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ_DIR = os.path.join(_HERE, "_build")
 
 HIPCC_FLAGS = [
@@ -33,17 +36,31 @@ def _run(cmd: list[str]) -> str:
     return res.stderr
 
 
-def _call_command() -> list[str]:
+def _call_command(out: str) -> list[str]:
     """The host compiler's line for the Python module: torch's headers, nothing of the GPU."""
-    import sysconfig
-
     import torch
     from torch.utils import cpp_extension
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"]]
     cmd += ["-isystem" + p for p in cpp_extension.include_paths()]
-    cmd += [os.path.join(CSRC, "pycall.cpp"), "-o", CALL_PATH]
+    cmd += [os.path.join(CSRC, "pycall.cpp"), "-o", out]
     return cmd + ["-L" + p for p in cpp_extension.library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"]
+
+
+def build_call_module(path: str = CALL_PATH) -> str:
+    """The Python module, put in place whole.  Without a host compiler or torch's headers there is none: every call goes
+    through ctypes then, some 3 to 5 us slower on the host."""
+    part = path + ".part"
+    try:
+        log = _run(_call_command(part))
+        os.replace(part, path)
+        return log
+    except (OSError, RuntimeError, ImportError) as e:
+        for p in (part, path):   # nor one that was built for other sources
+            if os.path.exists(p):
+                os.remove(p)
+        warnings.warn(f"{os.path.basename(path)} was not built, calls go through ctypes: {e}")
+        return ""
 
 
 def build_library(verbose: bool = False, jobs: int | None = None) -> str:
@@ -54,7 +71,7 @@ def build_library(verbose: bool = False, jobs: int | None = None) -> str:
     objs = [os.path.join(OBJ_DIR, os.path.basename(s)[:-4] + ".o") for s in srcs]
     jobs = jobs or min(len(srcs), os.cpu_count() or 1, 16)
     with ThreadPoolExecutor(max_workers=jobs) as pool:
-        call = pool.submit(_run, _call_command())
+        call = pool.submit(build_call_module)
         logs = list(pool.map(lambda so: _run([hipcc, *HIPCC_FLAGS, "-c", so[0], "-o", so[1]]), zip(srcs, objs)))
         logs.append(call.result())
     logs.append(_run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]))

@@ -7,6 +7,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <structmember.h>
+#include <torch/version.h>
 
 #include <cstdint>
 #include <cstring>
@@ -303,6 +304,10 @@ PyMODINIT_FUNC PyInit__call() {
     Py_INCREF(&ArgType);
     if (PyModule_AddObject(m, "Arg", reinterpret_cast<PyObject *>(&ArgType)) < 0) {
         Py_DECREF(&ArgType);
+        Py_DECREF(m);
+        return nullptr;
+    }
+    if (PyModule_AddStringConstant(m, "TORCH_VERSION", TORCH_VERSION) < 0) {   // whose headers this was built with
         Py_DECREF(m);
         return nullptr;
     }

@@ -116,3 +116,34 @@ def test_calls_of_the_decode_loop_refuse_what_the_general_binding_refuses(L):
             call()
     with pytest.raises(ValueError, match="of one dtype"):
         L.lvr_sparse_attention_static(K, K.bfloat16(), f, i, i, f, 0.0, st)
+
+
+def test_without_the_compiled_calls_the_package_works(tmp_path, monkeypatch):
+    """The compiled module is a short cut: a file of it that does not load, or was built for another torch, is passed over with a
+    warning, and so is a build without a host compiler, which leaves no old module behind."""
+    import shutil
+    import subprocess
+    import sys
+    from paper_2605_06763_amd import build as B
+    pkg = tmp_path / "paper_2605_06763_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "binding.py", "build.py"):
+        shutil.copy(os.path.join(ROOT, "paper_2605_06763_amd", name), pkg)
+    module = pkg / os.path.basename(B.CALL_PATH)
+    check = ("import warnings\nwith warnings.catch_warnings(record=True) as w:\n    warnings.simplefilter('always')\n"
+             "    import paper_2605_06763_amd.binding as b\n"
+             "assert b._call is None and any('calls go through ctypes' in str(x.message) for x in w)\n"
+             "assert issubclass(b.DeviceArg, b._Arg)")
+    for content in (b"", b"no module"):
+        module.write_bytes(content)
+        r = subprocess.run([sys.executable, "-c", check], cwd=tmp_path, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+    built = "import sys, types\nm = types.ModuleType('paper_2605_06763_amd._call')\nm.TORCH_VERSION = '0.0.0'\n" \
+            "sys.modules['paper_2605_06763_amd._call'] = m\n"   # stands for one that loads
+    r = subprocess.run([sys.executable, "-c", built + check], cwd=tmp_path, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    module.write_bytes(b"old")
+    with pytest.warns(UserWarning, match="was not built"):
+        assert B.build_call_module(str(module)) == ""
+    assert not module.exists() and not os.path.exists(str(module) + ".part")
