@@ -151,6 +151,17 @@ def _stream(stream=None):
     return C.c_void_p(stream.cuda_stream)
 
 
+def _early_stream(stream):
+    """The stream for a compiled call, or None: there is none, or the stream is not to be had (no GPU, no stream object), which the
+    general binding reports after it has looked at the tensors."""
+    if _lib is None or _call is None:   # (the library is loaded by the first call)
+        return None
+    try:
+        return _stream(stream)
+    except Exception:
+        return None
+
+
 def stream_arg(stream=None) -> C.c_void_p:
     """The stream argument marshalled once, for callers that issue many calls on one stream."""
     return _stream(stream)
@@ -240,12 +251,13 @@ def lvr_append(h, k_new: torch.Tensor, v_new: torch.Tensor, stream=None) -> None
 
 
 def lvr_query(h, q, tau, out_idx, out_count, stream=None) -> None:
-    st = _stream(stream)
-    code = _call.query(h, q, tau, out_idx, out_count, st) if _lib is not None and _call is not None else None
+    st = _early_stream(stream)
+    code = _call.query(h, q, tau, out_idx, out_count, st) if st is not None else None
     if code is None:   # not all plain tensors of the right type, or the first call
+        cap = out_idx.shape[-1]
         code = lib().lvr_query(h, _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
                                _dev(out_idx, torch.int32, "out_idx"), _dev(out_count, torch.int32, "out_count"),
-                               out_idx.shape[-1], st)
+                               cap, _stream(stream))
     if code != LVR_OK:
         raise LouverError(code, "lvr_query")
 
@@ -264,62 +276,66 @@ def lvr_subspace_thresholds(h, q, tau, tau_s_out, stream=None) -> None:
 
 
 def lvr_sparse_attention(h, q, idx, count, out, stream=None) -> None:
-    st = _stream(stream)
-    code = _call.sparse_attention(h, q, idx, count, out, st) if _lib is not None and _call is not None else None
+    st = _early_stream(stream)
+    code = _call.sparse_attention(h, q, idx, count, out, st) if st is not None else None
     if code is None:   # not all plain tensors of the right type, or the first call
+        cap = idx.shape[-1]
         code = lib().lvr_sparse_attention(h, _dev(q, torch.float32, "q"), _dev(idx, torch.int32, "idx"),
-                                          _dev(count, torch.int32, "count"), idx.shape[-1],
-                                          _dev(out, torch.float32, "out"), st)
+                                          _dev(count, torch.int32, "count"), cap,
+                                          _dev(out, torch.float32, "out"), _stream(stream))
     if code != LVR_OK:
         raise LouverError(code, "lvr_sparse_attention")
 
 
 def lvr_sparse_attention_static(K, V, q, idx, count, out, scale=0.0, stream=None) -> None:
     """K, V: contiguous device tensors [batch][n_kv_heads][n][128] (bf16 or fp32); no index object."""
-    st = _stream(stream)
-    code = _call.sparse_attention_static(K, V, q, idx, count, out, scale, st) if _lib is not None and _call is not None else None
+    st = _early_stream(stream)
+    code = _call.sparse_attention_static(K, V, q, idx, count, out, scale, st) if st is not None else None
     if code is None:   # not all plain tensors of the right type, or the first call
         if K.dim() != 4 or V.shape != K.shape or K.dtype != V.dtype:
             raise ValueError("K and V must be [batch][n_kv_heads][n][head_dim] of one dtype")
         if K.dtype not in (torch.bfloat16, torch.float32):
             raise ValueError("K and V must be bf16 or fp32")
+        cap = idx.shape[-1]
         code = lib().lvr_sparse_attention_static(_dev(K, name="K"), _dev(V, name="V"), K.shape[2],
                                                  LVR_BF16 if K.dtype == torch.bfloat16 else LVR_F32, K.shape[0],
                                                  q.shape[1], K.shape[1], float(scale), _dev(q, torch.float32, "q"),
                                                  _dev(idx, torch.int32, "idx"), _dev(count, torch.int32, "count"),
-                                                 idx.shape[-1], _dev(out, torch.float32, "out"), st)
+                                                 cap, _dev(out, torch.float32, "out"), _stream(stream))
     if code != LVR_OK:
         raise LouverError(code, "lvr_sparse_attention_static")
 
 
 def lvr_decode_step(h, q, tau, out, out_idx, out_count, stream=None) -> None:
-    st = _stream(stream)
-    code = _call.decode_step(h, q, tau, out, out_idx, out_count, st) if _lib is not None and _call is not None else None
+    st = _early_stream(stream)
+    code = _call.decode_step(h, q, tau, out, out_idx, out_count, st) if st is not None else None
     if code is None:   # not all plain tensors of the right type, or the first call
+        cap = out_idx.shape[-1]
         code = lib().lvr_decode_step(h, _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
                                      _dev(out, torch.float32, "out"), _dev(out_idx, torch.int32, "out_idx"),
-                                     _dev(out_count, torch.int32, "out_count"), out_idx.shape[-1], st)
+                                     _dev(out_count, torch.int32, "out_count"), cap, _stream(stream))
     if code != LVR_OK:
         raise LouverError(code, "lvr_decode_step")
 
 
 def lvr_append_decode_step(h, k_new, v_new, q, tau, out, out_idx, out_count, stream=None) -> None:
-    st = _stream(stream)
-    code = _call.append_decode_step(h, k_new, v_new, q, tau, out, out_idx, out_count, st) if _lib is not None and _call is not None else None
+    st = _early_stream(stream)
+    code = _call.append_decode_step(h, k_new, v_new, q, tau, out, out_idx, out_count, st) if st is not None else None
     if code is None:   # not all plain tensors of the right type, or the first call
+        cap = out_idx.shape[-1]
         code = lib().lvr_append_decode_step(h, _dev(k_new, name="k_new"), _dev(v_new, name="v_new"), k_new.shape[2],
                                             _dev(q, torch.float32, "q"), _dev(tau, torch.float32, "tau"),
                                             _dev(out, torch.float32, "out"), _dev(out_idx, torch.int32, "out_idx"),
-                                            _dev(out_count, torch.int32, "out_count"), out_idx.shape[-1], st)
+                                            _dev(out_count, torch.int32, "out_count"), cap, _stream(stream))
     if code != LVR_OK:
         raise LouverError(code, "lvr_append_decode_step")
 
 
 def lvr_dense_attention(h, q, out, stream=None) -> None:
-    st = _stream(stream)
-    code = _call.dense_attention(h, q, out, st) if _lib is not None and _call is not None else None
+    st = _early_stream(stream)
+    code = _call.dense_attention(h, q, out, st) if st is not None else None
     if code is None:   # not all plain tensors of the right type, or the first call
-        code = lib().lvr_dense_attention(h, _dev(q, torch.float32, "q"), _dev(out, torch.float32, "out"), st)
+        code = lib().lvr_dense_attention(h, _dev(q, torch.float32, "q"), _dev(out, torch.float32, "out"), _stream(stream))
     if code != LVR_OK:
         raise LouverError(code, "lvr_dense_attention")
 

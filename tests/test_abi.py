@@ -116,6 +116,13 @@ def test_calls_of_the_decode_loop_refuse_what_the_general_binding_refuses(L):
             call()
     with pytest.raises(ValueError, match="of one dtype"):
         L.lvr_sparse_attention_static(K, K.bfloat16(), f, i, i, f, 0.0, st)
+    # the tensors are looked at before the stream, which cannot be had here (no GPU, or no stream at all)
+    for st in (None, object()) if not torch.cuda.is_available() else (object(),):
+        for call in (lambda: L.lvr_query(h, f, f, i, i, st), lambda: L.lvr_decode_step(h, f, f, f, i, i, st),
+                     lambda: L.lvr_append_decode_step(h, K, K, f, f, f, i, i, st), lambda: L.lvr_sparse_attention(h, f, i, i, f, st),
+                     lambda: L.lvr_dense_attention(h, f, f, st), lambda: L.lvr_sparse_attention_static(K, K, f, i, i, f, 0.0, st)):
+            with pytest.raises(ValueError, match="must be a device tensor"):
+                call()
 
 
 def test_without_the_compiled_calls_the_package_works(tmp_path, monkeypatch):
