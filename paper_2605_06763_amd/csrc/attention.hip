@@ -200,14 +200,8 @@ sparse_attention_kernel(const int32_t *count, const int32_t *__restrict__ idx,  
     const float *po = part_o + hq * wgs * LVR_D + ch;
     constexpr int SLICES = SPLIT_WAVES / 2, EACH = 8;   // a slice takes every other partial, eight loads in flight
     float pv[EACH];
-    auto fetch = [&](int p0) {
 #pragma unroll
-        for (int i = 0; i < EACH; ++i) {
-            const int p = p0 + SLICES * i + slice;
-            pv[i] = p < used_wgs ? load(&po[(int64_t)p * LVR_D]) : 0.f;
-        }
-    };
-    fetch(0);
+    for (int i = 0; i < EACH; ++i) pv[i] = SLICES * i + slice < used_wgs ? load(&po[(SLICES * i + slice) * LVR_D]) : 0.f;
     M = m_p;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
@@ -216,12 +210,13 @@ sparse_attention_kernel(const int32_t *count, const int32_t *__restrict__ idx,  
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off, 64);
     num = 0.f;
-    for (int p0 = 0;;) {   // uniform
 #pragma unroll
-        for (int i = 0; i < EACH; ++i) num += __shfl(w_p, p0 + SLICES * i + slice, 64) * pv[i];   // past the partials in use: zero times zero
-        p0 += SLICES * EACH;
-        if (p0 >= used_wgs) break;
-        fetch(p0);
+    for (int i = 0; i < EACH; ++i) num += __shfl(w_p, SLICES * i + slice, 64) * pv[i];   // past the partials in use: zero times zero
+    for (int p0 = SLICES * EACH; p0 < used_wgs; p0 += SLICES * EACH) {   // uniform
+#pragma unroll
+        for (int i = 0; i < EACH; ++i) pv[i] = p0 + SLICES * i + slice < used_wgs ? load(&po[(p0 + SLICES * i + slice) * LVR_D]) : 0.f;
+#pragma unroll
+        for (int i = 0; i < EACH; ++i) num += __shfl(w_p, p0 + SLICES * i + slice, 64) * pv[i];
     }
     s_o[slice][ch] = num;
     __syncthreads();
