@@ -234,6 +234,8 @@ void prof_free(lvr_index *ix) {
 // One workgroup wins whenever there are many heads in the batch or few keys per head; with one sequence's 32 heads and several
 // hundred retrieved keys each, 32 workgroups cannot gather fast enough (measured crossover with the combine launch: between 32k
 // and 128k keys of context at 0.5-1 % retrieved).  The set sizes are not known on the host, so the context length stands in.
+// (Without the combine launch, for lists without scores, it lies lower than the line drawn here: bf16, one workgroup per head
+// against several, 32 heads of 330 / 500 / 1300 entries 6.6 / 7.4 / 16.2 against 6.1 / 6.4 / 8.4 us, 64 heads of 1300 17.0 against 13.1.)
 inline bool one_launch_attention(const lvr_index *ix, bool carried = false) {
     if (ix->attn_one_launch >= 0) return ix->attn_one_launch != 0;
     // bf16 lists that carry their scores take the one-launch kernels with two dependent trips (two workgroups per head

@@ -785,7 +785,7 @@ channel_step_kernel(ChannelArgs a, CopySide k, CopySide v, int64_t cap_rows, int
 
 // The workgroups' sums go through the attention's partial-output buffer (G * Pmax * 128 floats per (sequence, KV head),
 // Pmax >= 4), which no launch in flight on the same stream still needs once these run.
-// V != NULL: the launches also copy all n value rows and the key rows from k_first on.
+// V != NULL: the launch also copies all n value rows and the key rows from k_first on.
 hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t ks[3], int64_t n, hipStream_t st, const void *V,
                                      const int64_t *vs, int64_t k_first) {
     if (!ix->chan_scaled || n <= 0) return hipSuccess;

@@ -431,7 +431,8 @@ def test_attention_form_of_a_decode_step(G, oracle, dtype, n, one_launch):
 def test_attention_of_lists_by_several_workgroups(G, dtype, batch, hq, hkv, splits):
     """List lengths around the entries of a wave, of a workgroup and of all of a head's workgroups, whose last to end merges the
     others: a length per head, three calls in a row (tickets back at zero, the last one from a graph replayed twice), and the query
-    that hands its counts over followed by the attention over its lists."""
+    that hands its counts over followed by the attention over its lists.  Entries lost or taken twice are counted: with q = 0 and rows of V
+    that are a one in the coordinate position % 128, the output times the list's length is how often each remainder is listed."""
     L = G.L
     g = np.random.default_rng(hq + splits)
     n = 4200
@@ -439,7 +440,9 @@ def test_attention_of_lists_by_several_workgroups(G, dtype, batch, hq, hkv, spli
     K = W.round_to_bf16(g.standard_normal((batch, hkv, n, 128)).astype(np.float32))
     V = W.round_to_bf16(g.standard_normal((batch, hkv, n, 128)).astype(np.float32))
     q = g.standard_normal((batch, hq, 128)).astype(np.float32)
-    with G.Index(K, V, dtype, hq, capacity=n, group_size=4, attn_splits=splits) as ix:
+    ones = np.tile(np.eye(128, dtype=np.float32)[np.arange(n) % 128], (batch, hkv, 1, 1))
+    with G.Index(K, V, dtype, hq, capacity=n, group_size=4, attn_splits=splits) as ix, \
+            G.Index(K, ones, dtype, hq, capacity=n, group_size=4, attn_splits=splits) as counting:
         qd = torch.from_numpy(q).cuda()
         stream = torch.cuda.Stream()
         for call in range(3):
@@ -457,11 +460,15 @@ def test_attention_of_lists_by_several_workgroups(G, dtype, batch, hq, hkv, spli
                 for _ in range(2):
                     out.fill_(float("nan"))
                     graph.replay()
+            times = torch.full_like(out, np.nan)
+            L.lvr_sparse_attention(counting.h, torch.zeros_like(qd), idx_d, cnt_d, times)
             torch.cuda.synchronize()
-            got = out.cpu().numpy()
+            got, times = out.cpu().numpy(), times.cpu().numpy()
             for b in range(batch):
                 for h in range(hq):
                     l = idx[b, h, :cnt[b, h]]
+                    # weights are ones, their sums whole numbers; one quotient is rounded, by 2^-24 of at most 33
+                    assert np.abs(times[b, h] * len(l) - np.bincount(l % 128, minlength=128)).max() <= 1e-4, (call, b, h, len(l))
                     s = K[b, h * hkv // hq][l].astype(np.float64) @ q[b, h].astype(np.float64) / math.sqrt(128)
                     p = np.exp(s - s.max()) if len(l) else s
                     want = (p / max(p.sum(), 1e-300)) @ V[b, h * hkv // hq][l].astype(np.float64)
@@ -599,9 +606,9 @@ def test_marshalled_and_plain_arguments_are_the_same_call(G, oracle):
         k = G.to_device(K[:, :, :1].copy(), "bf16")
         other = torch.cuda.Stream()
         A = L.tensor_arg
+        wraps = (lambda t: t, A, lambda t: A(t) if t.dtype == torch.int32 else t, lambda t: A(t) if t.dtype == torch.int32 else t)
         results = []
-        for form in range(4):
-            w = (lambda t: t) if form == 0 else (A if form == 1 else (lambda t: A(t) if t.dtype == torch.int32 else t))
+        for form, w in enumerate(wraps):
             st = (None, L.stream_arg(), other, torch.cuda.current_stream())[form]
             out.fill_(float("nan"))
             torch.cuda.synchronize()
@@ -624,6 +631,19 @@ def test_marshalled_and_plain_arguments_are_the_same_call(G, oracle):
         L.lvr_append_decode_step(ix.h, A(k), k, A(qd), tau, out, A(idx), cnt)
         torch.cuda.synchronize()
         assert L.lvr_length(ix.h)[0] == n + 1
+        import paper_2605_06763_amd.binding as binding
+        calls = binding._call   # the compiled calls take all of these themselves: None would send them to ctypes
+        assert calls is not None
+        for form, w in enumerate(wraps[:3]):
+            arg = L.stream_arg()
+            assert calls.query(ix.h, w(qd), w(tau), w(idx), w(cnt), arg) == L.LVR_OK
+            assert calls.sparse_attention(ix.h, w(qd), w(idx), w(cnt), w(out), arg) == L.LVR_OK
+            assert calls.sparse_attention_static(ix.Kd, ix.Vd, w(qd), w(idx), w(cnt), w(out), 0.0, arg) == L.LVR_OK
+            assert calls.decode_step(ix.h, w(qd), w(tau), w(out), w(idx), w(cnt), arg) == L.LVR_OK
+            assert calls.dense_attention(ix.h, w(qd), w(out), arg) == L.LVR_OK
+            assert calls.append_decode_step(ix.h, w(k), k, w(qd), w(tau), w(out), w(idx), w(cnt), arg) == L.LVR_OK
+            torch.cuda.synchronize()
+            assert L.lvr_length(ix.h)[0] == n + form + 2
         for bad in (qd.double(), qd.transpose(1, 2), qd.cpu()):
             with pytest.raises(ValueError):
                 L.lvr_decode_step(ix.h, bad, tau, out, idx, cnt)

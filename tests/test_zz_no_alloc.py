@@ -1,6 +1,6 @@
 """The entry point that allocates nothing (lvr_sparse_attention_static) against the entry point
-it is a variant of (lvr_sparse_attention in its two-launch form, attn_splits = 64): same lists,
-same kernels, so the outputs must agree to the attention tolerance (they are expected to be
+it is a variant of (lvr_sparse_attention with attn_splits = 64, several workgroups per head): same lists,
+same kernel, so the outputs must agree to the attention tolerance (they are expected to be
 bit-equal); both are also checked against the CPU oracle on the same lists.  Two calls in a row,
 the second with a smaller input, so that what the first call left in the static array is there
 when the second one runs."""
@@ -51,7 +51,7 @@ def _run_case(G, oracle, L, *, n, batch, hq, hkv, dtype, counts, seed):
                 e_new = float(np.abs(b_[b, h] - ref).max()) / denom if cnt[b, h] else float(np.abs(b_[b, h]).max())
                 e_old = float(np.abs(a[b, h] - ref).max()) / denom if cnt[b, h] else float(np.abs(a[b, h]).max())
                 assert e_new <= G.ATTN_TOL and e_old <= G.ATTN_TOL, (b, h, e_new, e_old)
-        # same kernels, same split geometry: the two entry points agree to the last bit
+        # same kernel, same split geometry: the two entry points agree to the last bit
         assert np.array_equal(a, b_), float(np.abs(a - b_).max())
 
 
