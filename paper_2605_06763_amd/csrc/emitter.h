@@ -18,6 +18,7 @@ struct lvr_emit_target {
     float *out_score;        // [n_bhq][score_stride] raw scores of the emitted keys (emitters that carry them), or NULL
     int64_t score_stride;
     int32_t *out_count;      // the caller's set sizes, written by the launch itself (lvr_reserve_last), or NULL: a later launch does that
+    int32_t *head_stat;
 };
 
 // Range of a workgroup's last `tot` entries of a head, reserved once per workgroup by every workgroup of the head (`wgs` of them).
@@ -33,7 +34,7 @@ __device__ __forceinline__ int lvr_reserve_last(const lvr_emit_target &a, int64_
     if ((unsigned)(old >> 32) == wgs - 1) {
         const int32_t all = (int32_t)(unsigned)old + tot;
         a.out_count[hq] = all;
-        a.overflow[LVR_CNT_STRIDE + hq] = all;   // the statistics copy (lvr_head_stat) stands behind the flag's line
+        a.head_stat[hq] = all;
         *both = 0ull;
     }
     return (int)(unsigned)old;

@@ -240,6 +240,7 @@ hipError_t lvr_launch_filter(lvr_index *ix, const float *q, const float *tau, in
     a.emit.out_score = nullptr;
     a.emit.score_stride = 0;
     a.emit.out_count = nullptr;
+    a.emit.head_stat = nullptr;
     a.cap_rows = ix->cap_rows;
     a.max_groups = ix->max_groups;
     a.max_segs = lvr_max_segs(ix->max_groups);

@@ -227,6 +227,7 @@ hipError_t lvr_launch_query_f32(lvr_index *ix, const float *q, const float *tau,
     a.emit.out_score = ix->scores;
     a.emit.score_stride = ix->cap_rows;
     a.emit.out_count = out_count;
+    a.emit.head_stat = lvr_head_stat(ix);
     a.n_groups = ix->n_indexed / ix->cfg.group_size;
     a.max_groups = ix->max_groups;
     a.max_segs = lvr_max_segs(ix->max_groups);

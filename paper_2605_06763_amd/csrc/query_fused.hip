@@ -60,8 +60,8 @@ struct LeadArgs {
 // W = heads per head block: 4 (three exact bf16 terms of four heads in the 16 operand columns; HB blocks) or
 //     8 (two terms of eight heads fill the columns, the rarely non-zero third term has an operand of its own:
 //     one pass per tile for up to eight heads; balls with one threshold per head, HB = 1)
-// Three waves per SIMD are asked for with boxes of 8-bit corners and two head blocks, which take 157 to 161 registers
-// then.  Left alone the form with four thresholds per head took 170: 35.3 us instead of 30.6 (Query 1 of 64 heads on 8,
+// Three waves per SIMD are asked for with boxes of 8-bit corners and two head blocks, which take 158 to 162 registers
+// then.  Left alone the form with four thresholds per head took 171: 35.3 us instead of 30.7 (Query 1 of 64 heads on 8,
 // 32768 keys in groups of four; 32.3 before the launch handed the set sizes over, with a launch for that behind it).
 // Four waves per SIMD (four workgroups per compute unit) are asked for wherever the kernel fits 128 registers: one
 // head block of balls with at most four coordinate blocks, and the eight-head operand.  Left to itself the compiler
@@ -915,6 +915,7 @@ hipError_t lvr_launch_query_fused(lvr_index *ix, const float *q, const float *ta
     a.emit.out_score = ix->scores;
     a.emit.score_stride = ix->cap_rows;
     a.emit.out_count = out_count;
+    a.emit.head_stat = lvr_head_stat(ix);
     a.max_segs = lvr_max_segs(ix->max_groups);
     a.cap_rows = ix->cap_rows;
     a.n_indexed = ix->n_indexed;

@@ -386,6 +386,7 @@ hipError_t lvr_launch_label_filter(lvr_index *ix, const float *q, const float *t
     a.emit.out_score = ix->scores;
     a.emit.score_stride = ix->cap_rows;
     a.emit.out_count = nullptr;
+    a.emit.head_stat = nullptr;
     a.max_groups = ix->max_groups;
     a.max_segs = lvr_max_segs(ix->max_groups);
     a.cap_rows = ix->cap_rows;
