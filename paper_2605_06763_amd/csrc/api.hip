@@ -135,7 +135,7 @@ Sizes sizes_of(const lvr_config *c) {
         s.maps = per_subspace ? 0 : al((size_t)n_bh * s.cap_rows * sizeof(int32_t));   // rows stay in arrival order there
         s.tree_keybytes = al((size_t)s.tree_keys * sizeof(uint64_t));
         s.tree_axis = al((size_t)n_bh * gp * sizeof(int32_t));
-        s.tree_partial = al((size_t)n_bh * (np > 1024 ? np / 1024 : 1) * (4 * 256 * sizeof(double) + 2 * sizeof(int)));   // two levels' pieces and nodes
+        s.tree_partial = al((size_t)n_bh * (np > 1024 ? np / 1024 : 1) * 4 * 256 * sizeof(double));   // two levels' pieces and nodes
         s.chunk = per_subspace ? 0 : al((size_t)n_bh * c->buffer_size * LVR_D * elt);
         s.total += 2 * s.maps + 2 * s.tree_keybytes + s.tree_axis + s.tree_partial + 2 * s.chunk;
     }

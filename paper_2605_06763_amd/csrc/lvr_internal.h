@@ -55,7 +55,7 @@ struct lvr_index {
     // work space of the tree grouping (TREE grouping only)
     uint64_t *tree_keys_a, *tree_keys_b;   // [n_bh * padded entries]: a = the order before and after a split (two halves of 32-bit
                                            // positions), b = the codes of a level, at the end the finished order
-    int32_t *tree_axis;                    // [n_bh * nodes] split axis per node of the current level
+    int32_t *tree_axis;                    // [n_bh * groups] split axis per large node of the current level; two levels' words per node (tree.hip)
     double *tree_partial;                  // partial coordinate statistics of large nodes
     int64_t tree_cap_keys;                 // keys tree_keys_* can hold
     void *chunk_K, *chunk_V;               // [n_bh][B][d] staging of a buffer chunk being regrouped

@@ -102,6 +102,16 @@ def test_bench_refuses_more_than_one_gpu():
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
 
 
+def test_work_space_of_a_tree_is_what_its_arrays_hold(L):
+    """8 heads of 32768 keys: two position maps, two work arrays of 8 bytes per key, an axis per group, a chunk of keys and of values, and two
+    levels' sums and pieces, which fill 2 MB: an allocation a little larger than that takes 0.3 ms more to set up."""
+    ok = dict(batch=1, n_q_heads=32, n_kv_heads=8, kv_dtype=L.LVR_BF16, capacity=32768, group_size=4, buffer_size=256)
+    more = L.lvr_arena_bytes(L.make_config(grouping=L.LVR_GROUP_TREE, **ok)) - L.lvr_arena_bytes(L.make_config(**ok))
+    keys = 8 * 32768
+    assert more == 2 * 4 * keys + 2 * 8 * keys + 4 * keys // 4 + 2 * 8 * 256 * 256 + (2 << 20)
+
+
+
 def test_calls_of_the_decode_loop_refuse_what_the_general_binding_refuses(L):
     """Arguments that are no plain device tensors of the right type go to the general binding, which raises as it always did."""
     import torch
