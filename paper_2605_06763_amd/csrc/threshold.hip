@@ -45,7 +45,8 @@ __global__ void reservoir_update_kernel(int32_t *res, int R, uint64_t seed, int6
 // with a quarter of the 256 each (16 broadcast reads of LDS), and the score goes to the place its rank says.
 // With four waves, a dependent load of position and row per four keys, a bitonic sort (36 barriers) and a serial count of
 // the valid scores the launch took 28 us for 32 heads, with rows in flight and ranks but four waves 12.9; then 7.0 (threshold and step:
-// 50.0, 33.6, 27.7 us), and with two instructions per compared pair instead of five 0.4 less (27.24 -> 26.81).  The gaps and the mean are taken by
+// 50.0, 33.6, 27.7 us).  With two instructions per compared pair instead of five the launch alone, 32 / 512 / 4096 heads: 6.4 / 11.2 / 65.9 -> 5.9 /
+// 9.7 / 55.6 us (threshold and step: within what runs of one side differ by).  The gaps and the mean are taken by
 // all threads: by one thread, 4096 heads, of which only two workgroups of 16 waves fit a compute unit, took 99.3 and 76.9 us
 // where four waves each had taken 80.3 and 74.7; now 67.7 and 69.3.
 template <typename KT>

@@ -27,9 +27,10 @@
 //
 // A build of 8 x 32768 bf16 keys in groups of four and one step, us: 2321 with one wave per SIMD on the statistics, a device-wide radix
 // sort per level and four waves per small node; 424 with a workgroup per node that splits, statistics over all rows in a launch per
-// level, and small nodes of 1024 entries whose rows came from memory at every level; 302 now.  Builds alone, that form and this one: 2048
-// keys 176 / 81 (4 x 4 heads), 9000 keys 276 / 157 (2 heads), 32768 fp32 keys 553 / 417, 131072 keys 1574 / 1245; one tree per coordinate block,
-// S = 16, 32768 keys 5514 / 3761.
+// level, and small nodes of 1024 entries whose rows came from memory at every level; 302 without the question whether sums
+// tell (unsure), 304 with it.  Builds alone, that form and this one: 2048 keys 176 / 81 (4 x 4 heads), 9000 keys 276 / 157 (2 heads), 32768
+// fp32 keys 553 / 417, 131072 keys 1574 / 1245; one tree per coordinate block, S = 16, 32768 keys 5514 / 3761 (without the question,
+// which costs a build 0.4 to 2.5 %, fp32 keys most).
 #include <type_traits>
 
 #include "lvr_internal.h"
@@ -922,7 +923,7 @@ tree_small_kernel(TreeSrc src, const uint32_t *__restrict__ order, uint64_t *__r
     };
     // n rows: the entries that lanes `at` .. hold in `e`
     auto add_some = [&](int e, int at, int n, const Shift &p, double &a0, double &a1, double &b0, double &b1) {
-for (int j0 = 0; j0 < n; j0 += 4) {
+        for (int j0 = 0; j0 < n; j0 += 4) {
             float x0[4], x1[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
