@@ -661,15 +661,18 @@ namespace {
 // rescaled space against the centres as stored there); these make the coordinates of a key comparable in size, so that
 // the 32 coordinates that share a scale in the 6-bit code are not drowned by one large channel.
 //
-// CHAN_SPLITS workgroups per (sequence, KV head) (fewer where the work space is smaller) add up squares, 16 lanes per row with
+// Up to CHAN_SPLITS workgroups per (sequence, KV head) add up squares, 16 lanes per row with
 // 16-byte loads, four rows of every lane in flight; a sample of 4096 rows is one round trip to memory for 64 workgroups.  The last of
 // them to end adds the workgroups' sums in order (the exponents do not depend on timing) and forms the exponents: the sums are
 // stored and read with device scope, and a workgroup takes its ticket once its own are in memory.  What is left is the latency of one launch and its
 // trips, so where V has to be copied as well (contiguous groups) the copy rides behind the sums of each (sequence, KV head).
 // As one workgroup per (sequence, KV head) with a 2-byte load and an add per row the sums alone took 826 us.  With sums and exponents in
 // launches of their own, half of the copy behind each, and now, builds, us: 8 x 1500 keys 14.2 / 12.3, 8 x 9001 25.0 / 22.3, 8 x 32768
-// 53.9 / 51.3, 8 x 131072 198 / 194; 128 x 32768 791 / 807, which has no explanation yet (two launches of half the copy each, or all
-// sums ahead of the copy, measured the same 806).
+// 53.9 / 51.3, 8 x 131072 198 / 194.  A workgroup has a fixed cost (the sums' way out, the ticket, three barriers), so with 64 of them for every one
+// of many (sequence, KV head) the sums were no longer bound by memory (256 x 4096 rows 81 us alone, 64 with 16 each; a read of them 45)
+// and builds were slower than before the single launch: 128 x 32768 791 -> 807.  2048 workgroups, eight per compute unit and so one round,
+// and at least 16 per (sequence, KV head), from 64 each: 64 x 32768 404 / 400, 128 x 32768 820 / 806, 256 x 16384 863 / 844, 256 x 4096 in groups of four
+// 221 / 204, 512 x 4096 515 / 495; at least 8: 804, 849, 208, 498; 4096 workgroups: 808, 842, 204, 496, but 64 x 32768 405.
 constexpr int CHAN_SPLITS = 64;
 
 struct ChannelArgs {
@@ -800,6 +803,11 @@ hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t
     const int room = ix->G * (ix->P > ix->P_dense ? ix->P : ix->P_dense);
     a.splits = (int)((a.rows + 63) / 64);     // 64 rows: four per lane quarter of a workgroup
     if (a.splits > CHAN_SPLITS) a.splits = CHAN_SPLITS;
+    const int n_bh = lvr_n_bh(ix), most = n_bh >= 128 ? 16 : 2048 / n_bh;   // 2048 workgroups, at least 16 per (sequence, KV head)
+    if (a.splits > most) {
+        const int64_t each = (a.rows + 64 * most - 1) / (64 * most) * 64;   // whole rounds of 64 rows
+        a.splits = (int)((a.rows + each - 1) / each);
+    }
     if (a.splits > room) a.splits = room;
     a.part = ix->part_o;
     a.chan_exp = lvr_chan_exp(ix);
@@ -808,7 +816,7 @@ hipError_t lvr_launch_channel_scales(lvr_index *ix, const void *K, const int64_t
     CopySide k{a.K, static_cast<char *>(ix->K), ks[0], ks[1], ks[2], V ? k_first : n};
     CopySide v{static_cast<const char *>(V), static_cast<char *>(ix->V), V ? vs[0] : 0, V ? vs[1] : 0, V ? vs[2] : 0, 0};
     const unsigned v_blocks = V ? copy_blocks(n, 4, STEP_PIECES) : 0;
-    hipLaunchKernelGGL(channel_step_kernel, dim3((unsigned)a.splits + v_blocks + copy_blocks(n - k.first, 4, STEP_PIECES), (unsigned)lvr_n_bh(ix)),
+    hipLaunchKernelGGL(channel_step_kernel, dim3((unsigned)a.splits + v_blocks + copy_blocks(n - k.first, 4, STEP_PIECES), (unsigned)n_bh),
                        dim3(256), 0, st, a, k, v, ix->cap_rows, n, v_blocks);
     return hipGetLastError();
 }

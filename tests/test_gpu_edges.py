@@ -53,6 +53,35 @@ def test_channel_exponents_over_sample_sizes(G, n, splits):
         assert np.array_equal(e[kv][sure], np.clip(want + shift, -8, 8)[sure]), (n, kv)
 
 
+@pytest.mark.parametrize("batch,hkv,n", [(4, 8, 4096), (33, 1, 4096), (5, 8, 3009), (16, 8, 1025), (32, 8, 4097), (70, 8, 1100)])
+def test_channel_exponents_of_many_heads(G, batch, hkv, n):
+    """Where there are many (sequence, KV head) a workgroup adds up more rows, whole rounds of 64 and what is left of them: the exponents
+    of every sequence are those of an index that holds it alone (other sums of the same squares, so a channel at a rounding boundary aside)."""
+    L = G.L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    mag = 2.0 ** (8.0 * torch.rand((batch, hkv, 1, 128), generator=g, device="cuda") - 4.0)
+    K = (torch.randn((batch, hkv, n, 128), generator=g, device="cuda") * mag).to(torch.bfloat16)
+
+    def exponents(rows):
+        cfg = L.make_config(batch=rows.shape[0], n_q_heads=hkv, n_kv_heads=hkv, capacity=n, group_size=1)
+        h = L.lvr_create(cfg)
+        try:
+            for _ in range(2):   # the second finds the tickets where the first left them
+                L.lvr_build(h, rows, rows)
+            return L.lvr_export_channel_scales(h, cfg).astype(np.int64)
+        finally:
+            L.lvr_destroy(h)
+
+    got = exponents(K)
+    lg = 0.5 * torch.log2(K[:, :, ::(n + 4095) // 4096].double().square().mean(dim=2)).cpu().numpy()
+    for b in range(0, batch, 3):
+        alone = exponents(K[b:b + 1].contiguous())[0]
+        o = np.arctan2(np.sin(2 * np.pi * lg[b]).sum(-1), np.cos(2 * np.pi * lg[b]).sum(-1))[:, None] / (2 * np.pi)
+        sure = np.abs((lg[b] - o) - np.floor(lg[b] - o) - 0.5) > 1e-3
+        assert sure.mean() > 0.9 and np.array_equal(got[b][sure], alone[sure]), b
+
+
 @pytest.mark.parametrize("batch,n", [(1, 65), (3, 4096), (1, 20000)])
 def test_channel_exponents_of_builds_in_a_row(G, batch, n):
     """The last workgroup to end forms the exponents: a build after a build on the same index (tickets back at zero), with channels of
